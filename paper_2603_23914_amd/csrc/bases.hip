@@ -74,47 +74,121 @@ mask_coeffs(const uint16_t* __restrict__ C, int64_t c_bstride, const int32_t* __
   for (int j = threadIdx.x & 63; j < r; j += 64) dst[j] = j < rk ? src[j] : (uint16_t)0;
 }
 
-// ---- S = A A^T in fp64 for A [l][lda] fp32 (m columns used).  32 x 32 tiles of the lower
-//      triangle, mirrored on the way out.  grid (ceil(l/32), ceil(l/32), batch), 256 threads.
+// fp64 matrix-core product: A operand lane (i = lane & 15, k = lane >> 4), B operand lane
+// (j = lane & 15, k = lane >> 4), result element e of lane (j, g): row g + 4 e, column j.
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ f64x4_t mfma_f64(double a, double b, f64x4_t c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// ---- S = A A^T in fp64 for A [l][lda] fp32 (m columns used, m % 8 == 0), the lower triangle of
+//      tiles, mirrored on the way out.  Bound by the fp64 matrix pipe: a wave owns 32 x 32 results
+//      (2 x 2 products) and takes its operands straight from global memory, 16 bytes of a row per
+//      lane = four k of the product (the order of k is free as long as both operands agree), the
+//      next sixteen columns requested while the current ones are multiplied; no LDS, no barrier.
+//      SPLIT_K = false: a workgroup's four waves form a 64 x 64 tile.  SPLIT_K = true: they share
+//      ONE 32 x 32 tile, a quarter of the columns each, and meet in LDS: for few or small matrices,
+//      which would leave most of the chip idle.  Measured at 16 matrices of 544 x 4096: 1.29 ms with
+//      fp64 FMAs from LDS tiles, see launch_gram for both forms of this one.
+//      grid (tiles of the lower triangle, batch), 256 threads.
+template <bool SPLIT_K>
 __global__ void __launch_bounds__(256)
 gram_f64(const float* __restrict__ A, int64_t a_bstride, int lda, double* __restrict__ S, int64_t s_bstride,
          int l, int m) {
-  if (blockIdx.x > blockIdx.y) return;
-  __shared__ float As[32][33], Bs[32][33];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  A += (size_t)blockIdx.z * a_bstride;
-  S += (size_t)blockIdx.z * s_bstride;
-  double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  for (int k0 = 0; k0 < m; k0 += 32) {
-    for (int e = tid; e < 1024; e += 256) {
-      const int rr = e >> 5, kk = e & 31;
-      const bool kin = k0 + kk < m;
-      As[rr][kk] = (kin && i0 + rr < l) ? A[(size_t)(i0 + rr) * lda + k0 + kk] : 0.f;
-      Bs[rr][kk] = (kin && j0 + rr < l) ? A[(size_t)(j0 + rr) * lda + k0 + kk] : 0.f;
+  __shared__ double red[SPLIT_K ? 3 * 1024 : 1];
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // tile (ti, tj), tj <= ti, of the lower triangle
+  int ti = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+  while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+  while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
+  const int tj = (int)blockIdx.x - ti * (ti + 1) / 2;
+  const int i0 = SPLIT_K ? ti * 32 : ti * 64 + (w >> 1) * 32;
+  const int j0 = SPLIT_K ? tj * 32 : tj * 64 + (w & 1) * 32;
+  if (!SPLIT_K && (i0 >= l || j0 >= l)) return;          // (no barrier in this form)
+  A += (size_t)blockIdx.y * a_bstride;
+  S += (size_t)blockIdx.y * s_bstride;
+  const float* rows[4];                                  // rows past the end repeat the last one
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int ri = i0 + 16 * u + n, rj = j0 + 16 * u + n;
+    rows[u] = A + (size_t)(ri < l ? ri : l - 1) * lda;
+    rows[2 + u] = A + (size_t)(rj < l ? rj : l - 1) * lda;
+  }
+  const int chunks = (m + 15) >> 4;                      // sixteen columns each; the last may be half
+  const int c_lo = SPLIT_K ? (int)((int64_t)w * chunks / 4) : 0;
+  const int c_hi = SPLIT_K ? (int)((int64_t)(w + 1) * chunks / 4) : chunks;
+  f32x4_t nx[4];
+  auto load = [&](int c) {
+    const int col = c * 16 + 4 * g;
+    const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) nx[u] = col < m ? *(const f32x4_t*)(rows[u] + col) : z;
+  };
+  f64x4_t acc[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) acc[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  if (c_lo < c_hi) load(c_lo);
+  for (int c = c_lo; c < c_hi; ++c) {
+    f32x4_t cur[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cur[u] = nx[u];
+    load(c + 1 < c_hi ? c + 1 : c);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double a0 = cur[0][e], a1 = cur[1][e], b0 = cur[2][e], b1 = cur[3][e];
+      acc[0][0] = mfma_f64(a0, b0, acc[0][0]);
+      acc[0][1] = mfma_f64(a0, b1, acc[0][1]);
+      acc[1][0] = mfma_f64(a1, b0, acc[1][0]);
+      acc[1][1] = mfma_f64(a1, b1, acc[1][1]);
+    }
+  }
+  if (SPLIT_K) {                                         // the four partial tiles, added in wave order
+    if (w > 0) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) red[((w - 1) * 16 + (u * 2 + v) * 4 + e) * 64 + lane] = acc[u][v][e];
     }
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      const double a0 = As[2 * ty][kk], a1 = As[2 * ty + 1][kk];
-      const double b0 = Bs[2 * tx][kk], b1 = Bs[2 * tx + 1][kk];
-      acc[0][0] = fma(a0, b0, acc[0][0]);
-      acc[0][1] = fma(a0, b1, acc[0][1]);
-      acc[1][0] = fma(a1, b0, acc[1][0]);
-      acc[1][1] = fma(a1, b1, acc[1][1]);
-    }
-    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[u][v][e] += red[(k * 16 + (u * 2 + v) * 4 + e) * 64 + lane];
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int i = i0 + 2 * ty + u, j = j0 + 2 * tx + v;
-      if (i < l && j < l) {
-        S[(size_t)i * l + j] = acc[u][v];
-        S[(size_t)j * l + i] = acc[u][v];
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + 16 * u + g + 4 * e, j = j0 + 16 * v + n;
+        if (i < l && j < l) {
+          S[(size_t)i * l + j] = acc[u][v][e];
+          S[(size_t)j * l + i] = acc[u][v][e];
+        }
       }
-    }
+}
+
+void launch_gram(const float* A, int64_t a_bstride, int lda, double* S, int64_t s_bstride, int l, int m, int batch,
+                 hipStream_t st) {
+  // 64 x 64 tiles once they give every CU two workgroups; below that the quarter-size tiles with
+  // the column axis split over the four waves.
+  const int t64 = (l + 63) / 64, t32 = (l + 31) / 32;
+  if ((int64_t)t64 * (t64 + 1) / 2 * batch >= 512)
+    hipLaunchKernelGGL(gram_f64<false>, dim3(t64 * (t64 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
+  else
+    hipLaunchKernelGGL(gram_f64<true>, dim3(t32 * (t32 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
 }
 
 // ---- Cholesky S = L L^T in place (the lower triangle of S becomes L), fp64, in panels of 32
@@ -257,60 +331,96 @@ tri_inverse(const double* __restrict__ S, int64_t s_bstride, double* __restrict_
 }
 
 // ---- C = A B with A [M][K] fp64, B [K][N] fp32, fp64 accumulation; C as fp32 and / or in 16-bit
-//      storage.  lower: A is lower triangular (blocks above the diagonal are skipped).
-//      64 x 64 tiles, 256 threads x (4 x 4).  grid (ceil(N/64), ceil(M/64), batch).
+//      storage.  lower: A is lower triangular (a wave stops at its last row's diagonal).
+//      Bound by the fp64 matrix pipe.  A wave owns 32 rows x 64 columns (2 x 4 products) and takes
+//      its operands straight from global memory: a lane's 16 bytes of an A row are two k, its 16
+//      bytes of a B row are one k of FOUR column tiles (tile c holds columns 4 j + c, so a lane's
+//      results are four consecutive columns and leave as one 16-byte store).  Eight k per stage, the
+//      next stage requested while the current one is multiplied.  The four waves of a workgroup
+//      (2 x 2) share their operand rows in L1; XCD-aware numbering keeps a matrix's A (2.4 MB at
+//      l = 544) in one XCD's L2.
+//      grid (ceil(M / 64) * N / 128 (+ padding) * batch), 256 threads; N % 64 == 0, K even.
 template <class Tag>
 __global__ void __launch_bounds__(256)
 gemm_nn(const double* __restrict__ A, int64_t a_bstride, int lda, const float* __restrict__ Bm, int64_t b_bstride,
         int ldb, float* __restrict__ C32, int64_t c32_bstride, uint16_t* __restrict__ C16, int64_t c16_bstride,
-        int ldc, int M, int N, int K, int lower) {
-  __shared__ double As[16][65];
-  __shared__ float Bs[16][68];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  A += (size_t)blockIdx.z * a_bstride;
-  Bm += (size_t)blockIdx.z * b_bstride;
-  double acc[4][4];
+        int ldc, int M, int N, int K, int lower, int batch) {
+  const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int MT = (M + 63) >> 6, NT = (N + 127) >> 7, per = MT * NT;
+  int b, t;
+  const int id = (int)blockIdx.x;
+  if (batch % 8 == 0) {                                  // matrix b on XCD b % 8
+    const int k = id >> 3;
+    b = (k / per) * 8 + (id & 7);
+    t = k % per;
+  } else {
+    b = id / per;
+    t = id - b * per;
+  }
+  // longest row blocks first (lower: the work grows with the row)
+  const int mt = MT - 1 - t / NT, nt = t % NT;
+  const int m0 = mt * 64 + (w >> 1) * 32, n0 = nt * 128 + (w & 1) * 64;
+  if (m0 >= M || n0 >= N) return;
+  A += (size_t)b * a_bstride;
+  Bm += (size_t)b * b_bstride;
+  const double* arow[2];                                 // rows past the end repeat the last one
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < 2; ++u) {
+    const int i = m0 + 16 * u + n;
+    arow[u] = A + (size_t)(i < M ? i : M - 1) * lda;
+  }
+  const float* bcol = Bm + n0 + 4 * n;
+  f64x4_t acc[2][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-  const int kend = lower ? (m0 + 64 < K ? m0 + 64 : K) : K;
-  for (int k0 = 0; k0 < kend; k0 += 16) {
-    for (int e = tid; e < 1024; e += 256) {
-      const int mm = e >> 4, kk = e & 15;
-      As[kk][mm] = (m0 + mm < M && k0 + kk < K) ? A[(size_t)(m0 + mm) * lda + k0 + kk] : 0.0;
-      const int kb = e >> 6, nn = e & 63;
-      Bs[kb][nn] = (k0 + kb < K && n0 + nn < N) ? Bm[(size_t)(k0 + kb) * ldb + n0 + nn] : 0.f;
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  const int kend = lower ? (m0 + 32 < K ? m0 + 32 : K) : K;
+  f64x2_t na[2];
+  f32x4_t nb[2];
+  auto load = [&](int k0) {                              // k of element e: k0 + 2 g + e
+    const int k = k0 + 2 * g;
+    const bool in = k < kend;                            // kend is even: both elements or none
+    const int kc = in ? k : 0;
+    const f64x2_t z = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const f64x2_t v = *(const f64x2_t*)(arow[u] + kc);
+      na[u] = in ? v : z;
     }
-    __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      double a[4], bv[4];
+    for (int e = 0; e < 2; ++e) nb[e] = *(const f32x4_t*)(bcol + (size_t)(kc + e) * ldb);
+  };
+  load(0);
+  for (int k0 = 0; k0 < kend; k0 += 8) {
+    f64x2_t ca[2];
+    f32x4_t cb[2];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = As[kk][4 * ty + u];
+    for (int e = 0; e < 2; ++e) { ca[e] = na[e]; cb[e] = nb[e]; }
+    load(k0 + 8 < kend ? k0 + 8 : k0);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) bv[v] = (double)Bs[kk][4 * tx + v];
+    for (int e = 0; e < 2; ++e)
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], bv[v], acc[u][v]);
-    }
-    __syncthreads();
+      for (int v = 0; v < 4; ++v) {
+        const double bv = cb[e][v];
+        acc[0][v] = mfma_f64(ca[0][e], bv, acc[0][v]);
+        acc[1][v] = mfma_f64(ca[1][e], bv, acc[1][v]);
+      }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i = m0 + 4 * ty + u;
-    if (i >= M) continue;
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int j = n0 + 4 * tx + v;
-      if (j >= N) continue;
-      const float f = (float)acc[u][v];
-      if (C32) C32[(size_t)blockIdx.z * c32_bstride + (size_t)i * ldc + j] = f;
-      if (C16) C16[(size_t)blockIdx.z * c16_bstride + (size_t)i * ldc + j] = f32_to_bits(f, Tag{});
+    for (int e = 0; e < 4; ++e) {
+      const int i = m0 + 16 * u + g + 4 * e, j = n0 + 4 * n;
+      if (i >= M) continue;
+      const f32x4_t f = {(float)acc[u][0][e], (float)acc[u][1][e], (float)acc[u][2][e], (float)acc[u][3][e]};
+      if (C32) *(f32x4_t*)(C32 + (size_t)b * c32_bstride + (size_t)i * ldc + j) = f;
+      if (C16) {
+        const u32x2_t h = {pack2(f[0], f[1], Tag{}), pack2(f[2], f[3], Tag{})};
+        *(u32x2_t*)(C16 + (size_t)b * c16_bstride + (size_t)i * ldc + j) = h;
+      }
     }
-  }
 }
 
 // ---- fp64 -> fp32 copy of n values per batch item.
@@ -483,8 +593,9 @@ template <class Tag>
 void launch_gemm_nn(const double* A, int64_t a_bs, int lda, const float* Bm, int64_t b_bs, int ldb, float* C32,
                     int64_t c32_bs, uint16_t* C16, int64_t c16_bs, int ldc, int M, int N, int K, int lower, int batch,
                     hipStream_t st) {
-  hipLaunchKernelGGL((gemm_nn<Tag>), dim3((N + 63) / 64, (M + 63) / 64, batch), dim3(256), 0, st, A, a_bs, lda, Bm,
-                     b_bs, ldb, C32, c32_bs, C16, c16_bs, ldc, M, N, K, lower);
+  const int per = ((M + 63) / 64) * ((N + 127) / 128);
+  hipLaunchKernelGGL((gemm_nn<Tag>), dim3((unsigned)(per * batch)), dim3(256), 0, st, A, a_bs, lda, Bm,
+                     b_bs, ldb, C32, c32_bs, C16, c16_bs, ldc, M, N, K, lower, batch);
 }
 
 template <class Tag>
@@ -522,8 +633,7 @@ ap_status run_bases(const BasesArgs& a) {
     NtGemmArgs g2{Yt, (int64_t)l * np, np, Xt, (int64_t)HD * np, np, M32, (int64_t)l * HD, HD, nullptr, 0, B, l, HD, np, dt, 2, st};
     if ((s = launch_gemm_nt(g2)) != AP_OK) return s;
     // rows of M made orthonormal
-    hipLaunchKernelGGL(gram_f64, dim3((l + 31) / 32, (l + 31) / 32, B), dim3(256), 0, st, M32, (int64_t)l * HD, HD, S,
-                       (int64_t)l * l, l, HD);
+    launch_gram(M32, (int64_t)l * HD, HD, S, (int64_t)l * l, l, HD, B, st);
     hipLaunchKernelGGL(diag_max, dim3(B), dim3(256), 0, st, S, (int64_t)l * l, l, dmax);
     for (int c0 = 0; c0 < l; c0 += 32) {
       if (c0 > 0)
@@ -539,8 +649,7 @@ ap_status run_bases(const BasesArgs& a) {
   // Rayleigh-Ritz in the span of P
   NtGemmArgs g4{P16, (int64_t)l * HD, HD, a.X, (int64_t)n * HD, HD, Zt, (int64_t)l * np, np, nullptr, 0, B, l, n, HD, dt, 2, st};
   if ((s = launch_gemm_nt(g4)) != AP_OK) return s;
-  hipLaunchKernelGGL(gram_f64, dim3((l + 31) / 32, (l + 31) / 32, B), dim3(256), 0, st, Zt, (int64_t)l * np, np, S,
-                     (int64_t)l * l, l, n);
+  launch_gram(Zt, (int64_t)l * np, np, S, (int64_t)l * l, l, n, B, st);
   const size_t nel = (size_t)B * l * l;
   hipLaunchKernelGGL(to_f32, dim3((unsigned)((nel + 255) / 256)), dim3(256), 0, st, S, W, nel);
   hipLaunchKernelGGL(jacobi_reset, dim3((B + 63) / 64), dim3(64), 0, st, state, B);
