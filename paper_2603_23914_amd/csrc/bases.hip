@@ -12,7 +12,7 @@
 //                                   S = L L^T (chol_update / chol_panel, panels of 32 columns),
 //                                   P = L^-1 M (tri_inverse, gemm_nn; fp64 accumulation)
 //     Rayleigh-Ritz:           Zt = P X^T [l, n] fp32,  S = Zt Zt^T [l, l]  (= P X^T X P^T)
-//                              S = J Lambda J^T by one-sided Jacobi on the rows of S (jacobi_block)
+//                              S = J Lambda J^T by one-sided Jacobi on the rows of S (jacobi_pair)
 //                              D = (J^T P)[:r] in decreasing order of Lambda,  sigma = sqrt(Lambda)
 //
 // The matrices that lose information when rounded (M, whose singular values span the square of the
@@ -23,6 +23,7 @@
 // periodic re-compression decomposes again (next to the uncompressed tail).
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
+#include "mfma_ops.hpp"
 
 namespace ap {
 namespace {
@@ -32,6 +33,10 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
   return x;
 }
+
+constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done
+constexpr int kSweepSlots = 16;        // rotation counters per matrix, one per sweep
+constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16-bit storage of the result keeps
 
 // ---- out[c][r] = in[r][c] for 16-bit elements; columns rows .. ld_out-1 of out are zero-filled.
 //      grid (ceil(ld_out / 64), ceil(cols / 64), batch), 256 threads.
@@ -423,154 +428,276 @@ gemm_nn(const double* __restrict__ A, int64_t a_bstride, int lda, const float* _
     }
 }
 
-// ---- fp64 -> fp32 copy of n values per batch item.
-__global__ void to_f32(const double* __restrict__ in, float* __restrict__ out, size_t n) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) out[i] = (float)in[i];
+// ---- W [l][lp] fp32 <- S [l][l] fp64, columns l .. lp-1 zero; the sweeps' rotation counters to zero.
+//      grid (ceil(l * lp / 256), batch), 256 threads.
+__global__ void __launch_bounds__(256)
+jacobi_init(const double* __restrict__ S, int64_t s_bstride, float* __restrict__ W, int64_t w_bstride, int l, int lp,
+            int* __restrict__ rotations) {
+  const int e = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+  if (e < l * lp) {
+    const int i = e / lp, c = e - i * lp;
+    W[(size_t)b * w_bstride + e] = c < l ? (float)S[(size_t)b * s_bstride + (size_t)i * l + c] : 0.f;
+  }
+  if (e < kSweepSlots) rotations[b * kSweepSlots + e] = 0;
 }
 
-// ---- One-sided Jacobi on the rows of W [l][l] (fp32), block version.  The rows are cut into blocks
-//      of BS; one launch takes disjoint pairs of blocks (round-robin over the blocks), a workgroup
-//      per pair: its 2 BS rows come into LDS, one cyclic sweep over all their row pairs runs there
-//      (2 BS - 1 steps of BS disjoint pairs, each rotated in its plane so that the two rows become
-//      orthogonal), and the rows go back.  For a symmetric positive semi-definite W = S the rows
-//      converge to lambda_i j_i^T, the eigenvectors scaled by their eigenvalues.
-//      state[b]: [0] rotations in this sweep, [1] done.  grid (pairs, batch), 1024 threads.
-template <int BS>
-__global__ void __launch_bounds__(1024)
-jacobi_block(float* __restrict__ W, int64_t w_bstride, int l, int nblk, int step, float tol, int* __restrict__ state) {
-  extern __shared__ float rows_lds[];                   // [2 BS][l + 1]
-  constexpr int TPP = 1024 / BS;                        // threads per row pair (32 or 64: within one wave)
-  constexpr int NC = BS == 32 ? 19 : 16;                // a thread's columns of a row: l <= 599 / l <= 1024
-  const int b = blockIdx.y, tid = threadIdx.x;
-  if (state[2 * b + 1]) return;
+// ---- One-sided Jacobi on the rows of W [l][lp] (fp32), block version.  The rows are cut into blocks
+//      of 16; one launch takes disjoint pairs of blocks (round-robin over the blocks), a workgroup per
+//      pair.  For a symmetric positive semi-definite W = S the rows converge to lambda_i j_i^T, the
+//      eigenvectors scaled by their eigenvalues.
+//      A workgroup never holds its 32 rows: it forms their Gram matrix G on the fp32 matrix
+//      instructions, runs one cyclic sweep of two-sided rotations on G (31 steps of 16 disjoint pairs,
+//      the same rotations that the rows themselves would see) while the product Q of the rotations is
+//      built next to it, and multiplies the rows by Q on the matrix instructions.  The chain of 31
+//      steps is what bounds it, so a step is kept short: G and Q are 32 x 32 in LDS, double-buffered,
+//      one barrier a step.  The pairs of a step are always positions (k, 16 + k); what a step writes
+//      goes to the position of the next step's partner (the circle method: position 0 stays, the
+//      others move on by one, and after 31 steps everything is back), so all addresses are constants.
+//      Waves 0-3 own 2 x 2 of G per thread and each work out all 16 rotations themselves; waves 4-7
+//      follow one step behind with Q.
+//      Blocks of 16: 17 pairs of a 544-row matrix, which fills the chip from 16 matrices on; the
+//      number of steps per sweep hardly depends on the block (1023 against 1071 with blocks of 32),
+//      nor does the number of sweeps (8 in both, the last of which only looks).
+//      G is scaled by a power of two to a largest diagonal entry in [1, 2): no overflow in the angles.
+//      Measured at 16 matrices of 544 rows: 24 us a launch, 7.0 ms in all; with the rows themselves in
+//      LDS (blocks of 32, three dot products and a rotation of 544 columns per pair) 190 us a launch
+//      and 21.9 ms.
+//      rotations[b][sweep] counts the pairs of blocks that had work; a matrix whose previous sweep
+//      had none is done.
+//      grid (pairs * batch), 512 threads.
+__global__ void __launch_bounds__(512)
+jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, int step, int sweep, float tol,
+            int* __restrict__ rotations, int batch) {
+  constexpr int PITCH = 48;                             // 16 mod 32: two neighbouring rows fill the banks
+  __shared__ float part[8][3 * 256];
+  __shared__ float gm[2][32 * PITCH], qm[2][32 * PITCH];
+  __shared__ f32x2_t csn[2][16];                        // cosine and sine of a step's pairs
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int npair = nblk >> 1, id = (int)blockIdx.x;
+  int b, k;
+  if (batch % 8 == 0) {                                 // matrix b stays on XCD b % 8, in its L2
+    b = (id >> 3) / npair * 8 + (id & 7);
+    k = (id >> 3) % npair;
+  } else {
+    b = id / npair;
+    k = id - b * npair;
+  }
+  if (sweep > 0 && rotations[b * kSweepSlots + sweep - 1] == 0) return;
   // round-robin over nblk blocks (nblk even; a block index >= the real count is an empty block)
-  const int k = blockIdx.x, nm1 = nblk - 1;
+  const int nm1 = nblk - 1;
   int ba, bb;
   if (k == 0) { ba = nm1; bb = step; }
   else { ba = (step + k) % nm1; bb = (step + nm1 - k) % nm1; }
-  const int pitch = l + 1;
+  if (ba * 16 >= l && bb * 16 >= l) return;
   float* Wb = W + (size_t)b * w_bstride;
-  const int nreal = (l + BS - 1) / BS;
-  if (ba >= nreal && bb >= nreal) return;
-  for (int e = tid; e < 2 * BS * l; e += 1024) {
-    const int rr = e / l, c = e - rr * l;
-    const int gr = (rr < BS ? ba * BS + rr : bb * BS + rr - BS);
-    const bool real = (rr < BS ? ba : bb) < nreal && gr < l;
-    rows_lds[rr * pitch + c] = real ? Wb[(size_t)gr * l + c] : 0.f;
-  }
-  __syncthreads();
-  const int pr = tid / TPP, sub = tid - pr * TPP;
-  int nrot = 0;
-  constexpr int N2 = 2 * BS;
-  for (int s2 = 0; s2 < N2 - 1; ++s2) {
-    int ia, ib;
-    if (pr == 0) { ia = N2 - 1; ib = s2; }
-    else { ia = (s2 + pr) % (N2 - 1); ib = (s2 + N2 - 1 - pr) % (N2 - 1); }
-    float* ra = rows_lds + ia * pitch;
-    float* rb = rows_lds + ib * pitch;
-    // the pair's two rows stay in registers between the three dot products and the rotation
-    // (one LDS read of each element per step), and the sums cross the pair's lanes on the DPP path
-    float x[NC], y[NC];
-    float al = 0.f, be = 0.f, ga = 0.f;
+
+  // G = rows rows^T: lane n holds row n of either block, four columns of each sixteen
+  const int ra = ba * 16 + n, rb = bb * 16 + n;
+  const float* pa = Wb + (size_t)(ra < l ? ra : 0) * lp + 4 * g;
+  const float* pb = Wb + (size_t)(rb < l ? rb : 0) * lp + 4 * g;
+  f32x4_t g00 = {0.f, 0.f, 0.f, 0.f}, g01 = g00, g11 = g00;
+  const f32x4_t z4 = g00;
+  for (int c0 = w; c0 < lp >> 4; c0 += 40) {            // five sixteens of columns on their way at once
+    f32x4_t va[5], vb[5];
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      const int c = sub + k * TPP;
-      const bool in = c < l;
-      x[k] = in ? ra[c] : 0.f;
-      y[k] = in ? rb[c] : 0.f;
-      al = fmaf(x[k], x[k], al);
-      be = fmaf(y[k], y[k], be);
-      ga = fmaf(x[k], y[k], ga);
-    }
-    al = group_sum<32>(al);
-    be = group_sum<32>(be);
-    ga = group_sum<32>(ga);
-    if (TPP == 64) {
-      al += __shfl_xor(al, 32);
-      be += __shfl_xor(be, 32);
-      ga += __shfl_xor(ga, 32);
-    }
-    if (fabsf(ga) > tol * sqrtf(al * be)) {               // the same decision in all lanes of the pair
-      const float zeta = (be - al) / (2.f * ga);
-      const float t = (zeta >= 0.f ? 1.f : -1.f) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta));
-      const float cs = 1.f / sqrtf(1.f + t * t), sn = cs * t;
+    for (int t = 0; t < 5; ++t)
+      if (c0 + 8 * t < lp >> 4) {
+        va[t] = *(const f32x4_t*)(pa + (c0 + 8 * t) * 16);
+        vb[t] = *(const f32x4_t*)(pb + (c0 + 8 * t) * 16);
+      }
 #pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        const int c = sub + k * TPP;
-        if (c < l) {
-          ra[c] = cs * x[k] - sn * y[k];
-          rb[c] = sn * x[k] + cs * y[k];
+    for (int t = 0; t < 5; ++t)
+      if (c0 + 8 * t < lp >> 4) {
+        const f32x4_t x = ra < l ? va[t] : z4, y = rb < l ? vb[t] : z4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          g00 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], x[e], g00, 0, 0, 0);
+          g01 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], g01, 0, 0, 0);
+          g11 = __builtin_amdgcn_mfma_f32_16x16x4f32(y[e], y[e], g11, 0, 0, 0);
         }
       }
-      if (sub == 0) ++nrot;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int at = (4 * g + e) * 16 + n;
+    part[w][at] = g00[e];
+    part[w][256 + at] = g01[e];
+    part[w][512 + at] = g11[e];
+  }
+  __syncthreads();
+  float own[2];                                         // elements tid and tid + 512 of G
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    const int at = u == 0 ? (j < 16 ? i * 16 + j : 256 + i * 16 + j - 16)
+                          : (j < 16 ? 256 + j * 16 + i - 16 : 512 + (i - 16) * 16 + j - 16);
+    float s = part[0][at];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) s += part[q][at];
+    own[u] = s;
+    gm[0][i * PITCH + j] = s;
+  }
+  __syncthreads();
+  const float dg = gm[0][(lane & 31) * (PITCH + 1)];    // the diagonal, in every wave
+  float dmx = dg;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) dmx = fmaxf(dmx, __shfl_xor(dmx, o));
+  int work = 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    const float di = __shfl(dg, i), dj = __shfl(dg, j);
+    if (i != j && fabsf(own[u]) > tol * (sqrtf(di) * sqrtf(dj))) work = 1;
+  }
+  if (!__syncthreads_or(work)) return;                  // every pair is orthogonal already
+  if (tid == 0) atomicAdd(&rotations[b * kSweepSlots + sweep], 1);
+  const int sh = 1 - __builtin_amdgcn_frexp_expf(dmx);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    gm[0][i * PITCH + j] = ldexpf(own[u], sh);
+    qm[0][i * PITCH + j] = i == j ? 1.f : 0.f;
+  }
+  // the rows again, now a row of a block per (kk, g) and two columns per lane, on their way meanwhile
+  const int units = lp >> 5;
+  f32x2_t pre[3][8];
+  auto row_of = [&](int i) { return i < 16 ? ba * 16 + i : bb * 16 + i - 16; };
+  auto load_unit = [&](int u, f32x2_t (&v)[8]) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const int row = row_of(4 * kk + g);
+      v[kk] = *(const f32x2_t*)(Wb + (size_t)(row < l ? row : 0) * lp + u * 32 + 2 * n);
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+    if (w + 8 * t < units) load_unit(w + 8 * t, pre[t]);
+  __syncthreads();
+
+  const int I = 4 * (w & 3) + g;
+  auto moved = [](int p) { return p == 0 ? 0 : p == 15 ? 31 : p == 16 ? 1 : p < 15 ? p + 1 : p - 1; };
+  const int r0 = moved(I) * PITCH, r1 = moved(16 + I) * PITCH, c0 = moved(n), c1 = moved(16 + n);
+#pragma unroll 2
+  for (int s = 0; s < 32; ++s) {
+    if (w < 4) {
+      if (s < 31) {
+        const float* cur = gm[s & 1];
+        float* nxt = gm[(s & 1) ^ 1];
+        const float al = cur[n * (PITCH + 1)], be = cur[(16 + n) * (PITCH + 1)], ga = cur[n * PITCH + 16 + n];
+        const float a00 = cur[I * PITCH + n], a01 = cur[I * PITCH + 16 + n];
+        const float a10 = cur[(16 + I) * PITCH + n], a11 = cur[(16 + I) * PITCH + 16 + n];
+        // the rotation that makes the pair n orthogonal (any residue is far below the tolerance)
+        const float zeta = (be - al) * __builtin_amdgcn_rcpf(ga + ga);
+        float t = __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.f)));
+        t = fabsf(ga) > 1e-30f ? copysignf(t, zeta) : 0.f;
+        const float h = fmaf(t, t, 1.f);
+        float cs = __builtin_amdgcn_rsqf(h);
+        cs = fmaf(cs * 0.5f, fmaf(-h * cs, cs, 1.f), cs);   // one Newton step: cos^2 + sin^2 = 1 to rounding
+        const float sn = cs * t;
+        const float ci = __shfl(cs, I), si = __shfl(sn, I);
+        if (w == 0 && g == 0) csn[s & 1][n] = f32x2_t{cs, sn};
+        const float b00 = fmaf(ci, a00, -si * a10), b01 = fmaf(ci, a01, -si * a11);
+        const float b10 = fmaf(si, a00, ci * a10), b11 = fmaf(si, a01, ci * a11);
+        nxt[r0 + c0] = fmaf(cs, b00, -sn * b01);
+        nxt[r0 + c1] = fmaf(sn, b00, cs * b01);
+        nxt[r1 + c0] = fmaf(cs, b10, -sn * b11);
+        nxt[r1 + c1] = fmaf(sn, b10, cs * b11);
+      }
+    } else if (s > 0) {
+      const float* cur = qm[(s & 1) ^ 1];
+      float* nxt = qm[s & 1];
+      const f32x2_t r = csn[(s & 1) ^ 1][I];
+      const float a00 = cur[I * PITCH + n], a01 = cur[I * PITCH + 16 + n];
+      const float a10 = cur[(16 + I) * PITCH + n], a11 = cur[(16 + I) * PITCH + 16 + n];
+      nxt[r0 + n] = fmaf(r[0], a00, -r[1] * a10);
+      nxt[r0 + 16 + n] = fmaf(r[0], a01, -r[1] * a11);
+      nxt[r1 + n] = fmaf(r[1], a00, r[0] * a10);
+      nxt[r1 + 16 + n] = fmaf(r[1], a01, r[0] * a11);
     }
     __syncthreads();
   }
-  for (int e = tid; e < 2 * BS * l; e += 1024) {
-    const int rr = e / l, c = e - rr * l;
-    const int gr = (rr < BS ? ba * BS + rr : bb * BS + rr - BS);
-    const bool real = (rr < BS ? ba : bb) < nreal && gr < l;
-    if (real) Wb[(size_t)gr * l + c] = rows_lds[rr * pitch + c];
-  }
-  if (nrot) atomicAdd(&state[2 * b], nrot);
-}
 
-// after a sweep: a matrix without a rotation is done
-__global__ void jacobi_sweep_end(int* __restrict__ state, int batch) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  if (b < batch) {
-    if (state[2 * b] == 0) state[2 * b + 1] = 1;
-    state[2 * b] = 0;
-  }
-}
-__global__ void jacobi_reset(int* __restrict__ state, int batch) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  if (b < batch) { state[2 * b] = 0; state[2 * b + 1] = 0; }
-}
-
-// ---- eigenvalues = row norms, sorted in decreasing order (ties by row index); the r leading rows,
-//      normalised, become R [r][l] (fp64) and sigma[i] = sqrt(lambda_i).  One workgroup per matrix.
-__global__ void __launch_bounds__(1024)
-eig_select(const float* __restrict__ W, int64_t w_bstride, int l, int r, double* __restrict__ R, int64_t r_bstride,
-           float* __restrict__ sigma, int64_t sig_bstride) {
-  __shared__ double lam[1024];
-  __shared__ int pos[1024];
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const float* Wb = W + (size_t)b * w_bstride;
-  for (int i = w; i < l; i += 16) {
-    double s = 0.0;
-    for (int c = lane; c < l; c += 64) { const double v = Wb[(size_t)i * l + c]; s = fma(v, v, s); }
-    s = wave_sum_d(s);
-    if (lane == 0) lam[i] = sqrt(s);
-  }
-  __syncthreads();
-  for (int i = tid; i < l; i += 1024) {
-    int p = 0;
-    const double li = lam[i];
-    for (int j = 0; j < l; ++j) p += (lam[j] > li || (lam[j] == li && j < i)) ? 1 : 0;
-    pos[i] = p;
-    if (p < r && sigma) sigma[(size_t)b * sig_bstride + p] = (float)sqrt(li);
-  }
-  __syncthreads();
-  for (int i = w; i < l; i += 16) {
-    const int p = pos[i];
-    if (p >= r) continue;
-    const double inv = lam[i] > 0.0 ? 1.0 / lam[i] : 0.0;
-    for (int c = lane; c < l; c += 64) R[(size_t)b * r_bstride + (size_t)p * l + c] = (double)Wb[(size_t)i * l + c] * inv;
+  // rows <- Q rows
+  const float* Q = qm[1];
+  float qa[2][8];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qa[t][kk] = Q[(16 * t + n) * PITCH + 4 * kk + g];
+  auto apply_unit = [&](int u, const f32x2_t (&v)[8]) {
+    f32x4_t acc[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) { acc[t][0] = z4; acc[t][1] = z4; }
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const f32x2_t x = row_of(4 * kk + g) < l ? v[kk] : f32x2_t{0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[t][kk], x[c], acc[t][c], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = row_of(16 * t + 4 * g + e);
+        if (row < l) *(f32x2_t*)(Wb + (size_t)row * lp + u * 32 + 2 * n) = f32x2_t{acc[t][0][e], acc[t][1][e]};
+      }
+  };
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+    if (w + 8 * t < units) apply_unit(w + 8 * t, pre[t]);
+  for (int u = w + 24; u < units; u += 8) {
+    f32x2_t v[8];
+    load_unit(u, v);
+    apply_unit(u, v);
   }
 }
 
-constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done
-constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16-bit storage of the result keeps
+// ---- eigenvalues = row norms.  grid (ceil(l / 4), batch), 256 threads: a wave per row.
+__global__ void __launch_bounds__(256)
+eig_norms(const float* __restrict__ W, int64_t w_bstride, int l, int lp, double* __restrict__ lam) {
+  const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
+  if (i >= l) return;
+  const float* row = W + (size_t)b * w_bstride + (size_t)i * lp;
+  double s = 0.0;
+  for (int c = lane; c < l; c += 64) { const double v = row[c]; s = fma(v, v, s); }
+  s = wave_sum_d(s);
+  if (lane == 0) lam[(size_t)b * l + i] = sqrt(s);
+}
+
+// ---- rows in decreasing order of their norm (ties by row index); the r leading rows, normalised,
+//      become R [r][l] (fp64) and sigma[i] = sqrt(lambda_i).  grid (ceil(l / 4), batch), 256 threads:
+//      a wave per row, which counts the rows before its own (one workgroup per matrix, which also
+//      took the norms, needed 197 us at 16 x 544 rows).
+__global__ void __launch_bounds__(256)
+eig_select(const float* __restrict__ W, int64_t w_bstride, const double* __restrict__ lam, int l, int lp, int r,
+           double* __restrict__ R, int64_t r_bstride, float* __restrict__ sigma, int64_t sig_bstride) {
+  const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
+  if (i >= l) return;
+  const double* lb = lam + (size_t)b * l;
+  const double li = lb[i];
+  int p = 0;
+  for (int j = lane; j < l; j += 64) p += (lb[j] > li || (lb[j] == li && j < i)) ? 1 : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) p += __shfl_xor(p, o);
+  if (p >= r) return;
+  if (lane == 0 && sigma) sigma[(size_t)b * sig_bstride + p] = (float)sqrt(li);
+  const double inv = li > 0.0 ? 1.0 / li : 0.0;
+  const float* row = W + (size_t)b * w_bstride + (size_t)i * lp;
+  for (int c = lane; c < l; c += 64) R[(size_t)b * r_bstride + (size_t)p * l + c] = (double)row[c] * inv;
+}
 
 struct BasesLayout {
-  size_t xt, yt, m32, p16, p32, zt, s64, linv, w32, rsel, state, dmax, total;
-  int n_pad;
+  size_t xt, yt, m32, p16, p32, zt, s64, linv, w32, rsel, state, dmax, lam, total;
+  int n_pad, lp;
 };
 BasesLayout bases_layout(int B, int n, int HD, int l, int r) {
   BasesLayout w;
   w.n_pad = (n + 63) / 64 * 64;
+  w.lp = (l + 31) / 32 * 32;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off += round_up(bytes, 256); return at; };
   w.xt = take((size_t)B * HD * w.n_pad * 2);
@@ -581,10 +708,11 @@ BasesLayout bases_layout(int B, int n, int HD, int l, int r) {
   w.zt = take((size_t)B * l * w.n_pad * 4);
   w.s64 = take((size_t)B * l * l * 8);
   w.linv = take((size_t)B * l * l * 8);
-  w.w32 = take((size_t)B * l * l * 4);
+  w.w32 = take((size_t)B * l * w.lp * 4);
   w.rsel = take((size_t)B * r * l * 8);
-  w.state = take((size_t)B * 2 * 4);
+  w.state = take((size_t)B * kSweepSlots * 4);
   w.dmax = take((size_t)B * 8);
+  w.lam = take((size_t)B * l * 8);
   w.total = off;
   return w;
 }
@@ -613,8 +741,9 @@ ap_status run_bases(const BasesArgs& a) {
   double* Linv = (double*)(ws + w.linv);
   float* W = (float*)(ws + w.w32);
   double* Rsel = (double*)(ws + w.rsel);
-  int* state = (int*)(ws + w.state);
+  int* rotations = (int*)(ws + w.state);
   double* dmax = (double*)(ws + w.dmax);
+  double* lam = (double*)(ws + w.lam);
   hipStream_t st = a.stream;
   const int np = w.n_pad;
   const ap_dtype dt = a.dt;
@@ -650,37 +779,17 @@ ap_status run_bases(const BasesArgs& a) {
   NtGemmArgs g4{P16, (int64_t)l * HD, HD, a.X, (int64_t)n * HD, HD, Zt, (int64_t)l * np, np, nullptr, 0, B, l, n, HD, dt, 2, st};
   if ((s = launch_gemm_nt(g4)) != AP_OK) return s;
   launch_gram(Zt, (int64_t)l * np, np, S, (int64_t)l * l, l, n, B, st);
-  const size_t nel = (size_t)B * l * l;
-  hipLaunchKernelGGL(to_f32, dim3((unsigned)((nel + 255) / 256)), dim3(256), 0, st, S, W, nel);
-  hipLaunchKernelGGL(jacobi_reset, dim3((B + 63) / 64), dim3(64), 0, st, state, B);
-  {
-    // blocks of 32 rows while two of them fit the LDS next to each other, else 16
-    const bool big = (size_t)64 * (l + 1) * 4 <= 150 * 1024;
-    const int bs = big ? 32 : 16;
-    int nblk = (l + bs - 1) / bs;
-    nblk += nblk & 1;                                    // an even number of blocks (the last may be empty)
-    const size_t lds = (size_t)2 * bs * (l + 1) * 4;
-    static bool attr_set = false;
-    if (!attr_set) {
-      hipError_t e1 = hipFuncSetAttribute((const void*)jacobi_block<32>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      hipError_t e2 = hipFuncSetAttribute((const void*)jacobi_block<16>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e1 != hipSuccess || e2 != hipSuccess) {
-        set_error("hipFuncSetAttribute: %s", hipGetErrorString(e1 != hipSuccess ? e1 : e2));
-        return AP_ERR_HIP;
-      }
-      attr_set = true;
-    }
-    for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
-      for (int step = 0; step < nblk - 1; ++step) {
-        if (big)
-          hipLaunchKernelGGL(jacobi_block<32>, dim3(nblk / 2, B), dim3(1024), lds, st, W, (int64_t)l * l, l, nblk, step, kJacobiTol, state);
-        else
-          hipLaunchKernelGGL(jacobi_block<16>, dim3(nblk / 2, B), dim3(1024), lds, st, W, (int64_t)l * l, l, nblk, step, kJacobiTol, state);
-      }
-      hipLaunchKernelGGL(jacobi_sweep_end, dim3((B + 63) / 64), dim3(64), 0, st, state, B);
-    }
-  }
-  hipLaunchKernelGGL(eig_select, dim3(B), dim3(1024), 0, st, W, (int64_t)l * l, l, r, Rsel, (int64_t)r * l, a.sigma,
+  const int lp = w.lp;
+  const int64_t w_bs = (int64_t)l * lp;
+  hipLaunchKernelGGL(jacobi_init, dim3((l * lp + 255) / 256, B), dim3(256), 0, st, S, (int64_t)l * l, W, w_bs, l, lp, rotations);
+  int nblk = (l + 15) / 16;
+  nblk += nblk & 1;                                      // an even number of blocks (the last may be empty)
+  for (int sweep = 0; sweep < kJacobiSweeps; ++sweep)
+    for (int step = 0; step < nblk - 1; ++step)
+      hipLaunchKernelGGL(jacobi_pair, dim3(nblk / 2 * B), dim3(512), 0, st, W, w_bs, l, lp, nblk, step, sweep, kJacobiTol,
+                         rotations, B);
+  hipLaunchKernelGGL(eig_norms, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, l, lp, lam);
+  hipLaunchKernelGGL(eig_select, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, lam, l, lp, r, Rsel, (int64_t)r * l, a.sigma,
                      (int64_t)r);
   // D = R P  [r, HD]
   launch_gemm_nn<Tag>(Rsel, (int64_t)r * l, l, P32, (int64_t)l * HD, HD, nullptr, 0, (uint16_t*)a.Bm, (int64_t)r * HD,

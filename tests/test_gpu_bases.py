@@ -259,3 +259,28 @@ def test_algorithm1_loop_with_new_bases_at_every_trigger():
             T, T_u = n, 0
             compressions += 1
     assert compressions == 3 and T == n0 + 16 and T_u == 1
+
+
+@pytest.mark.parametrize("l", [2, 16, 18, 34, 64, 66, 598, 602, 1022, 1024])
+def test_bases_eigenvectors_at_the_edges_of_blocks(l):
+    """The eigenvalue step at sketch sizes around its blocks (16 rows, pairs of them, 32 padded columns,
+    the fixed part of its column loops), all l directions kept.  sigma_i = ||X d_i|| in decreasing
+    order, and the images X d_i are orthogonal; both up to D's rounding to fp16 (2^-11 per element:
+    an error e_i of norm <= 2^-11, ||X e_i|| <= 2^-11 sigma_1, twice for a pair)."""
+    dtype, HD = "f16", 1088 if l > 602 else 640
+    n = HD
+    X = cache_matrix(17, l, n, HD, 256, dtype)
+    Omega = wl.store(wl.rng_for(17, 7).standard_normal((l, HD)), dtype)
+    print(f"bases l={l} HD={HD}", flush=True)
+    D, sig = gpu_bases(X[None], Omega, l, 1, dtype)
+    Xd, Dd = oracle.promote(X, dtype), oracle.promote(D[0], dtype)
+    Z = Xd @ Dd.T
+    s = np.linalg.norm(Z, axis=0)
+    eps = 2.0 ** -11
+    G = Z.T @ Z
+    cosdiff = np.abs(G - np.diag(np.diag(G)))
+    bound = eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)
+    print(f"  sigma {np.abs(sig[0] - s).max() / s[0]:.1e} of sigma_1, orthogonality {(cosdiff / np.maximum(bound, 1e-300)).max():.2f} of its bound", flush=True)
+    assert np.abs(sig[0] - s).max() <= 2 * eps * s[0]
+    assert np.diff(sig[0]).max() <= 1e-6 * sig[0][0]
+    assert (cosdiff <= bound).all()
