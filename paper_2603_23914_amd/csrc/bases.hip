@@ -9,7 +9,7 @@
 //     power_iters + 1 times:   Yt = P X^T   [l, n]      matrix cores (compact_gemm.hip), 16-bit out
 //                              M  = Yt X    [l, HD]     matrix cores, fp32 out (X^T from transpose16)
 //                              P  = rows of M made orthonormal: S = M M^T in fp64 (gram_f64),
-//                                   S = L L^T (chol_update / chol_panel, panels of 32 columns),
+//                                   S = L L^T (chol_panel, panels of 32 columns),
 //                                   P = L^-1 M (tri_inverse, gemm_nn; fp64 accumulation)
 //     Rayleigh-Ritz:           Zt = P X^T [l, n] fp32,  S = Zt Zt^T [l, l]  (= P X^T X P^T)
 //                              S = J Lambda J^T by one-sided Jacobi on the rows of S (jacobi_pair)
@@ -196,15 +196,6 @@ void launch_gram(const float* A, int64_t a_bstride, int lda, double* S, int64_t 
     hipLaunchKernelGGL(gram_f64<true>, dim3(t32 * (t32 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
 }
 
-// ---- Cholesky S = L L^T in place (the lower triangle of S becomes L), fp64, in panels of 32
-//      columns.  Per panel two launches:
-//   chol_update   rows c0 .. l-1 of the panel minus the contribution of the columns left of it:
-//                 S[i][c] -= sum_{j < c0} L[i][j] L[c][j]; a workgroup per 32 x 32 tile
-//   chol_panel    one workgroup per matrix: the 32 x 32 diagonal block is factored in LDS, then
-//                 every row below solves its 32 unknowns against it (a thread per row)
-//      A pivot below 1e-13 of the largest diagonal entry (dmax) marks a direction that the rows
-//      do not span: its column of L and its diagonal entry are zero, its row of L^-1 is zero,
-//      so the corresponding row of P = L^-1 M is zero and drops out later.
 __global__ void __launch_bounds__(256)
 diag_max(const double* __restrict__ S, int64_t s_bstride, int l, double* __restrict__ dmax) {
   const double* Sb = S + (size_t)blockIdx.x * s_bstride;
@@ -218,121 +209,272 @@ diag_max(const double* __restrict__ S, int64_t s_bstride, int l, double* __restr
   if (threadIdx.x == 0) dmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
 }
 
-// grid (ceil((l - c0) / 32), batch), 256 threads = 16 x 16, 2 x 2 results each
+// Matrix b of a flat grid of `per` workgroups per matrix and the workgroup's number t within it;
+// matrix b on XCD b % 8 where that comes out even, so that what one launch leaves in an L2 is found
+// there by the next.
+__device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, int& t) {
+  if (batch % 8 == 0) {
+    b = (id >> 3) / per * 8 + (id & 7);
+    t = (id >> 3) % per;
+  } else {
+    b = id / per;
+    t = id - b * per;
+  }
+}
+
+// ---- Cholesky S = L L^T, fp64, in panels of 32 columns, one launch per panel; off the diagonal the
+//      lower triangle of S becomes L block by block, the diagonal blocks' INVERSES go to X (nothing
+//      needs the diagonal blocks themselves: later panels and the inverse use what is below them).
+//      A workgroup owns the 32 x 32 tile of its rows in this panel and works out the panel's diagonal
+//      block next to it, every workgroup for itself: the products with the columns on the left for
+//      both on the fp64 matrix instructions (a quarter of those columns per wave, added in LDS), the
+//      factor of the diagonal block by one wave with two lanes per row (32 dependent steps, the
+//      longest part of the chain), its inverse from two 16 x 16 halves, and the tile times that
+//      inverse transposed.  What bounds it is this chain, not the arithmetic: 13-22 us a panel at 16
+//      matrices of 544, 0.3 ms for all seventeen (an update launch and a one-workgroup factor launch
+//      per panel with fp64 FMAs from LDS: 92 us a panel, 1.5 ms).
+//      A pivot below 1e-13 of the largest diagonal entry (dmax) marks a direction that the rows
+//      do not span: its column of L and its diagonal entry are zero, its row of L^-1 is zero,
+//      so the corresponding row of P = L^-1 M is zero and drops out later.
+//      grid (tiles from the diagonal down * batch), 256 threads.  l even.
 __global__ void __launch_bounds__(256)
-chol_update(double* __restrict__ S, int64_t s_bstride, int l, int c0) {
-  __shared__ double As[32][33], Bs[32][33];
-  double* L = S + (size_t)blockIdx.y * s_bstride;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int i0 = c0 + blockIdx.x * 32;
-  double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
-  for (int k0 = 0; k0 < c0; k0 += 32) {              // c0 is a multiple of 32
-    for (int e = tid; e < 1024; e += 256) {
-      const int rr = e >> 5, kk = e & 31;
-      As[rr][kk] = i0 + rr < l ? L[(size_t)(i0 + rr) * l + k0 + kk] : 0.0;
-      Bs[rr][kk] = c0 + rr < l ? L[(size_t)(c0 + rr) * l + k0 + kk] : 0.0;
+chol_panel(double* __restrict__ S, double* __restrict__ X, int l, int c0, const double* __restrict__ dmax, int batch) {
+  constexpr int P = 33, PC = 34;
+  __shared__ double red[4][7 * 256];
+  __shared__ double Dt[32 * P], At[32 * P], Di[32 * P], Lc[32 * PC], invd[32];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int b, t;
+  matrix_of((int)blockIdx.x, (l - c0 + 31) >> 5, batch, b, t);
+  double* L = S + (size_t)b * l * l;
+  const int i0 = c0 + 32 * t;
+  if (c0 > 0) {
+    const double* rows[4];                               // the panel's rows, the tile's rows; past the end: the last
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int rc = c0 + 16 * u + n, ri = i0 + 16 * u + n;
+      rows[u] = L + (size_t)(rc < l ? rc : l - 1) * l + 2 * g;
+      rows[2 + u] = L + (size_t)(ri < l ? ri : l - 1) * l + 2 * g;
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      const double a0 = As[2 * ty][kk], a1 = As[2 * ty + 1][kk];
-      const double b0 = Bs[2 * tx][kk], b1 = Bs[2 * tx + 1][kk];
-      acc[0][0] = fma(a0, b0, acc[0][0]);
-      acc[0][1] = fma(a0, b1, acc[0][1]);
-      acc[1][0] = fma(a1, b0, acc[1][0]);
-      acc[1][1] = fma(a1, b1, acc[1][1]);
+    f64x4_t d00 = {0.0, 0.0, 0.0, 0.0}, d10 = d00, d11 = d00, a00 = d00, a01 = d00, a10 = d00, a11 = d00;
+    const int k_lo = (c0 >> 2) * w, k_hi = k_lo + (c0 >> 2);   // a multiple of 8 columns each
+    f64x2_t nx[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) nx[u] = *(const f64x2_t*)(rows[u] + k_lo);
+    for (int k = k_lo; k < k_hi; k += 8) {
+      f64x2_t cur[4];
+      const int kn = k + 8 < k_hi ? k + 8 : k;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { cur[u] = nx[u]; nx[u] = *(const f64x2_t*)(rows[u] + kn); }
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        d00 = mfma_f64(cur[0][e], cur[0][e], d00);
+        d10 = mfma_f64(cur[1][e], cur[0][e], d10);
+        d11 = mfma_f64(cur[1][e], cur[1][e], d11);
+        if (t > 0) {
+          a00 = mfma_f64(cur[2][e], cur[0][e], a00);
+          a01 = mfma_f64(cur[2][e], cur[1][e], a01);
+          a10 = mfma_f64(cur[3][e], cur[0][e], a10);
+          a11 = mfma_f64(cur[3][e], cur[1][e], a11);
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int at = (g + 4 * e) * 16 + n;
+      red[w][at] = d00[e];
+      red[w][256 + at] = d10[e];
+      red[w][512 + at] = d11[e];
+      red[w][768 + at] = a00[e];
+      red[w][1024 + at] = a01[e];
+      red[w][1280 + at] = a10[e];
+      red[w][1536 + at] = a11[e];
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      const int i = i0 + 2 * ty + u, c = c0 + 2 * tx + v;
-      if (i < l && c < l) L[(size_t)i * l + c] -= acc[u][v];
-    }
-}
-
-// grid (batch), 256 threads
-__global__ void __launch_bounds__(256)
-chol_panel(double* __restrict__ S, int64_t s_bstride, int l, int c0, const double* __restrict__ dmax) {
-  __shared__ double Dg[32][33];
-  double* L = S + (size_t)blockIdx.x * s_bstride;
-  const int tid = threadIdx.x;
-  const int nb = l - c0 < 32 ? l - c0 : 32;
-  const double tol = dmax[blockIdx.x] * 1e-13;
-  for (int e = tid; e < 1024; e += 256) {
-    const int rr = e >> 5, cc = e & 31;
-    Dg[rr][cc] = (rr < nb && cc < nb && cc <= rr) ? L[(size_t)(c0 + rr) * l + c0 + cc] : 0.0;
+  for (int q = 0; q < 7; ++q) {                          // S minus those products, tile by tile (tid = row, column)
+    const int tr = q < 3 ? (q > 0) : (q > 4), tc = q < 3 ? (q > 1) : (q + 1) & 1;
+    const int i = 16 * tr + (tid >> 4), c = 16 * tc + (tid & 15), row = (q < 3 ? c0 : i0) + i;
+    double v = row < l && c0 + c < l ? L[(size_t)row * l + c0 + c] : 0.0;
+    if (c0 > 0 && row < l && c0 + c < l)
+      v -= (red[0][q * 256 + tid] + red[1][q * 256 + tid]) + (red[2][q * 256 + tid] + red[3][q * 256 + tid]);
+    (q < 3 ? Dt : At)[i * P + c] = v;
   }
   __syncthreads();
-  // unblocked Cholesky of the diagonal block (right-looking, 32 short steps)
-  for (int k = 0; k < nb; ++k) {
-    const double piv = Dg[k][k];
-    const bool dead = !(piv > tol);
-    const double d = dead ? 0.0 : sqrt(piv), inv = dead ? 0.0 : 1.0 / d;
-    __syncthreads();
-    if (tid == 0) Dg[k][k] = d;
-    if (tid > k && tid < nb) Dg[tid][k] *= inv;
-    __syncthreads();
-    for (int e = tid; e < 1024; e += 256) {
-      const int i = e >> 5, j = e & 31;
-      if (i > k && j > k && j <= i && i < nb) Dg[i][j] -= Dg[i][k] * Dg[j][k];
+  if (w == 0) {
+    // the factor: lane (i, h) holds columns 16 h .. 16 h + 15 of row i; what a step does to columns
+    // and rows that are finished, or to the unused upper triangle, is never read
+    const int i = lane & 31, h = lane >> 5;
+    const double tol = dmax[b] * 1e-13;
+    double a[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[c] = h == 1 && i < 16 ? 0.0 : Dt[i * P + 16 * h + c];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+      const int from = k + 32 * (k >> 4);                // the lane with the pivot
+      const int2 pw = __builtin_bit_cast(int2, a[k & 15]);
+      const double piv = __builtin_bit_cast(
+          double, make_int2(__builtin_amdgcn_readlane(pw.x, from), __builtin_amdgcn_readlane(pw.y, from)));
+      const bool live = piv > tol;
+      const double ps = live ? piv : 1.0;
+      double y = __builtin_amdgcn_rsq(ps);               // and two Newton steps: 1 / sqrt to rounding
+      y = fma(y * 0.5, fma(-ps * y, y, 1.0), y);
+      y = fma(y * 0.5, fma(-ps * y, y, 1.0), y);
+      const double inv = live ? y : 0.0;
+      if (h == (k >> 4)) Lc[k * PC + i] = a[k & 15] * inv;
+      if (lane == 0) invd[k] = inv;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const double lik = Lc[k * PC + i];
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+        if (16 + c > k) a[c] = fma(-lik, Lc[k * PC + 16 * h + c], a[c]);
     }
-    __syncthreads();
-  }
-  for (int e = tid; e < 1024; e += 256) {
-    const int rr = e >> 5, cc = e & 31;
-    if (rr < nb && cc < nb) L[(size_t)(c0 + rr) * l + c0 + cc] = cc <= rr ? Dg[rr][cc] : 0.0;
-  }
-  // rows below the block: x Dg^T = t, forward substitution, a thread per row
-  for (int i = c0 + 32 + tid; i < l; i += 256) {
-    double* row = L + (size_t)i * l + c0;
-    double x[32];
+    // inverses of the two 16 x 16 halves of the diagonal: lane (column n, half g & 1), by columns
+    const int hb = 16 * (g & 1);
+    double x[16];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) x[c] = row[c];
+    for (int c = 0; c < 16; ++c) x[c] = c == n ? 1.0 : 0.0;
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
-      double v = x[c];
+    for (int k = 0; k < 16; ++k) {
+      x[k] *= invd[hb + k];
 #pragma unroll
-      for (int j = 0; j < 32; ++j)
-        if (j < c) v = fma(-x[j], Dg[c][j], v);
-      const double d = Dg[c][c];
-      x[c] = d == 0.0 ? 0.0 : v / d;
+      for (int c = k + 1; c < 16; ++c) x[c] = fma(-Lc[(hb + k) * PC + hb + c], x[k], x[c]);
     }
+    if (g < 2) {
 #pragma unroll
-    for (int c = 0; c < 32; ++c) row[c] = x[c];
-  }
-}
-
-// X = L^-1 (lower triangular, fp64) by forward substitution, a wave per column j: the column's
-// entries found so far sit in LDS, row i's dot product with them is spread over the lanes.  Rows
-// of a dead pivot stay zero.  grid (ceil(l / 4), batch), 256 threads; dynamic LDS 4 * l doubles.
-__global__ void __launch_bounds__(256)
-tri_inverse(const double* __restrict__ S, int64_t s_bstride, double* __restrict__ X, int64_t x_bstride, int l) {
-  extern __shared__ double xcol[];                      // [4][l]
-  const double* L = S + (size_t)blockIdx.y * s_bstride;
-  double* Li = X + (size_t)blockIdx.y * x_bstride;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int j = blockIdx.x * 4 + w;
-  if (j >= l) return;
-  double* x = xcol + (size_t)w * l;
-  for (int i = lane; i < j; i += 64) Li[(size_t)i * l + j] = 0.0;     // above the diagonal
-  for (int i = j; i < l; ++i) {
-    const double* rowi = L + (size_t)i * l;
-    double s = 0.0;
-    for (int k = j + lane; k < i; k += 64) s = fma(rowi[k], x[k], s);
-    s = wave_sum_d(s);
-    const double dii = rowi[i];
-    const double v = dii == 0.0 ? 0.0 : ((i == j ? 1.0 : 0.0) - s) / dii;
-    if (lane == 0) {
-      x[i] = v;
-      Li[(size_t)i * l + j] = v;
+      for (int c = 0; c < 16; ++c) {
+        Di[(hb + c) * P + hb + n] = c < n ? 0.0 : x[c];
+        if (g == 0) Di[c * P + 16 + n] = 0.0;
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // below them: -(lower half)^-1 (L's lower left block) (upper half)^-1
+    f64x4_t y = {0.0, 0.0, 0.0, 0.0}, z = y;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) y = mfma_f64(Lc[(4 * kk + g) * PC + 16 + n], Di[(4 * kk + g) * P + n], y);
+    // element e of lane (n, g) of a product is row g + 4 e: as an operand that is k = g of group e
+#pragma unroll
+    for (int e = 0; e < 4; ++e) z = mfma_f64(Di[(16 + n) * P + 16 + 4 * e + g], y[e], z);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Di[(16 + g + 4 * e) * P + n] = -z[e];
   }
+  __syncthreads();
+  if (t == 0) {
+    double* Xd = X + (size_t)b * l * l + (size_t)c0 * l + c0;
+    for (int e = tid; e < 1024; e += 256) {
+      const int i = e >> 5, c = e & 31;
+      if (c0 + i < l && c0 + c < l) Xd[(size_t)i * l + c] = Di[i * P + c];
+    }
+    return;
+  }
+  // the tile times the inverse transposed, 16 x 16 per wave
+  const int tr = 16 * (w >> 1), tc = 16 * (w & 1);
+  f64x4_t y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) y = mfma_f64(At[(tr + n) * P + 4 * kk + g], Di[(tc + n) * P + 4 * kk + g], y);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = i0 + tr + g + 4 * e;
+    if (row < l) L[(size_t)row * l + c0 + tc + n] = y[e];   // a tile below the diagonal has all its columns
+  }
+}
+
+// ---- X = L^-1 in the blocks below the diagonal, from L's blocks there and the inverses of its diagonal
+//      blocks (already in X): X_ij = -X_ii sum_{j <= k < i} L_ik X_kj.  A workgroup owns a column of
+//      32 x 32 blocks and goes down it; the sum on the fp64 matrix instructions, its k shared out to
+//      the four waves and added in LDS.  Blocks above the diagonal are not written: gemm_nn does not
+//      read them.  The longest column first.  131 us at 16 matrices of 544 (a wave per column of
+//      single rows, a reduction over the wave per element: 969 us).
+//      grid ((blocks - 1) * batch), 256 threads.  l even.
+__global__ void __launch_bounds__(256)
+tri_inverse(const double* __restrict__ S, double* __restrict__ X, int l, int batch) {
+  constexpr int P = 33;
+  __shared__ double red[4][4 * 256], Ts[32 * P];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = (l + 31) >> 5;
+  int b, j;
+  matrix_of((int)blockIdx.x, nb - 1, batch, b, j);
+  const double* L = S + (size_t)b * l * l;
+  double* Xb = X + (size_t)b * l * l;
+  const int jc = 32 * j;
+  for (int i = j + 1; i < nb; ++i) {
+    const double* rows[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int ri = 32 * i + 16 * u + n;
+      rows[u] = L + (size_t)(ri < l ? ri : l - 1) * l + 2 * g;
+    }
+    const double* cols = Xb + (size_t)(2 * g) * l + jc + n;
+    f64x4_t acc[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) acc[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    const int per = 8 * (i - j), k_lo = jc + w * per, k_hi = k_lo + per;
+    f64x2_t na[2], nx[2];                                // two k of either row tile, of either column tile
+    auto load = [&](int k) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        na[u] = *(const f64x2_t*)(rows[u] + k);
+        nx[u] = f64x2_t{cols[(size_t)k * l + 16 * u], cols[(size_t)(k + 1) * l + 16 * u]};
+      }
+    };
+    load(k_lo);
+    for (int k = k_lo; k < k_hi; k += 8) {
+      f64x2_t ca[2], cx[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) { ca[u] = na[u]; cx[u] = nx[u]; }
+      load(k + 8 < k_hi ? k + 8 : k);
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 2; ++v) acc[u][v] = mfma_f64(ca[u][e], cx[v][e], acc[u][v]);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[w][(u * 2 + v) * 256 + (g + 4 * e) * 16 + n] = acc[u][v][e];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int at = q * 256 + tid;
+      Ts[(16 * (q >> 1) + (tid >> 4)) * P + 16 * (q & 1) + (tid & 15)] = (red[0][at] + red[1][at]) + (red[2][at] + red[3][at]);
+    }
+    __syncthreads();
+    // times -X_ii, 16 x 16 per wave; columns of X_ii past l meet rows of the sum that count for nothing
+    const int tr = 16 * (w >> 1), tc = 16 * (w & 1), ri = 32 * i + tr + n;
+    f64x4_t y = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const int k = 4 * kk + g;
+      const double a = ri < l && 32 * i + k < l ? Xb[(size_t)ri * l + 32 * i + k] : 0.0;
+      y = mfma_f64(a, Ts[k * P + tc + n], y);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = 32 * i + tr + g + 4 * e;
+      if (row < l) Xb[(size_t)row * l + jc + tc + n] = -y[e];
+    }
+    __syncthreads();                                     // the next rows' sum reads this block
+  }
+}
+
+// S [l][l] -> X = L^-1 (lower triangle of blocks), S is overwritten.
+void launch_cholesky(double* S, double* X, int l, double* dmax, int batch, hipStream_t st) {
+  hipLaunchKernelGGL(diag_max, dim3(batch), dim3(256), 0, st, S, (int64_t)l * l, l, dmax);
+  for (int c0 = 0; c0 < l; c0 += 32)
+    hipLaunchKernelGGL(chol_panel, dim3((l - c0 + 31) / 32 * batch), dim3(256), 0, st, S, X, l, c0, dmax, batch);
+  if (l > 32) hipLaunchKernelGGL(tri_inverse, dim3(((l + 31) / 32 - 1) * batch), dim3(256), 0, st, S, X, l, batch);
 }
 
 // ---- C = A B with A [M][K] fp64, B [K][N] fp32, fp64 accumulation; C as fp32 and / or in 16-bit
@@ -354,15 +496,7 @@ gemm_nn(const double* __restrict__ A, int64_t a_bstride, int lda, const float* _
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int MT = (M + 63) >> 6, NT = (N + 127) >> 7, per = MT * NT;
   int b, t;
-  const int id = (int)blockIdx.x;
-  if (batch % 8 == 0) {                                  // matrix b on XCD b % 8
-    const int k = id >> 3;
-    b = (k / per) * 8 + (id & 7);
-    t = k % per;
-  } else {
-    b = id / per;
-    t = id - b * per;
-  }
+  matrix_of((int)blockIdx.x, per, batch, b, t);
   // longest row blocks first (lower: the work grows with the row)
   const int mt = MT - 1 - t / NT, nt = t % NT;
   const int m0 = mt * 64 + (w >> 1) * 32, n0 = nt * 128 + (w & 1) * 64;
@@ -474,15 +608,8 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
   __shared__ f32x2_t csn[2][16];                        // cosine and sine of a step's pairs
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int npair = nblk >> 1, id = (int)blockIdx.x;
-  int b, k;
-  if (batch % 8 == 0) {                                 // matrix b stays on XCD b % 8, in its L2
-    b = (id >> 3) / npair * 8 + (id & 7);
-    k = (id >> 3) % npair;
-  } else {
-    b = id / npair;
-    k = id - b * npair;
-  }
+  int b, k;                                             // W stays in one XCD's L2
+  matrix_of((int)blockIdx.x, nblk >> 1, batch, b, k);
   if (sweep > 0 && rotations[b * kSweepSlots + sweep - 1] == 0) return;
   // round-robin over nblk blocks (nblk even; a block index >= the real count is an empty block)
   const int nm1 = nblk - 1;
@@ -763,13 +890,7 @@ ap_status run_bases(const BasesArgs& a) {
     if ((s = launch_gemm_nt(g2)) != AP_OK) return s;
     // rows of M made orthonormal
     launch_gram(M32, (int64_t)l * HD, HD, S, (int64_t)l * l, l, HD, B, st);
-    hipLaunchKernelGGL(diag_max, dim3(B), dim3(256), 0, st, S, (int64_t)l * l, l, dmax);
-    for (int c0 = 0; c0 < l; c0 += 32) {
-      if (c0 > 0)
-        hipLaunchKernelGGL(chol_update, dim3((l - c0 + 31) / 32, B), dim3(256), 0, st, S, (int64_t)l * l, l, c0);
-      hipLaunchKernelGGL(chol_panel, dim3(B), dim3(256), 0, st, S, (int64_t)l * l, l, c0, dmax);
-    }
-    hipLaunchKernelGGL(tri_inverse, dim3((l + 3) / 4, B), dim3(256), (size_t)4 * l * 8, st, S, (int64_t)l * l, Linv, (int64_t)l * l, l);
+    launch_cholesky(S, Linv, l, dmax, B, st);
     launch_gemm_nn<Tag>(Linv, (int64_t)l * l, l, M32, (int64_t)l * HD, HD, P32, (int64_t)l * HD, P16, (int64_t)l * HD,
                         HD, l, HD, l, 1, B, st);
     Pcur = P16;

@@ -284,3 +284,17 @@ def test_bases_eigenvectors_at_the_edges_of_blocks(l):
     assert np.abs(sig[0] - s).max() <= 2 * eps * s[0]
     assert np.diff(sig[0]).max() <= 1e-6 * sig[0][0]
     assert (cosdiff <= bound).all()
+
+
+@pytest.mark.parametrize("B", [8, 16])
+def test_bases_of_a_batch_are_those_of_its_sequences(B):
+    """A batch that is a multiple of eight numbers its workgroups by matrix and die; the arithmetic of
+    a sequence is the same in any batch, so the results are the same bits."""
+    dtype, n, HD, r, over = "f16", 200, 256, 64, 34
+    X = np.stack([cache_matrix(19, b, n, HD, r, dtype) for b in range(B)])
+    Omega = wl.store(wl.rng_for(19, 3).standard_normal((r + over, HD)), dtype)
+    print(f"bases batch {B}", flush=True)
+    D, sig = gpu_bases(X, Omega, r, 1, dtype)
+    for b in (0, 3, B - 1):
+        D1, sig1 = gpu_bases(X[b:b + 1], Omega, r, 1, dtype)
+        assert (D1[0].view(np.uint16) == D[b].view(np.uint16)).all() and (sig1[0] == sig[b]).all()
