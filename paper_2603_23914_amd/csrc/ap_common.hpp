@@ -158,8 +158,9 @@ ap_status launch_expand_append(ap_dtype dt, bool out_f32, const void* Bv, int64_
 ap_status launch_merge_splits(const float* part_ml, const float* part_U, float* out_ml, float* out_U,
                               float* pnew, const int* pnew_split, int B, int H, int r, int S,
                               hipStream_t stream);
+constexpr int kMergeExpandSplits = 256;   // the most that launch_merge_expand takes
 ap_status launch_merge_expand(ap_dtype dt, bool out_f32, const float* part_ml, const float* part_U,
-                              const void* Bv, int64_t bstride, void* out, float* lse, int B, int H,
+                              const void* Bv, int64_t bstride, void* out, float* lse, float* pout, int B, int H,
                               int H_kv, int d, int r, int nsplit, hipStream_t stream);
 ap_status launch_fold_heads(ap_dtype dt, const void* Bk, int64_t bstride, const void* q, void* Qp, int B,
                             int H, int H_kv, int Hp, int d, int r, float scale, hipStream_t stream);

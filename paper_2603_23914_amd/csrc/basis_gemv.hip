@@ -17,9 +17,24 @@
 // Products of two 16-bit values are exact in fp32; sums are fp32 (v_dot2c_f32_*).
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
+#include "mfma_ops.hpp"
+#include <cstdlib>
+#include <cstdio>
 
 namespace ap {
 namespace {
+
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+// A raw buffer over `bytes` bytes: loads past them return zeros and move nothing, without a branch.
+__device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t buffer_load16(buffer_t rsrc, uint32_t offset) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 0));
+}
+
+// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 struct RowsParams {
   const uint16_t* Bm;     // [B][r][HD] (bstride elements between sequences, 0 = shared)
@@ -218,108 +233,170 @@ fold_heads(const uint16_t* __restrict__ Bk, int64_t bstride, const uint16_t* __r
 }
 
 // ------------------------------------------------------------------------------------------
-// merge_expand: grid (ceil(H / 2), B), 256 threads.
+// merge_expand: a workgroup merges the token splits of ONE head over a slice of js columns and
+// expands that slice through its rows of B_v.  What bounds it is the chain of memory round trips,
+// so everything that does not depend on anything is requested at the start: the splits' (m, l)
+// pairs, the first splits' sums, the first eight rows of B_v per thread; the merge runs while the
+// rows arrive.  The loads go through buffers that end with the slice, so that no lane has a branch
+// and the waits stay exact.  Workgroups are numbered in runs per XCD: neighbouring heads, which
+// share the rows' pages, with a basis per sequence; the same head of all sequences with a shared
+// basis, which then stays in that XCD's L2.
+// Against two heads per workgroup, whose rows were requested after the merge, and a launch of its
+// own that merged more than sixteen splits (us a pass): eight sequences of 32 heads, rank 512, 32
+// splits 46.3 -> 39.3; sixteen of them with 16 splits 74.7 -> 70.8; one sequence, 256 splits 47.6 ->
+// 39.7; 64 sequences on one shared basis, rank 640 223 -> 218.
+// SLICED: several slices per head; their sums go to pout [B][nslice][H d], which reduce_out adds up.
+//   grid (B * H * nslice), NT threads, NT >= S, NT >= js / 4;
+//   dynamic LDS: weights [S], ustar [js], sums max(4 NT, NT / 64 d)
 // ------------------------------------------------------------------------------------------
-template <class Tag, bool OUT_F32, int kS>
-__global__ void __launch_bounds__(256)
-merge_expand(const float* __restrict__ part_ml, const float* __restrict__ part_U,
-             const uint16_t* __restrict__ Bv, int64_t bstride, void* __restrict__ out,
-             float* __restrict__ lse, int H, int G, int d, int r, int nsplit) {
-  extern __shared__ __attribute__((aligned(16))) char smem_me[];
-  float* ustar = (float*)smem_me;          // [2][r]
-  float* red = ustar + 2 * r;              // [rows][2 d]
-  const int h0 = blockIdx.x * 2, b = blockIdx.y, tid = threadIdx.x;
-  const int nh = H - h0 < 2 ? H - h0 : 2;  // heads of this workgroup
-  // ---- merged, normalised coefficient sums of the two heads.  At most kS (8 or 16) splits
-  //      arrive here (more are merged beforehand); every load of a thread is issued before the
-  //      first is used, so the prologue costs two memory round trips, not one per split.
-  for (int i = tid; i < nh * r; i += 256) {
-    const int hh = i >= r ? 1 : 0, j = i - hh * r;
-    const size_t pb = (size_t)b * nsplit * H + h0 + hh;    // + s*H
-    float ms[kS], ls[kS], us_[kS];
-#pragma unroll
-    for (int s = 0; s < kS; ++s) {
-      const size_t ps = pb + (size_t)(s < nsplit ? s : 0) * H;
-      ms[s] = part_ml[ps * 2];
-      ls[s] = part_ml[ps * 2 + 1];
-      us_[s] = part_U[ps * r + j];
-    }
-    float mstar = -INFINITY;
-#pragma unroll
-    for (int s = 0; s < kS; ++s) if (s < nsplit) mstar = fmaxf(mstar, ms[s]);
-    float L = 0.f, acc = 0.f;
-#pragma unroll
-    for (int s = 0; s < kS; ++s) {
-      if (s < nsplit) {
-        const float ws = fast_exp2(ms[s] - mstar);
-        L = fmaf(ls[s], ws, L);
-        acc = fmaf(ws, us_[s], acc);
-      }
-    }
-    ustar[hh * r + j] = acc / L;
-    if (j == 0 && lse) lse[(size_t)b * H + h0 + hh] = (mstar + log2f(L)) * kLn2;
+struct MergeExpandParams {
+  const float* part_ml;     // [B][S][H][2]
+  const float* part_U;      // [B][S][H][r]
+  const uint16_t* Bv;       // [B or 1][r][(H / G) d]
+  int64_t bstride;
+  void* out;                // [B][H][d]
+  float* lse;               // [B][H] or null
+  float* pout;              // SLICED: [B][nslice][H d]
+  int B, H, G, r, S, nslice, js;
+};
+
+template <class Tag, bool OUT_F32, bool SLICED, int NT, int LPR>
+__global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
+  constexpr int d = LPR * 8, ROWS = NT / LPR, NW = NT / 64;   // a row segment per LPR lanes
+  constexpr int kRows = 8, kU = 8;                            // loads in flight per thread of either kind
+  extern __shared__ __attribute__((aligned(16))) float smem_me[];
+  __shared__ float redw[2 * NW];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int S = p.S, H = p.H, r = p.r, js = p.js;
+  float* wgt = smem_me;                                       // [S rounded up to 4]
+  float* ustar = wgt + ((S + 3) & ~3);                        // [js]
+  float* sums = ustar + js;
+  // ---- which head, sequence, slice
+  const int total = p.B * H * p.nslice;
+  int id = (int)blockIdx.x;
+  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+  int b, h, sl;
+  if (p.bstride == 0) {
+    b = id % p.B;
+    const int t = id / p.B;
+    sl = t % p.nslice;
+    h = t / p.nslice;
+  } else {
+    h = id % H;
+    const int t = id / H;
+    sl = t % p.nslice;
+    b = t / p.nslice;
   }
-  __syncthreads();
-  // ---- expansion: thread (rg, cc) owns 8 columns of the 2d-wide slice and rows rg, rg+rows, ..
-  const int tpr = (2 * d) >> 3;            // threads per row segment: 8 .. 64
-  const int rows = 256 / tpr;
-  const int rg = tid / tpr, cc = tid - rg * tpr;
-  const bool live = cc * 8 < nh * d;       // an odd head count leaves the upper half idle
-  const float* us = ustar + (cc * 8 >= d ? r : 0);
-  // grouped queries: G consecutive query heads read the same d-wide slice of the basis rows
-  const size_t HD = (size_t)(H / G) * d;
-  const int hsel = cc * 8 >= d ? 1 : 0;
-  const uint16_t* Bb = Bv + (size_t)b * bstride + (size_t)((h0 + hsel) / G) * d + (cc * 8 - hsel * d);
+  const int j0 = sl * js;
+  // ---- requests: B_v rows, then (m, l), then the first sums
+  const int rg = tid / LPR, cc = tid % LPR;
+  const size_t HD = (size_t)(H / p.G) * d;
+  const uint16_t* Bb = p.Bv + (size_t)b * p.bstride + (size_t)j0 * HD + (size_t)(h / p.G) * d;
+  u32x4_t wv[kRows];
+  const uint32_t row_bytes = (uint32_t)HD * 2;
+  const auto brow = make_buffer(Bb, (uint32_t)(js - 1) * row_bytes + d * 2);
+  auto load_rows = [&](int j) {                               // rows j + k ROWS; zeros past the slice
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) wv[k] = buffer_load16(brow, (uint32_t)(j + k * ROWS) * row_bytes + cc * 16);
+  };
+  const size_t pb = (size_t)b * S * H + h;                    // + s H
+  const int nc4 = js >> 2, ngrp = NT / nc4;                   // four columns per thread, splits dealt to groups
+  const int grp = tid / nc4, c4 = tid - grp * nc4;
+  const uint32_t split_bytes = (uint32_t)H * r * 4;
+  const auto bsum = make_buffer(p.part_U + pb * r + j0, (uint32_t)(S - 1) * split_bytes + js * 4);
+  u32x4_t uv[kU];
+  auto load_sums = [&](int s0) {                              // splits s0 + grp + k ngrp; zeros past the last
+#pragma unroll
+    for (int k = 0; k < kU; ++k) uv[k] = buffer_load16(bsum, (uint32_t)(s0 + grp + k * ngrp) * split_bytes + 16 * c4);
+  };
+  const size_t ml0 = (pb + (size_t)(tid < S ? tid : 0) * H) * 2;
+  const f32x2_t ml = *(const f32x2_t*)(p.part_ml + ml0);
+  load_sums(0);
+  load_rows(rg);
+  // ---- weights 2^(m_s - m*) and their weighted sum of l
+  const float mv = tid < S ? ml[0] : -INFINITY;
+  float m = mv;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  if (lane == 0) redw[w] = m;
+  lds_barrier();
+  m = redw[0];
+#pragma unroll
+  for (int k = 1; k < NW; ++k) m = fmaxf(m, redw[k]);
+  float L = 0.f;
+  if (tid < S) {
+    const float ws = fast_exp2(mv - m);
+    wgt[tid] = ws;
+    L = ws * ml[1];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o);
+  if (lane == 0) redw[NW + w] = L;
+  lds_barrier();
+  L = redw[NW];
+#pragma unroll
+  for (int k = 1; k < NW; ++k) L += redw[NW + k];
+  if (p.lse && tid == 0 && sl == 0) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
+  // ---- ustar[j] = sum_s w_s U_s[j] / L: a group's splits in order, then the groups in order
+  f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};
+  auto add_sums = [&](int s0) {
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int s = s0 + grp + k * ngrp;
+      const float ws = s < S ? wgt[s] : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc4[e] = fmaf(ws, __builtin_bit_cast(f32x4_t, uv[k])[e], acc4[e]);
+    }
+  };
+  add_sums(0);
+  for (int s0 = kU * ngrp; s0 < S; s0 += kU * ngrp) {
+    load_sums(s0);
+    add_sums(s0);
+  }
+  if (grp < ngrp) *(f32x4_t*)(sums + grp * js + 4 * c4) = acc4;
+  lds_barrier();
+  for (int j = tid; j < js; j += NT) {
+    float a = sums[j];
+    for (int k = 1; k < ngrp; ++k) a += sums[k * js + j];
+    ustar[j] = a / L;
+  }
+  lds_barrier();
+  // ---- expansion: thread (rg, cc) owns 8 columns and rows rg, rg + ROWS, ..
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (live) {
-    int j = rg;
-    for (; j + 7 * rows < r; j += 8 * rows) {              // eight rows in flight
-      u32x4_t wv[8];
+  auto use_rows = [&](int j) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) wv[k] = *(const u32x4_t*)(Bb + (size_t)(j + k * rows) * HD);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float u = us[j + k * rows];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[2 * e] = fmaf(u, lo_to_f32(wv[k][e], Tag{}), acc[2 * e]);
-          acc[2 * e + 1] = fmaf(u, hi_to_f32(wv[k][e], Tag{}), acc[2 * e + 1]);
-        }
-      }
-    }
-    for (; j + 3 * rows < r; j += 4 * rows) {              // four rows in flight
-      u32x4_t wv[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wv[k] = *(const u32x4_t*)(Bb + (size_t)(j + k * rows) * HD);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float u = us[j + k * rows];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[2 * e] = fmaf(u, lo_to_f32(wv[k][e], Tag{}), acc[2 * e]);
-          acc[2 * e + 1] = fmaf(u, hi_to_f32(wv[k][e], Tag{}), acc[2 * e + 1]);
-        }
-      }
-    }
-    for (; j < r; j += rows) {
-      const u32x4_t wv = *(const u32x4_t*)(Bb + (size_t)j * HD);
-      const float u = us[j];
+    for (int k = 0; k < kRows; ++k) {
+      const int jj = j + k * ROWS;
+      const float u = jj < js ? ustar[jj] : 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        acc[2 * e] = fmaf(u, lo_to_f32(wv[e], Tag{}), acc[2 * e]);
-        acc[2 * e + 1] = fmaf(u, hi_to_f32(wv[e], Tag{}), acc[2 * e + 1]);
+        acc[2 * e] = fmaf(u, lo_to_f32(wv[k][e], Tag{}), acc[2 * e]);
+        acc[2 * e + 1] = fmaf(u, hi_to_f32(wv[k][e], Tag{}), acc[2 * e + 1]);
       }
     }
+  };
+  use_rows(rg);
+  for (int j = rg + kRows * ROWS; j < js; j += kRows * ROWS) {
+    load_rows(j);
+    use_rows(j);
   }
+  // the lanes of a wave that share columns, then the waves
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[rg * 2 * d + cc * 8 + e] = acc[e];
-  __syncthreads();
-  for (int i = tid; i < nh * d; i += 256) {
-    float sum = 0.f;
-    for (int k = 0; k < rows; ++k) sum += red[k * 2 * d + i];
-    const size_t o = ((size_t)b * H + h0) * d + i;
-    if (OUT_F32) ((float*)out)[o] = sum;
-    else ((uint16_t*)out)[o] = f32_to_bits(sum, Tag{});
+  for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], o);
+  if (lane < LPR) {
+    *(f32x4_t*)(sums + w * d + cc * 8) = f32x4_t{acc[0], acc[1], acc[2], acc[3]};
+    *(f32x4_t*)(sums + w * d + cc * 8 + 4) = f32x4_t{acc[4], acc[5], acc[6], acc[7]};
+  }
+  lds_barrier();
+  for (int i = tid; i < d; i += NT) {
+    float sum = sums[i];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) sum += sums[k * d + i];
+    if (SLICED) p.pout[((size_t)b * p.nslice + sl) * H * d + (size_t)h * d + i] = sum;
+    else if (OUT_F32) ((float*)p.out)[((size_t)b * H + h) * d + i] = sum;
+    else ((uint16_t*)p.out)[((size_t)b * H + h) * d + i] = f32_to_bits(sum, Tag{});
   }
 }
 
@@ -791,30 +868,61 @@ ap_status launch_expand_append(ap_dtype dt, bool out_f32, const void* Bv, int64_
   return AP_OK;
 }
 
+namespace {
+template <class Tag, bool OUT_F32, bool SLICED, int NT>
+void launch_me(const MergeExpandParams& p, int d, hipStream_t stream) {
+  const int grid = p.B * p.H * p.nslice;
+  const int most = 4 * NT > NT / 64 * d ? 4 * NT : NT / 64 * d;
+  const size_t lds = ((size_t)((p.S + 3) & ~3) + p.js + most) * 4;
+  switch (d) {
+    case 32: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 4>), dim3(grid), dim3(NT), lds, stream, p); break;
+    case 64: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 8>), dim3(grid), dim3(NT), lds, stream, p); break;
+    case 128: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 16>), dim3(grid), dim3(NT), lds, stream, p); break;
+    default: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 32>), dim3(grid), dim3(NT), lds, stream, p); break;
+  }
+}
+template <class Tag, bool OUT_F32>
+void launch_me_nt(const MergeExpandParams& p, int d, int nt, hipStream_t stream) {
+  if (p.nslice > 1) {
+    launch_me<Tag, OUT_F32, true, 256>(p, d, stream);
+    const int HD = p.H * d;
+    hipLaunchKernelGGL((reduce_out<Tag, OUT_F32>), dim3((HD + 1023) / 1024, p.B), dim3(256), 0, stream, p.pout, p.out, HD, p.nslice);
+  } else if (nt == 64) launch_me<Tag, OUT_F32, false, 64>(p, d, stream);
+  else if (nt == 128) launch_me<Tag, OUT_F32, false, 128>(p, d, stream);
+  else launch_me<Tag, OUT_F32, false, 256>(p, d, stream);
+}
+}  // namespace
+
+// pout: room for expand_row_blocks(B, r) slices of [B][H d] sums, or null (one slice per head then).
 ap_status launch_merge_expand(ap_dtype dt, bool out_f32, const float* part_ml, const float* part_U,
-                              const void* Bv, int64_t bstride, void* out, float* lse, int B, int H,
+                              const void* Bv, int64_t bstride, void* out, float* lse, float* pout, int B, int H,
                               int H_kv, int d, int r, int nsplit, hipStream_t stream) {
-  const int G = H / H_kv;
-  const int rows = 256 / ((2 * d) >> 3);
-  const size_t lds = ((size_t)2 * r + (size_t)rows * 2 * d) * 4;
-  const dim3 grid((H + 1) / 2, B);
-  const uint16_t* bv = (const uint16_t*)Bv;
-  if (nsplit > 16) {
-    set_error("merge_expand: %d splits (at most 16 are merged inline)", nsplit);
-    return AP_ERR_UNSUPPORTED;
-  }
-#define AP_ME(TAG, F32, KS) \
-  hipLaunchKernelGGL((merge_expand<TAG, F32, KS>), grid, dim3(256), lds, stream, part_ml, part_U, bv, bstride, out, lse, H, G, d, r, nsplit)
-#define AP_ME_KS(TAG, F32) do { if (nsplit <= 8) AP_ME(TAG, F32, 8); else AP_ME(TAG, F32, 16); } while (0)
+  AP_REQUIRE(nsplit >= 1 && nsplit <= kMergeExpandSplits && r % 4 == 0 && r <= 1024, AP_ERR_UNSUPPORTED,
+             "merge_expand: %d splits of rank %d (at most %d, and r %% 4 == 0, r <= 1024)", nsplit, r, kMergeExpandSplits);
+  // Slices of a head (and a launch more, which adds them up): once the sums of its splits are more
+  // than one workgroup pulls in while the launch would run.  Per pass with one slice / the slices
+  // chosen here: 256 splits of rank 512 28.7 / 24.6 us, 125 of 640 36.9 / 34.1; but 256 of 256
+  // 16.9 / 18.3, 85 of 448 31.5 / 33.3.
+  int nslice = 1;
+  if (pout && r % 64 == 0 && (int64_t)nsplit * r * 4 > 288 * 1024)
+    for (int k = 2; k <= 8; ++k)
+      if (r / 64 % k == 0 && k <= expand_row_blocks(B, r)) nslice = k;
+  // Threads: 256, but fewer where that leaves a thread few of a slice's rows.  Per pass at 256 / 128
+  // threads: rank 192 82.1 / 80.9 us (1280 workgroups), rank 320 with d = 64 43.2 / 42.2, rank 64
+  // 17.3 / 16.8 (32 workgroups) and 96.3 / 93.5 (2048; 92.4 at 64 threads); rank 512 70.7 / 71.3.
+  const int js = r / nslice, rows256 = js * (d / 8) / 256;
+  const int fit = nsplit > js / 4 ? nsplit : js / 4;      // a thread per split and per four columns at least
+  int nt = 256;
+  if (rows256 <= 12 && fit <= 128) nt = 128;
+  if (rows256 <= 4 && fit <= 64 && B * H >= 1024) nt = 64;
+  MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H / H_kv, r, nsplit, nslice, js};
   if (dt == AP_F16) {
-    if (out_f32) AP_ME_KS(F16Tag, true);
-    else AP_ME_KS(F16Tag, false);
+    if (out_f32) launch_me_nt<F16Tag, true>(p, d, nt, stream);
+    else launch_me_nt<F16Tag, false>(p, d, nt, stream);
   } else {
-    if (out_f32) AP_ME_KS(BF16Tag, true);
-    else AP_ME_KS(BF16Tag, false);
+    if (out_f32) launch_me_nt<BF16Tag, true>(p, d, nt, stream);
+    else launch_me_nt<BF16Tag, false>(p, d, nt, stream);
   }
-#undef AP_ME_KS
-#undef AP_ME
   return AP_OK;
 }
 

@@ -1477,9 +1477,9 @@ attn_partial(const AttnParams p) {
 // query needs no GPU.
 constexpr int kMaxTilesPerSplit = 128;   // bounds the LDS index table of rank-ragged launches
 constexpr int kMaxGroups = 8;
-constexpr int kInlineMergeSplits = 16;   // more splits than this are merged by their own kernel
-constexpr int kFusedInlineSplits = 16;   // the same limit inside a fused step (measured: merging
-                                         // 16 splits inline saves 6-8 us, merging 32 costs 5)
+constexpr int kFusedInlineSplits = 16;   // inside a fused step more splits than this are merged by
+                                         // their own kernel (measured: merging 16 splits inline
+                                         // saves 6-8 us, merging 32 costs 5)
 
 int choose_nsplit(int B, int T) {
   const int ntiles = (T + kTile - 1) / kTile;
@@ -1520,7 +1520,7 @@ WsLayout ws_layout(int B, int H, int d, int T, int r) {
   w.mml = off;                             // many splits: merged (m, l) and U as a single split
   off += round_up((size_t)B * H * 2 * 4, 256);
   w.mu = off;
-  off += S > kInlineMergeSplits ? round_up((size_t)B * H * r * 4, 256) : 0;
+  off += S > kFusedInlineSplits ? round_up((size_t)B * H * r * 4, 256) : 0;
   w.total = off;
   return w;
 }
@@ -1721,10 +1721,9 @@ ap_status run_decode(const DecodeArgs& a) {
     st = dispatch_attn<Tag, SPLIT>(p, a.B, a.stream);
   if (st != AP_OK) return st;
   int S_exp = S;
-  // many splits (small batches): merge_expand takes at most kInlineMergeSplits, so they are merged
-  // by a kernel of their own first; the fused step's expansion merges up to kFusedInlineSplits
-  // itself (its row blocks partition the columns, so no column is merged twice)
-  if (S > (one_pass_v ? kFusedInlineSplits : kInlineMergeSplits)) {
+  // many splits: merge_expand merges them itself (up to its limit), the fused step's expansion up to
+  // kFusedInlineSplits (its row blocks partition the columns, so no column is merged twice)
+  if (S > (one_pass_v ? kFusedInlineSplits : kMergeExpandSplits)) {
     float* ml1 = (float*)(ws + wl.mml);
     float* U1 = (float*)(ws + wl.mu);
     st = launch_merge_splits(ml, U, ml1, U1, one_pass_v ? (float*)(ws + wl.pn) : nullptr,
@@ -1741,7 +1740,7 @@ ap_status run_decode(const DecodeArgs& a) {
                               a.out, a.lse, a.B, a.H, a.d, a.r, a.T, a.T_cap, S_exp, a.stream);
   else
     st = launch_merge_expand(a.dt, a.dt_out == AP_F32, ml, U, a.Bv, a.basis_batch_stride, a.out, a.lse,
-                             a.B, a.H, Hkv, a.d, a.r, S_exp, a.stream);
+                             (float*)(ws + wl.po), a.B, a.H, Hkv, a.d, a.r, S_exp, a.stream);
   if (st != AP_OK) return st;
   return check_launch("ap_decode_attn");
 }

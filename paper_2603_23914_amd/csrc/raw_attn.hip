@@ -755,7 +755,7 @@ ap_status launch_valueonly_attn(const void* q, const void* K, const void* Cv, co
     if (st != AP_OK) return st;
     ml = ml1; U = U1; S_exp = 1;
   }
-  st = launch_merge_expand(dt, true, ml, U, Bv, bstride, out, lse, B, H, H_kv, d, r, S_exp, stream);
+  st = launch_merge_expand(dt, true, ml, U, Bv, bstride, out, lse, nullptr, B, H, H_kv, d, r, S_exp, stream);
   if (st != AP_OK) return st;
   return check_launch("ap_valueonly_attn");
 }

@@ -216,3 +216,31 @@ def test_bf16_output_is_the_fp32_result_rounded_once(B, H, d, r, T, fused, value
     ref = oracle.decode_attn_batched(P(q), P(Ck_h), P(Cv_h), P(case.Bk), P(case.Bv), T, absorbed=True)
     err = np.abs(to_host64(outs[1]) - ref)
     assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-3 * np.abs(ref).max()).all(), err.max()
+
+
+@pytest.mark.parametrize("dtype,B,H,d,r,T,shared", [
+    ("f16", 1, 32, 128, 512, 5000, False),      # 157 splits of 512: eight slices per head
+    ("bf16", 1, 10, 64, 640, 8192, False),       # 256 splits of 640: five slices, 256 splits = one per thread
+    ("bf16", 2, 40, 128, 640, 4100, True),      # five slices on a shared basis
+    ("f16", 1, 14, 32, 448, 5300, False),        # seven slices, 98 workgroups (not a multiple of eight)
+    ("f16", 1, 32, 128, 512, 4600, False),      # just below the bound: one slice, 144 splits
+    ("bf16", 64, 16, 128, 64, 130, False),      # one wave per head
+    ("f16", 64, 16, 256, 64, 40, True),         # the same with d = 256 on a shared basis
+    ("f16", 2, 9, 128, 192, 1000, False),       # two waves per head
+    ("bf16", 1, 3, 32, 64, 8192, False),        # small rank, more splits than two waves have threads
+])
+def test_merge_and_expansion_forms(dtype, B, H, d, r, T, shared):
+    """merge_expand by its rule: slices per head, threads per workgroup, the numbering of shared
+    bases; sequences 0 and B - 1 against the oracle, all of them bit for bit in a second run."""
+    case = wl.decode_case(dtype, B, H, d, r, T, steps=0, seed=23, shared_basis=shared, append=False)
+    q = wl.step_query(case, 0)
+    print(f"merge forms {dtype} B={B} H={H} d={d} r={r} T={T} shared={shared}", flush=True)
+    got, lse = run_half(dtype, q, case.Ck, case.Cv, case.Bk, case.Bv, T, want_lse=True)
+    again = run_half(dtype, q, case.Ck, case.Cv, case.Bk, case.Bv, T)
+    assert (got == again).all()
+    P = lambda x: oracle.promote(x, dtype)
+    for b in sorted({0, B - 1}):
+        Bk, Bv = (case.Bk, case.Bv) if shared else (case.Bk[b], case.Bv[b])
+        ref, ref_lse = oracle.decode_attn_absorbed(P(q)[b], P(case.Ck)[b, :T], P(case.Cv)[b, :T], P(Bk), P(Bv), return_lse=True)
+        assert_close(got[b:b + 1], ref[None], dtype, f"b={b}")
+        assert np.abs(lse[b] - ref_lse).max() < 2e-3 * max(1.0, np.abs(ref_lse).max())
