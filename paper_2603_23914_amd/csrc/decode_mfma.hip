@@ -29,6 +29,7 @@
 #include <hip/hip_ext.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 namespace ap {
 namespace {
@@ -156,7 +157,8 @@ __device__ __forceinline__ void score_tile(const u32x4_t (&A)[NKW][2],
 // e of chunk g', so the 16 lanes of a row group read 64 contiguous bytes and the four row
 // groups fall on different banks (no LDS bank conflicts).  vA / vB: rows 0-15 / 16-31 of
 // the tile, already offset to this lane's dword.
-template <class Tag, int MT, bool SPLIT, int NGL>
+// Column groups I0 .. I1-1 only; the rescaling goes with the first part.
+template <class Tag, int MT, bool SPLIT, int NGL, int I0 = 0, int I1 = NGL>
 __device__ __forceinline__ void wsum_tile(const char* vA, const char* vB, int pitch,
                                           int cols_left, int n, const u32x4_t (&Phi)[MT],
                                           const u32x4_t (&Plo)[MT], const float (&alpha)[MT],
@@ -166,7 +168,7 @@ __device__ __forceinline__ void wsum_tile(const char* vA, const char* vB, int pi
   // are fetched while group i is multiplied
   // alpha is 1 except when a head's softmax reference exponent moved (rare: the reference
   // follows the maximum lazily), so the rescaling of the sums is skipped wave-wide otherwise
-  {
+  if constexpr (I0 == 0) {
     bool moved = false;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) moved |= alpha[mt] != 1.0f;
@@ -178,20 +180,20 @@ __device__ __forceinline__ void wsum_tile(const char* vA, const char* vB, int pi
     }
   }
   uint32_t nx[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (n * 2 < cols_left) {
+  if (I0 < I1 && I0 * 128 + n * 2 < cols_left) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      nx[e] = *(const uint32_t*)(vA + e * pitch);
-      nx[4 + e] = *(const uint32_t*)(vB + e * pitch);
+      nx[e] = *(const uint32_t*)(vA + e * pitch + I0 * 256);
+      nx[4 + e] = *(const uint32_t*)(vB + e * pitch + I0 * 256);
     }
   }
 #pragma unroll
-  for (int i = 0; i < NGL; ++i) {
+  for (int i = I0; i < I1; ++i) {
     if (i * 128 >= cols_left) break;         // wave-uniform: the group lies beyond the value rank
     uint32_t v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) { v[e] = nx[e]; nx[e] = 0; }
-    if (i + 1 < NGL && (i + 1) * 128 + n * 2 < cols_left) {
+    if (i + 1 < I1 && (i + 1) * 128 + n * 2 < cols_left) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         nx[e] = *(const uint32_t*)(vA + e * pitch + (i + 1) * 256);
@@ -271,14 +273,14 @@ __device__ __forceinline__ void score_tile_i8(const u32x4_t (&Araw)[NBW][2],
 // The codes enter the product as exact integers; a token's scale for the block is folded into
 // its softmax weight in fp32 (P32: the lane's eight weights per head tile, tokens 4g .. 4g+3
 // and 16+4g .. +3), and that product is rounded to fp16 once.
-template <int MT, int NGL>
+template <int MT, int NGL, int I0 = 0, int I1 = NGL>
 __device__ __forceinline__ void wsum_tile_i8(const char* vA, const char* vB, int pitch, int r,
                                              int cp, int g, const uint16_t* vs,
                                              const f32x4_t (&P32)[MT][2], const float (&alpha)[MT],
                                              f32x4_t (&U)[NGL][4][MT]) {
   // alpha is 1 except when a head's softmax reference exponent moved (rare): the rescaling of
   // the sums is skipped wave-wide otherwise, as in wsum_tile
-  {
+  if constexpr (I0 == 0) {
     bool moved = false;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) moved |= alpha[mt] != 1.0f;
@@ -292,7 +294,7 @@ __device__ __forceinline__ void wsum_tile_i8(const char* vA, const char* vB, int
     }
   }
 #pragma unroll
-  for (int i = 0; i < NGL; ++i) {
+  for (int i = I0; i < I1; ++i) {
     const int blk = 4 * i + cp;
     uint32_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     u32x2_t s01 = {0, 0}, s23 = {0, 0};
@@ -335,14 +337,14 @@ __device__ __forceinline__ void wsum_tile_i8(const char* vA, const char* vB, int
 // of the block, so all sixteen rows of a product share one scale block and the token's scale can
 // be folded into its weight as for int8.  vA / vB: rows 0-15 / 16-31 of the tile, offset to the
 // lane's token rows only.
-template <int MT, int NGL>
+template <int MT, int NGL, int I0 = 0, int I1 = NGL>
 __device__ __forceinline__ void wsum_tile_i4(const char* vA, const char* vB, int pitch, int r,
                                              int cp, int n, int g, const uint16_t* vs,
                                              const f32x4_t (&P32)[MT][2], const float (&alpha)[MT],
                                              f32x4_t (&U)[NGL][4][MT]) {
   const int doff = (n & 7) * 4;              // this row's dword inside a block
   const int sh0 = 16 * (n >> 3);             // its first nibble
-  {                                          // rescale only when a reference exponent moved (rare)
+  if constexpr (I0 == 0) {                   // rescale only when a reference exponent moved (rare)
     bool moved = false;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) moved |= alpha[mt] != 1.0f;
@@ -356,7 +358,7 @@ __device__ __forceinline__ void wsum_tile_i4(const char* vA, const char* vB, int
     }
   }
 #pragma unroll
-  for (int i = 0; i < NGL; ++i) {
+  for (int i = I0; i < I1; ++i) {
     {
       const int blk = 4 * i + cp;
       uint32_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -512,7 +514,7 @@ template <class Tag, int MT, bool SPLIT, bool RAGGED, int Q, bool TS = false>
 struct WaveCtx {
   static constexpr bool I8 = Q != 0, I4 = Q == 2;
   static constexpr int NSUB = TS ? 4 : 1;   // tiles per barrier pair
-  static constexpr int HPW = 2 * MT;     // heads finalised per wave
+  static constexpr int HPW = TS ? 2 * MT : 4 * MT;   // heads finalised per wave (token-split: all eight)
   // bytes of a coefficient row
   static __device__ __forceinline__ int row_bytes_of(int r) { return I4 ? r >> 1 : (I8 ? r : 2 * r); }
 
@@ -537,10 +539,12 @@ struct WaveCtx {
   float* scores;     // this sequence's [T_cap][H] logits, or null
   int T_cap;
   // softmax ownership: lane = 8*head_local + slot, slot = 4*tt + gg covers tokens
-  // 16*tt + 4*gg .. +3 of the tile for head o_hh
-  bool owner;
-  int o_hh, o_tt, o_gg, o_mt, o_lane;
-  float m_ref, l_part;
+  // 16*tt + 4*gg .. +3 of the tile for head o_hh.  Token-split mode: 2*MT heads for each of the eight
+  // waves.  Otherwise 4*MT heads for each score wave, eight at a time (NP passes).
+  static constexpr int NP = TS ? 1 : (MT + 1) / 2;
+  bool owner[NP];
+  int o_hh[NP], o_tt, o_gg;
+  float m_ref[NP], l_part[NP];
 
   __device__ __forceinline__ void init(const AttnParams& p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -592,11 +596,14 @@ struct WaveCtx {
       meta = idxb + uni(p.ntl_cap) * kTile;
       build_tile_table(p);
     }
-    owner = lane < 8 * HPW;
-    o_hh = w * HPW + (lane >> 3);
     o_tt = (lane >> 2) & 1; o_gg = lane & 3;
-    o_mt = o_hh >> 4; o_lane = (o_hh & 15) + 16 * o_gg;
-    m_ref = -INFINITY; l_part = 0.f;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int hl = 8 * q + (lane >> 3);
+      owner[q] = hl < HPW && (TS || w < 4);
+      o_hh[q] = owner[q] ? w * HPW + hl : 0;
+      m_ref[q] = -INFINITY; l_part[q] = 0.f;
+    }
   }
 
   // RAGGED: tiles of this split, their token indices and ranks into LDS (all 512 threads).
@@ -687,89 +694,101 @@ struct WaveCtx {
     return nl < tile_valid(t) ? nl : -1;
   }
 
-  // Softmax of this wave's heads for a tile whose first `valid` slots hold tokens (after
+  // Softmax of this score wave's heads for a tile whose first `valid` slots hold tokens (after
   // the score waves' partial tiles are in xchg).  newl: slot of the deferred token, if any:
-  // its weight counts in the sum, is exported, and stays out of the value products.
-  // sub: which of the NSUB tiles of this barrier pair (its scores sit in slot `sub` of xchg,
-  // its weights go to slot `sub` of Pbuf / abuf).
-  __device__ __forceinline__ void finalize_softmax(int valid, int newl, int t, int sub = 0) {
-    if (!owner) return;
-    const int xi = o_hh * 9 + (lane & 7);
-    f32x4_t sc;
-    if (TS) {
-      sc = xchg[sub * 16 * MT * 9 + xi];          // complete: one wave scored the whole rank axis
-    } else {
-      sc = xchg[xi];
+  // its weight counts in the sum, is exported, and stays out of the value products.  The passes
+  // are independent: all read before any writes.
+  __device__ __forceinline__ void finalize_softmax(int valid, int newl, int t) {
+    f32x4_t sc[NP];
 #pragma unroll
-      for (int sw = 1; sw < 4; ++sw) sc += xchg[sw * 16 * MT * 9 + xi];
+    for (int q = 0; q < NP; ++q) {
+      const int xi = o_hh[q] * 9 + (lane & 7);
+      sc[q] = xchg[xi];
+#pragma unroll
+      for (int sw = 1; sw < 4; ++sw) sc[q] += xchg[sw * 16 * MT * 9 + xi];
     }
-    if (scores && o_hh < H) {                   // logits out, for importance tracking: [token][head]
-      const int slot = 16 * o_tt + 4 * o_gg;
+    const int slot = 16 * o_tt + 4 * o_gg;
+    if (scores) {                               // logits out, for importance tracking: [token][head]
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (slot + i < valid) {
-          const int tok = RAGGED ? idxb[t * kTile + slot + i] : tok0(t) + slot + i;
-          scores[(size_t)tok * H + o_hh] = sc[i] * kLn2;
+      for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (owner[q] && o_hh[q] < H && slot + i < valid) {
+            const int tok = RAGGED ? idxb[t * kTile + slot + i] : tok0(t) + slot + i;
+            scores[(size_t)tok * H + o_hh[q]] = sc[q][i] * kLn2;
+          }
         }
-      }
     }
     if (valid < kTile) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (16 * o_tt + 4 * o_gg + i >= valid) sc[i] = -INFINITY;
+      for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (slot + i >= valid) sc[q][i] = -INFINITY;
     }
-    float tmax = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-    tmax = max8(tmax);
-    float alpha = 1.0f;
-    if (tmax > m_ref + kLazy) {                 // same decision in the 8 lanes of a head
-      const float m_upd = fmaxf(m_ref, tmax);   // finite: every tile holds a valid token
-      alpha = fast_exp2(m_ref - m_upd);
-      m_ref = m_upd;
-      l_part *= alpha;
+    float alpha[NP], pr[NP][4], pdef[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      float tmax = fmaxf(fmaxf(sc[q][0], sc[q][1]), fmaxf(sc[q][2], sc[q][3]));
+      tmax = max8(tmax);
+      // the same decision in the 8 lanes of a head; the new reference is finite: every tile holds
+      // a valid token
+      const bool move = tmax > m_ref[q] + kLazy;
+      const float m_upd = move ? fmaxf(m_ref[q], tmax) : m_ref[q];
+      alpha[q] = move ? fast_exp2(m_ref[q] - m_upd) : 1.0f;
+      m_ref[q] = m_upd;
+      l_part[q] *= alpha[q];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pr[q][i] = fast_exp2(sc[q][i] - m_upd);
+      pdef[q] = 0.f;
     }
-    float p0 = fast_exp2(sc[0] - m_ref), p1 = fast_exp2(sc[1] - m_ref);
-    float p2 = fast_exp2(sc[2] - m_ref), p3 = fast_exp2(sc[3] - m_ref);
-    float pdef = 0.f;
     if (newl >= 0 && newl < kTile) {            // wave-uniform: this tile holds the deferred token
-      const int li = newl - (16 * o_tt + 4 * o_gg);
-      if (li == 0) { pdef = p0; p0 = 0.f; }
-      if (li == 1) { pdef = p1; p1 = 0.f; }
-      if (li == 2) { pdef = p2; p2 = 0.f; }
-      if (li == 3) { pdef = p3; p3 = 0.f; }
-      if (li >= 0 && li < 4 && o_hh < H) {
-        pnew[(size_t)b * H + o_hh] = pdef;
-        if (o_hh == 0) pnew_split[b] = s;
+      const int li = newl - slot;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (li == i) { pdef[q] = pr[q][i]; pr[q][i] = 0.f; }
+        if (owner[q] && li >= 0 && li < 4 && o_hh[q] < H) {
+          pnew[(size_t)b * H + o_hh[q]] = pdef[q];
+          if (o_hh[q] == 0) pnew_split[b] = s;
+        }
       }
     }
-    u32x2_t hi, lo = {0, 0};
-    hi[0] = cvt_pack(p0, p1, Tag{});
-    hi[1] = cvt_pack(p2, p3, Tag{});
-    float k0 = lo_to_f32(hi[0], Tag{}), k1 = hi_to_f32(hi[0], Tag{});
-    float k2 = lo_to_f32(hi[1], Tag{}), k3 = hi_to_f32(hi[1], Tag{});
-    if (SPLIT) {
-      lo[0] = cvt_pack(p0 - k0, p1 - k1, Tag{});
-      lo[1] = cvt_pack(p2 - k2, p3 - k3, Tag{});
-      k0 += lo_to_f32(lo[0], Tag{});
-      k1 += hi_to_f32(lo[0], Tag{});
-      k2 += lo_to_f32(lo[1], Tag{});
-      k3 += hi_to_f32(lo[1], Tag{});
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int mt = o_hh[q] >> 4, ln = (o_hh[q] & 15) + 16 * o_gg;
+      if (I8) {
+        // int8 coefficients: the weights stay fp32 (the sum waves fold the value scales in before
+        // rounding); the two 16-byte slots of a lane hold tokens 4g .. 4g+3 and 16+4g .. +3
+        l_part[q] += (pr[q][0] + pr[q][1]) + (pr[q][2] + pr[q][3]);
+        const f32x4_t pv = {pr[q][0], pr[q][1], pr[q][2], pr[q][3]};
+        if (owner[q]) *(f32x4_t*)(Pbuf + (mt * 2 + o_tt) * 64 + ln) = pv;
+      } else {
+        u32x2_t hi, lo = {0, 0};
+        hi[0] = cvt_pack(pr[q][0], pr[q][1], Tag{});
+        hi[1] = cvt_pack(pr[q][2], pr[q][3], Tag{});
+        float k0 = lo_to_f32(hi[0], Tag{}), k1 = hi_to_f32(hi[0], Tag{});
+        float k2 = lo_to_f32(hi[1], Tag{}), k3 = hi_to_f32(hi[1], Tag{});
+        if (SPLIT) {
+          lo[0] = cvt_pack(pr[q][0] - k0, pr[q][1] - k1, Tag{});
+          lo[1] = cvt_pack(pr[q][2] - k2, pr[q][3] - k3, Tag{});
+          k0 += lo_to_f32(lo[0], Tag{});
+          k1 += hi_to_f32(lo[0], Tag{});
+          k2 += lo_to_f32(lo[1], Tag{});
+          k3 += hi_to_f32(lo[1], Tag{});
+        }
+        l_part[q] += (k0 + k1) + (k2 + k3) + pdef[q];   // the sum uses the values the MFMA will see
+        // weights in B-operand layout: lane (n, g) of head tile mt holds tokens 4g..4g+3
+        // (dwords 0,1) and 16+4g..+3 (dwords 2,3)
+        u32x2_t* ph = (u32x2_t*)(Pbuf + (mt * 2) * 64 + ln) + o_tt;
+        if (owner[q]) {
+          *ph = hi;
+          if (SPLIT) *(ph + 2 * 64) = lo;               // [mt][1][ln]
+        }
+      }
+      if (owner[q] && (lane & 7) == 0) abuf[o_hh[q]] = alpha[q];
     }
-    if (I8) {
-      // int8 coefficients: the weights stay fp32 (the sum waves fold the value scales in before
-      // rounding); the two 16-byte slots of a lane hold tokens 4g .. 4g+3 and 16+4g .. +3
-      l_part += (p0 + p1) + (p2 + p3);
-      const f32x4_t pv = {p0, p1, p2, p3};
-      *(f32x4_t*)(Pbuf + ((sub * MT + o_mt) * 2 + o_tt) * 64 + o_lane) = pv;
-      if ((lane & 7) == 0) abuf[sub * 16 * MT + o_hh] = alpha;
-      return;
-    }
-    l_part += (k0 + k1) + (k2 + k3) + pdef;     // the sum uses the values the MFMA will see
-    // weights in B-operand layout: lane (n, g) of head tile mt holds tokens 4g..4g+3
-    // (dwords 0,1) and 16+4g..+3 (dwords 2,3)
-    u32x2_t* ph = (u32x2_t*)(Pbuf + ((sub * MT + o_mt) * 2 + 0) * 64 + o_lane) + o_tt;
-    *ph = hi;
-    if (SPLIT) *(ph + 2 * 64) = lo;             // [sub][o_mt][1][o_lane]
-    if ((lane & 7) == 0) abuf[sub * 16 * MT + o_hh] = alpha;
   }
 
   // Token-split mode: the softmax of the four tiles t0 .. t0+3 of a round in one go (one
@@ -777,7 +796,10 @@ struct WaveCtx {
   // instead of four dependent passes.  The rescale factor goes with the first tile; the
   // other three carry 1.
   __device__ __forceinline__ void finalize_softmax4(int t0) {
-    if (!owner) return;
+    if (!owner[0]) return;
+    const int o_hh = this->o_hh[0], o_mt = o_hh >> 4, o_lane = (o_hh & 15) + 16 * o_gg;
+    float& m_ref = this->m_ref[0];
+    float& l_part = this->l_part[0];
     const int xi = o_hh * 9 + (lane & 7);
     const int slot = 16 * o_tt + 4 * o_gg;       // this lane's first token slot in a tile
     f32x4_t sc[4];
@@ -851,11 +873,14 @@ struct WaveCtx {
 
   // (reference exponent, sum) of the heads this wave finalised.
   __device__ __forceinline__ void store_ml(float* part_ml) {
-    const float l_tot = sum8(l_part);
-    if (owner && (lane & 7) == 0 && o_hh < H) {
-      const size_t pb = ((size_t)b * nsplit + s) * H + o_hh;
-      part_ml[pb * 2 + 0] = m_ref;
-      part_ml[pb * 2 + 1] = l_tot;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const float l_tot = sum8(l_part[q]);
+      if (owner[q] && (lane & 7) == 0 && o_hh[q] < H) {
+        const size_t pb = ((size_t)b * nsplit + s) * H + o_hh[q];
+        part_ml[pb * 2 + 0] = m_ref[q];
+        part_ml[pb * 2 + 1] = l_tot;
+      }
     }
   }
 };
@@ -1077,8 +1102,8 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
     return;
   }
   AP_T_START
-  // One tile: scores from the rows in A, then the same registers take the rows of tile t + lead.
-  auto tile_step = [&](int t, u32x4_t (&A)[NA][2], int lead) {
+  // One tile: scores from the rows in A, then the same registers take the rows of tile t + 1.
+  auto tile_step = [&](int t) {
     AP_T_STAMP(t)
     f32x4_t sp[MT][2];
 #pragma unroll
@@ -1100,7 +1125,7 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
     }
     if constexpr (I8) {
       // hand tile t's value scales to the sum waves (buffer t&1: its previous reader, the
-      // weighted sum of tile t-2, ended before the barrier this wave passed in tile t-1)
+      // weighted sum of tile t-2, ended before the last barrier of tile t-1)
       uint16_t* vs = cx.vsb + (t & 1) * nsb * kTile;
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -1115,12 +1140,12 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       if (!(cx.dbg & 2)) score_tile<Tag, MT, SPLIT, NKW>(A, qhi, qlo, sp, nlive);
     }
     AP_TICK(1)
-    if (t + lead < cx.ntl) load_A(t + lead, A);           // lands while the tile(s) in between are finished
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       cx.xchg[(w * 16 * MT + mt * 16 + n) * 9 + g] = sp[mt][0];
       cx.xchg[(w * 16 * MT + mt * 16 + n) * 9 + 4 + g] = sp[mt][1];
     }
+    if (t + 1 < cx.ntl) load_A(t + 1, A);                 // lands while the tile is finished
     wg_barrier();                                         // partial scores of tile t ready
     AP_TICK(2)
     cx.finalize_softmax(cx.tile_valid(t), cx.tile_new(t), t);
@@ -1129,7 +1154,7 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
     AP_TICK(4)
   };
   if (cx.ntl > 0) load_A(0, A);
-  for (int t = 0; t < cx.ntl; ++t) tile_step(t, A, 1);
+  for (int t = 0; t < cx.ntl; ++t) tile_step(t);
   AP_T_STAMP(62)
   cx.store_ml(part_ml);
   AP_TICK(6)
@@ -1195,8 +1220,8 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
     const int nb = (kHalf * (tile_chunks(lt) + 1) + 63) >> 6;
     return nb > cp ? (nb - cp + 3) >> 2 : 0;
   };
-  // both 16-row units of local tile lt into ring slots 2*(lt % RT), +1
-  auto issue_tile = [&](int lt) {
+  // one 16-row unit of local tile lt into ring slot 2*(lt % RT) + half
+  auto issue_half = [&](int lt, int half) {
     if (cx.dbg & 1) return;
     const int slot0 = 2 * (lt % RT);
     if (RAGGED) {
@@ -1205,8 +1230,7 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       // chunk L of a unit is (row L / cw, chunk L % cw): L < 1344 and cw <= 81, so the quotient
       // is exact as (L * ceil(2^20 / cw)) >> 20
       const uint32_t magic = ((1u << 20) + (uint32_t)cw - 1u) / (uint32_t)cw;
-#pragma nounroll
-      for (int half = 0; half < 2; ++half) {
+      {
         char* dst = cx.ring + (slot0 + half) * cx.unit_bytes;
         const int* ix = cx.idxb + lt * kTile + half * kHalf;
 #pragma unroll
@@ -1226,8 +1250,7 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       }
       return;
     }
-#pragma nounroll
-    for (int half = 0; half < 2; ++half) {
+    {
       const int tok_u = cx.tok0(lt) + half * kHalf;
       char* dst = cx.ring + (slot0 + half) * cx.unit_bytes;
       const uint32_t base = (uint32_t)tok_u * cx.row_bytes;
@@ -1251,6 +1274,10 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
         }
       }
     }
+  };
+  auto issue_tile = [&](int lt) {
+#pragma nounroll
+    for (int half = 0; half < 2; ++half) issue_half(lt, half);
   };
   // Only the first tile is requested up front: the rest of the ring is filled once the score
   // waves have their first tile, so the folded query and the first key tile (which everything
@@ -1313,71 +1340,89 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       AP_TICK(5)
     }
   } else {
-  for (int t = 0; t < cx.ntl; ++t) {
-    AP_T_STAMP(t)
-    wg_barrier();            // partial scores of tile t ready; every sum wave is past tile t-1
-    AP_TICK(2)
-    if (t == 0) {
-#pragma nounroll
-      for (int lt = 1; lt < RT && lt < cx.ntl; ++lt) issue_tile(lt);
-    } else if (t - 1 + RT < cx.ntl) {
-      issue_tile(t - 1 + RT);                                    // refill tile t-1's slots
-    }
-    cx.finalize_softmax(cx.tile_valid(t), cx.tile_new(t), t);
-    AP_TICK(3)
-    {
-      // tile t's rows must have landed; the tiles issued after it may stay in flight
-      int later = cx.ntl - t - 1;
-      later = later < RT - 1 ? later : RT - 1;
-      if (RAGGED) {
-        int pending = 0;
-        for (int lt = t + 1; lt <= t + later; ++lt) pending += 2 * tile_requests(lt);
-        wait_vmcnt(pending);
-      } else {
-        wait_vmcnt(later * 2 * n_issue);
-      }
-    }
-    wg_barrier();            // weights of tile t ready; tile t's rows visible to every wave
-    AP_TICK(4)
+    // ---- the weighted sum of tile t - 1 runs while the score waves score tile t (first part, up to
+    // the "partial scores ready" barrier) and take its softmax (second part)
     u32x4_t Phi[MT], Plo[MT];
+    f32x4_t P32[I8 ? MT : 1][2];
     float alpha[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      alpha[mt] = cx.abuf[mt * 16 + n];
-      Phi[mt] = cx.Pbuf[(mt * 2 + 0) * 64 + lane];
-      if (SPLIT) Plo[mt] = cx.Pbuf[(mt * 2 + 1) * 64 + lane];
-      else { u32x4_t z = {0, 0, 0, 0}; Plo[mt] = z; }
-    }
-    // lane (n, g): token rows 4g..4g+3 (and 16+4g..), dword n of this wave's 64 bytes
-    const int slot0 = 2 * (t % RT);
-    const int pitch_t = RAGGED ? (tile_chunks(t) + 1) * 16 : cx.pitch;
-    const char* vA = cx.ring + slot0 * cx.unit_bytes + (4 * g) * pitch_t + cp * 64 + n * 4;
-    const char* vB = vA + cx.unit_bytes;
-    if constexpr (I8) {
-      f32x4_t P32[MT][2];
+    auto read_weights = [&]() {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        P32[mt][0] = __builtin_bit_cast(f32x4_t, Phi[mt]);
-        P32[mt][1] = __builtin_bit_cast(f32x4_t, cx.Pbuf[(mt * 2 + 1) * 64 + lane]);
+        alpha[mt] = cx.abuf[mt * 16 + n];
+        Phi[mt] = cx.Pbuf[(mt * 2 + 0) * 64 + lane];
+        if (SPLIT) Plo[mt] = cx.Pbuf[(mt * 2 + 1) * 64 + lane];
+        else { u32x4_t z = {0, 0, 0, 0}; Plo[mt] = z; }
+        if constexpr (I8) {
+          P32[mt][0] = __builtin_bit_cast(f32x4_t, Phi[mt]);
+          P32[mt][1] = __builtin_bit_cast(f32x4_t, cx.Pbuf[(mt * 2 + 1) * 64 + lane]);
+        }
       }
+    };
+    // column groups I0 .. I1-1 of tile t
+    auto add_part = [&](int t, auto i0, auto i1) {
+      constexpr int I0 = decltype(i0)::value, I1 = decltype(i1)::value;
+      if (cx.dbg & 2) return;
+      // lane (n, g): token rows 4g..4g+3 (and 16+4g..), dword n of this wave's 64 bytes
+      const int slot0 = 2 * (t % RT);
+      const int pitch_t = RAGGED ? (tile_chunks(t) + 1) * 16 : cx.pitch;
+      const int rv_t = RAGGED ? uni(cx.meta[4 * t + 2]) : r;
+      const char* vA = cx.ring + slot0 * cx.unit_bytes + (4 * g) * pitch_t + cp * 64 + n * 4;
+      const char* vB = vA + cx.unit_bytes;
       if constexpr (I4) {
         // the 4-bit reader places its own block and dword: take the wave's and the lane's offsets off
-        if (!(cx.dbg & 2))
-          wsum_tile_i4<MT, NGRP>(vA - cp * 64 - n * 4, vB - cp * 64 - n * 4, pitch_t, RAGGED ? uni(cx.meta[4 * t + 2]) : r, cp, n, g,
-                                 cx.vsb + (t & 1) * (r >> 6) * kTile, P32, alpha, U);
+        wsum_tile_i4<MT, NGRP, I0, I1>(vA - cp * 64 - n * 4, vB - cp * 64 - n * 4, pitch_t, rv_t, cp, n, g,
+                                       cx.vsb + (t & 1) * (r >> 6) * kTile, P32, alpha, U);
+      } else if constexpr (I8) {
+        wsum_tile_i8<MT, NGRP, I0, I1>(vA, vB, pitch_t, rv_t, cp, g, cx.vsb + (t & 1) * (r >> 6) * kTile, P32, alpha, U);
       } else {
-        if (!(cx.dbg & 2))
-          wsum_tile_i8<MT, NGRP>(vA, vB, pitch_t, RAGGED ? uni(cx.meta[4 * t + 2]) : r, cp, g,
-                                 cx.vsb + (t & 1) * (r >> 6) * kTile, P32, alpha, U);
+        wsum_tile<Tag, MT, SPLIT, NGRP, I0, I1>(vA, vB, pitch_t, rv_t - cp * 32, n, Phi, Plo, alpha, U);
       }
-    } else {
-      if (!(cx.dbg & 2))
-        wsum_tile<Tag, MT, SPLIT, NGRP>(vA, vB, pitch_t,
-                                        (RAGGED ? uni(cx.meta[4 * t + 2]) : r) - cp * 32, n, Phi, Plo,
-                                        alpha, U);
+    };
+    constexpr int NA = (NGRP + 1) / 2;
+    using First = std::integral_constant<int, 0>;
+    using Mid = std::integral_constant<int, NA>;
+    using Last = std::integral_constant<int, NGRP>;
+    for (int t = 0; t < cx.ntl; ++t) {
+      AP_T_STAMP(t)
+      // tile t-2's slots are free (every sum wave passed the last barrier of tile t-1 after it)
+      const int refill = t >= 2 && t - 2 + RT < cx.ntl ? t - 2 + RT : -1;
+      if (refill >= 0) issue_half(refill, 0);
+      if (t > 0) {
+        read_weights();                                  // the next softmax overwrites them: before the barrier
+        add_part(t - 1, First{}, Mid{});
+      }
+      AP_TICK(1)
+      wg_barrier();                                      // partial scores of tile t ready
+      AP_TICK(2)
+      if (t == 0) {
+#pragma nounroll
+        for (int lt = 1; lt < RT && lt < cx.ntl; ++lt) issue_tile(lt);
+      } else {
+        add_part(t - 1, Mid{}, Last{});
+      }
+      if (refill >= 0) issue_half(refill, 1);
+      AP_TICK(3)
+      {
+        // tile t's rows must have landed; the tiles issued after it may stay in flight
+        int upto = t >= 2 ? t - 2 + RT : RT - 1;
+        upto = upto < cx.ntl ? upto : cx.ntl - 1;
+        if (RAGGED) {
+          int pending = 0;
+          for (int lt = t + 1; lt <= upto; ++lt) pending += 2 * tile_requests(lt);
+          wait_vmcnt(pending);
+        } else {
+          wait_vmcnt((upto - t) * 2 * n_issue);
+        }
+      }
+      wg_barrier();                                      // weights of tile t ready; its rows visible to every wave
+      AP_TICK(4)
+    }
+    if (cx.ntl > 0) {
+      read_weights();
+      add_part(cx.ntl - 1, First{}, Mid{});
+      add_part(cx.ntl - 1, Mid{}, Last{});
     }
     AP_TICK(5)
-  }
   }
   AP_T_STAMP(62)
   // U of this split, straight from the accumulators.  U[i][j][mt][e] is element (head 16mt+n,
@@ -1428,7 +1473,7 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       }
     }
   }
-  cx.store_ml(part_ml);
+  if (TS) cx.store_ml(part_ml);
   AP_TICK(6)
   AP_T_REPORT
 }
@@ -1541,7 +1586,7 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
     fixed += (size_t)p.ntl_cap * (kTile + 4) * 4;
   }
   const size_t budget = 160 * 1024;
-  AP_REQUIRE(fixed + 2 * unit <= budget, AP_ERR_UNSUPPORTED,
+  AP_REQUIRE(fixed + (TS ? 2 : 4) * unit <= budget, AP_ERR_UNSUPPORTED,   // two tiles; always so at H <= 64, r <= 640
              "ap_decode_attn: H=%d r=%d needs more LDS than 160 KiB", p.H, p.r);
   int nh = (int)((budget - fixed) / unit);
   if (TS) {
