@@ -141,6 +141,10 @@ ap_status launch_quantize_i4(const void* C, void* codes, void* scales, int B, in
                              int r, hipStream_t stream);
 
 // per-step passes over the bases in 16-bit storage (basis_gemv.hip)
+bool rows_grouped_applies(int G, int d, int HD);
+ap_status launch_rows_grouped(ap_dtype dt, const void* Bk, const void* Bv, int64_t bstride, const void* k_new,
+                              const void* v_new, const void* q, void* Ck, void* Cv, void* Qp, int B, int H, int H_kv,
+                              int Hp, int d, int r, int row, int T_cap, float scale, hipStream_t stream);
 bool basis_rows_applies(int HD, int B);
 // ap_set_fused_value_min_bytes: -1 = the library's rule
 int64_t fused_value_min_bytes();

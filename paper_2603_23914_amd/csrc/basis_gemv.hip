@@ -64,7 +64,8 @@ __device__ __forceinline__ void split_hi_lo(float x, uint16_t& hi, uint16_t& lo)
 // rows (HD * 2 bytes each) are in flight while one is reduced.
 // LPH = d / 8 lanes share a head (FOLD; 1 when the kernel does not fold).
 // PAIR: grid.z = 2; the workgroups of z = 1 run the second job (DOT only) on Bm2, x2, C2.
-template <class Tag, int KPC, int NBUF, bool DOT, bool FOLD, int LPH, bool PAIR = false>
+// G: query heads that read the same slice of a row (grouped queries; each has its own dot products).
+template <class Tag, int KPC, int NBUF, bool DOT, bool FOLD, int LPH, bool PAIR = false, int G = 1>
 __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
   extern __shared__ __attribute__((aligned(16))) float qtile[];   // FOLD: [Hp][4 rpw + 1]
   const int tid = threadIdx.x, lane = tid & 63;
@@ -98,15 +99,18 @@ __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
     }
   };
   // this lane's slices of the vectors: elements 512 pp + 8 lane .. +7 of the hidden axis.
+  constexpr int dshift = FOLD ? 31 - __builtin_clz((unsigned)(LPH * 8)) : 0;   // log2(d)
   // They are requested BEFORE the first rows, so that a row's arrival implies theirs and no
   // wait on them ever drains the row ring.
-  u32x4_t xs[DOT ? KPC : 1], qs[FOLD ? KPC : 1];
+  u32x4_t xs[DOT ? KPC : 1], qs[FOLD ? KPC : 1][G];
 #pragma unroll
   for (int pp = 0; pp < KPC; ++pp) {
     const int e0 = pp * 512 + lane * 8;
     const u32x4_t z = {0, 0, 0, 0};
     if (DOT) xs[pp] = e0 < HD ? *(const u32x4_t*)(xv + (size_t)b * HD + e0) : z;
-    if (FOLD) qs[pp] = e0 < HD && fold ? *(const u32x4_t*)(p.q + (size_t)b * HD + e0) : z;
+#pragma unroll
+    for (int k = 0; k < G; ++k)
+      if (FOLD) qs[pp][k] = e0 < HD && fold ? *(const u32x4_t*)(p.q + (size_t)b * G * HD + ((e0 >> dshift) * G + k) * (LPH * 8) + (e0 & (LPH * 8 - 1))) : z;
   }
   const int last = rpw - 1;
 #pragma unroll
@@ -115,8 +119,6 @@ __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
     for (int i = tid; i < p.Hp * pitch; i += 256) qtile[i] = 0.f;   // padded heads stay 0
     __syncthreads();
   }
-  constexpr int dshift = FOLD ? 31 - __builtin_clz((unsigned)(LPH * 8)) : 0;   // log2(d)
-
   auto reduce_row = [&](const u32x4_t (&row)[KPC], int i) {
     const int jl = w * rpw + i;
     const bool live = i < rpw && j0 + jl < r;
@@ -131,11 +133,14 @@ __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
     if (fold) {
 #pragma unroll
       for (int pp = 0; pp < KPC; ++pp) {
-        float part = dot8<Tag>(row[pp], qs[pp], 0.f);
-        part = group_sum<LPH>(part);
         const int e0 = pp * 512 + lane * 8;
-        if ((lane & (LPH - 1)) == 0 && e0 < HD && live)
-          qtile[(e0 >> dshift) * pitch + jl] = part * p.scale;
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+          float part = dot8<Tag>(row[pp], qs[pp][k], 0.f);
+          part = group_sum<LPH>(part);
+          if ((lane & (LPH - 1)) == 0 && e0 < HD && live)
+            qtile[((e0 >> dshift) * G + k) * pitch + jl] = part * p.scale;
+        }
       }
     }
   };
@@ -755,7 +760,46 @@ ap_status launch_rows(RowsParams p, int B, hipStream_t stream) {
   return AP_ERR_UNSUPPORTED;
 }
 
+// Grouped queries: the key row's append, the fold of all G query heads per slice, and the value row's
+// append in one launch.
+template <class Tag, int KPC, int LPH, int G>
+ap_status launch_rows_grouped(RowsParams p, int B, hipStream_t stream) {
+  const int rpw = basis_rows_per_wave(B, p.r);
+  p.rpw = rpw;
+  const dim3 grid((p.r + 4 * rpw - 1) / (4 * rpw), B, 2);
+  const size_t lds = (size_t)p.Hp * (4 * rpw + 1) * 4;
+  hipLaunchKernelGGL((basis_rows<Tag, KPC, 3, true, true, LPH, true, G>), grid, dim3(256), lds, stream, p);
+  return AP_OK;
+}
+template <class Tag, int KPC, int LPH>
+ap_status launch_rows_grouped(const RowsParams& p, int G, int B, hipStream_t stream) {
+  if (G == 2) return launch_rows_grouped<Tag, KPC, LPH, 2>(p, B, stream);
+  if (G == 4 || KPC > 2) return launch_rows_grouped<Tag, KPC, LPH, 4>(p, B, stream);
+  return launch_rows_grouped<Tag, KPC, LPH, (KPC > 2 ? 4 : 8)>(p, B, stream);
+}
+template <class Tag>
+ap_status launch_rows_grouped(const RowsParams& p, int G, int B, hipStream_t stream) {
+  if (p.HD <= 1024)
+    return p.d == 128 ? launch_rows_grouped<Tag, 2, 16>(p, G, B, stream) : launch_rows_grouped<Tag, 2, 8>(p, G, B, stream);
+  return p.d == 128 ? launch_rows_grouped<Tag, 4, 16>(p, G, B, stream) : launch_rows_grouped<Tag, 4, 8>(p, G, B, stream);
+}
+
 }  // namespace
+
+// A step of a grouped-query model whose basis rows are short (HD columns, H heads in groups of G): the
+// launch above.  One launch instead of two (the appends; fold_heads) and B_k once instead of twice:
+// 34.7 -> 31.9 us a pass at 21 sequences, 32 / 8 heads, rank 256, 3001 tokens.
+bool rows_grouped_applies(int G, int d, int HD) {
+  return (G == 2 || G == 4 || G == 8) && (d == 64 || d == 128) && HD <= (G == 8 ? 1024 : 2048);
+}
+ap_status launch_rows_grouped(ap_dtype dt, const void* Bk, const void* Bv, int64_t bstride, const void* k_new,
+                              const void* v_new, const void* q, void* Ck, void* Cv, void* Qp, int B, int H, int H_kv,
+                              int Hp, int d, int r, int row, int T_cap, float scale, hipStream_t stream) {
+  const RowsParams p{(const uint16_t*)Bk, bstride, (const uint16_t*)k_new, (const uint16_t*)q, (uint16_t*)Ck,
+                     (uint16_t*)Qp, H, Hp, d, H_kv * d, r, row, T_cap, 4, scale, (const uint16_t*)Bv,
+                     (const uint16_t*)v_new, (uint16_t*)Cv};
+  return dt == AP_F16 ? launch_rows_grouped<F16Tag>(p, H / H_kv, B, stream) : launch_rows_grouped<BF16Tag>(p, H / H_kv, B, stream);
+}
 
 bool basis_rows_applies(int HD, int B) { return HD % 8 == 0 && HD <= 8192 && B <= 65535; }
 

@@ -1711,6 +1711,9 @@ ap_status run_decode(const DecodeArgs& a) {
     st = launch_basis_rows(a.dt, a.Bk, a.basis_batch_stride, a.k_new, a.q, (void*)a.Ck, Qp, a.B, a.H, Hp,
                            a.d, a.H * a.d, a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream,
                            pair_v ? a.Bv : nullptr, pair_v ? a.v_new : nullptr, pair_v ? (void*)a.Cv : nullptr);
+  } else if (pair_v && rows_grouped_applies(a.H / Hkv, a.d, HDkv)) {
+    st = launch_rows_grouped(a.dt, a.Bk, a.Bv, a.basis_batch_stride, a.k_new, a.v_new, a.q, (void*)a.Ck, (void*)a.Cv, Qp,
+                             a.B, a.H, Hkv, Hp, a.d, a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream);
   } else {
     // grouped queries: the key row is appended by a pass of its own over the (small) basis,
     // the fold runs per query head

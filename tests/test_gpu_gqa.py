@@ -100,6 +100,19 @@ def test_decode_step_grouped_queries(dtype, B, H, Hkv, d, r, T0):
         assert np.abs(P(Ck_h)[0, T - 1] - c_ref).max() <= 2.0 ** -7 * np.abs(c_ref).max()
 
 
+@pytest.mark.parametrize("dtype,B,H,Hkv,d,r,T0", [
+    ("bf16", 1, 32, 16, 128, 192, 70),      # two heads per slice, rows of 2048: the widest the one launch takes
+    ("f16", 2, 64, 8, 128, 64, 40),         # eight heads per slice
+    ("f16", 3, 16, 2, 64, 64, 33),          # rows of 128 columns: a quarter of a wave has data
+    ("bf16", 1, 12, 3, 128, 128, 50),       # rows of 384
+    ("f16", 1, 34, 17, 128, 128, 50),       # just too wide: two launches
+    ("bf16", 2, 18, 6, 64, 128, 50),        # three heads per slice: two launches
+])
+def test_decode_step_grouped_forms(dtype, B, H, Hkv, d, r, T0):
+    """Both ways a grouped-query step appends and folds."""
+    test_decode_step_grouped_queries(dtype, B, H, Hkv, d, r, T0)
+
+
 def test_ragged_ranks_grouped_queries():
     from paper_2603_23914_amd import binding as ap
     dtype, B, H, Hkv, d, r, T = "f16", 2, 32, 8, 128, 256, 333
