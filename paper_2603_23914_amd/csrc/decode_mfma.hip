@@ -227,11 +227,12 @@ __device__ __forceinline__ void wsum_tile(const char* vA, const char* vB, int pi
 // scale of its row (token 16 tt + n).  Codes 0-7 feed one MFMA and codes 8-15 the next (q' is
 // loaded with the same column order), so a block is two k-steps.  The block's sum over the
 // integer codes is exact in fp32; it is multiplied by the token's scale in fp32 and added to the
-// scores.  A lane's results belong to tokens 16 tt + 4 g + e, whose scales sit in lanes 4 g + e.
+// scores.  A lane's results belong to tokens 16 tt + 4 g + e: ks, the tile's key scales in LDS as
+// [scale block][32 tokens], holds their scales side by side.
 // 4-bit codes (I4): the lane's 16 codes of a block are two dwords, one per k-step.
 template <int MT, int NBW, bool I4>
 __device__ __forceinline__ void score_tile_i8(const u32x4_t (&Araw)[NBW][2],
-                                              const uint32_t (&ksc)[NBW][2], int g,
+                                              const uint16_t* ks, int w, int nsb, int g,
                                               const u32x4_t (&qhi)[2 * NBW][MT],
                                               f32x4_t (&s)[MT][2]) {
 #pragma unroll
@@ -254,15 +255,17 @@ __device__ __forceinline__ void score_tile_i8(const u32x4_t (&Araw)[NBW][2],
       pb[mt][0] = Mfma<F16Tag>::run(a1[0], qhi[2 * i + 1][mt], pb[mt][0]);
       pb[mt][1] = Mfma<F16Tag>::run(a1[1], qhi[2 * i + 1][mt], pb[mt][1]);
     }
+    const int blk = w + 4 * i < nsb ? w + 4 * i : 0;     // a block beyond the rank has zero q': any scale
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
+    for (int tt = 0; tt < 2; ++tt) {
+      const u32x2_t sb = *(const u32x2_t*)(ks + blk * kTile + 16 * tt + 4 * g);
+      const float sc[4] = {lo_to_f32(sb[0], F16Tag{}), hi_to_f32(sb[0], F16Tag{}), lo_to_f32(sb[1], F16Tag{}),
+                           hi_to_f32(sb[1], F16Tag{})};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t sb = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (4 * g + e), (int)ksc[i][tt]);
-        const float sc = bits_to_f32((uint16_t)sb, F16Tag{});
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) s[mt][tt][e] = fmaf(sc, pb[mt][tt][e], s[mt][tt][e]);
-      }
+        for (int mt = 0; mt < MT; ++mt) s[mt][tt][e] = fmaf(sc[e], pb[mt][tt][e], s[mt][tt][e]);
+    }
   }
 }
 
@@ -526,6 +529,7 @@ struct WaveCtx {
   u32x4_t* Pbuf;     // [MT][hi,lo][64 lanes]
   float* abuf;       // [16*MT] rescale factors
   uint16_t* vsb;     // I8: [2][r/64][32] value scales of the tile in flight (fp16 bits)
+  uint16_t* ksb;     // I8: [2][r/64][32] key scales
   int* idxb;         // RAGGED: [ntl][32] token index of every tile slot (tail slots repeat the last)
   int* meta;         // RAGGED: [ntl][4] = tokens in the tile, key rank, value rank, 1 + slot of the
                      // deferred newest token (0: not in this tile)
@@ -571,6 +575,7 @@ struct WaveCtx {
     abuf = (float*)(Pbuf + NSUB * MT * 2 * 64);
     row_bytes = (uint32_t)row_bytes_of(r);
     vsb = (uint16_t*)(abuf + NSUB * 16 * MT);
+    ksb = vsb + 2 * (r >> 6) * kTile;
     tok_a = 0; tok_h = kTile; tok_rem = 0;
     if (!RAGGED && TS) {
       const int ntiles = (T + kTile - 1) / kTile;
@@ -592,7 +597,7 @@ struct WaveCtx {
       tok_h = ntl > 0 ? n_tok / ntl : 0;
       tok_rem = n_tok - tok_h * ntl;
     } else {
-      idxb = (int*)(vsb + (I8 ? 2 * (r >> 6) * kTile : 0));
+      idxb = (int*)(vsb + (I8 ? 4 * (r >> 6) * kTile : 0));
       meta = idxb + uni(p.ntl_cap) * kTile;
       build_tile_table(p);
     }
@@ -998,46 +1003,48 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       return *(const u32x4_t*)src;
     }
   };
-  // int8: the key scale of the lane's row for every owned block (both halves of a packed
-  // pair), and this wave's share of the tile's value scales, which the score waves pass to
-  // the sum waves through LDS as [scale block][32 tokens]
+  // int8: the score waves bring a tile's scales in, [token][scale block] as they lie in memory (one
+  // 2-byte element per lane, neighbouring lanes neighbouring elements: gathered per lane's own row
+  // and block instead they cost 1300 cycles a tile in requests), and hand them over through LDS as
+  // [scale block][32 tokens]: value scales one tile ahead, key scales, which the scores need first,
+  // two tiles ahead.
   const int nsb = r >> 6;
   const uint16_t* Sk_b = I8 ? uni_ptr(p.Sk) + (size_t)cx.b * uni(p.T_cap) * nsb : nullptr;
   const uint16_t* Sv_b = I8 ? uni_ptr(p.Sv) + (size_t)cx.b * uni(p.T_cap) * nsb : nullptr;
-  uint32_t ksc[I8 ? NBW : 1][2];
-  uint16_t vsr[2] = {0, 0};
-  const int vs_e0 = w * 64 + cx.lane;                      // entries vs_e0, vs_e0 + 256 of [block][token]
-  auto load_scales = [&](int tile) {
+  uint16_t vsr[2] = {0, 0}, ksr[2] = {0, 0};
+  int se_tok[2] = {0, 0}, se_lds[2] = {0, 0}, se_blk[2] = {0, 0};   // entries w * 64 + lane, + 256
+  const int se0 = w * 64 + cx.lane;
+  if constexpr (I8) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int e = se0 + 256 * j;
+      se_tok[j] = e / nsb;
+      se_blk[j] = e - se_tok[j] * nsb;
+      se_lds[j] = se_blk[j] * kTile + se_tok[j];
+    }
+  }
+  auto load_scales = [&](const uint16_t* S_b, uint16_t (&dst)[2], int tile) {
     if constexpr (I8) {
 #pragma unroll
-      for (int tt = 0; tt < 2; ++tt) {
-        int row;
-        if (RAGGED) {
-          row = cx.idxb[tile * kTile + 16 * tt + n];
-        } else {
-          row = cx.tok0(tile) + 16 * tt + n;
-          row = row < T ? row : T - 1;
-        }
-        const uint16_t* sp_ = Sk_b + (size_t)row * nsb + (my_nks > 0 ? w : 0);
-#pragma unroll
-        for (int i = 0; i < NBW; ++i) {
-          ksc[i][tt] = sp_[i < my_nks ? 4 * i : 0];
-        }
-      }
-#pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int e = vs_e0 + 256 * j;
-        if (e < nsb * kTile) {
+        if (se0 + 256 * j < nsb * kTile) {
           int row;
           if (RAGGED) {
-            row = cx.idxb[tile * kTile + (e & 31)];
+            row = cx.idxb[tile * kTile + se_tok[j]];
           } else {
-            row = cx.tok0(tile) + (e & 31);
+            row = cx.tok0(tile) + se_tok[j];
             row = row < T ? row : T - 1;
           }
-          vsr[j] = Sv_b[(size_t)row * nsb + (e >> 5)];
+          dst[j] = S_b[(size_t)row * nsb + se_blk[j]];
         }
       }
+    }
+  };
+  auto put_scales = [&](uint16_t* dst, const uint16_t (&src)[2]) {
+    if constexpr (I8) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (se0 + 256 * j < nsb * kTile) dst[se_lds[j]] = src[j];
     }
   };
   auto load_A = [&](int tile, u32x4_t (&A)[NA][2]) {      // tile: local index in this split
@@ -1051,7 +1058,6 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
 #pragma unroll
         for (int i = 0; i < NA; ++i) A[i][tt] = load_piece(rp + koff[i]);
       }
-      load_scales(tile);
     } else {
       // gathered rows; only this wave's units below the tile's key rank are fetched (a
       // wave-uniform count, so a low-rank tile costs fewer requests, not just fewer distinct
@@ -1068,7 +1074,6 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
         for (int i = 0; i < NA; ++i)
           if (i < nlive_t) A[i][tt] = load_piece(rp + (uint32_t)i * 4u * UB);
       }
-      load_scales(tile);
     }
   };
   if constexpr (TS) {
@@ -1124,13 +1129,14 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       }
     }
     if constexpr (I8) {
-      // hand tile t's value scales to the sum waves (buffer t&1: its previous reader, the
-      // weighted sum of tile t-2, ended before the last barrier of tile t-1)
-      uint16_t* vs = cx.vsb + (t & 1) * nsb * kTile;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        if (vs_e0 + 256 * j < nsb * kTile) vs[vs_e0 + 256 * j] = vsr[j];
-      if (!(cx.dbg & 2)) score_tile_i8<MT, NBW, I4>(A, ksc, g, qhi, sp);
+      if (!(cx.dbg & 2)) score_tile_i8<MT, NBW, I4>(A, cx.ksb + (t & 1) * nsb * kTile, w, nsb, g, qhi, sp);
+      // tile t's value scales for the sum waves (buffer t & 1: its previous reader, the weighted sum
+      // of tile t - 2, ended before the last barrier of tile t - 1), tile t + 1's key scales for the
+      // score waves (buffer (t + 1) & 1: last read for tile t - 1)
+      put_scales(cx.vsb + (t & 1) * nsb * kTile, vsr);
+      if (t + 1 < cx.ntl) put_scales(cx.ksb + ((t + 1) & 1) * nsb * kTile, ksr);
+      if (t + 1 < cx.ntl) load_scales(Sv_b, vsr, t + 1);
+      if (t + 2 < cx.ntl) load_scales(Sk_b, ksr, t + 2);
     } else {
       int nlive = NKW;
       if (RAGGED) {                                       // this wave's k-steps w, w + 4, ... below the key rank
@@ -1153,7 +1159,19 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
     wg_barrier();                                         // weights of tile t ready
     AP_TICK(4)
   };
-  if (cx.ntl > 0) load_A(0, A);
+  if constexpr (I8) {
+    // tile 0's key scales go to LDS before anything is scored (the barrier of its own)
+    if (cx.ntl > 0) {
+      load_scales(Sk_b, ksr, 0);
+      load_A(0, A);
+      put_scales(cx.ksb, ksr);
+      load_scales(Sv_b, vsr, 0);
+      if (cx.ntl > 1) load_scales(Sk_b, ksr, 1);
+    }
+    wg_barrier();
+  } else {
+    if (cx.ntl > 0) load_A(0, A);
+  }
   for (int t = 0; t < cx.ntl; ++t) tile_step(t);
   AP_T_STAMP(62)
   cx.store_ml(part_ml);
@@ -1378,6 +1396,7 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
         wsum_tile<Tag, MT, SPLIT, NGRP, I0, I1>(vA, vB, pitch_t, rv_t - cp * 32, n, Phi, Plo, alpha, U);
       }
     };
+    if constexpr (I8) wg_barrier();                      // the score waves' first key scales
     constexpr int NA = (NGRP + 1) / 2;
     using First = std::integral_constant<int, 0>;
     using Mid = std::integral_constant<int, NA>;
@@ -1578,7 +1597,7 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
   constexpr bool TS = !RAGGED && !I8 && RMAX == 128;
   constexpr int NSUB = TS ? 4 : 1;
   size_t fixed = (size_t)4 * 16 * MT * 9 * 16 + (size_t)NSUB * MT * 2 * 64 * 16 + (size_t)NSUB * MT * 16 * 4;
-  if (I8) fixed += (size_t)2 * (p.r / 64) * kTile * 2;     // value scales of two tiles
+  if (I8) fixed += (size_t)4 * (p.r / 64) * kTile * 2;     // value and key scales of two tiles
   if (RAGGED) {
     // every group may end in a partial tile; tiles are dealt round-robin to the splits
     const int ntiles_max = (p.T + kTile - 1) / kTile + p.F;
