@@ -733,12 +733,12 @@ merge_splits(const float* __restrict__ part_ml, const float* __restrict__ part_U
 }
 
 }  // namespace
-int basis_rows_per_wave(int B, int r);
+int basis_rows_per_wave(int B, int r, int HD);
 namespace {
 
 template <class Tag, bool DOT, bool FOLD, bool PAIR>
 ap_status launch_rows(RowsParams p, int B, hipStream_t stream) {
-  const int rpw = basis_rows_per_wave(B, p.r);
+  const int rpw = basis_rows_per_wave(B, p.r, p.HD);
   p.rpw = rpw;
   const int rows_wg = 4 * rpw;
   const dim3 grid((p.r + rows_wg - 1) / rows_wg, B, PAIR ? 2 : 1);
@@ -764,7 +764,7 @@ ap_status launch_rows(RowsParams p, int B, hipStream_t stream) {
 // append in one launch.
 template <class Tag, int KPC, int LPH, int G>
 ap_status launch_rows_grouped(RowsParams p, int B, hipStream_t stream) {
-  const int rpw = basis_rows_per_wave(B, p.r);
+  const int rpw = basis_rows_per_wave(B, p.r, p.HD);
   p.rpw = rpw;
   const dim3 grid((p.r + 4 * rpw - 1) / (4 * rpw), B, 2);
   const size_t lds = (size_t)p.Hp * (4 * rpw + 1) * 4;
@@ -847,11 +847,17 @@ ap_status launch_fold_heads(ap_dtype dt, const void* Bk, int64_t bstride, const 
   return AP_OK;
 }
 
-int basis_rows_per_wave(int B, int r) {
+int basis_rows_per_wave(int B, int r, int HD) {
   // about five workgroups per CU, two of them resident at a time: the start and the end of a
   // workgroup (vector slices in, folded tile out) then overlap other workgroups' streaming
   int rpw = (int)(((int64_t)B * r + 5119) / 5120);
-  return rpw < 4 ? 4 : (rpw > 32 ? 32 : rpw);
+  // At least four rows per wave (its vector slices are as long as a row) where the pass moves 32 MB
+  // and more; a shorter one is a matter of latency and takes two, the shortest one.  Us a pass at
+  // 4 / 2 / 1 rows: 34 MB 39.8 / 41.6 / 46.0 and 37.6 / 39.4 / 43.9, 26 MB 43.0 / 42.1 / 45.9, 11 MB
+  // 32.3 / 31.0 / 31.0, 8 MB 20.2 / 19.1 / 19.5, 4 MB 24.9 / 23.3 / 23.4, 64 rows in all 17.2 / 16.8 / 16.4.
+  const int64_t rows = (int64_t)B * r;
+  const int least = rows * HD * 2 >= (32ll << 20) ? 4 : (rows > 256 ? 2 : 1);
+  return rpw < least ? least : (rpw > 32 ? 32 : rpw);
 }
 // expand_append: about four two-wave workgroups per CU in one round, but never more than 16 row
 // blocks per sequence at large batches (each block writes an HD-wide partial output that
