@@ -9,7 +9,8 @@
 //
 // Both operands are contiguous along the contraction axis, so tiles go HBM -> LDS with
 // direct-to-LDS 16-byte loads and come back out as MFMA operands with one ds_read_b128 each.
-// A workgroup (8 waves, 4 x 2) owns a 256-token x 128-column tile and walks the hidden axis
+// A workgroup (8 waves) owns a 256-token x 128-column tile, or 128 x 256 where that wastes less of
+// the edges (see tall_tiles), and walks the hidden axis
 // in blocks of 64 through a three-stage LDS ring (two stages in flight while one is multiplied,
 // one barrier per block); each wave holds a 64 x 64 accumulator as 2 x 2 MFMA 32x32x16 tiles.
 // The LDS image of a tile is [row][8 chunks of 16 B] with the chunk index XOR-ed by (row/2 & 7): the loads pick their global source accordingly, and eight
@@ -27,13 +28,11 @@
 namespace ap {
 namespace {
 
-constexpr int kBM = 256;   // tokens per tile
-constexpr int kBN = 128;   // output columns (basis rows) per tile
+constexpr int kEdges = 384;   // a tile is BM tokens x (384 - BM) output columns, BM = 256 or 128
 constexpr int kBK = 64;    // hidden elements per stage
-constexpr int kStageBytes = (kBM + kBN) * kBK * 2;   // 48 KiB
+constexpr int kStageBytes = kEdges * kBK * 2;        // 48 KiB
 constexpr int kStages = 3;
 constexpr int kThreads = 512;
-constexpr int kEpiPitch = kBN + 8;                   // 16-bit elements per staged output row
 
 template <class Tag> struct Mfma32;
 template <> struct Mfma32<F16Tag> {
@@ -73,8 +72,11 @@ struct GemmParams {
   int G1;
 };
 
-template <class Tag>
+template <class Tag, int kBM>
 __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
+  constexpr int kBN = kEdges - kBM;
+  constexpr int kEpiPitch = kBN + 8;                       // 16-bit elements per staged output row
+  constexpr int WN = kBN / 64;                             // waves side by side over the columns
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -94,37 +96,30 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
                      (size_t)b * p.c_bstride * (p.out_kind == 0 ? 2 : (p.out_kind == 1 ? 1 : 4));
   uint16_t* const Sout = (second ? p.scale2 : p.scale) + (size_t)b * p.s_bstride;
 
-  // ---- direct-to-LDS loads: per stage 32 KiB of X rows then 16 KiB of basis rows; wave w
-  //      issues 1-KiB blocks 4w .. 4w+3 of the former and 2w, 2w+1 of the latter.  Block j,
-  //      lane i -> LDS chunk P = 64 j + i, holding (row P>>3, hidden chunk (P&7) ^ (row/2 & 7)).
-  uint32_t srcA[4], srcB[2];
+  // ---- direct-to-LDS loads: per stage the X rows, then the basis rows, 48 KiB; wave w issues the
+  //      1-KiB blocks 6w .. 6w+5.  Block j, lane i -> LDS chunk P = 64 j + i, holding
+  //      (row P>>3, hidden chunk (P&7) ^ (row/2 & 7)).
+  uint32_t src[6];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int P = (4 * w + i) * 64 + lane;
-    const int row = P >> 3, kc = (P & 7) ^ ((row >> 1) & 7);
-    int ra = m0 + row;  ra = ra < p.n ? ra : p.n - 1;        // rows past the end: finite duplicates
-    srcA[i] = ((uint32_t)ra * (uint32_t)p.lda + (uint32_t)kc * 8u) * 2u;
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int P = (2 * w + i) * 64 + lane;
-    const int row = P >> 3, kc = (P & 7) ^ ((row >> 1) & 7);
-    int rb = n0 + row;  rb = rb < p.r ? rb : p.r - 1;
-    srcB[i] = ((uint32_t)rb * (uint32_t)p.ldb + (uint32_t)kc * 8u) * 2u;
+  for (int i = 0; i < 6; ++i) {
+    const int P = (6 * w + i) * 64 + lane;
+    const bool isB = 6 * w + i >= kBM / 8;                 // a block is eight rows: wave-uniform
+    const int row = (P >> 3) - (isB ? kBM : 0), kc = (P & 7) ^ ((row >> 1) & 7);
+    int rr = (isB ? n0 : m0) + row;
+    const int lim = isB ? p.r : p.n;
+    rr = rr < lim ? rr : lim - 1;                          // rows past the end: finite duplicates
+    src[i] = ((uint32_t)rr * (uint32_t)(isB ? p.ldb : p.lda) + (uint32_t)kc * 8u) * 2u;
   }
   auto issue = [&](int stage, int kb) {
-    char* sA = smem + stage * kStageBytes + (4 * w) * 1024;
-    char* sB = smem + stage * kStageBytes + kBM * kBK * 2 + (2 * w) * 1024;
+    char* s6 = smem + stage * kStageBytes + (6 * w) * 1024;
     const uint32_t koff = (uint32_t)kb * (kBK * 2);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dma16(Xb + (srcA[i] + koff), sA + i * 1024);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) dma16(Bb + (srcB[i] + koff), sB + i * 1024);
+    for (int i = 0; i < 6; ++i) dma16((6 * w + i >= kBM / 8 ? Bb : Xb) + (src[i] + koff), s6 + i * 1024);
   };
 
   // ---- MFMA operands: wave (wn, wm) owns columns 64 wn .. and tokens 64 wm ..; operand row
   //      = lane & 31, hidden chunk of k-step ks = 2 ks + (lane >> 5)
-  const int wn = w & 1, wm = w >> 1;                       // wm = 0 .. 3
+  const int wn = w % WN, wm = w / WN;
   const int orow = lane & 31, ohalf = lane >> 5;
   uint32_t offN[2], offM[2], kx[4];
 #pragma unroll
@@ -226,10 +221,11 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
           *(f32x4_t*)(epf + tok * kPitch32 + col) = v;
         }
     __syncthreads();
-    const int c4 = tid & 31, colf = n0 + c4 * 4;
+    constexpr int CT = kBN / 4, RT = kThreads / CT;        // threads per row, rows per pass
+    const int c4 = tid % CT, colf = n0 + c4 * 4;
 #pragma unroll 1
-    for (int pass = 0; pass < kBM / 16; ++pass) {
-      const int tok = pass * 16 + (tid >> 5);
+    for (int pass = 0; pass < kBM / RT; ++pass) {
+      const int tok = pass * RT + tid / CT;
       const int t = m0 + tok;
       if (t < p.n && colf < p.r)      // r is a multiple of 8 on this path: whole 16-byte pieces
         *(f32x4_t*)((float*)Cout + (size_t)t * p.ldc + colf) = *(const f32x4_t*)(epf + tok * kPitch32 + c4 * 4);
@@ -252,11 +248,12 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
         *(u32x2_t*)(epi + tok * kEpiPitch + col) = v;
       }
   __syncthreads();
-  const int c8 = tid & 15;
+  constexpr int CT = kBN / 8, RT = kThreads / CT;
+  const int c8 = tid % CT;
   const int col = n0 + c8 * 8;
 #pragma unroll 1
-  for (int pass = 0; pass < kBM / 32; ++pass) {
-    const int tok = pass * 32 + (tid >> 4);
+  for (int pass = 0; pass < kBM / RT; ++pass) {
+    const int tok = pass * RT + tid / CT;
     const int t = m0 + tok;
     const u32x4_t v = *(const u32x4_t*)(epi + tok * kEpiPitch + c8 * 8);
     const bool live = t < p.n && col < p.r;
@@ -292,8 +289,9 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
   }
 }
 
-template <class Tag>
+template <class Tag, int kBM>
 ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
+  constexpr int kBN = kEdges - kBM;
   GemmParams p{};
   p.X = (const uint16_t*)a.A;
   p.Bm = (const uint16_t*)a.Bm;
@@ -317,7 +315,7 @@ ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
     p.scale2 = (uint16_t*)a2->scale;
   }
   const int grid = ((p.G + 7) / 8) * 8;
-  auto kern = compact_gemm<Tag>;
+  auto kern = compact_gemm<Tag, kBM>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -330,6 +328,16 @@ ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), kStages * kStageBytes, a.stream, p);
   return check_launch("matrix product");
+}
+
+// The tile whose count makes fewer rounds over the 256 CUs (fewer tiles when equal).  Measured at 16
+// products of 544 rows (three edges of 256 or five of 128): times 4224 columns 500 -> 475 us, times
+// 4096 columns 465 -> 446 us.
+bool tall_tiles(const NtGemmArgs& a, bool pair) {
+  auto tiles = [&](int bm) { return (int64_t)a.batch * ((a.M + bm - 1) / bm) * ((a.N + kEdges - bm - 1) / (kEdges - bm)) * (pair ? 2 : 1); };
+  const int64_t t = tiles(256), f = tiles(128);
+  const int64_t rt = (t + 255) / 256, rf = (f + 255) / 256;
+  return rt != rf ? rt < rf : t <= f;
 }
 
 NtGemmArgs nt_args_of(const CompactArgs& a) {
@@ -371,7 +379,9 @@ ap_status launch_gemm_nt(const NtGemmArgs& a, const NtGemmArgs* second) {
              AP_ERR_UNSUPPORTED, "matrix product: K %% 64, N %% 8 and 16-byte aligned rows are required");
   AP_REQUIRE((int64_t)a.M * a.lda * 2 < (1ll << 32) && (int64_t)a.N * a.ldb * 2 < (1ll << 32), AP_ERR_UNSUPPORTED,
              "matrix product: one operand must stay below 4 GiB");
-  return a.dt == AP_F16 ? run_gemm<F16Tag>(a, second) : run_gemm<BF16Tag>(a, second);
+  const bool tall = tall_tiles(a, second != nullptr);
+  if (a.dt == AP_F16) return tall ? run_gemm<F16Tag, 256>(a, second) : run_gemm<F16Tag, 128>(a, second);
+  return tall ? run_gemm<BF16Tag, 256>(a, second) : run_gemm<BF16Tag, 128>(a, second);
 }
 
 }  // namespace ap

@@ -261,7 +261,7 @@ def test_algorithm1_loop_with_new_bases_at_every_trigger():
     assert compressions == 3 and T == n0 + 16 and T_u == 1
 
 
-@pytest.mark.parametrize("l", [2, 16, 18, 34, 64, 66, 598, 602, 1022, 1024])
+@pytest.mark.parametrize("l", [2, 16, 18, 34, 64, 66, 256, 598, 602, 1022, 1024])
 def test_bases_eigenvectors_at_the_edges_of_blocks(l):
     """The eigenvalue step at sketch sizes around its blocks (16 rows, pairs of them, 32 padded columns,
     the fixed part of its column loops), all l directions kept.  sigma_i = ||X d_i|| in decreasing
