@@ -417,44 +417,55 @@ struct MergeArgs {
   size_t ostride, lstride;
 };
 
-// grid (ceil(H d / 256), B), 256 threads: one output element per thread.  Parts are taken eight
-// at a time so that their loads are in flight together (a list can hold 64 splits).
-template <class Tag, bool OUT_F32>
+// grid (ceil(H d / 256), B), 256 threads: one output element per thread.  Up to NP parts of a list
+// are requested at once, logarithms and outputs together, so that the usual merge is one round trip
+// to memory; longer lists go on with the running maximum.  (Eight at a time, first all logarithms and
+// then all outputs: 6.2 us for 32 parts of 8 x 32 heads of 128, now 4.2.)
+template <class Tag, bool OUT_F32, int NP>
 __global__ void __launch_bounds__(256)
 merge_parts(const MergeArgs a, void* __restrict__ out, float* __restrict__ lse, int H, int d) {
   const int b = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
   if (i >= H * d) return;
   const int h = i / d;
   const size_t lo = (size_t)b * H + h, oo = (size_t)b * H * d + i;
-  float m = -INFINITY;
-  for (int k = 0; k < kMaxLists; ++k)
-    for (int c0 = 0; c0 < a.cnt[k]; c0 += 8) {
-      float v[8];
+  float m = -INFINITY, acc = 0.f, z = 0.f;
+  auto add = [&](const float (&v)[NP], const float (&x)[NP]) {
+    float mb = m;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = c0 + u < a.cnt[k] ? a.lse[k][lo + (c0 + u) * a.lstride] : -INFINITY;
+    for (int u = 0; u < NP; ++u) mb = fmaxf(mb, v[u]);
+    if (mb > -INFINITY) {
+      const float s = __expf(m - mb);                     // 0 before the first part that holds something
+      acc *= s;
+      z *= s;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
-    }
-  float acc = 0.f, z = 0.f;
-  if (m > -INFINITY) {
-    for (int k = 0; k < kMaxLists; ++k)
-      for (int c0 = 0; c0 < a.cnt[k]; c0 += 8) {
-        float v[8], x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const bool on = c0 + u < a.cnt[k];
-          v[u] = on ? a.lse[k][lo + (c0 + u) * a.lstride] : -INFINITY;
-          x[u] = on ? a.out[k][oo + (c0 + u) * a.ostride] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const float w = __expf(v[u] - m);               // 0 for an empty part and beyond the list
-          acc = fmaf(w, x[u], acc);
-          z += w;
-        }
+      for (int u = 0; u < NP; ++u) {
+        const float w = __expf(v[u] - mb);                // 0 for an empty part and beyond the list
+        acc = fmaf(w, x[u], acc);
+        z += w;
       }
-    acc /= z;
-  }
+      m = mb;
+    }
+  };
+  // parts c0 .. c0 + NP - 1 of list k; past the end the last one again, with nothing in it
+  auto load = [&](int k, int c0, float (&v)[NP], float (&x)[NP]) {
+    const int last = a.cnt[k] - 1;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      const int c = c0 + u < last ? c0 + u : last;
+      v[u] = a.lse[k][lo + c * a.lstride];
+      x[u] = a.out[k][oo + c * a.ostride];
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) v[u] = c0 + u <= last ? v[u] : -INFINITY;
+  };
+  float v0[NP], x0[NP], v1[NP], x1[NP];
+  if (a.cnt[0] > 0) load(0, 0, v0, x0);
+  if (a.cnt[1] > 0) load(1, 0, v1, x1);
+  if (a.cnt[0] > 0) add(v0, x0);
+  for (int c0 = NP; c0 < a.cnt[0]; c0 += NP) { load(0, c0, v0, x0); add(v0, x0); }
+  if (a.cnt[1] > 0) add(v1, x1);
+  for (int c0 = NP; c0 < a.cnt[1]; c0 += NP) { load(1, c0, v1, x1); add(v1, x1); }
+  if (m > -INFINITY) acc /= z;
   if (OUT_F32) ((float*)out)[oo] = acc;
   else ((uint16_t*)out)[oo] = f32_to_bits(acc, Tag{});
   if (lse && i == h * d) lse[lo] = m > -INFINITY ? m + __logf(z) : -INFINITY;
@@ -514,12 +525,19 @@ void launch_raw_partial(const void* q, const void* K, const void* V, float* op, 
 #undef AP_RAW2
 }
 
+template <class Tag, bool OUT_F32>
+void launch_merge_np(const MergeArgs& a, void* out, float* lse, int B, int H, int d, hipStream_t stream) {
+  const dim3 grid((H * d + 255) / 256, B);
+  const int most = a.cnt[0] > a.cnt[1] ? a.cnt[0] : a.cnt[1];
+  if (most <= 1) hipLaunchKernelGGL((merge_parts<Tag, OUT_F32, 1>), grid, dim3(256), 0, stream, a, out, lse, H, d);
+  else if (most <= 8) hipLaunchKernelGGL((merge_parts<Tag, OUT_F32, 8>), grid, dim3(256), 0, stream, a, out, lse, H, d);
+  else hipLaunchKernelGGL((merge_parts<Tag, OUT_F32, 16>), grid, dim3(256), 0, stream, a, out, lse, H, d);
+}
 template <class Tag>
 void launch_merge(const MergeArgs& a, void* out, bool out_f32, float* lse, int B, int H, int d,
                   hipStream_t stream) {
-  const dim3 grid((H * d + 255) / 256, B);
-  if (out_f32) hipLaunchKernelGGL((merge_parts<Tag, true>), grid, dim3(256), 0, stream, a, out, lse, H, d);
-  else hipLaunchKernelGGL((merge_parts<Tag, false>), grid, dim3(256), 0, stream, a, out, lse, H, d);
+  if (out_f32) launch_merge_np<Tag, true>(a, out, lse, B, H, d, stream);
+  else launch_merge_np<Tag, false>(a, out, lse, B, H, d, stream);
 }
 
 // Key-only compression: about four workgroups per CU, a multiple of 8 splits (see the kernel),
