@@ -108,9 +108,13 @@ __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
     const int e0 = pp * 512 + lane * 8;
     const u32x4_t z = {0, 0, 0, 0};
     if (DOT) xs[pp] = e0 < HD ? *(const u32x4_t*)(xv + (size_t)b * HD + e0) : z;
+    if constexpr (FOLD && G == 1) {
+      qs[pp][0] = e0 < HD && fold ? *(const u32x4_t*)(p.q + (size_t)b * HD + e0) : z;
+    } else if constexpr (FOLD) {
 #pragma unroll
-    for (int k = 0; k < G; ++k)
-      if (FOLD) qs[pp][k] = e0 < HD && fold ? *(const u32x4_t*)(p.q + (size_t)b * G * HD + ((e0 >> dshift) * G + k) * (LPH * 8) + (e0 & (LPH * 8 - 1))) : z;
+      for (int k = 0; k < G; ++k)
+        qs[pp][k] = e0 < HD && fold ? *(const u32x4_t*)(p.q + (size_t)b * G * HD + ((e0 >> dshift) * G + k) * (LPH * 8) + (e0 & (LPH * 8 - 1))) : z;
+    }
   }
   const int last = rpw - 1;
 #pragma unroll
