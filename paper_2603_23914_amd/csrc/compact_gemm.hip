@@ -330,14 +330,19 @@ ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
   return check_launch("matrix product");
 }
 
-// The tile whose count makes fewer rounds over the 256 CUs (fewer tiles when equal).  Measured at 16
-// products of 544 rows (three edges of 256 or five of 128): times 4224 columns 500 -> 475 us, times
-// 4096 columns 465 -> 446 us.
+// The tile whose count makes fewer rounds over the 256 CUs; in equal rounds the smaller count, but
+// the larger one (or 256 x 128) when all fit one round: what is wasted of a tile is then repeats of
+// a few rows, and more tiles pull the operands in through more CUs.  Measured, 256 x 128 / 128 x 256:
+// 16 products of 544 rows times 4224 columns (7 / 6 rounds) 500 / 475 us, times 4096 465 / 446;
+// 37 pairs of 535 x 512 (4 / 3) 365 / 305; 12 pairs of 2260 x 64 (1 / 2) 32 / 50; 16 pairs of
+// 4224 x 512 (9 / 9, 2176 / 2112 tiles) 694 / 685; one round: 11 pairs of 104 x 448 77 / 88, 34 of
+// 108 x 384 37.8 / 39.6, 57 of 102 x 64 63.0 / 64.6.
 bool tall_tiles(const NtGemmArgs& a, bool pair) {
   auto tiles = [&](int bm) { return (int64_t)a.batch * ((a.M + bm - 1) / bm) * ((a.N + kEdges - bm - 1) / (kEdges - bm)) * (pair ? 2 : 1); };
   const int64_t t = tiles(256), f = tiles(128);
   const int64_t rt = (t + 255) / 256, rf = (f + 255) / 256;
-  return rt != rf ? rt < rf : t <= f;
+  if (rt != rf) return rt < rf;
+  return rt == 1 ? t >= f : t <= f;
 }
 
 NtGemmArgs nt_args_of(const CompactArgs& a) {

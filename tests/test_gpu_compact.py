@@ -176,3 +176,35 @@ def test_config5_chain_with_true_svd_bases():
     # planted directions lie beyond the rank kept)
     plain = oracle.raw_attn(P(q[0]), P(K), P(V))
     assert np.abs(ref - plain).max() < 0.5 * np.abs(plain).max()
+
+
+@pytest.mark.parametrize("B,n,HD,r", [
+    (12, 544, 512, 512),      # 128 x 256 tiles (one round instead of two), a ragged token tile
+    (12, 544, 448, 576),      # the same with a ragged column tile
+    (140, 250, 128, 64),      # 256 x 128 tiles (two rounds instead of three), half a column tile
+    (9, 104, 512, 448),       # one round: 256 x 128 tiles for more of them
+])
+def test_compact_tile_shapes(B, n, HD, r):
+    """Both tile shapes of the matrix product, 16-bit and int8 output.  The int8 epilogue quantises what
+    the 16-bit one stores, so its codes and scales are those of ap_quantize_i8 on that output."""
+    from paper_2603_23914_amd import binding as ap
+    dtype = "f16"
+    rng = wl.rng_for(29, B, n)
+    K, V = (wl.store(rng.standard_normal((B, n, HD)), dtype) for _ in range(2))
+    Bk, Bv = (wl.store(rng.standard_normal((B, r, HD)) / np.sqrt(HD), dtype) for _ in range(2))
+    print(f"tile shapes B={B} n={n} HD={HD} r={r}", flush=True)
+    dK, dV, dBk, dBv = (to_dev(x, dtype) for x in (K, V, Bk, Bv))
+    C = [torch.zeros((B, n, r), dtype=torch.float16, device="cuda") for _ in range(2)]
+    ap.ap_compact(dK, dV, dBk, dBv, C[0], C[1], n=n, row0=0)
+    Q = [torch.zeros((B, n, r), dtype=torch.int8, device="cuda") for _ in range(2)]
+    S = [torch.zeros((B, n, r // 64), dtype=torch.float16, device="cuda") for _ in range(2)]
+    ap.ap_compact(dK, dV, dBk, dBv, Q[0], Q[1], S[0], S[1], n=n, row0=0)
+    Qr, Sr = torch.zeros_like(Q[0]), torch.zeros_like(S[0])
+    for X, Bm, c, q, s in ((K, Bk, C[0], Q[0], S[0]), (V, Bv, C[1], Q[1], S[1])):
+        ap.ap_quantize_i8(c, Qr, Sr, T=n)
+        torch.cuda.synchronize()
+        assert (Qr == q).all() and (Sr == s).all()
+        got = to_host64(c)
+        for b in sorted({0, B // 2, B - 1}):
+            ref = oracle.compact(oracle.promote(X[b], dtype), oracle.promote(Bm[b], dtype))
+            assert (np.abs(got[b] - ref) <= ROUND[dtype] * np.abs(ref) + 1e-5 * np.abs(ref).max()).all()
