@@ -13,10 +13,10 @@
 // split).  Coefficient tiles of 32 tokens travel HBM -> LDS with direct-to-LDS loads
 // through a ring of 16-row units (K rows, K rows, V rows, V rows, ...), several units in
 // flight while two are consumed, so no VGPR is spent on staging.  Every wave serves all
-// heads on an eighth of the rank axis, so each tile byte is read from LDS exactly once:
+// heads on a quarter of the rank axis, so each tile byte is read from LDS exactly once:
 //   S^T[t,h]  = Ck_tile[t,:] . q'^T      MFMA 16x16x32, A = tile rows (LDS), B = q' (VGPR);
-//                                         the eight waves' partial sums meet in LDS and
-//                                         each wave finalises the softmax of 1/8 of the heads
+//                                         the score waves' partial sums meet in LDS and each
+//                                         of them finalises the softmax of a quarter of the heads
 //   U^T[j,h] += Cv_tile^T[j,t] . P^T     MFMA 16x16x32, A = register transpose of the tile
 //                                         (v_perm), B = P read back in operand layout
 // For bf16 storage q' and P are split into hi+lo bf16 pairs (two MFMAs) so that the
@@ -474,14 +474,16 @@ struct AttnParams {
 //                     stream the C_v rows HBM -> LDS with direct-to-LDS loads through a ring
 //                     of 16-row units, several tiles ahead, so no VGPR is spent on staging
 //                     and every LDS byte is read exactly once.
-//   all eight waves:  finalise the softmax of 2*MT heads each (eight lanes per head): they
-//                     keep (reference exponent, sum) and publish the weights in MFMA operand
-//                     layout plus a per-head rescale factor.
-// The score waves work on tile t+1 while the sum waves accumulate tile t; two workgroup
-// barriers per tile ("partial scores ready", "weights ready") keep them in step.  The two
-// roles are separate non-inlined functions (same barrier sequence), so q' and U never
-// compete for registers.  The softmax reference exponent only moves when a score exceeds
-// it by more than kLazy, so the rescale factor is 1 on almost every tile.
+//   softmax:          the score waves, 4*MT heads each (eight lanes per head): they keep
+//                     (reference exponent, sum) and publish the weights in MFMA operand layout
+//                     plus a per-head rescale factor.  (Token-split mode: all eight waves.)
+// The sum waves are a tile behind: they add up tile t-1 in two parts, next to the scores and next
+// to the softmax of tile t; two workgroup barriers per tile ("partial scores ready", "weights
+// ready") keep the roles in step.  A tile then costs about what its longer role needs; with the
+// softmax of tile t on all eight waves, between the scores and the sum, it cost that plus the
+// softmax (us a pass: 21 sequences, 32 / 8 heads, rank 256 36.7 -> 34.7, 8 of rank 512 36.9 -> 36.2).
+// The softmax reference exponent only moves when a score exceeds it by more than kLazy, so the
+// rescale factor is 1 on almost every tile.
 //
 // Workgroup id -> (sequence, split).  Consecutive workgroup ids go to different XCDs (8 of
 // them, each with its own L2).  With whole groups of 8 sequences (xcd_aware), sequence b lives
@@ -702,11 +704,22 @@ struct WaveCtx {
   // Softmax of this score wave's heads for a tile whose first `valid` slots hold tokens (after
   // the score waves' partial tiles are in xchg).  newl: slot of the deferred token, if any:
   // its weight counts in the sum, is exported, and stays out of the value products.  The passes
-  // are independent: all read before any writes.
+  // are independent: all read before any writes.  Four head tiles leave no registers for two passes
+  // at once (they spilled, 165 against 128 us a step at 64 heads of rank 640): one after the other.
   __device__ __forceinline__ void finalize_softmax(int valid, int newl, int t) {
+    if constexpr (MT == 4) {
+      finalize_passes<0, 1>(valid, newl, t);
+      __builtin_amdgcn_sched_barrier(0);
+      finalize_passes<NP - 1, NP>(valid, newl, t);
+    } else {
+      finalize_passes<0, NP>(valid, newl, t);
+    }
+  }
+  template <int Q0, int Q1>
+  __device__ __forceinline__ void finalize_passes(int valid, int newl, int t) {
     f32x4_t sc[NP];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
       const int xi = o_hh[q] * 9 + (lane & 7);
       sc[q] = xchg[xi];
 #pragma unroll
@@ -715,7 +728,7 @@ struct WaveCtx {
     const int slot = 16 * o_tt + 4 * o_gg;
     if (scores) {                               // logits out, for importance tracking: [token][head]
 #pragma unroll
-      for (int q = 0; q < NP; ++q)
+      for (int q = Q0; q < Q1; ++q)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (owner[q] && o_hh[q] < H && slot + i < valid) {
@@ -726,14 +739,14 @@ struct WaveCtx {
     }
     if (valid < kTile) {
 #pragma unroll
-      for (int q = 0; q < NP; ++q)
+      for (int q = Q0; q < Q1; ++q)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (slot + i >= valid) sc[q][i] = -INFINITY;
     }
     float alpha[NP], pr[NP][4], pdef[NP];
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
       float tmax = fmaxf(fmaxf(sc[q][0], sc[q][1]), fmaxf(sc[q][2], sc[q][3]));
       tmax = max8(tmax);
       // the same decision in the 8 lanes of a head; the new reference is finite: every tile holds
@@ -750,7 +763,7 @@ struct WaveCtx {
     if (newl >= 0 && newl < kTile) {            // wave-uniform: this tile holds the deferred token
       const int li = newl - slot;
 #pragma unroll
-      for (int q = 0; q < NP; ++q) {
+      for (int q = Q0; q < Q1; ++q) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (li == i) { pdef[q] = pr[q][i]; pr[q][i] = 0.f; }
@@ -761,7 +774,7 @@ struct WaveCtx {
       }
     }
 #pragma unroll
-    for (int q = 0; q < NP; ++q) {
+    for (int q = Q0; q < Q1; ++q) {
       const int mt = o_hh[q] >> 4, ln = (o_hh[q] & 15) + 16 * o_gg;
       if (I8) {
         // int8 coefficients: the weights stay fp32 (the sum waves fold the value scales in before
@@ -1397,7 +1410,9 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       }
     };
     if constexpr (I8) wg_barrier();                      // the score waves' first key scales
-    constexpr int NA = (NGRP + 1) / 2;
+    // (with four head tiles and wide rows the weights do not stay in registers over the barrier: all of
+    // it before)
+    constexpr int NA = MT == 4 && RMAX >= 512 ? NGRP : (NGRP + 1) / 2;
     using First = std::integral_constant<int, 0>;
     using Mid = std::integral_constant<int, NA>;
     using Last = std::integral_constant<int, NGRP>;
