@@ -444,9 +444,13 @@ merge_parts(const MergeArgs a, void* __restrict__ out, float* __restrict__ lse, 
         z += w;
       }
       m = mb;
+    } else {
+#pragma unroll
+      for (int u = 0; u < NP; ++u) z = v[u] != v[u] ? v[u] : z;   // the maximum passes a NaN over: it counts all the same
     }
   };
-  // parts c0 .. c0 + NP - 1 of list k; past the end the last one again, with nothing in it
+  // parts c0 .. c0 + NP - 1 of list k; past the end the last one's address again, with nothing in it: zero
+  // for the output too, which may be infinite
   auto load = [&](int k, int c0, float (&v)[NP], float (&x)[NP]) {
     const int last = a.cnt[k] - 1;
 #pragma unroll
@@ -456,7 +460,11 @@ merge_parts(const MergeArgs a, void* __restrict__ out, float* __restrict__ lse, 
       x[u] = a.out[k][oo + c * a.ostride];
     }
 #pragma unroll
-    for (int u = 0; u < NP; ++u) v[u] = c0 + u <= last ? v[u] : -INFINITY;
+    for (int u = 0; u < NP; ++u) {
+      const bool in = c0 + u <= last;
+      v[u] = in ? v[u] : -INFINITY;
+      x[u] = in ? x[u] : 0.f;
+    }
   };
   float v0[NP], x0[NP], v1[NP], x1[NP];
   if (a.cnt[0] > 0) load(0, 0, v0, x0);

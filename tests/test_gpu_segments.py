@@ -54,6 +54,57 @@ def test_raw_attn_small(dtype, B, H, d, T_u, T_cap):
         assert np.abs(to_host64(lse[b]) - ref_lse).max() <= 2e-3 * max(1.0, np.abs(ref_lse).max())
 
 
+@pytest.mark.parametrize("T_u,t_inf", [
+    (160, 158),        # five parts: fewer than are requested at once
+    (576, 574),        # eighteen: the last request holds two
+    (576, 33),
+    (2049, 2047),      # 64, the last of them empty
+    (32, 30),          # one part
+])
+def test_infinite_value_stays_infinite_through_the_merge(T_u, t_inf):
+    """A cached value that is infinite makes its own output column infinite, of the head that reads it,
+    and nothing else (16-bit storage overflows that way; the definition has no 0 * inf in it: every
+    weight of a softmax is positive)."""
+    dtype, B, H, d, col = "f16", 1, 8, 256, 3 * 256 + 17
+    q, K, V = raw_case(dtype, B, H, d, T_u, 48)
+    V[0, t_inf, col] = np.inf
+    print(f"raw with an infinite value T_u={T_u} t={t_inf}", flush=True)
+    out, _ = gpu_raw(dtype, q, K, V, T_u)
+    got = to_host64(out[0]).reshape(-1)
+    assert got[col] == np.inf
+    V[0, t_inf, col] = 0.0
+    P = lambda x: oracle.promote(x, dtype)
+    ref = oracle.raw_attn(P(q)[0], P(K)[0], P(V)[0]).reshape(-1)
+    got[col] = ref[col]
+    assert_close(got, ref, dtype, "the other columns")
+
+
+@pytest.mark.parametrize("bad", [0, 1])
+def test_merge_does_not_hide_a_nan_logarithm(bad):
+    """A segment whose logarithm is NaN (a NaN reached its scores) makes the head's result NaN in either
+    position, as it would under one softmax; the other heads are the plain merge."""
+    from paper_2603_23914_amd import binding as ap
+    B, H, d = 2, 3, 64
+    rng = wl.rng_for(49, bad)
+    outs = [rng.standard_normal((B, H, d)).astype(np.float32) for _ in range(2)]
+    lses = [rng.standard_normal((B, H)).astype(np.float32) for _ in range(2)]
+    lses[bad][1, 2] = np.nan
+    print(f"merge with a NaN logarithm in segment {bad}", flush=True)
+    out = torch.empty((B, H, d), dtype=torch.float32, device="cuda")
+    lse = torch.empty((B, H), dtype=torch.float32, device="cuda")
+    t = [torch.from_numpy(x).cuda() for x in (outs[0], lses[0], outs[1], lses[1])]
+    ap.ap_merge_segments(*t, out, lse=lse)
+    torch.cuda.synchronize()
+    got, gl = to_host64(out), to_host64(lse)
+    a, b = (x.astype(np.float64) for x in lses)
+    ref_l = np.logaddexp(a, b)
+    ref = np.exp(a - ref_l)[..., None] * outs[0] + np.exp(b - ref_l)[..., None] * outs[1]
+    assert np.isnan(got[1, 2]).all() and np.isnan(gl[1, 2])
+    ok = ~np.isnan(ref_l)
+    # fp32 throughout: exponent arguments of up to 6, a handful of roundings
+    assert np.abs(got[ok] - ref[ok]).max() <= 1e-5 * np.abs(ref[ok]).max() and np.abs(gl[ok] - ref_l[ok]).max() <= 1e-5
+
+
 def test_raw_attn_empty_segment():
     q, K, V = raw_case("f16", 2, 8, 128, 8, 42)
     out, lse = gpu_raw("f16", q, K, V, 0)
