@@ -255,10 +255,12 @@ __device__ __forceinline__ void score_tile_i8(const u32x4_t (&Araw)[NBW][2],
       pb[mt][0] = Mfma<F16Tag>::run(a1[0], qhi[2 * i + 1][mt], pb[mt][0]);
       pb[mt][1] = Mfma<F16Tag>::run(a1[1], qhi[2 * i + 1][mt], pb[mt][1]);
     }
-    const int blk = w + 4 * i < nsb ? w + 4 * i : 0;     // a block beyond the rank has zero q': any scale
+    const bool in = w + 4 * i < nsb;                       // a block beyond the rank adds nothing: zero q', and
+    const int blk = in ? w + 4 * i : 0;                    // a scale of 0, as another block's may be infinite
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
-      const u32x2_t sb = *(const u32x2_t*)(ks + blk * kTile + 16 * tt + 4 * g);
+      u32x2_t sb = *(const u32x2_t*)(ks + blk * kTile + 16 * tt + 4 * g);
+      if (!in) sb = u32x2_t{0, 0};
       const float sc[4] = {lo_to_f32(sb[0], F16Tag{}), hi_to_f32(sb[0], F16Tag{}), lo_to_f32(sb[1], F16Tag{}),
                            hi_to_f32(sb[1], F16Tag{})};
 #pragma unroll

@@ -149,3 +149,23 @@ def test_decode_i8_with_per_token_ranks(B, H, d, r, T, granks, cum, den, use_k, 
                                              rank_k=rank_np[b] if use_k else None,
                                              rank_v=rank_np[b] if use_v else None)
     assert_close(to_host64(out), ref, "f16", "int8 with per-token ranks")
+
+
+@pytest.mark.parametrize("r", [320, 192])
+def test_decode_i8_infinite_scale_stays_in_its_token(r):
+    """A key scale that overflowed to infinity, on a token whose block sum is negative for every head: the
+    token's score is -inf and its weight 0.  The waves of the score pass hold whole rounds of four scale
+    blocks, and a block beyond the rank (r = 320: five of eight slots filled) must not meet that scale."""
+    B, H, d, T, t = 1, 8, 128, 64, 5
+    case = wl.decode_case("f16", B, H, d, r, T, steps=0, seed=19, append=False)
+    q = np.abs(wl.step_query(case, 0))
+    Bk = case.Bk.copy()
+    Bk[0, :64] = np.abs(Bk[0, :64])                        # folded query positive over block 0
+    Ck8, sk, Cv8, sv = quantize_case(case, T)
+    Ck8[0, t, :64] = -1
+    sk[0, t, 0] = np.inf
+    print(f"int8 decode, one infinite key scale, r={r}", flush=True)
+    got = run_i8(q, Ck8, sk, Cv8, sv, Bk, case.Bv, T)
+    keep = [i for i in range(T) if i != t]                 # the same attention without the token
+    ref = oracle_i8(q, Ck8[:, keep], sk[:, keep], Cv8[:, keep], sv[:, keep], Bk, case.Bv, T - 1)
+    assert_close(got[0], ref[0], "f16", "int8 with an infinite scale")
