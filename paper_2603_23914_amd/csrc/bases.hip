@@ -40,8 +40,11 @@ constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16
 
 // ---- out[c][r] = in[r][c] for 16-bit elements; columns rows .. ld_out-1 of out are zero-filled.
 //      Bound by memory: 16 bytes per lane in and out, 2-byte pieces only in LDS (195 us against 437 with
-//      2-byte loads and stores at 16 x 4224 x 4096).  ld_in, cols, ld_out multiples of 8, 16-byte
-//      aligned rows.  grid (ceil(ld_out / 64), ceil(cols / 64), batch), 256 threads.
+//      2-byte loads and stores at 16 x 4224 x 4096).  ld_in, cols, ld_out multiples of 8, out with
+//      16-byte aligned rows.  WIDE: in too; without it only `in` itself is aligned and the batches may
+//      lie any number of elements apart.
+//      grid (ceil(ld_out / 64), ceil(cols / 64), batch), 256 threads.
+template <bool WIDE>
 __global__ void __launch_bounds__(256)
 transpose16(const uint16_t* __restrict__ in, int64_t in_bstride, int ld_in, uint16_t* __restrict__ out,
             int64_t out_bstride, int ld_out, int rows, int cols) {
@@ -55,7 +58,16 @@ transpose16(const uint16_t* __restrict__ in, int64_t in_bstride, int ld_in, uint
   for (int u = 0; u < 2; ++u) {                          // lanes 0-7 one row, ...: 128-byte pieces
     const int rr = (tid >> 3) + 32 * u, c = c0 + (tid & 7) * 8;
     const u32x4_t z = {0, 0, 0, 0};
-    v[u] = r0 + rr < rows && c < cols ? *(const u32x4_t*)(in + (size_t)(r0 + rr) * ld_in + c) : z;
+    const uint16_t* src = in + (size_t)(r0 + rr) * ld_in + c;
+    v[u] = z;
+    if (r0 + rr < rows && c < cols) {
+      if constexpr (WIDE) {
+        v[u] = *(const u32x4_t*)src;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = (uint32_t)src[2 * e] | (uint32_t)src[2 * e + 1] << 16;
+      }
+    }
   }
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -890,7 +902,7 @@ ap_status run_bases(const BasesArgs& a) {
   const int np = w.n_pad;
   const ap_dtype dt = a.dt;
 
-  hipLaunchKernelGGL(transpose16, dim3(np / 64, (HD + 63) / 64, B), dim3(256), 0, st, (const uint16_t*)a.X,
+  hipLaunchKernelGGL((transpose16<true>), dim3(np / 64, (HD + 63) / 64, B), dim3(256), 0, st, (const uint16_t*)a.X,
                      (int64_t)n * HD, HD, Xt, (int64_t)HD * np, np, n, HD);
   if (np > n) hipLaunchKernelGGL(fill_pad16, dim3(l, B), dim3(64), 0, st, Yt, (int64_t)l * np, np, n);
   const void* Pcur = a.Omega;
@@ -952,7 +964,10 @@ ap_status launch_decompress(const void* C, const void* Bm, int64_t bstride, cons
                             int T_cap, int HD, int r, ap_dtype dt, void* workspace, hipStream_t st) {
   uint16_t* Dt = (uint16_t*)workspace;                                     // [B or 1][HD][r]
   const int nb = bstride ? B : 1;
-  hipLaunchKernelGGL(transpose16, dim3((r + 63) / 64, (HD + 63) / 64, nb), dim3(256), 0, st, (const uint16_t*)Bm,
+  // any distance between the bases is taken; one that is no multiple of 8 elements leaves their rows
+  // without the 16-byte alignment that wide loads need
+  auto kern = bstride % 8 == 0 ? transpose16<true> : transpose16<false>;
+  hipLaunchKernelGGL(kern, dim3((r + 63) / 64, (HD + 63) / 64, nb), dim3(256), 0, st, (const uint16_t*)Bm,
                      bstride, HD, Dt, (int64_t)HD * r, r, r, HD);
   const void* A = C;
   int64_t a_bs = (int64_t)T_cap * r;

@@ -121,6 +121,30 @@ def test_decompress_is_the_retrieve_step(dtype, B, T, cap, HD, r, ranked, shared
         assert (np.abs(got[b] - ref) <= eps * np.abs(ref) + 1e-5 * np.abs(ref).max()).all()
 
 
+@pytest.mark.parametrize("gap", [1, 2, 4, 5, 8])
+def test_decompress_takes_any_distance_between_the_bases(gap):
+    """Bases that lie r HD + gap elements apart, rows of the later ones off 16-byte boundaries: the same
+    bits as from bases that follow one another."""
+    from paper_2603_23914_amd import binding as ap
+    dtype, B, T, HD, r = "f16", 3, 70, 136, 64
+    rng = wl.rng_for(14, gap)
+    C = to_dev(wl.store(rng.standard_normal((B, T, r)), dtype), dtype)
+    Bm = to_dev(wl.store(rng.standard_normal((B, r, HD)) / math.sqrt(HD), dtype), dtype)
+    apart = torch.full((B, r * HD + gap), float("nan"), dtype=torch.float16, device="cuda")
+    apart[:, :r * HD] = Bm.view(B, r * HD)
+    out = [torch.zeros((B, T, HD), dtype=torch.float16, device="cuda") for _ in range(2)]
+    ws = workspace(ap.ap_decompress_workspace_bytes(B, T, HD, r, False))
+    print(f"decompress with a gap of {gap}", flush=True)
+    ap.ap_decompress(C, Bm, out[0], ws, T=T)
+    # the C entry point: the binding's tensors are contiguous
+    ap._check(ap._lib.ap_decompress(C.data_ptr(), apart.data_ptr(), r * HD + gap, None, out[1].data_ptr(), B, T, T, HD, r,
+                                    ap.AP_F16, ws.data_ptr(), ws.numel(), ap._stream(None)))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16))
+    ref = oracle.decompress(to_host64(C[B - 1]), to_host64(Bm[B - 1]))
+    assert (np.abs(to_host64(out[1][B - 1]) - ref) <= 2.0 ** -10 * np.abs(ref) + 1e-5 * np.abs(ref).max()).all()
+
+
 def test_recompression_of_a_compressed_cache_with_a_raw_tail():
     """Alg. 1's compress step when the uncompressed tail has grown: the retrieved cache
     (decompressed coefficients, then the raw rows) is decomposed again.  The new basis must serve
