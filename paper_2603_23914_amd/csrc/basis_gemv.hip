@@ -255,7 +255,7 @@ fold_heads(const uint16_t* __restrict__ Bk, int64_t bstride, const uint16_t* __r
 // splits 46.3 -> 39.3; sixteen of them with 16 splits 74.7 -> 70.8; one sequence, 256 splits 47.6 ->
 // 39.7; 64 sequences on one shared basis, rank 640 223 -> 218.
 // SLICED: several slices per head; their sums go to pout [B][nslice][H d], which reduce_out adds up.
-//   grid (B * H * nslice), NT threads, NT >= S, NT >= js / 4;
+//   grid (H * nslice, B), one dimension being too short for all of them; NT threads, NT >= S, NT >= js / 4;
 //   dynamic LDS: weights [S], ustar [js], sums max(4 NT, NT / 64 d)
 // ------------------------------------------------------------------------------------------
 struct MergeExpandParams {
@@ -281,20 +281,20 @@ __global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
   float* ustar = wgt + ((S + 3) & ~3);                        // [js]
   float* sums = ustar + js;
   // ---- which head, sequence, slice
-  const int total = p.B * H * p.nslice;
-  int id = (int)blockIdx.x;
+  const uint32_t total = gridDim.x * gridDim.y;               // < 2^32: B and H are at most 65535
+  uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
   if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
   int b, h, sl;
   if (p.bstride == 0) {
-    b = id % p.B;
-    const int t = id / p.B;
-    sl = t % p.nslice;
-    h = t / p.nslice;
+    b = (int)(id % (uint32_t)p.B);
+    const uint32_t t = id / (uint32_t)p.B;
+    sl = (int)(t % (uint32_t)p.nslice);
+    h = (int)(t / (uint32_t)p.nslice);
   } else {
-    h = id % H;
-    const int t = id / H;
-    sl = t % p.nslice;
-    b = t / p.nslice;
+    h = (int)(id % (uint32_t)H);
+    const uint32_t t = id / (uint32_t)H;
+    sl = (int)(t % (uint32_t)p.nslice);
+    b = (int)(t / (uint32_t)p.nslice);
   }
   const int j0 = sl * js;
   // ---- requests: B_v rows, then (m, l), then the first sums
@@ -925,14 +925,14 @@ ap_status launch_expand_append(ap_dtype dt, bool out_f32, const void* Bv, int64_
 namespace {
 template <class Tag, bool OUT_F32, bool SLICED, int NT>
 void launch_me(const MergeExpandParams& p, int d, hipStream_t stream) {
-  const int grid = p.B * p.H * p.nslice;
+  const dim3 grid(p.H * p.nslice, p.B);
   const int most = 4 * NT > NT / 64 * d ? 4 * NT : NT / 64 * d;
   const size_t lds = ((size_t)((p.S + 3) & ~3) + p.js + most) * 4;
   switch (d) {
-    case 32: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 4>), dim3(grid), dim3(NT), lds, stream, p); break;
-    case 64: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 8>), dim3(grid), dim3(NT), lds, stream, p); break;
-    case 128: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 16>), dim3(grid), dim3(NT), lds, stream, p); break;
-    default: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 32>), dim3(grid), dim3(NT), lds, stream, p); break;
+    case 32: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 4>), grid, dim3(NT), lds, stream, p); break;
+    case 64: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 8>), grid, dim3(NT), lds, stream, p); break;
+    case 128: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 16>), grid, dim3(NT), lds, stream, p); break;
+    default: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 32>), grid, dim3(NT), lds, stream, p); break;
   }
 }
 template <class Tag, bool OUT_F32>

@@ -53,6 +53,29 @@ def test_valueonly_attn(dtype, B, H, Hkv, d, r, T):
         assert np.abs(to_host64(lse[b]) - ref_lse).max() <= 2e-3 * max(1.0, np.abs(ref_lse).max())
 
 
+def test_valueonly_more_heads_than_one_grid_dimension_holds():
+    """257 sequences of 65535 query heads: with 256 threads per head more than 2^32 threads, the limit of a
+    launch's first dimension.  One token, so every head's output is its value row: C_v[b] B_v, its slice.
+    2^-20: a sum of eight exact products in fp32, in either order."""
+    from paper_2603_23914_amd import binding as ap
+    B, H, Hkv, d, r = 257, 65535, 255, 32, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(93)
+    N = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.float16)
+    q = torch.zeros((B, H, d), dtype=torch.float16, device="cuda")
+    K, Cv, Bv = N(B, 1, Hkv * d), N(B, 1, r), N(r, Hkv * d)
+    out = torch.full((B, H, d), float("nan"), dtype=torch.float32, device="cuda")
+    print(f"value-only B={B} H={H}", flush=True)
+    ap.ap_valueonly_attn(q, K, Cv, Bv, out, workspace(ap.ap_valueonly_workspace_bytes(B, H, Hkv, d, 1, r)), T=1, sm_scale=1.0)
+    torch.cuda.synchronize()
+    ref = (Cv[:, 0, :, None].float() * Bv.float()).sum(dim=1).view(B, Hkv, 1, d)
+    err = 0.0
+    for b in range(0, B, 32):
+        n = min(32, B - b)
+        err = max(err, (out[b:b + n].view(n, Hkv, H // Hkv, d) - ref[b:b + n]).abs().max().item())
+    assert err <= 2.0 ** -20 * ref.abs().max().item()
+
+
 def test_valueonly_shared_basis_joined_with_raw_tail():
     from paper_2603_23914_amd import binding as ap
     dtype, B, H, Hkv, d, r, T, T_u = "f16", 3, 16, 4, 128, 128, 500, 41
