@@ -737,12 +737,12 @@ merge_splits(const float* __restrict__ part_ml, const float* __restrict__ part_U
 }
 
 }  // namespace
-int basis_rows_per_wave(int B, int r, int HD);
+int basis_rows_per_wave(int B, int r, int HD, int jobs, int G, bool shared);
 namespace {
 
 template <class Tag, bool DOT, bool FOLD, bool PAIR>
 ap_status launch_rows(RowsParams p, int B, hipStream_t stream) {
-  const int rpw = basis_rows_per_wave(B, p.r, p.HD);
+  const int rpw = basis_rows_per_wave(B, p.r, p.HD, PAIR ? 2 : 1, 1, p.bstride == 0);
   p.rpw = rpw;
   const int rows_wg = 4 * rpw;
   const dim3 grid((p.r + rows_wg - 1) / rows_wg, B, PAIR ? 2 : 1);
@@ -768,7 +768,7 @@ ap_status launch_rows(RowsParams p, int B, hipStream_t stream) {
 // append in one launch.
 template <class Tag, int KPC, int LPH, int G>
 ap_status launch_rows_grouped(RowsParams p, int B, hipStream_t stream) {
-  const int rpw = basis_rows_per_wave(B, p.r, p.HD);
+  const int rpw = basis_rows_per_wave(B, p.r, p.HD, 2, G, p.bstride == 0);
   p.rpw = rpw;
   const dim3 grid((p.r + 4 * rpw - 1) / (4 * rpw), B, 2);
   const size_t lds = (size_t)p.Hp * (4 * rpw + 1) * 4;
@@ -851,17 +851,41 @@ ap_status launch_fold_heads(ap_dtype dt, const void* Bk, int64_t bstride, const 
   return AP_OK;
 }
 
-int basis_rows_per_wave(int B, int r, int HD) {
-  // about five workgroups per CU, two of them resident at a time: the start and the end of a
-  // workgroup (vector slices in, folded tile out) then overlap other workgroups' streaming
-  int rpw = (int)(((int64_t)B * r + 5119) / 5120);
-  // At least four rows per wave (its vector slices are as long as a row) where the pass moves 32 MB
-  // and more; a shorter one is a matter of latency and takes two, the shortest one.  Us a pass at
-  // 4 / 2 / 1 rows: 34 MB 39.8 / 41.6 / 46.0 and 37.6 / 39.4 / 43.9, 26 MB 43.0 / 42.1 / 45.9, 11 MB
-  // 32.3 / 31.0 / 31.0, 8 MB 20.2 / 19.1 / 19.5, 4 MB 24.9 / 23.3 / 23.4, 64 rows in all 17.2 / 16.8 / 16.4.
-  const int64_t rows = (int64_t)B * r;
-  const int least = rows * HD * 2 >= (32ll << 20) ? 4 : (rows > 256 ? 2 : 1);
-  return rpw < least ? least : (rpw > 32 ? 32 : rpw);
+// Rows of a basis per wave.  jobs: 2 where the launch also appends the value row; G: query heads per slice;
+// shared: one basis for all sequences, whose rows come out of the L2s.
+// Many rows: about five workgroups per CU, two of them resident at a time: the start and the end of a
+// workgroup (vector slices in, folded tile out) then overlap other workgroups' streaming.
+// Few: what counts is how evenly the workgroups fall on the 256 CUs, against a wave's vector slices, which
+// are as long as a row (two where it also appends).  Alone in its launch a job wants every CU used once:
+// two rows up to 256 workgroups, four up to 256 of those, and beyond that two again, as three rounds of
+// two rows are fewer than two of four.  Two jobs go through one CU at a time: the same with 512.
+// Us a pass at 4 / 2 rows, HD = 4096: one job 2048 rows 17.9 / 17.2, 2560 19.0 / 19.6, 4160 28.8 / 27.3; two
+// jobs 2048 rows 23.9 / 22.9, 3072 26.8 / 27.7, 4608 36.9 / 34.6.  Rows of at most 2048 elements are too
+// short for more than two to pay (HD = 2048, two jobs: 15.8 / 15.1 at 2048 rows, 20.4 / 19.6 at 4160).
+// HD 4097 - 5120, two jobs: its ring of two rows leaves room for one workgroup, 256 again, and then four
+// (2048 rows 28.8 / 29.3, 4608 40.6 / 41.6); above that no ring, more waves help longer (HD = 6144: 2496
+// rows 27.4 / 26.4, 3072 36.4 / 36.9, 4608 48.6 / 46.1).  One basis for all: 2560 rows of 4096 21.7 / 21.2
+// (two jobs) and 16.8 / 16.5, 2048 of 5120 24.1 / 23.5, 3072 25.3 / 27.4 and 17.7 / 18.3.
+// More than 5120 rows: HD = 4096 8192 rows 49.1 / 50.3, shared 10240 31.7 / 34.9; only short ones gain
+// (12288 rows of 512 17.7 / 17.1, 6144 of 1024 17.2 / 16.8, two jobs), and odd numbers of rows, whose folded
+// pieces are not aligned, do not pay elsewhere (15360 rows of 5120 at 4 / 3: 55.5 / 92.0).
+// Several heads per slice are work that grows with the rows: 32 heads on 8 of 64 6144 rows 19.1 / 18.1, 64
+// on 16 of 128 6144 rows 34.9 / 33.2, shared 7296 30.7 / 31.4, 10240 rows 47.4 / 49.2.
+// One row: 64 rows in all 17.2 / 16.8 at 4 / 2 and 16.4, 256 rows of 8192 22.5 / 19.6 and 18.5.
+int basis_rows_per_wave(int B, int r, int HD, int jobs, int G, bool shared) {
+  const int64_t rows = (int64_t)B * r, bytes = rows * HD * 2;
+  const int rpw = (int)((rows + 5119) / 5120);
+  if (rpw > 4) return rpw > 32 ? 32 : rpw;
+  if (rows <= 256) return 1;
+  if (G > 1) return bytes >= (28ll << 20) ? 4 : (rpw < 2 ? 2 : rpw);
+  if (rows > 5120) return jobs == 2 && bytes < (16ll << 20) ? rpw : 4;
+  if (HD <= 2048) return 2;
+  const bool short_ring = HD > 4096 && HD <= 5120;
+  if (jobs == 1 && shared && !short_ring) return 2;
+  const int64_t wg2 = (int64_t)((r + 7) / 8) * B * jobs, wg4 = (int64_t)((r + 15) / 16) * B * jobs;
+  if (jobs == 1) return wg2 <= 256 || wg4 > 256 ? 2 : 4;
+  if (short_ring) return wg2 <= (shared ? 512 : 256) ? 2 : 4;
+  return wg2 <= (shared || HD > 5120 ? 640 : 512) || wg4 > 512 ? 2 : 4;
 }
 // expand_append: about four two-wave workgroups per CU in one round, but never more than 16 row
 // blocks per sequence at large batches (each block writes an HD-wide partial output that
