@@ -12,14 +12,12 @@
 //                           share one pass over B_k.
 //   merge_expand            combine the token splits of attn_partial and expand through B_v:
 //                           out[h, :] = (sum_s w_s U_s[h, :] / sum_s w_s l_s) . Bv[:, head h]
-//                           (Alg. 1 output by associativity).  A workgroup owns two heads
-//                           (512-byte row segments) and keeps eight rows in flight per thread.
+//                           (Alg. 1 output by associativity).  A workgroup owns one head, or a
+//                           slice of its columns, and keeps eight rows in flight per thread.
 // Products of two 16-bit values are exact in fp32; sums are fp32 (v_dot2c_f32_*).
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
 #include "mfma_ops.hpp"
-#include <cstdlib>
-#include <cstdio>
 
 namespace ap {
 namespace {
@@ -31,6 +29,9 @@ __device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes
 }
 __device__ __forceinline__ u32x4_t buffer_load16(buffer_t rsrc, uint32_t offset) {
   return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 0));
+}
+__device__ __forceinline__ float buffer_load4(buffer_t rsrc, uint32_t offset) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, offset, 0, 0));
 }
 
 // Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
@@ -249,14 +250,21 @@ fold_heads(const uint16_t* __restrict__ Bk, int64_t bstride, const uint16_t* __r
 // rows arrive.  The loads go through buffers that end with the slice, so that no lane has a branch
 // and the waits stay exact.  Workgroups are numbered in runs per XCD: neighbouring heads, which
 // share the rows' pages, with a basis per sequence; the same head of all sequences with a shared
-// basis, which then stays in that XCD's L2.
+// basis, which then stays in that XCD's L2.  plain: in launch order, so that all XCDs walk the rows of
+// the same few sequences, where the bases do not fit the L2s anyway.
 // Against two heads per workgroup, whose rows were requested after the merge, and a launch of its
 // own that merged more than sixteen splits (us a pass): eight sequences of 32 heads, rank 512, 32
 // splits 46.3 -> 39.3; sixteen of them with 16 splits 74.7 -> 70.8; one sequence, 256 splits 47.6 ->
 // 39.7; 64 sequences on one shared basis, rank 640 223 -> 218.
+// FEW: at most kFewSplits.  Every thread then takes all (m, l) pairs and one column at a time, so that
+// the merge needs no exchange and half the registers (62 against 112: eight waves per SIMD, not four),
+// which is what many heads with little work each want; without it 48 x 40 heads of rank 64 lost a tenth
+// against two heads per workgroup.  Us a pass there / without FEW / with it: 64 sequences of 40 heads,
+// rank 128 on a shared basis 25.4 / 27.3 / 25.0, 48 of 64 heads, rank 320 51.2 / 53.8 / 47.6, 24 of 32
+// heads of 64, rank 64 13.4 / 14.1 / 12.8.
 // SLICED: several slices per head; their sums go to pout [B][nslice][H d], which reduce_out adds up.
-//   grid (H * nslice, B), one dimension being too short for all of them; NT threads, NT >= S, NT >= js / 4;
-//   dynamic LDS: weights [S], ustar [js], sums max(4 NT, NT / 64 d)
+//   grid (H * nslice, B), one dimension being too short for all of them; NT threads, without FEW NT >= S
+//   and NT >= js / 4; dynamic LDS: (without FEW) weights [S], ustar [js], sums max(4 NT, NT / 64 d)
 // ------------------------------------------------------------------------------------------
 struct MergeExpandParams {
   const float* part_ml;     // [B][S][H][2]
@@ -266,10 +274,11 @@ struct MergeExpandParams {
   void* out;                // [B][H][d]
   float* lse;               // [B][H] or null
   float* pout;              // SLICED: [B][nslice][H d]
-  int B, H, G, r, S, nslice, js;
+  int B, H, G, r, S, nslice, js, plain;
 };
+constexpr int kFewSplits = 8;
 
-template <class Tag, bool OUT_F32, bool SLICED, int NT, int LPR>
+template <class Tag, bool OUT_F32, bool SLICED, bool FEW, int NT, int LPR>
 __global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
   constexpr int d = LPR * 8, ROWS = NT / LPR, NW = NT / 64;   // a row segment per LPR lanes
   constexpr int kRows = 8, kU = 8;                            // loads in flight per thread of either kind
@@ -278,12 +287,12 @@ __global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int S = p.S, H = p.H, r = p.r, js = p.js;
   float* wgt = smem_me;                                       // [S rounded up to 4]
-  float* ustar = wgt + ((S + 3) & ~3);                        // [js]
+  float* ustar = FEW ? smem_me : wgt + ((S + 3) & ~3);        // [js]
   float* sums = ustar + js;
   // ---- which head, sequence, slice
   const uint32_t total = gridDim.x * gridDim.y;               // < 2^32: B and H are at most 65535
   uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
-  if ((total & 7) == 0) id = (id & 7) * (total >> 3) + (id >> 3);
+  if ((total & 7) == 0 && !p.plain) id = (id & 7) * (total >> 3) + (id >> 3);
   int b, h, sl;
   if (p.bstride == 0) {
     b = (int)(id % (uint32_t)p.B);
@@ -309,67 +318,102 @@ __global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
     for (int k = 0; k < kRows; ++k) wv[k] = buffer_load16(brow, (uint32_t)(j + k * ROWS) * row_bytes + cc * 16);
   };
   const size_t pb = (size_t)b * S * H + h;                    // + s H
-  const int nc4 = js >> 2, ngrp = NT / nc4;                   // four columns per thread, splits dealt to groups
-  const int grp = tid / nc4, c4 = tid - grp * nc4;
-  const uint32_t split_bytes = (uint32_t)H * r * 4;
+  const uint32_t split_bytes = (uint32_t)H * r * 4;           // H <= 64 here, or S <= 8: far below 4 GiB
   const auto bsum = make_buffer(p.part_U + pb * r + j0, (uint32_t)(S - 1) * split_bytes + js * 4);
-  u32x4_t uv[kU];
-  auto load_sums = [&](int s0) {                              // splits s0 + grp + k ngrp; zeros past the last
+  if constexpr (FEW) {
+    float wv[kFewSplits], lv[kFewSplits], uv[kFewSplits];
 #pragma unroll
-    for (int k = 0; k < kU; ++k) uv[k] = buffer_load16(bsum, (uint32_t)(s0 + grp + k * ngrp) * split_bytes + 16 * c4);
-  };
-  const size_t ml0 = (pb + (size_t)(tid < S ? tid : 0) * H) * 2;
-  const f32x2_t ml = *(const f32x2_t*)(p.part_ml + ml0);
-  load_sums(0);
-  load_rows(rg);
-  // ---- weights 2^(m_s - m*) and their weighted sum of l
-  const float mv = tid < S ? ml[0] : -INFINITY;
-  float m = mv;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if (lane == 0) redw[w] = m;
-  lds_barrier();
-  m = redw[0];
-#pragma unroll
-  for (int k = 1; k < NW; ++k) m = fmaxf(m, redw[k]);
-  float L = 0.f;
-  if (tid < S) {
-    const float ws = fast_exp2(mv - m);
-    wgt[tid] = ws;
-    L = ws * ml[1];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o);
-  if (lane == 0) redw[NW + w] = L;
-  lds_barrier();
-  L = redw[NW];
-#pragma unroll
-  for (int k = 1; k < NW; ++k) L += redw[NW + k];
-  if (p.lse && tid == 0 && sl == 0) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
-  // ---- ustar[j] = sum_s w_s U_s[j] / L: a group's splits in order, then the groups in order
-  f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};
-  auto add_sums = [&](int s0) {
-#pragma unroll
-    for (int k = 0; k < kU; ++k) {
-      const int s = s0 + grp + k * ngrp;
-      const float ws = s < S ? wgt[s] : 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc4[e] = fmaf(ws, __builtin_bit_cast(f32x4_t, uv[k])[e], acc4[e]);
+    for (int k = 0; k < kFewSplits; ++k) {
+      const f32x2_t ml = *(const f32x2_t*)(p.part_ml + (pb + (size_t)(k < S ? k : 0) * H) * 2);
+      wv[k] = ml[0];
+      lv[k] = ml[1];
     }
-  };
-  add_sums(0);
-  for (int s0 = kU * ngrp; s0 < S; s0 += kU * ngrp) {
-    load_sums(s0);
-    add_sums(s0);
+    auto load_sums = [&](int c) {                             // zeros past the last split
+#pragma unroll
+      for (int k = 0; k < kFewSplits; ++k) uv[k] = buffer_load4(bsum, (uint32_t)k * split_bytes + 4 * c);
+    };
+    load_sums(tid < js ? tid : 0);
+    load_rows(rg);
+    // ---- weights 2^(m_s - m*) and their weighted sum of l
+    float m = wv[0], L = 0.f;
+#pragma unroll
+    for (int k = 1; k < kFewSplits; ++k) m = k < S ? fmaxf(m, wv[k]) : m;
+#pragma unroll
+    for (int k = 0; k < kFewSplits; ++k) {
+      wv[k] = k < S ? fast_exp2(wv[k] - m) : 0.f;
+      L = k < S ? fmaf(wv[k], lv[k], L) : L;
+    }
+    if (p.lse && tid == 0 && sl == 0) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
+    // ---- ustar[j] = sum_s w_s U_s[j] / L
+    for (int c = tid; c < js; c += NT) {
+      if (c != tid) load_sums(c);
+      float a = 0.f;
+#pragma unroll
+      for (int k = 0; k < kFewSplits; ++k) a = fmaf(wv[k], uv[k], a);
+      ustar[c] = a / L;
+    }
+    lds_barrier();
+  } else {
+    const int nc4 = js >> 2, ngrp = NT / nc4;                   // four columns per thread, splits dealt to groups
+    const int grp = tid / nc4, c4 = tid - grp * nc4;
+    u32x4_t uv[kU];
+    auto load_sums = [&](int s0) {                              // splits s0 + grp + k ngrp; zeros past the last
+#pragma unroll
+      for (int k = 0; k < kU; ++k) uv[k] = buffer_load16(bsum, (uint32_t)(s0 + grp + k * ngrp) * split_bytes + 16 * c4);
+    };
+    const size_t ml0 = (pb + (size_t)(tid < S ? tid : 0) * H) * 2;
+    const f32x2_t ml = *(const f32x2_t*)(p.part_ml + ml0);
+    load_sums(0);
+    load_rows(rg);
+    // ---- weights 2^(m_s - m*) and their weighted sum of l
+    const float mv = tid < S ? ml[0] : -INFINITY;
+    float m = mv;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (lane == 0) redw[w] = m;
+    lds_barrier();
+    m = redw[0];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) m = fmaxf(m, redw[k]);
+    float L = 0.f;
+    if (tid < S) {
+      const float ws = fast_exp2(mv - m);
+      wgt[tid] = ws;
+      L = ws * ml[1];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o);
+    if (lane == 0) redw[NW + w] = L;
+    lds_barrier();
+    L = redw[NW];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) L += redw[NW + k];
+    if (p.lse && tid == 0 && sl == 0) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
+    // ---- ustar[j] = sum_s w_s U_s[j] / L: a group's splits in order, then the groups in order
+    f32x4_t acc4 = {0.f, 0.f, 0.f, 0.f};
+    auto add_sums = [&](int s0) {
+#pragma unroll
+      for (int k = 0; k < kU; ++k) {
+        const int s = s0 + grp + k * ngrp;
+        const float ws = s < S ? wgt[s] : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc4[e] = fmaf(ws, __builtin_bit_cast(f32x4_t, uv[k])[e], acc4[e]);
+      }
+    };
+    add_sums(0);
+    for (int s0 = kU * ngrp; s0 < S; s0 += kU * ngrp) {
+      load_sums(s0);
+      add_sums(s0);
+    }
+    if (grp < ngrp) *(f32x4_t*)(sums + grp * js + 4 * c4) = acc4;
+    lds_barrier();
+    for (int j = tid; j < js; j += NT) {
+      float a = sums[j];
+      for (int k = 1; k < ngrp; ++k) a += sums[k * js + j];
+      ustar[j] = a / L;
+    }
+    lds_barrier();
   }
-  if (grp < ngrp) *(f32x4_t*)(sums + grp * js + 4 * c4) = acc4;
-  lds_barrier();
-  for (int j = tid; j < js; j += NT) {
-    float a = sums[j];
-    for (int k = 1; k < ngrp; ++k) a += sums[k * js + j];
-    ustar[j] = a / L;
-  }
-  lds_barrier();
   // ---- expansion: thread (rg, cc) owns 8 columns and rows rg, rg + ROWS, ..
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   auto use_rows = [&](int j) {
@@ -947,27 +991,54 @@ ap_status launch_expand_append(ap_dtype dt, bool out_f32, const void* Bv, int64_
 }
 
 namespace {
-template <class Tag, bool OUT_F32, bool SLICED, int NT>
+template <class Tag, bool OUT_F32, bool SLICED, bool FEW, int NT>
 void launch_me(const MergeExpandParams& p, int d, hipStream_t stream) {
   const dim3 grid(p.H * p.nslice, p.B);
-  const int most = 4 * NT > NT / 64 * d ? 4 * NT : NT / 64 * d;
-  const size_t lds = ((size_t)((p.S + 3) & ~3) + p.js + most) * 4;
+  const int most = FEW ? NT / 64 * d : (4 * NT > NT / 64 * d ? 4 * NT : NT / 64 * d);
+  const size_t lds = ((size_t)(FEW ? 0 : (p.S + 3) & ~3) + p.js + most) * 4;
   switch (d) {
-    case 32: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 4>), grid, dim3(NT), lds, stream, p); break;
-    case 64: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 8>), grid, dim3(NT), lds, stream, p); break;
-    case 128: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 16>), grid, dim3(NT), lds, stream, p); break;
-    default: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, NT, 32>), grid, dim3(NT), lds, stream, p); break;
+    case 32: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, FEW, NT, 4>), grid, dim3(NT), lds, stream, p); break;
+    case 64: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, FEW, NT, 8>), grid, dim3(NT), lds, stream, p); break;
+    case 128: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, FEW, NT, 16>), grid, dim3(NT), lds, stream, p); break;
+    default: hipLaunchKernelGGL((merge_expand<Tag, OUT_F32, SLICED, FEW, NT, 32>), grid, dim3(NT), lds, stream, p); break;
   }
 }
-template <class Tag, bool OUT_F32>
+template <class Tag, bool OUT_F32, bool FEW>
 void launch_me_nt(const MergeExpandParams& p, int d, int nt, hipStream_t stream) {
+  if (nt == 64) launch_me<Tag, OUT_F32, false, FEW, 64>(p, d, stream);
+  else if (nt == 128) launch_me<Tag, OUT_F32, false, FEW, 128>(p, d, stream);
+  else launch_me<Tag, OUT_F32, false, FEW, 256>(p, d, stream);
+}
+template <class Tag, bool OUT_F32>
+void launch_me_form(const MergeExpandParams& p, int d, int nt, hipStream_t stream) {
   if (p.nslice > 1) {
-    launch_me<Tag, OUT_F32, true, 256>(p, d, stream);
+    launch_me<Tag, OUT_F32, true, false, 256>(p, d, stream);
     const int HD = p.H * d;
     hipLaunchKernelGGL((reduce_out<Tag, OUT_F32>), dim3((HD + 1023) / 1024, p.B), dim3(256), 0, stream, p.pout, p.out, HD, p.nslice);
-  } else if (nt == 64) launch_me<Tag, OUT_F32, false, 64>(p, d, stream);
-  else if (nt == 128) launch_me<Tag, OUT_F32, false, 128>(p, d, stream);
-  else launch_me<Tag, OUT_F32, false, 256>(p, d, stream);
+  } else if (p.S <= kFewSplits) {
+    launch_me_nt<Tag, OUT_F32, true>(p, d, nt, stream);
+  } else {
+    launch_me_nt<Tag, OUT_F32, false>(p, d, nt, stream);
+  }
+}
+// Threads per workgroup.  passes: of 256 threads over a slice's rows.  Fewer threads where that leaves one
+// few rows, the sooner the more workgroups there are to fill the chip; 32 lanes' rows (d = 32) are too
+// short for the middle form.  Us a pass at 256 / 128 / 64 threads:
+//   few splits: 1 pass, 3072 heads 21.8 / 18.6 / 17.0; 2, 384 11.1 / 10.7 / 10.4; 4, 384 11.2 / 10.6 / 10.8;
+//   4, 4096 28.4 / 24.6 / 23.3; 8, 64 10.1 / 10.3 / 11.3; 8, 2560 26.1 / 25.0 / 24.7; 20, 1920 40.1 / 38.8 / 40.6;
+//   d = 32, 8 passes, 4096 heads 92.0 / 102.2 / 98.8
+//   more: rank 192 82.1 / 80.9 (1280 heads), rank 64 17.3 / 16.8 (32 heads) and 96.3 / 93.5 / 92.4 (2048), 640
+//   heads, 12 splits 16.7 / 16.1 / 15.0; 47 splits, 32 heads, 8 passes 12.8 / 13.4 / 14.5
+int merge_expand_threads(int64_t heads, int d, int js, int S) {
+  const int passes = js * (d / 8) / 256;
+  if (S <= kFewSplits) {
+    if (passes <= 2 || (passes <= 4 && heads >= 2048)) return 64;
+    if (d == 32) return 256;
+    return passes <= 4 || (passes <= 24 && heads >= 768) ? 128 : 256;
+  }
+  const int fit = S > js / 4 ? S : js / 4;                // a thread per split and per four columns at least
+  if (S <= 32 && fit <= 64 && (passes <= 2 || (passes <= 4 && heads >= 512))) return 64;
+  return fit <= 128 && (passes <= 4 || (passes <= 12 && S <= 32)) ? 128 : 256;
 }
 }  // namespace
 
@@ -985,21 +1056,19 @@ ap_status launch_merge_expand(ap_dtype dt, bool out_f32, const float* part_ml, c
   if (pout && r % 64 == 0 && (int64_t)nsplit * r * 4 > 288 * 1024)
     for (int k = 2; k <= 8; ++k)
       if (r / 64 % k == 0 && k <= expand_row_blocks(B, r)) nslice = k;
-  // Threads: 256, but fewer where that leaves a thread few of a slice's rows.  Per pass at 256 / 128
-  // threads: rank 192 82.1 / 80.9 us (1280 workgroups), rank 320 with d = 64 43.2 / 42.2, rank 64
-  // 17.3 / 16.8 (32 workgroups) and 96.3 / 93.5 (2048; 92.4 at 64 threads); rank 512 70.7 / 71.3.
-  const int js = r / nslice, rows256 = js * (d / 8) / 256;
-  const int fit = nsplit > js / 4 ? nsplit : js / 4;      // a thread per split and per four columns at least
-  int nt = 256;
-  if (rows256 <= 12 && fit <= 128) nt = 128;
-  if (rows256 <= 4 && fit <= 64 && B * H >= 1024) nt = 64;
-  MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H / H_kv, r, nsplit, nslice, js};
+  const int js = r / nslice, nt = merge_expand_threads((int64_t)B * H, d, js, nsplit);
+  // Bases that do not fit the XCDs' L2s (32 MB) in launch order: 64 sequences of 64 heads of 128, rank 64
+  // 42.4 us with two heads per workgroup, 44.5 in runs per XCD, 42.0 in launch order; 16 of them, rank 512,
+  // 16 splits 84.4, 87.0, 80.8.  Not with heads of 32, whose 64-byte pieces would share their lines across
+  // XCDs (64 x 64 heads, rank 320 63.4 / 71.8), nor of 256 (no difference).
+  const int plain = bstride && (d == 64 || d == 128) && (int64_t)B * r * H_kv * d * 2 >= (32ll << 20);
+  MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H / H_kv, r, nsplit, nslice, js, plain};
   if (dt == AP_F16) {
-    if (out_f32) launch_me_nt<F16Tag, true>(p, d, nt, stream);
-    else launch_me_nt<F16Tag, false>(p, d, nt, stream);
+    if (out_f32) launch_me_form<F16Tag, true>(p, d, nt, stream);
+    else launch_me_form<F16Tag, false>(p, d, nt, stream);
   } else {
-    if (out_f32) launch_me_nt<BF16Tag, true>(p, d, nt, stream);
-    else launch_me_nt<BF16Tag, false>(p, d, nt, stream);
+    if (out_f32) launch_me_form<BF16Tag, true>(p, d, nt, stream);
+    else launch_me_form<BF16Tag, false>(p, d, nt, stream);
   }
   return AP_OK;
 }

@@ -224,8 +224,14 @@ def test_bf16_output_is_the_fp32_result_rounded_once(B, H, d, r, T, fused, value
     ("bf16", 2, 40, 128, 640, 4100, True),      # five slices on a shared basis
     ("f16", 1, 14, 32, 448, 5300, False),        # seven slices, 98 workgroups (not a multiple of eight)
     ("f16", 1, 32, 128, 512, 4600, False),      # just below the bound: one slice, 144 splits
-    ("bf16", 64, 16, 128, 64, 130, False),      # one wave per head
+    ("bf16", 64, 16, 128, 64, 130, False),      # few splits: two waves per head
     ("f16", 64, 16, 256, 64, 40, True),         # the same with d = 256 on a shared basis
+    ("f16", 40, 20, 64, 64, 100, False),        # few splits: one wave per head
+    ("bf16", 64, 32, 64, 128, 33, False),       # the same by the number of heads; 32 MB of bases, in launch order
+    ("f16", 48, 16, 128, 320, 40, True),        # two waves by the number of heads, several columns per thread
+    ("f16", 2, 11, 32, 320, 250, False),        # four waves, eight splits, heads of 32
+    ("bf16", 1, 7, 128, 640, 256, False),       # four waves, eight splits, three columns per thread
+    ("bf16", 1, 7, 128, 640, 257, False),       # nine splits
     ("f16", 2, 9, 128, 192, 1000, False),       # two waves per head
     ("bf16", 1, 3, 32, 64, 8192, False),        # small rank, more splits than two waves have threads
 ])
