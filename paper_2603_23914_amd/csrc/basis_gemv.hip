@@ -909,7 +909,7 @@ ap_status launch_fold_heads(ap_dtype dt, const void* Bk, int64_t bstride, const 
 // HD 4097 - 5120, two jobs: its ring of two rows leaves room for one workgroup, 256 again, and then four
 // (2048 rows 28.8 / 29.3, 4608 40.6 / 41.6); above that no ring, more waves help longer (HD = 6144: 2496
 // rows 27.4 / 26.4, 3072 36.4 / 36.9, 4608 48.6 / 46.1).  One basis for all: 2560 rows of 4096 21.7 / 21.2
-// (two jobs) and 16.8 / 16.5, 2048 of 5120 24.1 / 23.5, 3072 25.3 / 27.4 and 17.7 / 18.3.
+// (two jobs) and 16.8 / 16.5, 5120 26.6 / 29.7, 2048 of 5120 24.1 / 23.5, 3072 25.3 / 27.4 and 17.7 / 18.3.
 // More than 5120 rows: HD = 4096 8192 rows 49.1 / 50.3, shared 10240 31.7 / 34.9; only short ones gain
 // (12288 rows of 512 17.7 / 17.1, 6144 of 1024 17.2 / 16.8, two jobs), and odd numbers of rows, whose folded
 // pieces are not aligned, do not pay elsewhere (15360 rows of 5120 at 4 / 3: 55.5 / 92.0).
@@ -929,7 +929,7 @@ int basis_rows_per_wave(int B, int r, int HD, int jobs, int G, bool shared) {
   const int64_t wg2 = (int64_t)((r + 7) / 8) * B * jobs, wg4 = (int64_t)((r + 15) / 16) * B * jobs;
   if (jobs == 1) return wg2 <= 256 || wg4 > 256 ? 2 : 4;
   if (short_ring) return wg2 <= (shared ? 512 : 256) ? 2 : 4;
-  return wg2 <= (shared || HD > 5120 ? 640 : 512) || wg4 > 512 ? 2 : 4;
+  return wg2 <= (shared || HD > 5120 ? 640 : 512) || (wg4 > 512 && !shared) ? 2 : 4;
 }
 // expand_append: about four two-wave workgroups per CU in one round, but never more than 16 row
 // blocks per sequence at large batches (each block writes an HD-wide partial output that
