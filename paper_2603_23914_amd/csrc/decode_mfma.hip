@@ -1414,15 +1414,22 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
     if constexpr (I8) wg_barrier();                      // the score waves' first key scales
     // (with four head tiles and wide rows the weights do not stay in registers over the barrier: all of
     // it before)
-    constexpr int NA = MT == 4 && RMAX >= 512 ? NGRP : (NGRP + 1) / 2;
+    constexpr bool kWhole = MT == 4 && RMAX >= 512;
+    constexpr int NA = kWhole ? NGRP : (NGRP + 1) / 2;
     using First = std::integral_constant<int, 0>;
     using Mid = std::integral_constant<int, NA>;
     using Last = std::integral_constant<int, NGRP>;
+    // With the whole sum of tile t-1 before the barrier its slots are free behind it.  A ring of two tiles,
+    // which is what rank 640 leaves room for, needs that: a tile is then asked for a step ahead and not
+    // within its own (attn_partial, 16 x 4000 tokens of rank 640: 56 heads fp16 48.5 -> 45.5 us, 64 heads
+    // bf16 61.6 -> 59.1); a longer one is better off with the requests in two parts (rank 512 68.7 / 69.2).
+    const bool early = kWhole && RT == 2;
+    const int done = early ? 1 : 2;
     for (int t = 0; t < cx.ntl; ++t) {
       AP_T_STAMP(t)
       // tile t-2's slots are free (every sum wave passed the last barrier of tile t-1 after it)
-      const int refill = t >= 2 && t - 2 + RT < cx.ntl ? t - 2 + RT : -1;
-      if (refill >= 0) issue_half(refill, 0);
+      const int refill = t >= done && t - done + RT < cx.ntl ? t - done + RT : -1;
+      if (refill >= 0 && !early) issue_half(refill, 0);
       if (t > 0) {
         read_weights();                                  // the next softmax overwrites them: before the barrier
         add_part(t - 1, First{}, Mid{});
@@ -1436,11 +1443,12 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       } else {
         add_part(t - 1, Mid{}, Last{});
       }
+      if (refill >= 0 && early) issue_half(refill, 0);
       if (refill >= 0) issue_half(refill, 1);
       AP_TICK(3)
       {
         // tile t's rows must have landed; the tiles issued after it may stay in flight
-        int upto = t >= 2 ? t - 2 + RT : RT - 1;
+        int upto = t >= done ? t - done + RT : RT - 1;
         upto = upto < cx.ntl ? upto : cx.ntl - 1;
         if (RAGGED) {
           int pending = 0;
