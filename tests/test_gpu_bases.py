@@ -312,8 +312,9 @@ def test_bases_eigenvectors_at_the_edges_of_blocks(l):
 
 @pytest.mark.parametrize("B", [8, 16])
 def test_bases_of_a_batch_are_those_of_its_sequences(B):
-    """A batch that is a multiple of eight numbers its workgroups by matrix and die; the arithmetic of
-    a sequence is the same in any batch, so the results are the same bits."""
+    """A batch that is a multiple of eight numbers its workgroups by matrix and die.  The sums of a sequence
+    are taken in the same order in these batches (a larger launch of Gram matrices, from 512 tiles of
+    64 x 64 on, does not split its columns), so the results are the same bits."""
     dtype, n, HD, r, over = "f16", 200, 256, 64, 34
     X = np.stack([cache_matrix(19, b, n, HD, r, dtype) for b in range(B)])
     Omega = wl.store(wl.rng_for(19, 3).standard_normal((r + over, HD)), dtype)
@@ -322,3 +323,51 @@ def test_bases_of_a_batch_are_those_of_its_sequences(B):
     for b in (0, 3, B - 1):
         D1, sig1 = gpu_bases(X[b:b + 1], Omega, r, 1, dtype)
         assert (D1[0].view(np.uint16) == D[b].view(np.uint16)).all() and (sig1[0] == sig[b]).all()
+
+
+@pytest.mark.parametrize("B,n,HD,l", [
+    (16, 576, 576, 544),       # 720 tiles of 64 x 64, half a tile at the edge
+    (8, 680, 704, 674),        # 528, two rows of one
+])
+def test_bases_of_a_batch_with_large_gram_tiles(B, n, HD, l):
+    """Gram matrices of a batch that fills the chip with 64 x 64 tiles, all directions kept: the bounds of
+    the test of single sequences, on every sequence."""
+    dtype = "f16"
+    X = np.stack([cache_matrix(41, b, n, HD, 256, dtype) for b in range(B)])
+    Omega = wl.store(wl.rng_for(41, 7).standard_normal((l, HD)), dtype)
+    print(f"bases batch {B} l={l}", flush=True)
+    D, sig = gpu_bases(X, Omega, l, 1, dtype)
+    eps = 2.0 ** -11
+    for b in range(B):
+        Z = oracle.promote(X[b], dtype) @ oracle.promote(D[b], dtype).T
+        s = np.linalg.norm(Z, axis=0)
+        G = Z.T @ Z
+        assert np.abs(sig[b] - s).max() <= 2 * eps * s[0] and np.diff(sig[b]).max() <= 1e-6 * sig[b][0]
+        assert (np.abs(G - np.diag(np.diag(G))) <= eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)).all()
+
+
+@pytest.mark.parametrize("l", [34, 66, 256, 602])
+def test_bases_small_directions(l):
+    """A cache of l directions whose singular values fall from 4 to 1 and nothing else, so that bounds by
+    sigma_1 hold the last direction to a few of its own roundings.  sigma against the exact values: the
+    16-bit rounding of the block P costs at most its norm, 2^-11, times sigma_1.  Rows: images X d_i
+    orthogonal up to D's rounding, which leaves 2^-11 sigma_1 of each."""
+    dtype, n, HD = "f16", 704, 640
+    rng = wl.rng_for(43, l)
+    U, W = (np.linalg.qr(rng.standard_normal((m, l)))[0] for m in (n, HD))
+    X = wl.store((U * np.linspace(4.0, 1.0, l) * 30.0) @ W.T, dtype)
+    Omega = wl.store(wl.rng_for(43, 1).standard_normal((l, HD)), dtype)
+    print(f"bases small directions l={l}", flush=True)
+    D, sig = gpu_bases(X[None], Omega, l, 2, dtype)
+    Xd, Dd = oracle.promote(X, dtype), oracle.promote(D[0], dtype)
+    exact = np.linalg.svd(Xd, compute_uv=False)[:l]
+    Z = Xd @ Dd.T
+    s = np.linalg.norm(Z, axis=0)
+    G = Z.T @ Z
+    eps = 2.0 ** -11
+    off = np.abs(G - np.diag(np.diag(G)))
+    bound = eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)
+    print(f"  sigma {np.abs(sig[0] / exact - 1).max():.1e}, orthogonality {(off / bound).max():.2f} of its bound", flush=True)
+    assert np.abs(sig[0] - exact).max() <= eps * exact[0]
+    assert np.abs(sig[0] - s).max() <= 2 * eps * s[0]
+    assert (off <= bound).all()

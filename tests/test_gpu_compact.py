@@ -178,15 +178,24 @@ def test_config5_chain_with_true_svd_bases():
     assert np.abs(ref - plain).max() < 0.5 * np.abs(plain).max()
 
 
-@pytest.mark.parametrize("B,n,HD,r", [
-    (12, 544, 512, 512),      # 128 x 256 tiles (one round instead of two), a ragged token tile
-    (12, 544, 448, 576),      # the same with a ragged column tile
-    (140, 250, 128, 64),      # 256 x 128 tiles (two rounds instead of three), half a column tile
-    (9, 104, 512, 448),       # one round: 256 x 128 tiles for more of them
+def takes_256x128(B, n, r):
+    """The matrix product's choice for a pair: the tile that makes fewer rounds over 256 CUs."""
+    t, f = (2 * B * -(-n // bm) * -(-r // (384 - bm)) for bm in (256, 128))
+    rt, rf = -(-t // 256), -(-f // 256)
+    return rt < rf if rt != rf else (t >= f if rt == 1 else t <= f)
+
+
+@pytest.mark.parametrize("B,n,HD,r,tall", [
+    (12, 544, 512, 512, False),     # 128 x 256 tiles (one round instead of two), a ragged token tile
+    (34, 264, 448, 192, False),     # the same (one instead of two), ragged in tokens and columns
+    (12, 544, 448, 576, True),      # 256 x 128 tiles (as many of either), ragged in tokens and columns
+    (140, 250, 128, 64, True),      # 256 x 128 tiles (two rounds instead of three), half a column tile
+    (9, 104, 512, 448, True),       # one round: 256 x 128 tiles for more of them
 ])
-def test_compact_tile_shapes(B, n, HD, r):
+def test_compact_tile_shapes(B, n, HD, r, tall):
     """Both tile shapes of the matrix product, 16-bit and int8 output.  The int8 epilogue quantises what
     the 16-bit one stores, so its codes and scales are those of ap_quantize_i8 on that output."""
+    assert takes_256x128(B, n, r) == tall
     from paper_2603_23914_amd import binding as ap
     dtype = "f16"
     rng = wl.rng_for(29, B, n)
