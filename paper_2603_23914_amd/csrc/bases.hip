@@ -620,6 +620,9 @@ jacobi_init(const double* __restrict__ S, int64_t s_bstride, float* __restrict__
 //      number of steps per sweep hardly depends on the block (1023 against 1071 with blocks of 32),
 //      nor does the number of sweeps (8 in both, the last of which only looks).
 //      G is scaled by a power of two to a largest diagonal entry in [1, 2): no overflow in the angles.
+//      A pair (x, y) is turned as x - sn (y + ta x), y + sn (x - ta y), ta the tangent of half the angle: the
+//      cosine of a small angle rounds to 1 in fp32, and thousands of such rotations made the rows longer
+//      (sigma of 544 equal directions 4.9e-5 too large with cosine and sine, see the test of it).
 //      Measured at 16 matrices of 544 rows: 24 us a launch, 7.0 ms in all; with the rows themselves in
 //      LDS (blocks of 32, three dot products and a rotation of 544 columns per pair) 190 us a launch
 //      and 21.9 ms.
@@ -632,7 +635,7 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
   constexpr int PITCH = 48;                             // 16 mod 32: two neighbouring rows fill the banks
   __shared__ float part[8][3 * 256];
   __shared__ float gm[2][32 * PITCH], qm[2][32 * PITCH];
-  __shared__ f32x2_t csn[2][16];                        // cosine and sine of a step's pairs
+  __shared__ f32x2_t rot[2][16];                        // sine and tangent of half the angle of a step's pairs
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int b, k;                                             // W stays in one XCD's L2
@@ -745,29 +748,27 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
         const float zeta = (be - al) * __builtin_amdgcn_rcpf(ga + ga);
         float t = __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.f)));
         t = fabsf(ga) > 1e-30f ? copysignf(t, zeta) : 0.f;
-        const float h = fmaf(t, t, 1.f);
-        float cs = __builtin_amdgcn_rsqf(h);
-        cs = fmaf(cs * 0.5f, fmaf(-h * cs, cs, 1.f), cs);   // one Newton step: cos^2 + sin^2 = 1 to rounding
-        const float sn = cs * t;
-        const float ci = __shfl(cs, I), si = __shfl(sn, I);
-        if (w == 0 && g == 0) csn[s & 1][n] = f32x2_t{cs, sn};
-        const float b00 = fmaf(ci, a00, -si * a10), b01 = fmaf(ci, a01, -si * a11);
-        const float b10 = fmaf(si, a00, ci * a10), b11 = fmaf(si, a01, ci * a11);
-        nxt[r0 + c0] = fmaf(cs, b00, -sn * b01);
-        nxt[r0 + c1] = fmaf(sn, b00, cs * b01);
-        nxt[r1 + c0] = fmaf(cs, b10, -sn * b11);
-        nxt[r1 + c1] = fmaf(sn, b10, cs * b11);
+        const float cs = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f)), sn = cs * t;
+        const float ta = sn * __builtin_amdgcn_rcpf(1.f + cs);   // tan of half the angle: cos = 1 - sn ta
+        const float si = __shfl(sn, I), ti = __shfl(ta, I);
+        if (w == 0 && g == 0) rot[s & 1][n] = f32x2_t{sn, ta};
+        const float b00 = fmaf(-si, fmaf(ti, a00, a10), a00), b01 = fmaf(-si, fmaf(ti, a01, a11), a01);
+        const float b10 = fmaf(si, fmaf(-ti, a10, a00), a10), b11 = fmaf(si, fmaf(-ti, a11, a01), a11);
+        nxt[r0 + c0] = fmaf(-sn, fmaf(ta, b00, b01), b00);
+        nxt[r0 + c1] = fmaf(sn, fmaf(-ta, b01, b00), b01);
+        nxt[r1 + c0] = fmaf(-sn, fmaf(ta, b10, b11), b10);
+        nxt[r1 + c1] = fmaf(sn, fmaf(-ta, b11, b10), b11);
       }
     } else if (s > 0) {
       const float* cur = qm[(s & 1) ^ 1];
       float* nxt = qm[s & 1];
-      const f32x2_t r = csn[(s & 1) ^ 1][I];
+      const f32x2_t r = rot[(s & 1) ^ 1][I];
       const float a00 = cur[I * PITCH + n], a01 = cur[I * PITCH + 16 + n];
       const float a10 = cur[(16 + I) * PITCH + n], a11 = cur[(16 + I) * PITCH + 16 + n];
-      nxt[r0 + n] = fmaf(r[0], a00, -r[1] * a10);
-      nxt[r0 + 16 + n] = fmaf(r[0], a01, -r[1] * a11);
-      nxt[r1 + n] = fmaf(r[1], a00, r[0] * a10);
-      nxt[r1 + 16 + n] = fmaf(r[1], a01, r[0] * a11);
+      nxt[r0 + n] = fmaf(-r[0], fmaf(r[1], a00, a10), a00);
+      nxt[r0 + 16 + n] = fmaf(-r[0], fmaf(r[1], a01, a11), a01);
+      nxt[r1 + n] = fmaf(r[0], fmaf(-r[1], a10, a00), a10);
+      nxt[r1 + 16 + n] = fmaf(r[0], fmaf(-r[1], a11, a01), a11);
     }
     __syncthreads();
   }

@@ -371,3 +371,22 @@ def test_bases_small_directions(l):
     assert np.abs(sig[0] - exact).max() <= eps * exact[0]
     assert np.abs(sig[0] - s).max() <= 2 * eps * s[0]
     assert (off <= bound).all()
+
+
+@pytest.mark.parametrize("l", [130, 544])
+def test_bases_rotations_keep_lengths(l):
+    """l equal directions: nothing converges early, every row takes part in thousands of rotations, and
+    what they do to its length shows in sigma.  In the mean over the directions only a drift remains;
+    a row is rounded to fp32 once a launch (2^-24 of lambda = length, half of that of sigma), eight sweeps
+    of as many launches as there are pairs of blocks of 16."""
+    dtype, n, HD = "f16", 704, 640
+    rng = wl.rng_for(47, l)
+    U, W = (np.linalg.qr(rng.standard_normal((m, l)))[0] for m in (n, HD))
+    X = wl.store(U @ W.T * 100.0, dtype)
+    Omega = wl.store(wl.rng_for(47, 1).standard_normal((l, HD)), dtype)
+    print(f"bases of equal directions l={l}", flush=True)
+    _, sig = gpu_bases(X[None], Omega, l, 2, dtype)
+    exact = np.linalg.svd(oracle.promote(X, dtype), compute_uv=False)[:l]
+    drift = np.mean(sig[0] / exact - 1)
+    print(f"  drift {drift:.1e}", flush=True)
+    assert abs(drift) <= 8 * (l / 16) * 2.0 ** -24 / 2
