@@ -744,10 +744,13 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
         const float al = cur[n * (PITCH + 1)], be = cur[(16 + n) * (PITCH + 1)], ga = cur[n * PITCH + 16 + n];
         const float a00 = cur[I * PITCH + n], a01 = cur[I * PITCH + 16 + n];
         const float a10 = cur[(16 + I) * PITCH + n], a11 = cur[(16 + I) * PITCH + 16 + n];
-        // the rotation that makes the pair n orthogonal (any residue is far below the tolerance)
-        const float zeta = (be - al) * __builtin_amdgcn_rcpf(ga + ga);
-        float t = __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(fmaf(zeta, zeta, 1.f)));
-        t = fabsf(ga) > 1e-30f ? copysignf(t, zeta) : 0.f;
+        // the rotation that makes the pair n orthogonal (any residue is far below the tolerance): the tangent
+        // of its angle, 2 ga / (|d| + sqrt(d^2 + 4 ga^2)) with d's sign, whose denominator is at least |2 ga|
+        // also where the squares vanish
+        const float d = be - al, g2 = ga + ga;
+        const float den = fmaxf(fabsf(d) + __builtin_amdgcn_sqrtf(fmaf(d, d, g2 * g2)), fabsf(g2));
+        float t = (d < 0.f ? -g2 : g2) * __builtin_amdgcn_rcpf(den);
+        t = fabsf(ga) > 1e-30f ? t : 0.f;
         const float cs = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f)), sn = cs * t;
         const float ta = sn * __builtin_amdgcn_rcpf(1.f + cs);   // tan of half the angle: cos = 1 - sn ta
         const float si = __shfl(sn, I), ti = __shfl(ta, I);
