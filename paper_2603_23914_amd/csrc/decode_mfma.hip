@@ -10,11 +10,11 @@
 //   expand:  out[h,i] = sum_j u[h,j] Bv[j, h*d+i]
 //
 // attn_partial is the HBM-bound kernel.  One workgroup (8 waves) owns one (sequence, token
-// split).  Coefficient tiles of 32 tokens travel HBM -> LDS with direct-to-LDS loads
-// through a ring of 16-row units (K rows, K rows, V rows, V rows, ...), several units in
-// flight while two are consumed, so no VGPR is spent on staging.  Every wave serves all
-// heads on a quarter of the rank axis, so each tile byte is read from LDS exactly once:
-//   S^T[t,h]  = Ck_tile[t,:] . q'^T      MFMA 16x16x32, A = tile rows (LDS), B = q' (VGPR);
+// split), in tiles of 32 tokens.  Four waves score: each takes a quarter of the rank axis of the
+// key rows straight from memory into registers, a tile ahead.  Four waves sum: the value rows
+// travel HBM -> LDS with direct-to-LDS loads through a ring of 16-row units, several in flight
+// while two are consumed, and each wave takes a quarter of the columns, so each byte is read once:
+//   S^T[t,h]  = Ck_tile[t,:] . q'^T      MFMA 16x16x32, A = tile rows (VGPR), B = q' (VGPR);
 //                                         the score waves' partial sums meet in LDS and each
 //                                         of them finalises the softmax of a quarter of the heads
 //   U^T[j,h] += Cv_tile^T[j,t] . P^T     MFMA 16x16x32, A = register transpose of the tile

@@ -735,7 +735,9 @@ ap_status launch_keyonly_attn(const void* q, const void* Ck, const void* Bk, int
 }
 
 // value-only compression: [part_ml | part_U | merged ml | merged U (only with more than 8 splits)]
-constexpr int kValueOnlyInlineSplits = 8;               // what merge_expand merges by itself
+// More than eight splits are merged by merge_splits first: the workspace has room for the result, and what
+// merge_expand would save by taking them itself (it takes up to kMergeExpandSplits) was not measured here.
+constexpr int kValueOnlyInlineSplits = 8;
 struct ValueOnlyWs { size_t ml, u, mml, mu, total; };
 static ValueOnlyWs valueonly_layout(int B, int H, int H_kv, int d, int T, int r) {
   const int S = valueonly_splits(B, H, H_kv, d, T, r);
