@@ -1060,8 +1060,10 @@ ap_status launch_merge_expand(ap_dtype dt, bool out_f32, const float* part_ml, c
   // Bases that do not fit the XCDs' L2s (32 MB) in launch order: 64 sequences of 64 heads of 128, rank 64
   // 42.4 us with two heads per workgroup, 44.5 in runs per XCD, 42.0 in launch order; 16 of them, rank 512,
   // 16 splits 84.4, 87.0, 80.8.  Not with heads of 32, whose 64-byte pieces would share their lines across
-  // XCDs (64 x 64 heads, rank 320 63.4 / 71.8), nor of 256 (no difference).
-  const int plain = bstride && (d == 64 || d == 128) && (int64_t)B * r * H_kv * d * 2 >= (32ll << 20);
+  // XCDs (64 x 64 heads, rank 320 63.4 / 71.8), nor of 256 (no difference), nor with
+  // grouped queries, whose heads share a slice that every XCD would then fetch (40 x 32/8 heads, rank 448
+  // 43.6 / 52.5).
+  const int plain = bstride && H == H_kv && (d == 64 || d == 128) && (int64_t)B * r * H_kv * d * 2 >= (32ll << 20);
   MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H / H_kv, r, nsplit, nslice, js, plain};
   if (dt == AP_F16) {
     if (out_f32) launch_me_form<F16Tag, true>(p, d, nt, stream);
