@@ -1753,7 +1753,12 @@ ap_status run_decode(const DecodeArgs& a) {
   // a value row that the expansion pass does not produce is appended in the same launch as the
   // key row (second job of the basis pass)
   const bool pair_v = a.v_new && !one_pass_v && a.k_new;
-  if (Hkv == a.H) {
+  // one basis for all sequences: matrix products where they are the shorter way
+  const bool shared = a.basis_batch_stride == 0 && !one_pass_v;
+  if (shared && shared_project_applies(a.B, a.H, Hkv, a.d, a.r, a.k_new != nullptr)) {
+    st = launch_shared_project(a.dt, a.Bk, a.Bv, a.k_new, a.v_new, a.q, (void*)a.Ck, (void*)a.Cv, Qp, a.B, a.H, Hkv, Hp, a.d,
+                               a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream);
+  } else if (Hkv == a.H) {
     st = launch_basis_rows(a.dt, a.Bk, a.basis_batch_stride, a.k_new, a.q, (void*)a.Ck, Qp, a.B, a.H, Hp,
                            a.d, a.H * a.d, a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream,
                            pair_v ? a.Bv : nullptr, pair_v ? a.v_new : nullptr, pair_v ? (void*)a.Cv : nullptr);
@@ -1832,6 +1837,8 @@ ap_status run_decode(const DecodeArgs& a) {
                               (void*)a.Cv, ml, U, (const float*)(ws + wl.pn),
                               !small && S_exp > 1 ? pnew_split : nullptr, a.rank_v, (float*)(ws + wl.po),
                               a.out, a.lse, a.B, a.H, a.d, a.r, a.T, a.T_cap, S_exp, a.stream);
+  else if (shared && shared_expand_applies(a.B, a.H, a.d, a.r, S_exp))
+    st = launch_shared_expand(a.dt, a.dt_out == AP_F32, ml, U, a.Bv, a.out, a.lse, a.B, a.H, Hkv, a.d, a.r, S_exp, a.stream);
   else
     st = launch_merge_expand(a.dt, a.dt_out == AP_F32, ml, U, a.Bv, a.basis_batch_stride, a.out, a.lse,
                              (float*)(ws + wl.po), a.B, a.H, Hkv, a.d, a.r, S_exp, a.stream);

@@ -1,0 +1,79 @@
+"""GPU parity: one basis for all sequences (basis_batch_stride = 0).  From some size on the appends, the
+fold and the expansion are matrix products over the batch (shared_basis.hip); checked against the fp64
+oracle on some sequences and, on all, against the same call with the basis written out per sequence."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import TORCH_DT, TOL, to_host64, workspace
+
+pytestmark = pytest.mark.gpu
+
+
+def run(ap, step, q, kn, vn, Ck, Cv, Bk, Bv, T, dt_out):
+    B, H, d = q.shape
+    Ck, Cv = Ck.clone(), Cv.clone()
+    out = torch.full((B, H, d), float("nan"), device="cuda").to(dt_out)
+    lse = torch.full((B, H), float("nan"), device="cuda")
+    ws = workspace(ap.ap_decode_workspace_bytes(B, H, d, T, Ck.shape[2], ap._DT[q.dtype]))
+    ws.fill_(255)                                    # padded heads of the folded query must be written
+    if step:
+        ap.ap_decode_step(q, kn, vn, Ck, Cv, Bk, Bv, out, ws, T=T, sm_scale=1.0 / math.sqrt(d), lse=lse)
+    else:
+        ap.ap_decode_attn(q, Ck, Cv, Bk, Bv, out, ws, T=T, sm_scale=1.0 / math.sqrt(d), lse=lse)
+    torch.cuda.synchronize()
+    return out, lse, Ck, Cv
+
+
+@pytest.mark.parametrize("step", [False, True], ids=["attend", "step"])
+@pytest.mark.parametrize("dtype,B,H,Hkv,d,r,T,scale", [
+    ("bf16", 2, 40, 40, 64, 64, 33, 1.0),            # smallest fold: one column tile, half a rank block
+    ("f16", 2, 7, 1, 256, 128, 5, 1.0),              # one key/value head
+    ("bf16", 33, 40, 40, 128, 192, 40, 1.0),         # three column tiles, the last with one sequence
+    ("f16", 17, 24, 8, 64, 320, 97, 1.0),            # grouped queries, ragged tiles, odd rank block
+    ("bf16", 16, 33, 33, 32, 320, 64, 1.0),          # hidden axis of 1056: the last stage a quarter full
+    ("f16", 65, 48, 48, 64, 640, 33, 1.0),           # expansion: ragged column tile, largest rank
+    ("bf16", 65, 48, 48, 64, 640, 33, 1.0),
+    ("f16", 64, 64, 4, 128, 256, 70, 1.0),           # expansion, sixteen heads per slice, several splits
+    ("bf16", 80, 64, 64, 32, 640, 31, 1.0),          # expansion, narrow heads
+    ("f16", 64, 32, 32, 256, 192, 300, 1.0),         # expansion, wide heads
+    ("f16", 65, 48, 48, 64, 640, 33, 6.0e3),         # coefficients to the end of fp16, and down where
+    ("f16", 65, 48, 48, 64, 640, 33, 2.0e-6),        # most of them are subnormal
+    ("bf16", 65, 48, 48, 64, 640, 33, 1.0e30),
+])
+def test_shared_basis(dtype, B, H, Hkv, d, r, T, scale, step):
+    from paper_2603_23914_amd import binding as ap
+    print(f"shared basis {dtype} B={B} H={H} Hkv={Hkv} d={d} r={r} T={T} scale={scale} step={step}", flush=True)
+    dt, HD = TORCH_DT[dtype], Hkv * d
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 + B + r)
+    N = lambda *s: torch.randn(s, generator=g, device="cuda")
+    law = 4.0 * torch.arange(1, r + 1, device="cuda", dtype=torch.float32) ** -0.7
+    Ck = (N(B, T + 7, r) * law).to(dt)
+    Cv = (N(B, T + 7, r).clamp(-2.5, 2.5) * law * scale).to(dt)
+    Bk, Bv = ((N(r, HD) / math.sqrt(HD)).to(dt) for _ in range(2))
+    q, kn, vn = N(B, H, d).to(dt), N(B, HD).to(dt), (N(B, HD) * min(scale, 1.0)).to(dt)
+    dt_out = dt if scale == 1.0 and B % 2 else torch.float32
+    own = [x[None].expand(B, r, HD).contiguous() for x in (Bk, Bv)]
+    out, lse, ck, cv = run(ap, step, q, kn, vn, Ck, Cv, Bk, Bv, T, dt_out)
+    out2, lse2, ck2, cv2 = run(ap, step, q, kn, vn, Ck, Cv, *own, T, dt_out)
+    rnd = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11          # one rounding to storage
+    sub = 0.0 if dtype == "bf16" else 2.0 ** -25               # and of an fp16 subnormal: half of 2^-24
+    for name, a, b, tol in (("out", out, out2, TOL[dtype] + (rnd if dt_out == dt else 0)), ("lse", lse, lse2, TOL[dtype]),
+                            ("Ck", ck, ck2, 2 * rnd), ("Cv", cv, cv2, 2 * rnd)):
+        a, b = to_host64(a), to_host64(b)
+        assert np.isfinite(a).all(), name
+        assert np.abs(a - b).max() <= tol * np.abs(b).max() + (2 * sub if name[0] == "C" else 0), name
+    for b in (0, B // 2, B - 1):
+        P = lambda x: to_host64(x)
+        ref = oracle.decode_attn_batched(P(q[b:b + 1]), P(ck[b:b + 1]), P(cv[b:b + 1]), P(Bk)[None], P(Bv)[None], T,
+                                         absorbed=True, kv_heads=Hkv)
+        err = np.abs(to_host64(out[b:b + 1]) - ref).max()
+        assert err <= (TOL[dtype] + (rnd if dt_out == dt else 0)) * np.abs(ref).max(), (b, err)
+        if step:
+            for x, basis, c in ((kn, Bk, ck), (vn, Bv, cv)):
+                row = oracle.compact(P(x[b:b + 1]), P(basis))[0]
+                assert np.abs(P(c[b, T - 1]) - row).max() <= 2 * rnd * np.abs(row).max() + sub
