@@ -34,6 +34,22 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
+// Matrix b of a flat grid of `per` workgroups per matrix and the workgroup's number t within it;
+// matrix b on XCD b % 8 where that comes out even, so that what one launch leaves in an L2 is found
+// there by the next.
+__device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, int& t) {
+  if (batch % 8 == 0) {
+    b = (id >> 3) / per * 8 + (id & 7);
+    t = (id >> 3) % per;
+  } else {
+    b = id / per;
+    t = id - b * per;
+  }
+}
+
+// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done
 constexpr int kSweepSlots = 16;        // rotation counters per matrix, one per sweep
 constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16-bit storage of the result keeps
@@ -115,20 +131,103 @@ __device__ __forceinline__ f64x4_t mfma_f64(double a, double b, f64x4_t c) {
 }
 
 // ---- S = A A^T in fp64 for A [l][lda] fp32 (m columns used, m % 8 == 0), the lower triangle of
-//      tiles, mirrored on the way out.  Bound by the fp64 matrix pipe: a wave owns 32 x 32 results
-//      (2 x 2 products) and takes its operands straight from global memory, 16 bytes of a row per
-//      lane = four k of the product (the order of k is free as long as both operands agree), the
-//      next sixteen columns requested while the current ones are multiplied; no LDS, no barrier.
-//      SPLIT_K = false: a workgroup's four waves form a 64 x 64 tile.  SPLIT_K = true: they share
-//      ONE 32 x 32 tile, a quarter of the columns each, and meet in LDS: for few or small matrices,
-//      which would leave most of the chip idle.  Measured at 16 matrices of 544 x 4096: 1.29 ms with
-//      fp64 FMAs from LDS tiles, see launch_gram for both forms of this one.
-//      grid (tiles of the lower triangle, batch), 256 threads.
-template <bool SPLIT_K>
+//      tiles, mirrored on the way out.  Bound by the fp64 matrix pipe.  The order of k is free as long as
+//      both operands agree: a lane's 16 bytes of a row are four k of the product.
+//      gram_f64 (64 x 64 tiles, a wave 32 x 32): 32 columns a stage go through LDS, the next stage's in
+//      registers meanwhile.  Straight from memory, as gram_split takes them, a load's neighbouring lanes
+//      are in different rows, which costs the CU 60 cycles an instruction against 16, as much as the
+//      products take.  XCD-aware numbering keeps a matrix in one XCD's L2.  Waves whose 32 x 32 lies past the
+//      end or above the diagonal do not multiply.  16 matrices of 544 x 4096: 512 us (612 straight from
+//      memory, 1290 with fp64 FMAs), 20.5 GFLOP at 40 TFLOP/s; the pipe itself gives 47.5 (products of
+//      registers, two waves per SIMD).
+//      grid (tiles of the lower triangle * batch), 256 threads.
+constexpr int kGramPitch = 36;                           // floats per LDS row: 16 rows start in 16 quads of banks
 __global__ void __launch_bounds__(256)
 gram_f64(const float* __restrict__ A, int64_t a_bstride, int lda, double* __restrict__ S, int64_t s_bstride,
+         int l, int m, int batch) {
+  __shared__ __attribute__((aligned(16))) float stage[2][128 * kGramPitch];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t64 = (l + 63) >> 6;
+  int b, t;
+  matrix_of((int)blockIdx.x, t64 * (t64 + 1) / 2, batch, b, t);
+  // tile (ti, tj), tj <= ti, of the lower triangle
+  int ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+  while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+  while (ti * (ti + 1) / 2 > t) --ti;
+  const int tj = t - ti * (ti + 1) / 2;
+  A += (size_t)b * a_bstride;
+  S += (size_t)b * s_bstride;
+  const int row = tid >> 3, piece = (tid & 7) * 4;       // a stage: 64 rows of either side, 128 bytes each
+  const float* src[4];                                   // rows past the end repeat the last one
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int i = (u < 2 ? ti : tj) * 64 + (u & 1) * 32 + row;
+    src[u] = A + (size_t)(i < l ? i : l - 1) * lda;
+  }
+  f32x4_t nx[4];
+  auto load = [&](int c) {
+    const int col = c * 32 + piece;
+    const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const f32x4_t v = *(const f32x4_t*)(src[u] + (col < m ? col : 0));
+      nx[u] = col < m ? v : z;
+    }
+  };
+  f64x4_t acc[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) acc[u][v] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  const int stages = (m + 31) >> 5;
+  const int ra = ((w >> 1) * 32 + n) * kGramPitch + 4 * g, rb = (64 + (w & 1) * 32 + n) * kGramPitch + 4 * g;
+  const int i0 = ti * 64 + (w >> 1) * 32, j0 = tj * 64 + (w & 1) * 32;
+  const bool mine = i0 < l && j0 <= i0;                  // else past the end, or the mirror image of another wave's
+  load(0);
+  for (int c = 0; c < stages; ++c) {
+    float* buf = stage[c & 1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) *(f32x4_t*)(buf + (u * 32 + row) * kGramPitch + piece) = nx[u];
+    if (c + 1 < stages) load(c + 1);
+    lds_barrier();
+    if (!mine) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f32x4_t a0v = *(const f32x4_t*)(buf + ra + 16 * h), a1v = *(const f32x4_t*)(buf + ra + 16 * kGramPitch + 16 * h);
+      const f32x4_t b0v = *(const f32x4_t*)(buf + rb + 16 * h), b1v = *(const f32x4_t*)(buf + rb + 16 * kGramPitch + 16 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double a0 = a0v[e], a1 = a1v[e], b0 = b0v[e], b1 = b1v[e];
+        acc[0][0] = mfma_f64(a0, b0, acc[0][0]);
+        acc[0][1] = mfma_f64(a0, b1, acc[0][1]);
+        acc[1][0] = mfma_f64(a1, b0, acc[1][0]);
+        acc[1][1] = mfma_f64(a1, b1, acc[1][1]);
+      }
+    }
+  }
+  if (!mine) return;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + 16 * u + g + 4 * e, j = j0 + 16 * v + n;
+        if (i < l && j < l) {
+          S[(size_t)i * l + j] = acc[u][v][e];
+          S[(size_t)j * l + i] = acc[u][v][e];
+        }
+      }
+}
+
+// ---- the same for few or small matrices, which would leave most of the chip idle: the four waves share ONE
+//      32 x 32 tile, a quarter of the columns each, operands straight from memory, and meet in LDS.
+//      grid (tiles of the lower triangle, batch), 256 threads.
+__global__ void __launch_bounds__(256)
+gram_split(const float* __restrict__ A, int64_t a_bstride, int lda, double* __restrict__ S, int64_t s_bstride,
          int l, int m) {
-  __shared__ double red[SPLIT_K ? 3 * 1024 : 1];
+  __shared__ double red[3 * 1024];
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // tile (ti, tj), tj <= ti, of the lower triangle
@@ -136,9 +235,7 @@ gram_f64(const float* __restrict__ A, int64_t a_bstride, int lda, double* __rest
   while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
   while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
   const int tj = (int)blockIdx.x - ti * (ti + 1) / 2;
-  const int i0 = SPLIT_K ? ti * 32 : ti * 64 + (w >> 1) * 32;
-  const int j0 = SPLIT_K ? tj * 32 : tj * 64 + (w & 1) * 32;
-  if (!SPLIT_K && (i0 >= l || j0 >= l)) return;          // (no barrier in this form)
+  const int i0 = ti * 32, j0 = tj * 32;
   A += (size_t)blockIdx.y * a_bstride;
   S += (size_t)blockIdx.y * s_bstride;
   const float* rows[4];                                  // rows past the end repeat the last one
@@ -149,8 +246,7 @@ gram_f64(const float* __restrict__ A, int64_t a_bstride, int lda, double* __rest
     rows[2 + u] = A + (size_t)(rj < l ? rj : l - 1) * lda;
   }
   const int chunks = (m + 15) >> 4;                      // sixteen columns each; the last may be half
-  const int c_lo = SPLIT_K ? (int)((int64_t)w * chunks / 4) : 0;
-  const int c_hi = SPLIT_K ? (int)((int64_t)(w + 1) * chunks / 4) : chunks;
+  const int c_lo = (int)((int64_t)w * chunks / 4), c_hi = (int)((int64_t)(w + 1) * chunks / 4);
   f32x4_t nx[4];
   auto load = [&](int c) {
     const int col = c * 16 + 4 * g;
@@ -178,26 +274,25 @@ gram_f64(const float* __restrict__ A, int64_t a_bstride, int lda, double* __rest
       acc[1][1] = mfma_f64(a1, b1, acc[1][1]);
     }
   }
-  if (SPLIT_K) {                                         // the four partial tiles, added in wave order
-    if (w > 0) {
+  // the four partial tiles, added in wave order
+  if (w > 0) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 2; ++v)
+      for (int v = 0; v < 2; ++v)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) red[((w - 1) * 16 + (u * 2 + v) * 4 + e) * 64 + lane] = acc[u][v][e];
-    }
-    __syncthreads();
-    if (w > 0) return;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int v = 0; v < 2; ++v)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[u][v][e] += red[(k * 16 + (u * 2 + v) * 4 + e) * 64 + lane];
+        for (int e = 0; e < 4; ++e) red[((w - 1) * 16 + (u * 2 + v) * 4 + e) * 64 + lane] = acc[u][v][e];
   }
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[u][v][e] += red[(k * 16 + (u * 2 + v) * 4 + e) * 64 + lane];
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -218,9 +313,9 @@ void launch_gram(const float* A, int64_t a_bstride, int lda, double* S, int64_t 
   // the column axis split over the four waves.
   const int t64 = (l + 63) / 64, t32 = (l + 31) / 32;
   if ((int64_t)t64 * (t64 + 1) / 2 * batch >= 512)
-    hipLaunchKernelGGL(gram_f64<false>, dim3(t64 * (t64 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
+    hipLaunchKernelGGL(gram_f64, dim3(t64 * (t64 + 1) / 2 * batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m, batch);
   else
-    hipLaunchKernelGGL(gram_f64<true>, dim3(t32 * (t32 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
+    hipLaunchKernelGGL(gram_split, dim3(t32 * (t32 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
 }
 
 __global__ void __launch_bounds__(256)
@@ -234,19 +329,6 @@ diag_max(const double* __restrict__ S, int64_t s_bstride, int l, double* __restr
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) dmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-}
-
-// Matrix b of a flat grid of `per` workgroups per matrix and the workgroup's number t within it;
-// matrix b on XCD b % 8 where that comes out even, so that what one launch leaves in an L2 is found
-// there by the next.
-__device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, int& t) {
-  if (batch % 8 == 0) {
-    b = (id >> 3) / per * 8 + (id & 7);
-    t = (id >> 3) % per;
-  } else {
-    b = id / per;
-    t = id - b * per;
-  }
 }
 
 // ---- Cholesky S = L L^T, fp64, in panels of 32 columns, one launch per panel; off the diagonal the
@@ -922,8 +1004,9 @@ ap_status run_bases(const BasesArgs& a) {
     // rows of M made orthonormal
     launch_gram(M32, (int64_t)l * HD, HD, S, (int64_t)l * l, l, HD, B, st);
     launch_cholesky(S, Linv, l, dmax, B, st);
-    launch_gemm_nn<Tag>(Linv, (int64_t)l * l, l, M32, (int64_t)l * HD, HD, P32, (int64_t)l * HD, P16, (int64_t)l * HD,
-                        HD, l, HD, l, 1, B, st);
+    // (the fp32 copy is what D is made from in the end: the last iteration's only)
+    launch_gemm_nn<Tag>(Linv, (int64_t)l * l, l, M32, (int64_t)l * HD, HD, it == a.power_iters ? P32 : nullptr,
+                        (int64_t)l * HD, P16, (int64_t)l * HD, HD, l, HD, l, 1, B, st);
     Pcur = P16;
     p_bs = (int64_t)l * HD;
   }
