@@ -50,6 +50,8 @@ __device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, in
 // Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+constexpr int kFirstCheck = 4;         // sweeps before this one do not ask whether the matrix is done
+constexpr int kFullEvery = 4, kFullFrom = 8;   // steps and sweeps that turn the pairs within the blocks too
 constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done
 constexpr int kSweepSlots = 16;        // rotation counters per matrix, one per sweep
 constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16-bit storage of the result keeps
@@ -684,18 +686,26 @@ jacobi_init(const double* __restrict__ S, int64_t s_bstride, float* __restrict__
   if (e < kSweepSlots) rotations[b * kSweepSlots + e] = 0;
 }
 
+// The pairs of blocks that a launch takes from the round-robin over nblk blocks: those of one step, `skip` left
+// out (none if skip >= nblk / 2), or (gather) pair `skip` of `count` steps from `step` on.
+struct PairSet { int step, skip, gather, count; };
+
 // ---- One-sided Jacobi on the rows of W [l][lp] (fp32), block version.  The rows are cut into blocks
 //      of 16; one launch takes disjoint pairs of blocks (round-robin over the blocks), a workgroup per
 //      pair.  For a symmetric positive semi-definite W = S the rows converge to lambda_i j_i^T, the
 //      eigenvectors scaled by their eigenvalues.
 //      A workgroup never holds its 32 rows: it forms their Gram matrix G on the fp32 matrix
-//      instructions, runs one cyclic sweep of two-sided rotations on G (31 steps of 16 disjoint pairs,
-//      the same rotations that the rows themselves would see) while the product Q of the rotations is
-//      built next to it, and multiplies the rows by Q on the matrix instructions.  The chain of 31
+//      instructions, turns pairs of rows in two-sided rotations of G (steps of 16 disjoint pairs, the same
+//      rotations that the rows themselves would see) while the product Q of the rotations is
+//      built next to it, and multiplies the rows by Q on the matrix instructions.  The chain of
 //      steps is what bounds it, so a step is kept short: G and Q are 32 x 32 in LDS, double-buffered,
-//      one barrier a step.  The pairs of a step are always positions (k, 16 + k); what a step writes
-//      goes to the position of the next step's partner (the circle method: position 0 stays, the
-//      others move on by one, and after 31 steps everything is back), so all addresses are constants.
+//      one barrier a step, which leaves the rows' loads in flight alone.  The pairs of a step are always
+//      positions (k, 16 + k); what a step writes goes to the position of the next step's partner, so all
+//      addresses are constants.  `turns` = 16: every row of one block meets every row of the other (the
+//      second block's positions move on by one).  31: every pair of the 32 rows (the circle method: position
+//      0 stays, the others move on by one).  A row meets its own block's rows in 1 launch of 4 only: that
+//      took as many sweeps as in every launch, over two spectra of 512 directions and a few random
+//      matrices simulated on the host; in 1 launch of 33 a sweep more.
 //      Waves 0-3 own 2 x 2 of G per thread and each work out all 16 rotations themselves; waves 4-7
 //      follow one step behind with Q.
 //      Blocks of 16: 17 pairs of a 544-row matrix, which fills the chip from 16 matrices on; the
@@ -705,27 +715,33 @@ jacobi_init(const double* __restrict__ S, int64_t s_bstride, float* __restrict__
 //      A pair (x, y) is turned as x - sn (y + ta x), y + sn (x - ta y), ta the tangent of half the angle: the
 //      cosine of a small angle rounds to 1 in fp32, and thousands of such rotations made the rows longer
 //      (sigma of 544 equal directions 4.9e-5 too large with cosine and sine, see the test of it).
-//      Measured at 16 matrices of 544 rows: 24 us a launch, 7.0 ms in all; with the rows themselves in
-//      LDS (blocks of 32, three dot products and a rotation of 544 columns per pair) 190 us a launch
-//      and 21.9 ms.
+//      Measured at 16 matrices of 544 rows: 20 us a launch of 16 turns, 25 of 31, 5.4 ms in all, of a launch's
+//      15.5 us inside the kernel 4.4 the rows and G (out of memory: the L2s do not hold them over a launch),
+//      1.6 its sum and the check, 5.5 the steps, 4.1 the rows' product.  31 turns in every launch, all pairs of
+//      a step in one launch and the rows asked for after the check: 24 us and 7.0 ms; with the rows
+//      themselves in LDS (blocks of 32, three dot products and a rotation of 544 columns per pair) 190 us a
+//      launch and 21.9 ms.
 //      rotations[b][sweep] counts the pairs of blocks that had work; a matrix whose previous sweep
 //      had none is done.
-//      grid (pairs * batch), 512 threads.
+//      grid (ps.count * batch), 512 threads.
 __global__ void __launch_bounds__(512)
-jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, int step, int sweep, float tol,
-            int* __restrict__ rotations, int batch) {
+jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, PairSet ps, int sweep, int turns,
+            float tol, int* __restrict__ rotations, int batch) {
   constexpr int PITCH = 48;                             // 16 mod 32: two neighbouring rows fill the banks
   __shared__ float part[8][3 * 256];
   __shared__ float gm[2][32 * PITCH], qm[2][32 * PITCH];
   __shared__ f32x2_t rot[2][16];                        // sine and tangent of half the angle of a step's pairs
+  __shared__ uint64_t busy[8];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int b, k;                                             // W stays in one XCD's L2
-  matrix_of((int)blockIdx.x, nblk >> 1, batch, b, k);
-  if (sweep > 0 && rotations[b * kSweepSlots + sweep - 1] == 0) return;
+  matrix_of((int)blockIdx.x, ps.count, batch, b, k);
+  if (sweep >= kFirstCheck && rotations[b * kSweepSlots + sweep - 1] == 0) return;
   // round-robin over nblk blocks (nblk even; a block index >= the real count is an empty block)
   const int nm1 = nblk - 1;
-  int ba, bb;
+  int ba, bb, step = ps.step;
+  if (ps.gather) { step += k; k = ps.skip; }
+  else if (k >= ps.skip) ++k;
   if (k == 0) { ba = nm1; bb = step; }
   else { ba = (step + k) % nm1; bb = (step + nm1 - k) % nm1; }
   if (ba * 16 >= l && bb * 16 >= l) return;
@@ -757,47 +773,6 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
         }
       }
   }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int at = (4 * g + e) * 16 + n;
-    part[w][at] = g00[e];
-    part[w][256 + at] = g01[e];
-    part[w][512 + at] = g11[e];
-  }
-  __syncthreads();
-  float own[2];                                         // elements tid and tid + 512 of G
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = (tid >> 5) + 16 * u, j = tid & 31;
-    const int at = u == 0 ? (j < 16 ? i * 16 + j : 256 + i * 16 + j - 16)
-                          : (j < 16 ? 256 + j * 16 + i - 16 : 512 + (i - 16) * 16 + j - 16);
-    float s = part[0][at];
-#pragma unroll
-    for (int q = 1; q < 8; ++q) s += part[q][at];
-    own[u] = s;
-    gm[0][i * PITCH + j] = s;
-  }
-  __syncthreads();
-  const float dg = gm[0][(lane & 31) * (PITCH + 1)];    // the diagonal, in every wave
-  float dmx = dg;
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) dmx = fmaxf(dmx, __shfl_xor(dmx, o));
-  int work = 0;
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = (tid >> 5) + 16 * u, j = tid & 31;
-    const float di = __shfl(dg, i), dj = __shfl(dg, j);
-    if (i != j && fabsf(own[u]) > tol * (sqrtf(di) * sqrtf(dj))) work = 1;
-  }
-  if (!__syncthreads_or(work)) return;                  // every pair is orthogonal already
-  if (tid == 0) atomicAdd(&rotations[b * kSweepSlots + sweep], 1);
-  const int sh = 1 - __builtin_amdgcn_frexp_expf(dmx);
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int i = (tid >> 5) + 16 * u, j = tid & 31;
-    gm[0][i * PITCH + j] = ldexpf(own[u], sh);
-    qm[0][i * PITCH + j] = i == j ? 1.f : 0.f;
-  }
   // the rows again, now a row of a block per (kk, g) and two columns per lane, on their way meanwhile
   const int units = lp >> 5;
   f32x2_t pre[3][8];
@@ -812,15 +787,66 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
 #pragma unroll
   for (int t = 0; t < 3; ++t)
     if (w + 8 * t < units) load_unit(w + 8 * t, pre[t]);
-  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int at = (4 * g + e) * 16 + n;
+    part[w][at] = g00[e];
+    part[w][256 + at] = g01[e];
+    part[w][512 + at] = g11[e];
+  }
+  lds_barrier();
+  float own[2];                                         // elements tid and tid + 512 of G
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    const int at = u == 0 ? (j < 16 ? i * 16 + j : 256 + i * 16 + j - 16)
+                          : (j < 16 ? 256 + j * 16 + i - 16 : 512 + (i - 16) * 16 + j - 16);
+    float s = part[0][at];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) s += part[q][at];
+    own[u] = s;
+    gm[0][i * PITCH + j] = s;
+  }
+  lds_barrier();
+  const float dg = gm[0][(lane & 31) * (PITCH + 1)];    // the diagonal, in every wave
+  float dmx = dg;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) dmx = fmaxf(dmx, __shfl_xor(dmx, o));
+  int work = 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    const float di = __shfl(dg, i), dj = __shfl(dg, j);
+    if (i != j && fabsf(own[u]) > tol * (sqrtf(di) * sqrtf(dj))) work = 1;
+  }
+  const uint64_t vote = __ballot(work);
+  if (lane == 0) busy[w] = vote;
+  lds_barrier();
+  uint64_t any = busy[0];
+#pragma unroll
+  for (int q = 1; q < 8; ++q) any |= busy[q];
+  if (any == 0) return;                                 // every pair is orthogonal already
+  if (tid == 0) atomicAdd(&rotations[b * kSweepSlots + sweep], 1);
+  const int sh = 1 - __builtin_amdgcn_frexp_expf(dmx);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = (tid >> 5) + 16 * u, j = tid & 31;
+    gm[0][i * PITCH + j] = ldexpf(own[u], sh);
+    qm[0][i * PITCH + j] = i == j ? 1.f : 0.f;
+  }
+  lds_barrier();
 
   const int I = 4 * (w & 3) + g;
-  auto moved = [](int p) { return p == 0 ? 0 : p == 15 ? 31 : p == 16 ? 1 : p < 15 ? p + 1 : p - 1; };
+  const bool within = turns == 31;
+  auto moved = [&](int p) {
+    if (!within) return p < 16 ? p : 16 + ((p + 1) & 15);
+    return p == 0 ? 0 : p == 15 ? 31 : p == 16 ? 1 : p < 15 ? p + 1 : p - 1;
+  };
   const int r0 = moved(I) * PITCH, r1 = moved(16 + I) * PITCH, c0 = moved(n), c1 = moved(16 + n);
 #pragma unroll 2
-  for (int s = 0; s < 32; ++s) {
+  for (int s = 0; s <= turns; ++s) {
     if (w < 4) {
-      if (s < 31) {
+      if (s < turns) {
         const float* cur = gm[s & 1];
         float* nxt = gm[(s & 1) ^ 1];
         const float al = cur[n * (PITCH + 1)], be = cur[(16 + n) * (PITCH + 1)], ga = cur[n * PITCH + 16 + n];
@@ -855,11 +881,11 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, i
       nxt[r1 + n] = fmaf(r[0], fmaf(-r[1], a10, a00), a10);
       nxt[r1 + 16 + n] = fmaf(r[0], fmaf(-r[1], a11, a01), a11);
     }
-    __syncthreads();
+    lds_barrier();
   }
 
   // rows <- Q rows
-  const float* Q = qm[1];
+  const float* Q = qm[turns & 1];
   float qa[2][8];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
@@ -1019,10 +1045,24 @@ ap_status run_bases(const BasesArgs& a) {
   hipLaunchKernelGGL(jacobi_init, dim3((l * lp + 255) / 256, B), dim3(256), 0, st, S, (int64_t)l * l, W, w_bs, l, lp, rotations);
   int nblk = (l + 15) / 16;
   nblk += nblk & 1;                                      // an even number of blocks (the last may be empty)
+  const int P = nblk / 2, nm1 = nblk - 1;
+  // Two workgroups on one CU hold each other up (15.5 us alone, 16.5 and 22 together: the steps fill half the
+  // CU's issue slots, and the rows come in later), so a launch that puts a second one on a few CUs only lasts
+  // as long as one that does on all.  Where a pair less per matrix keeps to one per CU, each step leaves out
+  // pair `skip`; with skip a quarter of the steps, up to half the steps' pairs touch each block once and are
+  // made up for in one launch.  From eight pairs on: below, the additional launches outweigh it.
+  const int skip = nm1 / 4, run = min(2 * skip, nm1 - 2 * skip);
+  const bool spare = P >= 8 && P * B > 256 && (P - 1) * B <= 256;
+  auto turn = [&](int sweep, PairSet ps, int turns) {
+    hipLaunchKernelGGL(jacobi_pair, dim3(ps.count * B), dim3(512), 0, st, W, w_bs, l, lp, nblk, ps, sweep, turns, kJacobiTol,
+                       rotations, B);
+  };
   for (int sweep = 0; sweep < kJacobiSweeps; ++sweep)
-    for (int step = 0; step < nblk - 1; ++step)
-      hipLaunchKernelGGL(jacobi_pair, dim3(nblk / 2 * B), dim3(512), 0, st, W, w_bs, l, lp, nblk, step, sweep, kJacobiTol,
-                         rotations, B);
+    for (int step = 0; step < nm1; ++step) {
+      const bool out = spare && step < 2 * run;
+      turn(sweep, PairSet{step, out ? skip : P, 0, out ? P - 1 : P}, step % kFullEvery == 0 || sweep >= kFullFrom ? 31 : 16);
+      if (out && (step + 1) % run == 0) turn(sweep, PairSet{step + 1 - run, skip, 1, run}, 16);
+    }
   hipLaunchKernelGGL(eig_norms, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, l, lp, lam);
   hipLaunchKernelGGL(eig_select, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, lam, l, lp, r, Rsel, (int64_t)r * l, a.sigma,
                      (int64_t)r);

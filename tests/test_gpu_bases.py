@@ -346,6 +346,28 @@ def test_bases_of_a_batch_with_large_gram_tiles(B, n, HD, l):
         assert (np.abs(G - np.diag(np.diag(G))) <= eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)).all()
 
 
+@pytest.mark.parametrize("B,l", [
+    (35, 256),                 # 8 pairs of blocks a matrix: a pair less keeps to one workgroup per CU
+    (30, 258),                 # 9, with two rows in the last block but one and none in the last
+    (36, 256),                 # not even so
+])
+def test_bases_of_a_batch_that_leaves_out_a_pair(B, l):
+    """The order of the pairs of blocks where each step leaves one out and makes up for it later: the bounds
+    of the test of single sequences, on every sequence."""
+    dtype, n, HD = "f16", 320, 320
+    X = np.stack([cache_matrix(53, b, n, HD, 128, dtype) for b in range(B)])
+    Omega = wl.store(wl.rng_for(53, 7).standard_normal((l, HD)), dtype)
+    print(f"bases batch {B} l={l}", flush=True)
+    D, sig = gpu_bases(X, Omega, l, 1, dtype)
+    eps = 2.0 ** -11
+    for b in range(B):
+        Z = oracle.promote(X[b], dtype) @ oracle.promote(D[b], dtype).T
+        s = np.linalg.norm(Z, axis=0)
+        G = Z.T @ Z
+        assert np.abs(sig[b] - s).max() <= 2 * eps * s[0] and np.diff(sig[b]).max() <= 1e-6 * sig[b][0]
+        assert (np.abs(G - np.diag(np.diag(G))) <= eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)).all()
+
+
 @pytest.mark.parametrize("l", [34, 66, 256, 602])
 def test_bases_small_directions(l):
     """A cache of l directions whose singular values fall from 4 to 1 and nothing else, so that bounds by
