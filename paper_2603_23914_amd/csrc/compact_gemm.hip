@@ -72,7 +72,7 @@ struct GemmParams {
   int G1;
 };
 
-template <class Tag, int kBM>
+template <class Tag, int kBM, bool kEdges64>
 __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
   constexpr int kBN = kEdges - kBM;
   constexpr int kEpiPitch = kBN + 8;                       // 16-bit elements per staged output row
@@ -198,9 +198,22 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
     __builtin_amdgcn_sched_barrier(0);     // keep the requests ahead of the products
     multiply(fa_cur, fb_cur);
   };
-  for (int kb = 0; kb < nk; kb += 2) {
-    step(kb, fa0, fb0, fa1, fb1);
-    if (kb + 1 < nk) step(kb + 1, fa1, fb1, fa0, fb0);
+  // A wave whose 64 x 64 lies past the end of an edge tile only fetches its share (kEdges64): the tile's other waves
+  // have the LDS and the power to themselves.  16 products of 544 rows (4.25 tiles) times 4224 columns 475 -> 458
+  // us, times 4096 454 -> 440; products without such waves lose 0.5 % to the second loop and keep the plain kernel.
+  // (Halves of a 64 x 64 likewise, in loops of their own: the kernel then spills and is slower.)
+  if (!kEdges64 || (m0 + wm * 64 < p.n && n0 + wn * 64 < p.r)) {
+    for (int kb = 0; kb < nk; kb += 2) {
+      step(kb, fa0, fb0, fa1, fb1);
+      if (kb + 1 < nk) step(kb + 1, fa1, fb1, fa0, fb0);
+    }
+  } else {
+    for (int kb = 0; kb < nk; ++kb) {                      // the waits and barriers of step
+      if (kb + 2 < nk) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      asm volatile("s_barrier" ::: "memory");
+      if (kb + 3 < nk) issue(kb % kStages, kb + 3);
+    }
   }
   __syncthreads();                                         // the ring becomes the output staging area
 
@@ -289,8 +302,8 @@ __global__ void __launch_bounds__(kThreads) compact_gemm(const GemmParams p) {
   }
 }
 
-template <class Tag, int kBM>
-ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
+template <class Tag, int kBM, bool kEdges64>
+ap_status run_gemm_as(const NtGemmArgs& a, const NtGemmArgs* a2) {
   constexpr int kBN = kEdges - kBM;
   GemmParams p{};
   p.X = (const uint16_t*)a.A;
@@ -315,7 +328,7 @@ ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
     p.scale2 = (uint16_t*)a2->scale;
   }
   const int grid = ((p.G + 7) / 8) * 8;
-  auto kern = compact_gemm<Tag, kBM>;
+  auto kern = compact_gemm<Tag, kBM, kEdges64>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -328,6 +341,13 @@ ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), kStages * kStageBytes, a.stream, p);
   return check_launch("matrix product");
+}
+
+template <class Tag, int kBM>
+ap_status run_gemm(const NtGemmArgs& a, const NtGemmArgs* a2) {
+  constexpr int kBN = kEdges - kBM;
+  const bool edges = (a.M + kBM - 1) / kBM * kBM - a.M >= 64 || (a.N + kBN - 1) / kBN * kBN - a.N >= 64;
+  return edges ? run_gemm_as<Tag, kBM, true>(a, a2) : run_gemm_as<Tag, kBM, false>(a, a2);
 }
 
 // The tile whose count makes fewer rounds over the 256 CUs; in equal rounds the smaller count, but
