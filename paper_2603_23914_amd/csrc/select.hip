@@ -4,25 +4,20 @@
 // and cut at fixed sorted positions into F groups.  Nothing is sorted: a group boundary at
 // sorted position p is fully described by the p-th largest key kappa and by how many of the
 // tokens whose key equals kappa still fall in front of it (the quota), so
-//   1. a radix select finds (kappa, quota) of all F-1 boundaries at once (four passes over
-//      the row with digits of 12, 8, 8 and 4 bits, histograms in LDS; when few keys share the
-//      boundaries' first digits, the last three passes give way to a bit-by-bit search over
-//      those few keys in registers);
-//   2. every thread owns a contiguous run of tokens; block-wide prefix sums of "key == kappa"
-//      give each token its position among equal keys, which decides its group;
-//   3. block-wide prefix sums of the group counts give each token its slot in its group's
-//      ascending index list.
-// One workgroup of 1024 threads per batch row; rows of up to 32768 tokens are first copied to
-// LDS as sort keys, so the four radix passes and the two walks read LDS, not memory.  The LDS
-// copy skips one word after every 32 tokens: a thread's contiguous run of tokens then starts
-// in a different bank than its neighbours' and the walks are free of bank conflicts.  Group
-// ids replace the keys in that copy once they are known, and the ranks leave in a coalesced
-// pass.  All integer work, results are unique.  Few, long rows take the same steps with a row
-// split over workgroups (the split_* kernels below).
+//   1. a radix select finds (kappa, quota) of all F-1 boundaries at once, with histograms of the
+//      keys' digits in LDS, most significant first;
+//   2. prefix sums of "key == kappa" give each token its position among equal keys, which
+//      decides its group;
+//   3. prefix sums of the group counts give each token its slot in its group's ascending index
+//      list.
+// Rows of up to 32768 tokens: one workgroup per row, the keys in registers (select_rows).  Longer rows take the
+// same steps split over workgroups (the split_* kernels); a row that these give up on is done by one workgroup
+// that re-reads it from memory in every pass (select_ranks_kernel).  All integer work, results are unique.
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
 
-#include <cstdlib>
+#include <type_traits>
+
 namespace ap {
 namespace {
 
@@ -41,16 +36,7 @@ struct SelectParams {
   int32_t* bucket_idx;
   uint32_t* split_ws;         // rows split over workgroups: per-row scratch (see SplitLayout), else null
   int per;                    // ... and the tokens each thread owns there
-#ifdef AP_KERNEL_TIMERS
-  unsigned long long* stamps;   // kernel studies: 16 time stamps of row 0's first and last thread (100 MHz counter)
-#endif
 };
-
-#ifdef AP_KERNEL_TIMERS
-#define AP_SELECT_STAMP(i) do { if (blockIdx.x == 0 && (threadIdx.x == 0 || threadIdx.x == 1023)) p.stamps[(threadIdx.x ? 16 : 0) + (i)] = wall_clock64(); } while (0)
-#else
-#define AP_SELECT_STAMP(i) do { } while (0)
-#endif
 
 // Order-preserving map float -> uint32 (larger value, larger key); -0 and +0 share a key.
 __device__ __forceinline__ uint32_t key_of(float m) {
@@ -100,7 +86,6 @@ __device__ __forceinline__ void block_excl_scan_n(int (&v)[N], int n, int* wave_
 }
 
 constexpr int kCand = 256;             // candidate keys per boundary that the short cut after the first pass takes
-constexpr int kStagedMax = 32768;      // tokens whose keys fit the dynamic LDS slice (132 KiB with padding)
 
 // Rows split over workgroups (long rows, few of them): a workgroup of 256 threads owns a chunk of
 // 256 * per consecutive tokens, a thread `per` consecutive ones.  Per-row scratch in the caller's
@@ -116,8 +101,6 @@ constexpr int kSplitWaves = kSplitThreads / 64;
 constexpr int kSplitMaxChunks = 64;
 constexpr int kEqMax = 256;            // tokens per boundary that may share kappa itself
 constexpr int kStage = 2048;           // candidates of a boundary that are walked from LDS
-constexpr int kSplitMinT = 24576;      // rows at least this long ...
-constexpr int kSplitMaxB = 32;         // ... in batches of at most this many rows, or rows beyond kStagedMax
 constexpr int kCtlNcand = 0, kCtlGaveUp = 7, kCtlDigit = 8, kCtlNeed = 16;
 struct SplitLayout {
   int G, cap;
@@ -142,9 +125,8 @@ inline int split_per(int T) {
   return per < 8 ? 8 : (per + 7) / 8 * 8;
 }
 
-template <bool STAGED>
+// One workgroup per row, the keys read from memory in every pass: rows that the split kernels gave up on.
 __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectParams p) {
-  extern __shared__ __attribute__((aligned(16))) uint32_t keys_lds[];   // STAGED: [T]
   __shared__ uint32_t hist[kMaxF - 1][256];
   __shared__ uint32_t hist0[4096];           // first pass: 12-bit digits, shared by all boundaries
   __shared__ uint32_t mark[128];             // one bit per first digit: some boundary's prefix
@@ -157,27 +139,8 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
   const float* m = p.mass + (size_t)b * T;
   // after the split kernels: only the rows they gave up on (too many keys share a boundary's
   // leading bits) are done here
-  if (p.split_ws && p.split_ws[split_layout(T, p.per).stride * b + split_layout(T, p.per).ctl + kCtlGaveUp] == 0u) return;
-  AP_SELECT_STAMP(0);
-  auto slot_of = [](int t) -> int { return t + (t >> 5); };      // one pad word per 32 tokens
-  if (STAGED) {
-    for (int t0 = tid; t0 < T; t0 += 8 * kThreads) {        // eight loads in flight per thread
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = t0 + u * kThreads;
-        v[u] = m[t < T ? t : T - 1];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = t0 + u * kThreads;
-        if (t < T) keys_lds[slot_of(t)] = key_of(v[u]);
-      }
-    }
-    __syncthreads();
-  }
-  auto key_at = [&](int t) -> uint32_t { return STAGED ? keys_lds[slot_of(t)] : key_of(m[t]); };
-  AP_SELECT_STAMP(1);
+  if (p.split_ws[split_layout(T, p.per).stride * b + split_layout(T, p.per).ctl + kCtlGaveUp] == 0u) return;
+  auto key_at = [&](int t) -> uint32_t { return key_of(m[t]); };
 
   // a cut at 0 or at T needs no threshold search
   bool active[kMaxF - 1];
@@ -228,7 +191,6 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
       }
     }
     __syncthreads();
-    AP_SELECT_STAMP(2 + 2 * pass);
     // wave g walks boundary g's histogram from the top: lane l owns `per` consecutive digits
     bool act_w = false;
 #pragma unroll
@@ -278,7 +240,6 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
       }
     }
     __syncthreads();
-    AP_SELECT_STAMP(3 + 2 * pass);
     if (pass == 0) {
       // ---- short cut: when at most kCand keys share the first digit of every boundary (the
       //      usual case: one key in hundreds does), the remaining 20 bits are not found by
@@ -330,7 +291,6 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
           }
         }
         __syncthreads();
-        AP_SELECT_STAMP(9);
         break;
       }
     }
@@ -358,9 +318,7 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
     for (int g = 0; g < kMaxF - 1; ++g)
       if (g < nb) eq[g] += (key == kappa[g]) ? 1 : 0;       // nb is the same for all: a scalar branch
   }
-  AP_SELECT_STAMP(10);
   block_excl_scan_n<kMaxF - 1>(eq, nb, wave_tot);               // now: equal keys before t0
-  AP_SELECT_STAMP(11);
   int cnt[kMaxF];
 #pragma unroll
   for (int g = 0; g < kMaxF; ++g) cnt[g] = 0;
@@ -377,51 +335,310 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
         eq[g] += same ? 1 : 0;
       }
     }
-    if (STAGED) keys_lds[slot_of(t)] = (uint32_t)grp;       // the key is not needed again
-    else rank_row[t] = grp;                                 // group id for now, rank below
+    rank_row[t] = grp;                                      // group id for now, rank below
 #pragma unroll
     for (int g = 0; g < kMaxF; ++g)
       if (g < F) cnt[g] += (grp == g) ? 1 : 0;
   }
 
   // ---- 3. slot inside the group's ascending index list
-  AP_SELECT_STAMP(12);
   block_excl_scan_n<kMaxF>(cnt, F, wave_tot);
-  AP_SELECT_STAMP(13);
   int32_t* idx_row = p.bucket_idx + (size_t)b * T;
   for (int t = t0; t < t1; ++t) {
-    const int grp = STAGED ? (int)keys_lds[slot_of(t)] : rank_row[t];
+    const int grp = rank_row[t];
     int slot = 0, rk = 0;
 #pragma unroll
     for (int g = 0; g < kMaxF; ++g) {
       if (g < F && grp == g) { slot = p.bound[g] + cnt[g]; rk = p.grank[g]; cnt[g] += 1; }
     }
-    if (!STAGED) rank_row[t] = rk;
+    rank_row[t] = rk;
     if (slot < T) idx_row[slot] = t;    // always true; keeps a logic error inside the buffer
-  }
-  AP_SELECT_STAMP(14);
-  if (STAGED) {                         // ranks out, consecutive threads to consecutive tokens
-    __syncthreads();
-    for (int t = tid; t < T; t += kThreads) {
-      const int grp = (int)keys_lds[slot_of(t)];
-      int rk = 0;
-#pragma unroll
-      for (int g = 0; g < kMaxF; ++g)
-        if (g < F) rk = grp == g ? p.grank[g] : rk;
-      rank_row[t] = rk;
-    }
   }
   int cut = 0;
 #pragma unroll
   for (int g = 0; g <= kMaxF; ++g) cut = tid == g ? p.bound[g] : cut;
   if (tid <= F) p.bucket_off[(size_t)b * (F + 1) + tid] = cut;
-  AP_SELECT_STAMP(15);
 }
 
 
 // ------------------------------------------------------------------------------------------
-// The same selection with a row split over workgroups, for batches too small to fill the chip
-// with one workgroup per row.  Four launches over grid (G chunks, B rows), 256 threads:
+// Rows of up to 32768 tokens: one workgroup of 1024 threads per row, N tokens per thread, whose keys stay in
+// registers (thread i holds tokens i, i + 1024, ...; loads and stores are coalesced).  What bounds it is the chain
+// of barriers (ten, a few hundred cycles each) and, on long rows, the LDS additions of the first histogram.
+//   - Digits of 13, 10 and 9 bits, all in LDS and cleared while the row is on its way.  A wide first digit, because
+//     importance values share their leading bits: half a Zipf row lies within a factor of two, eight values of the
+//     four mantissa bits' sixteen, and equal counters are added to one lane at a time.
+//   - The first histogram is searched by all threads at once, eight counters each, the later ones by a wave
+//     per boundary; sums across lanes are DPP prefix sums.
+//   - A token's position in front of which nothing else has to be counted comes from ballots: tokens in front
+//     of a cut in each (64 tokens, cut), prefix sums of these by a wave per cut.  Equal keys are counted only where
+//     a cut falls among them.
+// Measured: 64 rows of 4225 tokens, two groups, 19-23 us -> 10 (T = 4225; 27 -> 11 with four groups); one row of 32768, four groups, 51 us split over 16
+// workgroups -> 34; 64 rows of 16384: 57 -> 33.
+// ------------------------------------------------------------------------------------------
+constexpr int kRowMax = 32768;
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ int dpp_add_int(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, true);
+}
+__device__ __forceinline__ int wave_prefix_sum(int x) {               // sum over lanes <= lane
+  x = dpp_add_int<0x111>(x);             // row_shr 1, 2, 4, 8
+  x = dpp_add_int<0x112>(x);
+  x = dpp_add_int<0x114>(x);
+  x = dpp_add_int<0x118>(x);
+  x = dpp_add_int<0x142, 0xa>(x);        // row_bcast15: rows 1 and 3 take the row in front
+  return dpp_add_int<0x143, 0xc>(x);     // row_bcast31: rows 2 and 3 take lane 31
+}
+__device__ __forceinline__ int lanes_below(uint64_t mask, int add) {  // add + set bits of lanes < lane
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)add));
+}
+// One wave finds the digit that holds the k-th largest entry (1-based) of a histogram of NBINS counters, the
+// position left inside it and its count.  Lane l owns NBINS / 64 digits, the largest ones at lane 0.
+template <int NBINS>
+__device__ __forceinline__ void find_digit(const uint32_t* h, int k, uint32_t* digit, uint32_t* rest, uint32_t* count) {
+  constexpr int per = NBINS / 64;
+  const int first = per * (63 - (int)(threadIdx.x & 63));
+  u32x4_t c[per / 4];
+  int tot = 0;
+#pragma unroll
+  for (int j = 0; j < per / 4; ++j) c[j] = *(const u32x4_t*)(h + first + 4 * j);
+#pragma unroll
+  for (int j = 0; j < per; ++j) tot += (int)c[j >> 2][j & 3];
+  const int incl = wave_prefix_sum(tot);
+  int above = incl - tot;
+  if (above < k && k <= incl) {                                        // exactly one lane
+#pragma unroll
+    for (int j = per - 1; j >= 0; --j) {
+      const int cj = (int)c[j >> 2][j & 3];
+      if (above < k && k <= above + cj) { *digit = (uint32_t)(first + j); *rest = (uint32_t)(k - above); *count = (uint32_t)cj; }
+      above += cj;
+    }
+  }
+}
+
+template <int N, int kCuts>
+__global__ void __launch_bounds__(kThreads) select_rows(const SelectParams p) {
+  constexpr int B1 = 8192, B2 = 1024, B3 = 512;
+  __shared__ __attribute__((aligned(16))) uint32_t h1[B1], h2[kCuts * B2];
+  uint32_t* const h3 = h1;                                // [kCuts][B3], once the first digits are known
+  int* const base = (int*)h1 + kCuts * B3;                // [kCuts][N * kWaves]: tokens in front, per 64 tokens
+  static_assert(kCuts * (B3 + N * kWaves) <= B1, "base overlaps");
+  __shared__ int wave_tot[kWaves];
+  __shared__ uint32_t s_key[kCuts], s_need[kCuts], s_dig[kCuts], s_rest[kCuts], s_count[kCuts];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.x, T = p.T;
+  const int n = (T + kThreads - 1) / kThreads;            // <= N
+  const int nw = (T - 64 * w + kThreads - 1) / kThreads;  // blocks of 64 tokens of this wave (T < 64 w: none)
+  const float* m = p.mass + (size_t)b * T;
+  uint32_t key[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < nw) {
+      const int t = i * kThreads + tid;
+      const float v = m[t < T ? t : T - 1];
+      key[i] = t < T ? key_of(v) : 0u;                    // past the end: behind every token
+    }
+  // a cut at 0 or at T needs no search
+  bool active[kCuts];
+#pragma unroll
+  for (int g = 0; g < kCuts; ++g) active[g] = p.bound[g + 1] > 0 && p.bound[g + 1] < T;
+  const u32x4_t z4 = {0u, 0u, 0u, 0u};
+  for (int i = tid; i < B1 / 4; i += kThreads) ((u32x4_t*)h1)[i] = z4;
+  for (int i = tid; i < kCuts * B2 / 4; i += kThreads) ((u32x4_t*)h2)[i] = z4;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < nw) atomicAdd(&h1[key[i] >> 19], 1u);
+  __syncthreads();
+  {
+    const int first = 8 * (kThreads - 1 - tid);           // the largest digits at thread 0
+    const u32x4_t lo = *(const u32x4_t*)(h1 + first), hi = *(const u32x4_t*)(h1 + first + 4);
+    const int tot = (int)(lo[0] + lo[1] + lo[2] + lo[3] + hi[0] + hi[1] + hi[2] + hi[3]);
+    const int incl = wave_prefix_sum(tot);
+    if (lane == 63) wave_tot[w] = incl;
+    __syncthreads();
+    int front = incl - tot;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) front += i < w ? wave_tot[i] : 0;
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g) {
+      const int k = p.bound[g + 1];
+      if (active[g] && front < k && k <= front + tot) {   // exactly one thread
+        int above = front;
+#pragma unroll
+        for (int j = 7; j >= 0; --j) {
+          const int c = (int)(j < 4 ? lo[j & 3] : hi[j & 3]);
+          if (above < k && k <= above + c) { s_key[g] = (uint32_t)(first + j); s_need[g] = (uint32_t)(k - above); }
+          above += c;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  // ---- the later digits: few keys share a cut's first one, the others stop at one branch
+  for (int i = tid; i < kCuts * B3 / 4; i += kThreads) ((u32x4_t*)h3)[i] = z4;
+  uint32_t hit = 0u;                                      // blocks of the wave with a key that shares one
+  auto count_digit = [&](auto shift, const uint32_t (&pre)[kCuts], uint32_t* h) {
+    constexpr int bins = shift == 19 ? B2 : B3, low = shift == 19 ? 9 : 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (!(shift == 19 ? i < nw : (hit >> i) & 1u)) continue;
+      bool any = false;
+#pragma unroll
+      for (int g = 0; g < kCuts; ++g) any |= key[i] >> shift == pre[g];
+      if (!__any(any)) continue;
+      hit |= 1u << i;
+#pragma unroll
+      for (int g = 0; g < kCuts; ++g)
+        if (key[i] >> shift == pre[g]) atomicAdd(&h[g * bins + (int)((key[i] >> low) & (uint32_t)(bins - 1))], 1u);
+    }
+  };
+  bool act_w = false;
+#pragma unroll
+  for (int g = 0; g < kCuts; ++g) act_w = act_w || (w == g && active[g]);
+  uint32_t pre[kCuts];
+#pragma unroll
+  for (int g = 0; g < kCuts; ++g) pre[g] = active[g] ? s_key[g] : kNone;
+  count_digit(std::integral_constant<int, 19>{}, pre, h2);
+  __syncthreads();
+  if (act_w) find_digit<B2>(h2 + w * B2, (int)s_need[w], &s_dig[w], &s_rest[w], &s_count[w]);
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < kCuts; ++g) pre[g] = active[g] ? pre[g] << 10 | s_dig[g] : kNone;
+  count_digit(std::integral_constant<int, 9>{}, pre, h3);
+  __syncthreads();
+  if (act_w) {
+    uint32_t d = 0u, q = 0u, c = 0u;
+    find_digit<B3>(h3 + w * B3, (int)s_rest[w], &d, &q, &c);
+    if (c) {                                              // the one lane that found it
+      s_key[w] = (s_key[w] << 10 | s_dig[w]) << 9 | d;
+      s_need[w] = q;
+      s_count[w] = c;
+    }
+  }
+  __syncthreads();
+
+  uint32_t kappa[kCuts];
+  bool tie[kCuts], plain = true;
+#pragma unroll
+  for (int g = 0; g < kCuts; ++g) {
+    kappa[g] = 0u;                                        // a cut at T: everybody
+    tie[g] = false;
+    plain = plain && p.bound[g + 1] > 0;
+    if (active[g]) {
+      kappa[g] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_key[g]);
+      tie[g] = __builtin_amdgcn_readfirstlane((int)s_need[g]) < __builtin_amdgcn_readfirstlane((int)s_count[g]);
+      plain = plain && !tie[g];
+    }
+  }
+  // Tokens of a block of 64 for which pred(i) holds go to base[g]; a wave adds the blocks up; bases_of takes
+  // them back (lane i: block i of the wave), and before counts the tokens in front of a thread's own.
+  auto count_blocks = [&](int g, auto pred) {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (i < nw) {
+        const int k = __popcll(__ballot(pred(i)));
+        c = lane == i ? k : c;
+      }
+    if (lane < n) base[g * N * kWaves + lane * kWaves + w] = c;
+  };
+  auto sum_blocks = [&](int g) {
+    int* at = base + g * N * kWaves;
+    int carry = 0;
+    for (int e = lane; e - lane < n * kWaves; e += 64) {
+      const int v = e < n * kWaves ? at[e] : 0;
+      const int incl = wave_prefix_sum(v);
+      if (e < n * kWaves) at[e] = carry + incl - v;
+      carry += __builtin_amdgcn_readlane(incl, 63);
+    }
+  };
+  auto bases_of = [&](int g) { return lane < n ? base[g * N * kWaves + lane * kWaves + w] : 0; };
+  auto before = [&](int bases, int i, bool in) { return lanes_below(__ballot(in), __builtin_amdgcn_readlane(bases, i)); };
+
+  // ranks, and slots in the groups' ascending lists; in_front(g, i): the thread's token i lies in front of cut g
+  int32_t* rank_row = p.rank_out + (size_t)b * T;
+  int32_t* idx_row = p.bucket_idx + (size_t)b * T;
+  auto emit = [&](auto in_front) {
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g)
+      count_blocks(g, [&](int i) { return in_front(g, i); });
+    __syncthreads();
+    if (w < kCuts) sum_blocks(w);
+    __syncthreads();
+    int at[kCuts], sum = 0;                                     // with the cuts added up: a slot is a difference
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g) {
+      sum += p.bound[g];
+      at[g] = bases_of(g) + sum;
+    }
+    sum += p.bound[kCuts];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (i < nw) {
+        const int t = i * kThreads + tid;
+        int slot = 0, rk = 0, last = 0;                         // last: the count at the cut before
+        bool placed = false;
+#pragma unroll
+        for (int g = 0; g < kCuts; ++g) {                       // membership is nested: the first cut that has it
+          const bool in = in_front(g, i);
+          const int c = before(at[g], i, in);
+          const bool here = in && !placed;
+          slot = here ? c - last : slot;
+          rk = here ? p.grank[g] : rk;
+          placed = in;
+          last = c;
+        }
+        slot = placed ? slot : t + sum - last;
+        rk = placed ? rk : p.grank[kCuts];
+        if (t < T) {
+          rank_row[t] = rk;
+          if ((uint32_t)slot < (uint32_t)T) idx_row[slot] = t;  // always true; keeps a logic error inside the buffer
+        }
+      }
+  };
+  if (plain) {
+    emit([&](int g, int i) { return key[i] >= kappa[g]; });
+  } else {
+    // equal keys at a cut are in front of it by token order; cuts at 0 and T have nobody and everybody in front
+    uint32_t front[kCuts];
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g)
+      if (tie[g]) count_blocks(g, [&](int i) { return key[i] == kappa[g] && i * kThreads + tid < T; });
+    __syncthreads();
+    bool tie_w = false;
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g) tie_w = tie_w || (w == g && tie[g]);
+    if (tie_w) sum_blocks(w);
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kCuts; ++g) {
+      front[g] = 0u;
+      if (p.bound[g + 1] > 0) {
+        const int at = tie[g] ? bases_of(g) : 0, quota = tie[g] ? (int)s_need[g] : T;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          if (i < nw) {
+            const bool in_row = i * kThreads + tid < T, same = key[i] == kappa[g] && in_row;
+            bool in = in_row && (!active[g] || key[i] > kappa[g] || same);
+            if (tie[g] && before(at, i, same) >= quota && same) in = false;
+            front[g] |= in ? 1u << i : 0u;
+          }
+      }
+    }
+    __syncthreads();                                            // base is free again
+    emit([&](int g, int i) { return ((front[g] >> i) & 1u) != 0u; });
+  }
+  int cut = 0;
+#pragma unroll
+  for (int g = 0; g <= kMaxF; ++g) cut = tid == g ? p.bound[g] : cut;
+  if (tid <= p.F) p.bucket_off[(size_t)b * (p.F + 1) + tid] = cut;
+}
+
+// ------------------------------------------------------------------------------------------
+// The same selection with a row split over workgroups, for rows longer than one workgroup's registers hold.
+// Four launches over grid (G chunks, B rows), 256 threads:
 //   split_hist    first-digit (12-bit) histogram of every chunk, to the workspace;
 //   split_cand    every workgroup adds the chunks' histograms up, finds each boundary's first
 //                 digit, and lists the keys of its chunk that share it (with their tokens);
@@ -896,25 +1113,14 @@ ap_status launch_update_importance(const float* scores, const float* lse, float*
   return check_launch("ap_update_importance");
 }
 
-// One workgroup per row fills the chip when there are many rows, and a short row is done before
-// four more launches would be (each hands its results to the next through memory: about 45 us in
-// all, whatever the length): the split is for few, long rows (measured at four groups: 32768
-// tokens 45-55 us against 92-96, 16384 tokens about even), and for rows too long for the one
-// workgroup's LDS copy, which it would otherwise re-read from memory seven times (131072 tokens:
-// 61-95 us against 650).
-static bool split_applies(int B, int T) {
-#ifdef AP_KERNEL_TIMERS
-  return false;                          // the stamps live where the split's scratch would
-#else
-#ifdef AP_SELECT_SPLIT_ENV
-  if (const char* e = getenv("AP_SELECT_SPLIT")) return atoi(e) != 0;
-#endif
-  return T > kStagedMax || (T >= kSplitMinT && B <= kSplitMaxB);
-#endif
-}
+// One workgroup per row as long as its threads hold the keys: four launches that hand their results on through
+// memory take 45 us and more whatever the length (one row of 32768 tokens, four groups: 51 us split, 34 in one
+// workgroup; 24576: 47 and 27; 32 rows of 32768: 70 and 35).  Longer rows would be re-read from memory seven
+// times (131072 tokens: 61-95 us split against 650).
+static bool split_applies(int T) { return T > kRowMax; }
 size_t select_workspace(int B, int T, int) {
-  // without the split every intermediate lives in LDS
-  return split_applies(B, T) ? 256 + (size_t)B * split_layout(T, split_per(T)).stride * 4 : 256;
+  // without the split every intermediate lives in LDS and registers
+  return split_applies(T) ? 256 + (size_t)B * split_layout(T, split_per(T)).stride * 4 : 256;
 }
 
 ap_status launch_select_ranks(const float* mass, int B, int T, int F, const int32_t* group_rank,
@@ -936,10 +1142,7 @@ ap_status launch_select_ranks(const float* mass, int B, int T, int F, const int3
   p.bucket_idx = bucket_idx;
   p.split_ws = nullptr;
   p.per = 0;
-#ifdef AP_KERNEL_TIMERS
-  p.stamps = (unsigned long long*)ws;
-#endif
-  if (split_applies(B, T)) {
+  if (split_applies(T)) {
     SplitParams sp;
     sp.mass = mass;
     sp.ws = (uint32_t*)ws;
@@ -956,25 +1159,17 @@ ap_status launch_select_ranks(const float* mass, int B, int T, int F, const int3
     hipLaunchKernelGGL(split_cand, grid, dim3(kSplitThreads), 0, stream, sp);
     hipLaunchKernelGGL(split_groups, grid, dim3(kSplitThreads), 0, stream, sp);
     hipLaunchKernelGGL(split_emit, grid, dim3(kSplitThreads), 0, stream, sp);
-    p.split_ws = sp.ws;               // the one-workgroup kernel below: flagged rows only
+    p.split_ws = sp.ws;
     p.per = sp.per;
-  }
-  if (T <= kStagedMax) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute((const void*)select_ranks_kernel<true>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (kStagedMax + kStagedMax / 32 + 1) * 4);
-      if (e != hipSuccess) {
-        set_error("hipFuncSetAttribute: %s", hipGetErrorString(e));
-        return AP_ERR_HIP;
-      }
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(select_ranks_kernel<true>, dim3(B), dim3(kThreads), ((size_t)T + T / 32 + 1) * 4,
-                       stream, p);
+    hipLaunchKernelGGL(select_ranks_kernel, dim3(B), dim3(kThreads), 0, stream, p);   // flagged rows only
   } else {
-    hipLaunchKernelGGL(select_ranks_kernel<false>, dim3(B), dim3(kThreads), 0, stream, p);
+    auto of = [&](auto cuts) {
+      constexpr int C = cuts;
+      return T <= 2 * kThreads ? select_rows<2, C> : T <= 8 * kThreads ? select_rows<8, C> : select_rows<32, C>;
+    };
+    using std::integral_constant;
+    auto kern = F <= 2 ? of(integral_constant<int, 1>{}) : F <= 4 ? of(integral_constant<int, 3>{}) : of(integral_constant<int, 7>{});
+    hipLaunchKernelGGL(kern, dim3(B), dim3(kThreads), 0, stream, p);
   }
   return check_launch("ap_select_ranks");
 }

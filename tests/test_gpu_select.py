@@ -75,8 +75,8 @@ def test_select_group_shapes():
     check(mass[:, :3], (512, 256, 128, 64), (1, 2, 3, 4), 4, "fewer tokens than groups")
 
 
-# ---- long rows in small batches (24576 tokens and more in at most 32 rows, or any row beyond
-#      32768 tokens): the row is split over workgroups.  Uniform random values put at most a
+# ---- long rows: beyond 32768 tokens the row is split over workgroups (shorter ones here: the same
+#      inputs on one workgroup).  Uniform random values put at most a
 #      sixteenth of the keys on one leading digit, inside the candidate lists; coarse values and long
 #      runs of equal keys are what the lists cannot hold.
 def test_select_split_rows_random_and_odd_lengths():
@@ -136,3 +136,20 @@ def test_select_split_rows_give_way_to_one_workgroup_on_heavy_ties():
         r_ref, o_ref, i_ref = oracle.select_ranks(row[0], *QUART)
         assert (rank[0].cpu().numpy() == r_ref).all() and (idx[0].cpu().numpy() == i_ref).all()
         assert (off[0].cpu().numpy() == o_ref).all()
+
+
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("T", [64, 1023, 2048, 2049, 8192, 8193, 31745, 32768])
+def test_select_rows_in_registers(T, F):
+    """Sizes around the tokens per thread (2, 8, 32), whole and ragged blocks of 64, every number of groups that
+    has a kernel of its own and those that use the next one's: distinct values, ties in and between blocks at the
+    cuts, one value only, infinities, signed zeros and negative values, cuts that coincide."""
+    rng = wl.rng_for(29, T, F)
+    ranks, cum = tuple(64 * (F - g) for g in range(F)), tuple(range(1, F + 1))
+    mass = np.stack([
+        rng.random(T), np.floor(rng.random(T) * 3), np.zeros(T), np.repeat(rng.random((T + 99) // 100), 100)[:T],
+        rng.choice([np.inf, -np.inf, 0.0, -0.0, 1.0], T), rng.standard_normal(T), np.full(T, -2.5),
+    ]).astype(np.float32)
+    check(mass, ranks, cum, F, f"rows in registers T={T} F={F}")
+    if F > 2:
+        check(mass, ranks, (0,) + cum[1:-2] + (F, F), F, "nobody in the first group, coinciding cuts at the end")
