@@ -430,7 +430,9 @@ __device__ __forceinline__ P* uni_ptr(P* ptr) {
   const uint64_t v = (uint64_t)ptr;
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return (P*)(((uint64_t)hi << 32) | lo);
+  // a pointer made of an integer has no address space, and loads through it are flat ones, which count as LDS
+  // traffic too: say that it is device memory
+  return (P*)(__attribute__((address_space(1))) P*)(((uint64_t)hi << 32) | lo);
 }
 
 // ------------------------------------------------------------------------------------------
