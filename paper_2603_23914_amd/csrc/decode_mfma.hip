@@ -624,12 +624,15 @@ struct WaveCtx {
     const int32_t* bidx = uni_ptr(p.bucket_idx) + (size_t)b * T;
     const int32_t* rk_arr = uni_ptr(p.rank_k);
     const int32_t* rv_arr = uni_ptr(p.rank_v);
+    const int32_t* rk_any = rk_arr ? rk_arr : rv_arr;    // (one of them is there: no branch around the loads)
+    const int32_t* rv_any = rv_arr ? rv_arr : rk_arr;
     int off[9], ts[9];                     // group g: list positions off[g]..off[g+1], first tile ts[g]
-    off[0] = boff[0];
+    const int bo = boff[lane < F ? lane : F];            // all cuts in one load
+    off[0] = __builtin_amdgcn_readlane(bo, 0);
     ts[0] = 0;
 #pragma unroll
     for (int g2 = 0; g2 < 8; ++g2) {
-      off[g2 + 1] = g2 < F ? boff[g2 + 1] : off[g2];
+      off[g2 + 1] = __builtin_amdgcn_readlane(bo, g2 + 1);   // past F: the last cut again
       int c = off[g2 + 1] - off[g2];
       c = c < 0 ? 0 : c;
       ts[g2 + 1] = ts[g2] + ((c + kTile - 1) >> 5);
@@ -651,7 +654,7 @@ struct WaveCtx {
     }
     for (int e = threadIdx.x; e < ntl * kTile; e += 512) {
       const int i = e >> 5, l = e & 31;
-      const int isrc = ntl > 1 ? (int)(((int64_t)i * stride) % ntl) : 0;
+      const int isrc = ntl > 1 ? (int)((uint32_t)(i * stride) % (uint32_t)ntl) : 0;
       const int j = s + isrc * nsplit;
       int o0 = off[0], o1 = off[1], t0 = 0;
 #pragma unroll
@@ -669,8 +672,9 @@ struct WaveCtx {
       const unsigned long long hit = __ballot(Tv != T && tok == T - 1 && l < cnt);
       const uint32_t hit32 = (uint32_t)((lane & 32) ? hit >> 32 : hit);
       if (l == 0) {
-        int rk = rk_arr ? rk_arr[(size_t)b * T + tok] : r;
-        int rv = rv_arr ? rv_arr[(size_t)b * T + tok] : r;
+        const int rk_in = rk_any[(size_t)b * T + tok], rv_in = rv_any[(size_t)b * T + tok];
+        int rk = rk_arr ? rk_in : r;
+        int rv = rv_arr ? rv_in : r;
         rk = rk < 0 ? 0 : (rk < r ? rk : r);
         rv = rv < 0 ? 0 : (rv < r ? rv : r);
         meta[4 * i + 0] = cnt;
