@@ -58,7 +58,7 @@ constexpr int kMaxSmallTiles = 136;     // tiles a split can own with per-token 
 // list position) of its tiles into LDS; a wave then gathers a tile's rows through the index
 // list.  Columns at or beyond a tile's rank are not fetched (their loads are redirected to the
 // row's first chunk) and enter the products as zeros.
-template <class Tag, int MT, int NKS, bool RAGGED>
+template <class Tag, int MT, int NKS, bool RAGGED, bool LOGITS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AP_SMALL_WPE)))
 attn_small(const SmallParams p) {
   constexpr int Hp = MT * 16;
@@ -69,7 +69,6 @@ attn_small(const SmallParams p) {
   constexpr int CPR = R / 8;                         // 16-byte chunks per coefficient row
   constexpr int NV = CPR / 2;                        // value chunks per lane and tile (32 rows / 64 lanes)
   constexpr int kPitch = 2 * R + 16;                 // LDS row pitch: consecutive row quads on different banks
-  constexpr int kDepth = 1;                          // tiles in flight per wave (two measured no faster)
   __shared__ __attribute__((aligned(16))) char vt[kWaves][kTileBytesMax];
   __shared__ float st_m[kWaves][Hp], st_l[kWaves][Hp], st_p[kWaves][Hp];
   static_assert(kWaves * kTileBytesMax >= Hp * R * 4, "the combine buffer reuses the tile regions");
@@ -101,7 +100,11 @@ attn_small(const SmallParams p) {
       qh[ks][mt] = *(const u32x4_t*)qp;
       if (SPLIT) ql[ks][mt] = *(const u32x4_t*)(qp + (size_t)Hp * R);
     }
-  float* logits = p.scores ? p.scores + (size_t)b * H * p.T_cap : nullptr;
+  // logits out (LOGITS), through a buffer that drops what lies past its end: no lane has a branch, so the waits
+  // for the next tile's rows, which are asked for first, do not count the stores behind them in
+  __amdgpu_buffer_rsrc_t logits;
+  if constexpr (LOGITS)
+    logits = __builtin_amdgcn_make_buffer_rsrc(p.scores + (size_t)b * H * p.T_cap, 0, (int)((uint32_t)p.T_cap * (uint32_t)H * 4u), 0x00020000);
   const uint16_t* Cb = p.Ck + (size_t)b * p.T_cap * R + g * 8;
   const uint16_t* Vb = p.Cv + (size_t)b * p.T_cap * R;
   // tiles of this split (the same cuts as attn_partial's)
@@ -158,18 +161,16 @@ attn_small(const SmallParams p) {
   for (int k2 = 0; k2 < NV; ++k2) tokV[k2] = 0;
 #pragma unroll
   for (int e = 0; e < 8; ++e) tokS[e] = 0;
-  auto fetch_idx = [&](int lt) {                     // RAGGED: token indices of local tile lt for this lane
+  auto in_row = [&](int tok) { return tok < 0 ? 0 : (tok < T ? tok : T - 1); };
+  auto fetch_idx = [&](int lt) {                     // RAGGED: token indices of local tile lt for this lane, as listed
     const int cnt = __builtin_amdgcn_readfirstlane(meta[lt][0]);
     const int32_t* lst = bidx + __builtin_amdgcn_readfirstlane(meta[lt][3]);
-    auto at = [&](int slot) {
-      int tok = lst[slot < cnt ? slot : cnt - 1];    // slots beyond the tile repeat its last token (masked)
-      return tok < 0 ? 0 : (tok < T ? tok : T - 1);
-    };
+    auto at = [&](int slot) { return lst[slot < cnt ? slot : cnt - 1]; };   // beyond the tile its last token again (masked)
     tokA[0] = at(n);
     tokA[1] = at(16 + n);
 #pragma unroll
     for (int k2 = 0; k2 < NV; ++k2) tokV[k2] = at((lane + 64 * k2) / CPR);
-    if (logits) {
+    if constexpr (LOGITS) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) { tokS[e] = at(4 * g + e); tokS[4 + e] = at(16 + 4 * g + e); }
     }
@@ -199,7 +200,7 @@ attn_small(const SmallParams p) {
       const int rv = __builtin_amdgcn_readfirstlane(meta[lt][2]);
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
-        const uint16_t* crow = Cb + (size_t)tokA[tt] * R;
+        const uint16_t* crow = Cb + (size_t)in_row(tokA[tt]) * R;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks)
           A[ks][tt] = *(const u32x4_t*)(crow + (ks * 32 + g * 8 < rk ? ks * 32 : -g * 8));
@@ -207,8 +208,24 @@ attn_small(const SmallParams p) {
 #pragma unroll
       for (int k2 = 0; k2 < NV; ++k2) {
         const int cc = (lane + 64 * k2) % CPR;
-        Vr[k2] = *(const u32x4_t*)(Vb + (size_t)tokV[k2] * R + (cc * 8 < rv ? cc * 8 : 0));
+        Vr[k2] = *(const u32x4_t*)(Vb + (size_t)in_row(tokV[k2]) * R + (cc * 8 < rv ? cc * 8 : 0));
       }
+    }
+  };
+
+  // One tile in flight per wave (two measured no faster).  RAGGED: the indices of the tile after it are asked for
+  // behind its rows, a tile before they are needed; asked for in the tile that needs them, and with a branch per
+  // lane around the logits' stores (which the wait for the rows then counted in), 64 x 4225 tokens of rank 64
+  // with a quarter of the value rows whole and logits out took 29.5 us instead of 27.0.
+  int tokN[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  auto next_tile = [&](TileRegs& tr, int lt) {
+    load_tile(tr, lt);
+    if constexpr (RAGGED) {
+      if constexpr (LOGITS) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) tokN[e] = tokS[e];
+      }
+      if (lt + kWaves < ntl) fetch_idx(lt + kWaves);
     }
   };
 
@@ -232,10 +249,9 @@ attn_small(const SmallParams p) {
     const int rv = RAGGED ? __builtin_amdgcn_readfirstlane(meta[lt][2]) : R;
     const int slot_new = !RAGGED && p.defer_v ? T - 1 - base : -1;  // the deferred token's slot, if in [0, 32)
     int tokC[8];                                       // RAGGED: this tile's tokens of the lane's score slots
-    if constexpr (RAGGED) {
+    if constexpr (RAGGED && LOGITS) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) tokC[e] = tokS[e];
-      if (lt + kWaves < ntl) fetch_idx(lt + kWaves);   // indices of the next tile's rows, used below
+      for (int e = 0; e < 8; ++e) tokC[e] = in_row(tokN[e]);
     }
 #pragma unroll
     for (int k2 = 0; k2 < NV; ++k2) {
@@ -262,7 +278,7 @@ attn_small(const SmallParams p) {
           if (SPLIT) sp[mt][tt] = Mfma<Tag>::run(A[ks][tt], ql[ks][mt], sp[mt][tt]);
         }
       }
-    if (lt + kDepth * kWaves < ntl) load_tile(tr, lt + kDepth * kWaves);   // the registers are free again
+    if (lt + kWaves < ntl) next_tile(tr, lt + kWaves);   // the registers are free again
     // ---- softmax of head 16 mt + n: this lane holds tokens 4g+e (tt = 0) and 16+4g+e (tt = 1)
     u32x4_t Phi[MT], Plo[SPLIT ? MT : 1];
 #pragma unroll
@@ -273,16 +289,16 @@ attn_small(const SmallParams p) {
         s[e] = 4 * g + e < cnt ? sp[mt][0][e] : -INFINITY;
         s[4 + e] = 16 + 4 * g + e < cnt ? sp[mt][1][e] : -INFINITY;
       }
-      if (logits && mt * 16 + n < H) {
+      if constexpr (LOGITS) {
         // logits out, for importance tracking: [token][head], so the sixteen lanes of a row group
         // write 64 contiguous bytes per token, also when the tile's tokens are gathered
-        float* hcol = logits + (mt * 16 + n);
+        const int head = mt * 16 + n;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ta = RAGGED ? tokC[e] : base + 4 * g + e;
-          const int tb = RAGGED ? tokC[4 + e] : base + 16 + 4 * g + e;
-          if (4 * g + e < cnt) hcol[(size_t)ta * H] = s[e] * kLn2;
-          if (16 + 4 * g + e < cnt) hcol[(size_t)tb * H] = s[4 + e] * kLn2;
+        for (int e = 0; e < 8; ++e) {
+          const int slot = (e < 4 ? 0 : 12) + 4 * g + e;
+          const uint32_t at = ((uint32_t)(RAGGED ? tokC[e] : base + slot) * (uint32_t)H + (uint32_t)head) * 4u;
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, s[e] * kLn2), logits,
+                                                slot < cnt && head < H ? at : 0xffffffffu, 0, 0);
         }
       }
       float tmax = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
@@ -350,14 +366,10 @@ attn_small(const SmallParams p) {
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next tile is written
   };
-  TileRegs tr0, tr1;
+  TileRegs tr;
   if (RAGGED && wave < ntl) fetch_idx(wave);
-  if (wave < ntl) load_tile(tr0, wave);
-  if (kDepth > 1 && wave + kWaves < ntl) load_tile(tr1, wave + kWaves);
-  for (int lt = wave; lt < ntl; lt += kDepth * kWaves) {
-    process(tr0, lt);
-    if (kDepth > 1 && lt + kWaves < ntl) process(tr1, lt + kWaves);
-  }
+  if (wave < ntl) next_tile(tr, wave);
+  for (int lt = wave; lt < ntl; lt += kWaves) process(tr, lt);
 
   // ---- combine the four waves: statistics first, then the sums, one wave after the other
 #pragma unroll
@@ -440,8 +452,9 @@ ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, const void* Ck, con
   const bool timed = prof_events(&ev0, &ev1);          // the coefficient-streaming kernel of this call
 #define AP_AS3(TAG, M, N, RG)                                                                          \
   do {                                                                                                 \
-    if (timed) hipExtLaunchKernelGGL((attn_small<TAG, M, N, RG>), dim3(nb), dim3(256), 0, stream, ev0, ev1, 0u, p); \
-    else hipLaunchKernelGGL((attn_small<TAG, M, N, RG>), dim3(nb), dim3(256), 0, stream, p);           \
+    auto kern = scores ? attn_small<TAG, M, N, RG, true> : attn_small<TAG, M, N, RG, false>;           \
+    if (timed) hipExtLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, stream, ev0, ev1, 0u, p);           \
+    else hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, stream, p);                                  \
   } while (0)
 #define AP_AS2(TAG, M, N)                                                                              \
   do { if (ragged) AP_AS3(TAG, M, N, true); else AP_AS3(TAG, M, N, false); } while (0)

@@ -1745,7 +1745,9 @@ ap_status run_decode(const DecodeArgs& a) {
   // (with per-token ranks only on the two-role kernel, whose gathered tiles know the newest token)
   const bool one_pass_v = a.v_new && a.T >= 2 && Hkv == a.H && v_long &&
                           !(ragged && attn_small_applies(a.H, a.r, a.T, false));
-  const bool small = !quant && attn_small_applies(a.H, a.r, a.T, one_pass_v);
+  // (attn_small reaches a sequence's logits by 32-bit offsets)
+  const bool small = !quant && attn_small_applies(a.H, a.r, a.T, one_pass_v) &&
+                     (!a.scores || (int64_t)a.T_cap * a.H * 4 < (1ll << 32));
   int* pnew_split = (int*)((char*)a.workspace + ws_layout(a.B, a.H, a.d, a.T, a.r).pn + (size_t)a.B * a.H * 4);
   const int S = choose_nsplit(a.B, a.T);     // the same count for both kernels (twice the splits for
                                              // the small-rank kernel measured slower)
