@@ -1118,9 +1118,11 @@ ap_status launch_update_importance(const float* scores, const float* lse, float*
 // workgroup; 24576: 47 and 27; 32 rows of 32768: 70 and 35).  Longer rows would be re-read from memory seven
 // times (131072 tokens: 61-95 us split against 650).
 static bool split_applies(int T) { return T > kRowMax; }
+// What ap_select_ranks asks for, whether it then uses it or not: a call that was refused for its workspace stays
+// refused.  24576 tokens in up to 32 rows were split too before one workgroup held their keys.
 size_t select_workspace(int B, int T, int) {
-  // without the split every intermediate lives in LDS and registers
-  return split_applies(T) ? 256 + (size_t)B * split_layout(T, split_per(T)).stride * 4 : 256;
+  const bool room = split_applies(T) || (T >= 24576 && B <= 32);
+  return room ? 256 + (size_t)B * split_layout(T, split_per(T)).stride * 4 : 256;
 }
 
 ap_status launch_select_ranks(const float* mass, int B, int T, int F, const int32_t* group_rank,

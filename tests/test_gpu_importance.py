@@ -66,6 +66,41 @@ def test_scores_give_the_attention_weights(dtype, B, H, d, r, T):
     assert torch.equal(out, out2)
 
 
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("dtype,B,H,r,T", [("bf16", 2, 40, 64, 301), ("f16", 1, 5, 128, 64), ("bf16", 1, 32, 128, 33),
+                                           ("f16", 2, 64, 64, 1057)])
+def test_scores_at_small_ranks(dtype, B, H, r, T, ragged):
+    """Ranks 64 and 128, also with per-token ranks: heads that end inside a tile of 16, tokens inside one of 32,
+    fewer tiles than waves and more.  Every attended token's logits are there, nothing behind them is touched,
+    and the output is the call's without them, bit for bit."""
+    from paper_2603_23914_amd import binding as ap
+    d = 64
+    case = wl.decode_case(dtype, B, H, d, r, T, steps=0, seed=35, append=False)
+    q = wl.step_query(case, 0)
+    print(f"scores at small ranks {dtype} B={B} H={H} r={r} T={T} ragged={ragged}", flush=True)
+    dq, dCk, dCv, dBk, dBv = (to_dev(x, dtype) for x in (q, case.Ck, case.Cv, case.Bk, case.Bv))
+    T_cap = case.Ck.shape[1]
+    out, out2 = (torch.empty((B, H, d), dtype=torch.float32, device="cuda") for _ in range(2))
+    lse = torch.empty((B, H), dtype=torch.float32, device="cuda")
+    scores = torch.full((B, T_cap, H), 123.0, dtype=torch.float32, device="cuda")
+    ws = workspace(ap.ap_decode_workspace_bytes(B, H, d, T, r, ap._DT[TORCH_DT[dtype]]))
+    kw, rank = {}, None
+    if ragged:
+        mass = wl.rng_for(35, T).random((B, T)).astype(np.float32)
+        rank, off, idx = (torch.empty((B, n), dtype=torch.int32, device="cuda") for n in (T, 3, T))
+        ap.ap_select_ranks(torch.from_numpy(mass).cuda(), (r, 16), (1, 4), 4, rank, off, idx,
+                           workspace(ap.ap_select_workspace_bytes(B, T, 2)))
+        kw = dict(rank_k=rank, rank_v=rank, bucket_off=off, bucket_idx=idx, F=2)
+    ap.ap_decode_attn(dq, dCk, dCv, dBk, dBv, out, ws, T=T, sm_scale=1.0 / math.sqrt(d), lse=lse, scores=scores, **kw)
+    ap.ap_decode_attn(dq, dCk, dCv, dBk, dBv, out2, ws, T=T, sm_scale=1.0 / math.sqrt(d), **kw)
+    torch.cuda.synchronize()
+    A = np.exp(to_host64(scores)[:, :T, :].transpose(0, 2, 1) - to_host64(lse)[:, :, None])
+    ref = oracle_probs(dtype, q, case.Ck, case.Bk, T, None if rank is None else rank.cpu().numpy())
+    assert np.abs(A - ref).max() <= PROB_TOL * ref.max()
+    assert (scores[:, T:] == 123.0).all()
+    assert torch.equal(out, out2)
+
+
 @pytest.mark.parametrize("B,H,T,T_cap,stride,alpha", [(3, 40, 1000, 1024, 1100, 0.9), (1, 7, 5, 5, 5, 0.0),
                                                       (2, 32, 257, 300, 257, 1.0), (2, 8, 4224, 4224, 4224, 0.5),
                                                       (1, 256, 200, 200, 200, 0.3), (1, 260, 130, 131, 130, 0.3)])
