@@ -843,8 +843,7 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, P
     return p == 0 ? 0 : p == 15 ? 31 : p == 16 ? 1 : p < 15 ? p + 1 : p - 1;
   };
   const int r0 = moved(I) * PITCH, r1 = moved(16 + I) * PITCH, c0 = moved(n), c1 = moved(16 + n);
-#pragma unroll 2
-  for (int s = 0; s <= turns; ++s) {
+  for (int s = 0; s <= turns; ++s) {                    // (by twos, with constant buffers: the same time)
     if (w < 4) {
       if (s < turns) {
         const float* cur = gm[s & 1];
