@@ -171,7 +171,7 @@ bool shared_project_applies(int B, int H, int H_kv, int d, int r, bool appends);
 ap_status launch_shared_project(ap_dtype dt, const void* Bk, const void* Bv, const void* k_new, const void* v_new,
                                 const void* q, void* Ck, void* Cv, void* Qp, int B, int H, int H_kv, int Hp, int d,
                                 int r, int row, int T_cap, float scale, hipStream_t stream);
-bool shared_expand_applies(int B, int H, int d, int r, int S);
+bool shared_expand_applies(ap_dtype dt, int B, int H, int d, int r, int S);
 ap_status launch_shared_expand(ap_dtype dt, bool out_f32, const float* part_ml, const float* part_U, const void* Bv,
                                void* out, float* lse, int B, int H, int H_kv, int d, int r, int nsplit, hipStream_t stream);
 ap_status launch_fold_heads(ap_dtype dt, const void* Bk, int64_t bstride, const void* q, void* Qp, int B,

@@ -1845,7 +1845,7 @@ ap_status run_decode(const DecodeArgs& a) {
                               (void*)a.Cv, ml, U, (const float*)(ws + wl.pn),
                               !small && S_exp > 1 ? pnew_split : nullptr, a.rank_v, (float*)(ws + wl.po),
                               a.out, a.lse, a.B, a.H, a.d, a.r, a.T, a.T_cap, S_exp, a.stream);
-  else if (shared && shared_expand_applies(a.B, a.H, a.d, a.r, S_exp))
+  else if (shared && shared_expand_applies(a.dt, a.B, a.H, a.d, a.r, S_exp))
     st = launch_shared_expand(a.dt, a.dt_out == AP_F32, ml, U, a.Bv, a.out, a.lse, a.B, a.H, Hkv, a.d, a.r, S_exp, a.stream);
   else
     st = launch_merge_expand(a.dt, a.dt_out == AP_F32, ml, U, a.Bv, a.basis_batch_stride, a.out, a.lse,

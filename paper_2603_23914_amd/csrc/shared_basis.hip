@@ -7,8 +7,9 @@
 //                    in one launch
 //   shared_expand    out[b, h, :] = (sum_s w_s U_s[b, h, :] / sum_s w_s l_s) . Bv[:, slice of h]
 //
-// Products of two 16-bit values are exact in the matrix cores' fp32 sums; the expansion multiplies fp32
-// sums with fp32 copies of the basis (v_mfma_f32_16x16x4_f32), so nothing is rounded that was not before.
+// Products of two 16-bit values are exact in the matrix cores' fp32 sums.  The expansion multiplies the merged fp32
+// sums with the basis: fp16 in fp32 products (v_mfma_f32_16x16x4_f32); bfloat16 with the sums cut into three
+// bfloat16 values, whose products are exact, so the result is that of fp32 products.
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
 #include "mfma_ops.hpp"
@@ -202,38 +203,43 @@ struct SharedExpandParams {
   int B, H, G, HD, r, S, units;
 };
 
-// Two fp32 values as sums of three 16-bit values each.  bfloat16 (8 bits each, the exponents of fp32) holds all
-// 24 bits; for fp16 the caller scales by a power of two first.  What is not finite stays in the first part.
-template <class Tag>
+// Two fp32 values as sums of three bfloat16 values each (8 bits each, the exponents of fp32).  What is not finite
+// stays in the first part.
 __device__ __forceinline__ void split3(float x, float y, uint32_t (&v)[3]) {
-  v[0] = cvt_pack(x, y, Tag{});
-  const float hx = lo_to_f32(v[0], Tag{}), hy = hi_to_f32(v[0], Tag{});
+  constexpr BF16Tag tag{};
+  v[0] = cvt_pack(x, y, tag);
+  const float hx = lo_to_f32(v[0], tag), hy = hi_to_f32(v[0], tag);
   const float rx = __builtin_isfinite(hx) ? x - hx : 0.f, ry = __builtin_isfinite(hy) ? y - hy : 0.f;
-  v[1] = cvt_pack(rx, ry, Tag{});
-  v[2] = cvt_pack(rx - lo_to_f32(v[1], Tag{}), ry - hi_to_f32(v[1], Tag{}), Tag{});
+  v[1] = cvt_pack(rx, ry, tag);
+  v[2] = cvt_pack(rx - lo_to_f32(v[1], tag), ry - hi_to_f32(v[1], tag), tag);
 }
 
 // A workgroup (512 threads) merges and expands 16 (sequence, query head) columns of one key/value head.
-// The merge (32 lanes a column) leaves L U*, as three 16-bit parts, in LDS; the waves then take every eighth
-// group of 32 basis rows.  A lane loads VEC = d / 16 consecutive elements of eight rows and turns them into the
-// operands of VEC products with byte permutes: product i holds the hidden columns VEC a + i, so a lane ends with
-// VEC consecutive columns per accumulator row.  The parts' products are exact and summed in fp32, smallest first:
-// the result is that of fp32 products (v_mfma_f32_16x16x4_f32 took 13300 cycles where this takes 4700).  64 x 640,
-// 40 heads, four splits: 12.7 us (26.3 with a workgroup per head and sequence), most of it loads on their way.
+// The merge (32 lanes a column) leaves L U* in LDS; the waves then take every eighth group of 32 basis rows.
+// A lane loads VEC = d / 16 consecutive elements of eight rows: product i holds the hidden columns VEC a + i, so a
+// lane ends with VEC consecutive columns per accumulator row.
+//   bfloat16  L U* as three 16-bit parts, eight rows of an element the operand of one product (byte permutes); the
+//             parts' products are exact and summed in fp32, smallest first
+//   fp16      fp32 products (v_mfma_f32_16x16x4_f32), four rows each: fp16 has too few exponents for parts of a
+//             sum that is small beside its column's largest
+// 64 x 640, 40 heads, four splits: bfloat16 12.3 us (26.3 with a workgroup per head and sequence), most of it loads on
+// their way; fp16 15.9 us (12.1 with three fp16 parts, which were 7e-4 off where 2^-30 of the largest was all).
 template <class Tag, bool OUT_F32, int VEC>
 __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p) {
   constexpr int d = VEC * 16, DW = VEC / 2;                   // DW dwords of a row per lane
   constexpr int kChunks = 5, kU = 4;                          // 4 x 32 columns a chunk, r <= 640; splits at a time
-  constexpr bool kScale = __is_same(Tag, F16Tag);
+  constexpr bool kParts = __is_same(Tag, BF16Tag);
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int u = run_per_xcd(blockIdx.x, p.units);
   if (u >= p.units) return;
   const int S = p.S, H = p.H, r = p.r, G = p.G, N = p.B * G, nct = (N + 15) >> 4;
-  const int kvh = u / nct, ct = u - kvh * nct, pitch = r + 8, sp = S + 1;
-  uint16_t* ustar = (uint16_t*)smem;                          // [3][16][pitch]
-  float* wgt = smem + 3 * 16 * pitch / 2;                     // [16][sp] weights, then their sum
+  const int kvh = u / nct, ct = u - kvh * nct, sp = S + 1;
+  const int pitch = kParts ? r + 8 : r + 4;
+  uint16_t* parts = (uint16_t*)smem;                          // [3][16][pitch]
+  float* ustar = smem;                                        // fp16: [16][pitch]
+  float* wgt = smem + (kParts ? 3 * 16 * pitch / 2 : 16 * pitch);   // [16][sp] weights, then their sum
   float* sums = smem;                                         // [4][16][d + 4], once U* is used up
   // ---- this thread's column; the first splits' sums
   const int c = tid >> 5, ci = tid & 31;
@@ -308,29 +314,18 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
       }
     }
   }
-  float up = 1.f, down = 1.f;
-  if (kScale) {                                               // the column's largest element into [2^14, 2^15)
-    float big = 0.f;
-#pragma unroll
-    for (int k = 0; k < kChunks; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) big = fmaxf(big, fabsf(ua[k][e]));
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) big = fmaxf(big, __shfl_xor(big, o));
-    int e = (int)(__builtin_bit_cast(uint32_t, big) >> 23) - 127;
-    e = e < -100 ? -100 : e;
-    up = __builtin_bit_cast(float, (uint32_t)(14 - e + 127) << 23);
-    down = __builtin_bit_cast(float, (uint32_t)(e - 14 + 127) << 23);
-  }
 #pragma unroll
   for (int k = 0; k < kChunks; ++k) {
     if (128 * k + 4 * ci < r) {
-      uint32_t v[2][3];
+      if constexpr (kParts) {
+        uint32_t v[2][3];
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
-        split3<Tag>(kScale ? ua[k][2 * e] * up : ua[k][2 * e], kScale ? ua[k][2 * e + 1] * up : ua[k][2 * e + 1], v[e]);
+        for (int e = 0; e < 2; ++e) split3(ua[k][2 * e], ua[k][2 * e + 1], v[e]);
 #pragma unroll
-      for (int q = 0; q < 3; ++q) *(u32x2_t*)(ustar + (q * 16 + c) * pitch + 128 * k + 4 * ci) = u32x2_t{v[0][q], v[1][q]};
+        for (int q = 0; q < 3; ++q) *(u32x2_t*)(parts + (q * 16 + c) * pitch + 128 * k + 4 * ci) = u32x2_t{v[0][q], v[1][q]};
+      } else {
+        *(f32x4_t*)(ustar + c * pitch + 128 * k + 4 * ci) = ua[k];
+      }
     }
   }
   lds_barrier();
@@ -338,23 +333,46 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
   f32x4_t acc[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  constexpr int kWide = VEC < 4 ? VEC : 4;                    // products in flight side by side
   auto use_group = [&](const uint32_t (&src)[8][DW], int gi) {
-    u32x4_t uq[3];
+    if constexpr (kParts) {
+      constexpr int kWide = VEC < 4 ? VEC : 4;                // products in flight side by side
+      u32x4_t uq[3];
 #pragma unroll
-    for (int q = 0; q < 3; ++q) uq[q] = *(const u32x4_t*)(ustar + (q * 16 + n) * pitch + gi * 32 + 8 * g);
+      for (int q = 0; q < 3; ++q) uq[q] = *(const u32x4_t*)(parts + (q * 16 + n) * pitch + gi * 32 + 8 * g);
 #pragma unroll
-    for (int i0 = 0; i0 < VEC; i0 += kWide) {
-      u32x4_t a[kWide];
+      for (int i0 = 0; i0 < VEC; i0 += kWide) {
+        u32x4_t a[kWide];
 #pragma unroll
-      for (int i = 0; i < kWide; ++i)
+        for (int i = 0; i < kWide; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          a[i][e] = __builtin_amdgcn_perm(src[2 * e + 1][(i0 + i) >> 1], src[2 * e][(i0 + i) >> 1], (i & 1) ? 0x07060302 : 0x05040100);
+          for (int e = 0; e < 4; ++e)
+            a[i][e] = __builtin_amdgcn_perm(src[2 * e + 1][(i0 + i) >> 1], src[2 * e][(i0 + i) >> 1], (i & 1) ? 0x07060302 : 0x05040100);
 #pragma unroll
-      for (int q = 2; q >= 0; --q)
+        for (int q = 2; q >= 0; --q)
 #pragma unroll
-        for (int i = 0; i < kWide; ++i) acc[i0 + i] = Mfma<Tag>::run(a[i], uq[q], acc[i0 + i]);
+          for (int i = 0; i < kWide; ++i) acc[i0 + i] = Mfma<Tag>::run(a[i], uq[q], acc[i0 + i]);
+      }
+    } else {
+      float uf[8];
+#pragma unroll
+      for (int t = 0; t < 8; t += 4) {
+        const f32x4_t v = *(const f32x4_t*)(ustar + n * pitch + gi * 32 + 8 * g + t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) uf[t + e] = v[e];
+      }
+      f32x4_t part[VEC];                                      // a group's sum by itself: shorter chains of roundings
+#pragma unroll
+      for (int t = 0; t < 8; ++t)                             // rows 8 g' + t, g' = 0 .. 3
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const float x = i & 1 ? hi_to_f32(src[t][i >> 1], Tag{}) : lo_to_f32(src[t][i >> 1], Tag{});
+          const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+          part[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, uf[t], t ? part[i] : zero, 0, 0, 0);
+        }
+#pragma unroll
+      for (int i = 0; i < VEC; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][e] += part[i][e];
     }
   };
   for (int gi = w; gi < groups; gi += 8 * kAhead) {
@@ -392,7 +410,7 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
       for (int e = 0; e < 4; ++e) s[e] += t[e];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] = (kScale ? s[e] * down : s[e]) / L;
+    for (int e = 0; e < 4; ++e) s[e] /= L;
     const size_t o = ((size_t)b * H + h) * d + 4 * e4;
     if (OUT_F32) *(f32x4_t*)((float*)p.out + o) = s;
     else *(u32x2_t*)((uint16_t*)p.out + o) = u32x2_t{pack2(s[0], s[1], Tag{}), pack2(s[2], s[3], Tag{})};
@@ -417,13 +435,17 @@ void launch_project(const ProjectParams& p, int d, int blocks, hipStream_t strea
 template <class Tag, bool OUT_F32>
 void launch_expand(const SharedExpandParams& p, int d, hipStream_t stream) {
   const dim3 grid((p.units + 7) / 8 * 8);
-  const size_t merge = ((size_t)3 * 16 * (p.r + 8) / 2 + 16 * (p.S + 1)) * 4, sums = (size_t)4 * 16 * (d + 4) * 4;
+  const size_t u = __is_same(Tag, BF16Tag) ? (size_t)3 * 16 * (p.r + 8) / 2 : (size_t)16 * (p.r + 4);
+  const size_t merge = (u + 16 * (p.S + 1)) * 4, sums = (size_t)4 * 16 * (d + 4) * 4;
   const size_t lds = merge > sums ? merge : sums;
   switch (d) {
     case 32: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 2>), grid, dim3(512), lds, stream, p); break;
     case 64: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 4>), grid, dim3(512), lds, stream, p); break;
     case 128: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 8>), grid, dim3(512), lds, stream, p); break;
-    default: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 16>), grid, dim3(512), lds, stream, p); break;
+    default:
+      if constexpr (__is_same(Tag, BF16Tag))
+        hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 16>), grid, dim3(512), lds, stream, p);
+      break;
   }
 }
 
@@ -443,10 +465,13 @@ bool shared_project_applies(int B, int H, int H_kv, int d, int r, bool appends) 
 }
 // The expansion's merge is longer than that of a workgroup per head (all columns' sums pass through B H / 16
 // workgroups, four splits at a time): few splits and much to expand.  Us a call there / here: 64 x 256, 64 heads
-// 43.0 / 38.3, 64 x 640, 40 heads 68 / 55, but 48 x 256, 40 heads 34.0 / 34.3, 24 x 640, 32 / 8 heads, ten splits
-// 50.3 / 54.3.
-bool shared_expand_applies(int B, int H, int d, int r, int S) {
-  return S <= 8 && (int64_t)B * r * H * d * 2 >= (192ll << 20);
+// 34.4 / 29.8, 64 x 640, 64 heads of 64 60.5 / 54.3, but 48 x 256, 40 heads 27.2 / 28.0, 40 x 320, 32 heads of 256
+// 29.5 / 30.8.  The fp32 products of fp16 are worth it with one round of splits and heads up to 128: 64 x 256, 64
+// heads 32.9 / 30.4, 64 x 448, 32 heads 33.0 / 31.9, but with six and eight splits 40 x 640, 32 heads 32.1 / 35.7 and
+// 32 x 640, 40 heads 35.6 / 38.9, with heads of 256 48 x 320, 32 heads 28.1 / 33.9.
+bool shared_expand_applies(ap_dtype dt, int B, int H, int d, int r, int S) {
+  if (dt == AP_F16 && (S > 4 || d > 128)) return false;
+  return S <= 8 && (int64_t)B * r * H * d * 2 >= (d > 128 ? 224ll : 192ll) << 20;
 }
 
 // Fold of q (and, with k_new and v_new, both appended rows) on shared bases, r % 64 == 0.

@@ -77,3 +77,39 @@ def test_shared_basis(dtype, B, H, Hkv, d, r, T, scale, step):
             for x, basis, c in ((kn, Bk, ck), (vn, Bv, cv)):
                 row = oracle.compact(P(x[b:b + 1]), P(basis))[0]
                 assert np.abs(P(c[b, T - 1]) - row).max() <= 2 * rnd * np.abs(row).max() + sub
+
+
+def expansion_inputs(dtype, B, H, d, r, T, seed):
+    """Inputs of a shared expansion with all logits zero: the merged sums are the tokens' mean."""
+    dt, HD = TORCH_DT[dtype], H * d
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    N = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q = torch.zeros((B, H, d), dtype=dt, device="cuda")
+    return q, N(B, T, r).to(dt), N(B, T, r), (N(r, HD) / 8).to(dt), (N(r, HD) / 8).to(dt)
+
+
+def written_out(B, *bases):
+    return [x[None].expand(B, *x.shape).contiguous() for x in bases]
+
+
+@pytest.mark.parametrize("dtype,large,small,live", [("f16", 1.0e4, 1.0e-5, 4), ("f16", 1.0e4, 1.0e-3, 624),
+                                                    ("bf16", 1.0e30, 1.0e-6, 4)])
+def test_shared_expansion_of_small_sums(dtype, large, small, live):
+    """Sixteen ranks hold large values that half of the hidden columns do not see: there the output is made of the
+    `live` ranks behind them, 2^-20 to 2^-30 of their row's largest and less.  Either expansion is a sum of 640 fp32
+    products of a mean of three: at most (640 + 4) 2^-24 of their magnitudes away."""
+    from paper_2603_23914_amd import binding as ap
+    B, H, d, r, T = 65, 48, 64, 640, 3
+    print(f"small sums {dtype} {large} {small} {live}", flush=True)
+    q, Ck, Cv, Bk, Bv = expansion_inputs(dtype, B, H, d, r, T, 77)
+    Cv[:, :, :16] *= large
+    Cv[:, :, 16:] *= small
+    Cv[:, :, 16 + live:] = 0.0
+    Cv = Cv.to(Bv.dtype)
+    Bv[:16, 1::2] = 0.0
+    c, b = to_host64(Cv), to_host64(Bv)
+    ref, mag = c.mean(axis=1) @ b, np.abs(c).mean(axis=1) @ np.abs(b)
+    for bases in ((Bk, Bv), written_out(B, Bk, Bv)):
+        out = run(ap, False, q, None, None, Ck, Cv, *bases, T, torch.float32)[0]
+        assert (np.abs(to_host64(out).reshape(B, H * d) - ref) <= 644 * 2.0 ** -24 * mag).all()
