@@ -203,26 +203,31 @@ struct SharedExpandParams {
   int B, H, G, HD, r, S, units;
 };
 
-// Two fp32 values as sums of three bfloat16 values each (8 bits each, the exponents of fp32).  What is not finite
-// stays in the first part.
+// Two fp32 values as sums of three bfloat16 values each, eight bits at a time from the top: exact from 2^-100 on, and
+// never above the value itself (rounded, a sum between the largest bfloat16 and the largest fp32 would be infinite).
+// What is not finite stays in the first part.
 __device__ __forceinline__ void split3(float x, float y, uint32_t (&v)[3]) {
-  constexpr BF16Tag tag{};
-  v[0] = cvt_pack(x, y, tag);
-  const float hx = lo_to_f32(v[0], tag), hy = hi_to_f32(v[0], tag);
-  const float rx = __builtin_isfinite(hx) ? x - hx : 0.f, ry = __builtin_isfinite(hy) ? y - hy : 0.f;
-  v[1] = cvt_pack(rx, ry, tag);
-  v[2] = cvt_pack(rx - lo_to_f32(v[1], tag), ry - hi_to_f32(v[1], tag), tag);
+  auto top = [](float f) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, f) & 0xffff0000u); };
+  auto pack = [](float lo, float hi) {
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo), 0x07060302);
+  };
+  const float rx = __builtin_isfinite(x) ? x - top(x) : 0.f, ry = __builtin_isfinite(y) ? y - top(y) : 0.f;
+  v[0] = pack(x, y);
+  v[1] = pack(rx, ry);
+  v[2] = pack(rx - top(rx), ry - top(ry));
 }
 
 // A workgroup (512 threads) merges and expands 16 (sequence, query head) columns of one key/value head.
-// The merge (32 lanes a column) leaves L U* in LDS; the waves then take every eighth group of 32 basis rows.
-// A lane loads VEC = d / 16 consecutive elements of eight rows: product i holds the hidden columns VEC a + i, so a
+// The merge (32 lanes a column) leaves U* (times a half to one) in LDS; the waves then take every eighth group of 32
+// basis rows.  A lane loads VEC = d / 16 consecutive elements of eight rows: product i holds the hidden columns VEC a + i, so a
 // lane ends with VEC consecutive columns per accumulator row.
-//   bfloat16  L U* as three 16-bit parts, eight rows of an element the operand of one product (byte permutes); the
-//             parts' products are exact and summed in fp32, smallest first
+//   bfloat16  U* as three 16-bit parts, eight rows of an element the operand of one product (byte permutes); the
+//             parts' products are exact and summed in fp32, smallest first.  With an infinite basis element the parts
+//             could cancel, and parts of a sum below 2^-100 lose bits: a wave that ends with something that is not
+//             finite, or a workgroup with such sums, does the fp32 products
 //   fp16      fp32 products (v_mfma_f32_16x16x4_f32), four rows each: fp16 has too few exponents for parts of a
 //             sum that is small beside its column's largest
-// 64 x 640, 40 heads, four splits: bfloat16 12.3 us (26.3 with a workgroup per head and sequence), most of it loads on
+// 64 x 640, 40 heads, four splits: bfloat16 13.0 us (26.3 with a workgroup per head and sequence), most of it loads on
 // their way; fp16 15.9 us (12.1 with three fp16 parts, which were 7e-4 off where 2^-30 of the largest was all).
 template <class Tag, bool OUT_F32, int VEC>
 __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p) {
@@ -236,10 +241,11 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
   if (u >= p.units) return;
   const int S = p.S, H = p.H, r = p.r, G = p.G, N = p.B * G, nct = (N + 15) >> 4;
   const int kvh = u / nct, ct = u - kvh * nct, sp = S + 1;
-  const int pitch = kParts ? r + 8 : r + 4;
-  uint16_t* parts = (uint16_t*)smem;                          // [3][16][pitch]
-  float* ustar = smem;                                        // fp16: [16][pitch]
-  float* wgt = smem + (kParts ? 3 * 16 * pitch / 2 : 16 * pitch);   // [16][sp] weights, then their sum
+  const int pitch = r + 8, pitch32 = r + 4;
+  uint16_t* parts = (uint16_t*)smem;                          // bfloat16: U* as [3][16][pitch]
+  float* ustar = smem;                                        // fp16: as [16][pitch32]
+  float* wgt = smem + (kParts ? 3 * 16 * pitch / 2 : 16 * pitch32);   // [16][sp] weights
+  int* flags = (int*)(wgt + 16 * sp);                         // bfloat16: per wave, sums too small for parts
   float* sums = smem;                                         // [4][16][d + 4], once U* is used up
   // ---- this thread's column; the first splits' sums
   const int c = tid >> 5, ci = tid & 31;
@@ -297,7 +303,9 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
   if (ci + 32 < S) wgt[c * sp + ci + 32] = w1;
   if (p.lse && ci == 0 && ct * 16 + c < N) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
   __builtin_amdgcn_wave_barrier();                            // a column's weights stay within its half wave
-  // ---- sum_s w_s U_s (the division by L is left to the results, which are fewer)
+  // ---- sum_s w_s U_s, divided by the power of two that brings L to [0.5, 1): with the division by what is left of L
+  // left to the results, which are fewer, nothing on the way is larger than with U* itself
+  const int le = __builtin_amdgcn_frexp_expf(L);
   f32x4_t ua[kChunks];
 #pragma unroll
   for (int k = 0; k < kChunks; ++k) ua[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -314,25 +322,79 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
       }
     }
   }
+  bool tiny = false;
 #pragma unroll
   for (int k = 0; k < kChunks; ++k) {
     if (128 * k + 4 * ci < r) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ua[k][e] = ldexpf(ua[k][e], -le);
       if constexpr (kParts) {
         uint32_t v[2][3];
 #pragma unroll
         for (int e = 0; e < 2; ++e) split3(ua[k][2 * e], ua[k][2 * e + 1], v[e]);
 #pragma unroll
         for (int q = 0; q < 3; ++q) *(u32x2_t*)(parts + (q * 16 + c) * pitch + 128 * k + 4 * ci) = u32x2_t{v[0][q], v[1][q]};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tiny |= ua[k][e] != 0.f && fabsf(ua[k][e]) < 0x1p-100f;
       } else {
-        *(f32x4_t*)(ustar + c * pitch + 128 * k + 4 * ci) = ua[k];
+        *(f32x4_t*)(ustar + c * pitch32 + 128 * k + 4 * ci) = ua[k];
       }
     }
   }
-  lds_barrier();
+  int whole = 0;                                              // bfloat16: U* is in LDS as fp32 after all
+  if constexpr (kParts) {
+    const bool any = __any(tiny);
+    if (lane == 0) flags[w] = any;
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) whole |= flags[k];
+    if (whole) {
+#pragma unroll
+      for (int k = 0; k < kChunks; ++k)
+        if (128 * k + 4 * ci < r) *(f32x4_t*)(ustar + c * pitch32 + 128 * k + 4 * ci) = ua[k];
+    }
+  }
+  if (!kParts || whole) lds_barrier();
   // ---- expansion
   f32x4_t acc[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto use_group_f32 = [&](const uint32_t (&src)[8][DW], int gi) {
+    float uf[8];                                              // of rows 8 g + t
+    if (kParts && !whole) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) uf[t] = 0.f;
+#pragma unroll
+      for (int q = 2; q >= 0; --q) {
+        const u32x4_t v = *(const u32x4_t*)(parts + (q * 16 + n) * pitch + gi * 32 + 8 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          uf[2 * e] += lo_to_f32(v[e], Tag{});
+          uf[2 * e + 1] += hi_to_f32(v[e], Tag{});
+        }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; t += 4) {
+        const f32x4_t v = *(const f32x4_t*)(ustar + n * pitch32 + gi * 32 + 8 * g + t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) uf[t + e] = v[e];
+      }
+    }
+    f32x4_t part[VEC];                                        // a group's sum by itself: shorter chains of roundings
+#pragma unroll
+    for (int t = 0; t < 8; ++t)                               // rows 8 g' + t, g' = 0 .. 3
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) {
+        const float x = i & 1 ? hi_to_f32(src[t][i >> 1], Tag{}) : lo_to_f32(src[t][i >> 1], Tag{});
+        const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+        part[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, uf[t], t ? part[i] : zero, 0, 0, 0);
+      }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][e] += part[i][e];
+  };
   auto use_group = [&](const uint32_t (&src)[8][DW], int gi) {
     if constexpr (kParts) {
       constexpr int kWide = VEC < 4 ? VEC : 4;                // products in flight side by side
@@ -353,33 +415,29 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
           for (int i = 0; i < kWide; ++i) acc[i0 + i] = Mfma<Tag>::run(a[i], uq[q], acc[i0 + i]);
       }
     } else {
-      float uf[8];
-#pragma unroll
-      for (int t = 0; t < 8; t += 4) {
-        const f32x4_t v = *(const f32x4_t*)(ustar + n * pitch + gi * 32 + 8 * g + t);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) uf[t + e] = v[e];
-      }
-      f32x4_t part[VEC];                                      // a group's sum by itself: shorter chains of roundings
-#pragma unroll
-      for (int t = 0; t < 8; ++t)                             // rows 8 g' + t, g' = 0 .. 3
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-          const float x = i & 1 ? hi_to_f32(src[t][i >> 1], Tag{}) : lo_to_f32(src[t][i >> 1], Tag{});
-          const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-          part[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, uf[t], t ? part[i] : zero, 0, 0, 0);
-        }
-#pragma unroll
-      for (int i = 0; i < VEC; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][e] += part[i][e];
+      use_group_f32(src, gi);
     }
   };
-  for (int gi = w; gi < groups; gi += 8 * kAhead) {
+  for (int gi = whole ? groups : w; gi < groups; gi += 8 * kAhead) {
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       if (gi + 8 * k < groups) use_group(bv[k], gi + 8 * k);
       if (gi + 8 * (k + kAhead) < groups) load_group(bv[k], gi + 8 * (k + kAhead));
+    }
+  }
+  if constexpr (kParts) {
+    int again = whole;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) again |= !__builtin_isfinite(acc[i][e]);
+    if (__any(again)) {
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int gi = w; gi < groups; gi += 8) {
+        load_group(bv[0], gi);
+        use_group_f32(bv[0], gi);
+      }
     }
   }
   // ---- the waves' sums in a fixed order: 4..7 onto 0..3, then those four
@@ -410,7 +468,7 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
       for (int e = 0; e < 4; ++e) s[e] += t[e];
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[e] /= L;
+    for (int e = 0; e < 4; ++e) s[e] /= ldexpf(L, -le);
     const size_t o = ((size_t)b * H + h) * d + 4 * e4;
     if (OUT_F32) *(f32x4_t*)((float*)p.out + o) = s;
     else *(u32x2_t*)((uint16_t*)p.out + o) = u32x2_t{pack2(s[0], s[1], Tag{}), pack2(s[2], s[3], Tag{})};
@@ -436,7 +494,7 @@ template <class Tag, bool OUT_F32>
 void launch_expand(const SharedExpandParams& p, int d, hipStream_t stream) {
   const dim3 grid((p.units + 7) / 8 * 8);
   const size_t u = __is_same(Tag, BF16Tag) ? (size_t)3 * 16 * (p.r + 8) / 2 : (size_t)16 * (p.r + 4);
-  const size_t merge = (u + 16 * (p.S + 1)) * 4, sums = (size_t)4 * 16 * (d + 4) * 4;
+  const size_t merge = (u + 16 * (p.S + 1) + 8) * 4, sums = (size_t)4 * 16 * (d + 4) * 4;
   const size_t lds = merge > sums ? merge : sums;
   switch (d) {
     case 32: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 2>), grid, dim3(512), lds, stream, p); break;

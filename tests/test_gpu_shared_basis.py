@@ -113,3 +113,48 @@ def test_shared_expansion_of_small_sums(dtype, large, small, live):
     for bases in ((Bk, Bv), written_out(B, Bk, Bv)):
         out = run(ap, False, q, None, None, Ck, Cv, *bases, T, torch.float32)[0]
         assert (np.abs(to_host64(out).reshape(B, H * d) - ref) <= 644 * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_shared_expansion_with_infinities(dtype):
+    """Infinite and NaN elements in the basis, infinite coefficients: signed infinities and NaNs are where the call
+    with the basis written out per sequence has them, and everything else is what it has."""
+    from paper_2603_23914_amd import binding as ap
+    B, H, d, r, T = 65, 48, 64, 640, 33
+    print(f"infinities {dtype}", flush=True)
+    q, Ck, Cv, Bk, Bv = expansion_inputs(dtype, B, H, d, r, T, 78)
+    Cv[5, 3, 40], Cv[6, 32, 639], Cv[7, 0, 0] = float("inf"), float("-inf"), float("nan")
+    Cv = Cv.to(Bv.dtype)
+    Bv[0, 3], Bv[333, 70], Bv[639, 3071] = float("inf"), float("-inf"), float("inf")
+    Bv[17, 200], Bv[400, 200] = float("inf"), float("-inf")               # both signs in one column
+    Bv[100, 1000] = float("nan")
+    Bv[40, 64:128] = 0.0                                                  # 0 x infinity
+    out = to_host64(run(ap, False, q, None, None, Ck, Cv, Bk, Bv, T, torch.float32)[0])
+    ref = to_host64(run(ap, False, q, None, None, Ck, Cv, *written_out(B, Bk, Bv), T, torch.float32)[0])
+    assert np.isinf(ref[0]).sum() >= 3 and np.isnan(ref[7]).all() and np.isfinite(ref[0]).sum() > 3000
+    for kind in (np.isnan, np.isposinf, np.isneginf):
+        assert (kind(out) == kind(ref)).all(), kind.__name__
+    ok = np.isfinite(ref)
+    assert np.abs(out[ok] - ref[ok]).max() <= 2 * 644 * 2.0 ** -24 * 2.0 * np.abs(ref[ok]).max()
+
+
+@pytest.mark.parametrize("case", ["above the largest bfloat16", "below parts of full length"])
+def test_shared_expansion_at_the_ends_of_bfloat16(case):
+    """Sums of two tokens between the largest bfloat16 and the largest fp32 value; sums so small that bfloat16 parts
+    of them are subnormal.  Bounds as for small sums, and half of fp32's smallest value per product."""
+    from paper_2603_23914_amd import binding as ap
+    B, H, d, r, T = 65, 48, 64, 640, 3
+    q, Ck, Cv, Bk, Bv = expansion_inputs("bf16", B, H, d, r, T, 79)
+    if case[0] == "a":
+        T = 2
+        Cv[:, 0, 0], Cv[:, 1, 0] = 2.0 ** 127, 2.0 ** 127 * (1 - 2.0 ** -8)
+    else:
+        Cv *= 1.0e-37
+        Cv[:, :, 4:] = 0.0
+    Ck, Cv = Ck[:, :T].contiguous(), Cv[:, :T].bfloat16().contiguous()
+    print(f"ends of bfloat16: {case}", flush=True)
+    c, b = to_host64(Cv), to_host64(Bv)
+    ref, mag = c.mean(axis=1) @ b, np.abs(c).mean(axis=1) @ np.abs(b)
+    for bases in ((Bk, Bv), written_out(B, Bk, Bv)):
+        out = to_host64(run(ap, False, q, None, None, Ck, Cv, *bases, T, torch.float32)[0]).reshape(B, H * d)
+        assert (np.abs(out - ref) <= 644 * 2.0 ** -24 * mag + 640 * 2.0 ** -150).all()
