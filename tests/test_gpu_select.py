@@ -75,28 +75,38 @@ def test_select_group_shapes():
     check(mass[:, :3], (512, 256, 128, 64), (1, 2, 3, 4), 4, "fewer tokens than groups")
 
 
-# ---- long rows: beyond 32768 tokens the row is split over workgroups (shorter ones here: the same
-#      inputs on one workgroup).  Uniform random values put at most a
-#      sixteenth of the keys on one leading digit, inside the candidate lists; coarse values and long
-#      runs of equal keys are what the lists cannot hold.
+# ---- long rows: beyond 32768 tokens the row is split over workgroups; the shorter rows here are the same inputs
+#      on one workgroup.  Uniform random values put at most a sixteenth of the keys on one leading digit, inside
+#      the candidate lists; coarse values and long runs of equal keys are what the lists cannot hold.
+def gave_up(ws, B, T):
+    """The flags of the rows that the split kernels left to the one-workgroup kernel: word 7 behind the chunks'
+    histograms of 4096 counters, a chunk being 2048 tokens up to 131072 of them."""
+    words = ws.view(torch.int32)[:(ws.numel() - 256) // 4].view(B, -1)
+    return words[:, (T + 2047) // 2048 * 4096 + 7].cpu().tolist()
+
+
 def test_select_split_rows_random_and_odd_lengths():
     for T, B in ((24576, 1), (25001, 2), (32768, 8), (40000, 3), (70001, 1), (200000, 2), (33000, 40)):
         rng = wl.rng_for(24, T)
         mass = rng.random((B, T)).astype(np.float32)
         check(mass, *QUART, "split rows, uniform random")
+
+
+@pytest.mark.parametrize("T", [30000, 36001])
+def test_select_split_rows_group_shapes(T):
     rng = wl.rng_for(25)
-    mass = (rng.standard_exponential((2, 30000)) * 1e-4).astype(np.float32)
+    mass = (rng.standard_exponential((2, T)) * 1e-4).astype(np.float32)
     check(mass, (512, 512, 448, 384, 320, 256, 128, 64), (1, 2, 3, 5, 8, 13, 21, 34), 34, "split rows, F=8 uneven")
     check(mass, (640,), (1,), 1, "split rows, F=1")
     check(mass, (512, 256, 128), (0, 5, 5), 5, "split rows, empty first and last group")
     check(mass, (640, 64), (1, 10), 10, "split rows, paper-style F=2")
 
 
-def test_select_split_rows_equal_keys_at_the_cuts():
+@pytest.mark.parametrize("T", [27001, 37001, 70003])
+def test_select_split_rows_equal_keys_at_the_cuts(T):
     """A few tokens share the key a cut falls on: their order is by token index, and which of
     them lie in front of the cut is decided by counting the listed equal keys."""
     rng = wl.rng_for(26)
-    T = 27001
     mass = rng.random((2, T)).astype(np.float32)
     for b in range(2):
         order = np.argsort(-mass[b], kind="stable")
@@ -111,11 +121,11 @@ def test_select_split_rows_equal_keys_at_the_cuts():
     check(mass, *QUART, "split rows, more equal keys than are listed")      # that row goes to one workgroup
 
 
-def test_select_split_rows_give_way_to_one_workgroup_on_heavy_ties():
+@pytest.mark.parametrize("T", [32768, 33001, 40000])
+def test_select_split_rows_give_way_to_one_workgroup_on_heavy_ties(T):
     """More keys share a cut's leading bits than the candidate list holds: the row is flagged and
     done by the one-workgroup kernel; other rows of the batch stay on the split path."""
     rng = wl.rng_for(27)
-    T = 32768
     mass = rng.random((3, T)).astype(np.float32)
     mass[1] = np.floor(mass[1] * 16) / 16                                    # 16 distinct values
     check(mass, *QUART, "split rows, one row of coarse values")
@@ -130,12 +140,13 @@ def test_select_split_rows_give_way_to_one_workgroup_on_heavy_ties():
     rank = torch.empty((1, T), dtype=torch.int32, device="cuda")
     off = torch.empty((1, 5), dtype=torch.int32, device="cuda")
     idx = torch.empty((1, T), dtype=torch.int32, device="cuda")
-    for row in (np.full((1, T), 0.5, np.float32), mass[:1], mass[1:2], mass[2:3]):
+    for row, flag in ((np.full((1, T), 0.5, np.float32), 1), (mass[:1], 0), (mass[1:2], 1), (mass[2:3], 0)):
         ap.ap_select_ranks(torch.from_numpy(row).cuda(), QUART[0], QUART[1], QUART[2], rank, off, idx, ws)
         torch.cuda.synchronize()
         r_ref, o_ref, i_ref = oracle.select_ranks(row[0], *QUART)
         assert (rank[0].cpu().numpy() == r_ref).all() and (idx[0].cpu().numpy() == i_ref).all()
         assert (off[0].cpu().numpy() == o_ref).all()
+        assert T <= 32768 or gave_up(ws, 1, T) == [flag]
 
 
 @pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 8])
