@@ -67,19 +67,21 @@ def test_scores_give_the_attention_weights(dtype, B, H, d, r, T):
 
 
 @pytest.mark.parametrize("ragged", [False, True])
-@pytest.mark.parametrize("dtype,B,H,r,T", [("bf16", 2, 40, 64, 301), ("f16", 1, 5, 128, 64), ("bf16", 1, 32, 128, 33),
+@pytest.mark.parametrize("dtype,B,H,r,T", [("bf16", 2, 40, 64, 301), ("f16", 2, 5, 128, 64), ("bf16", 2, 32, 128, 33),
                                            ("f16", 2, 64, 64, 1057)])
 def test_scores_at_small_ranks(dtype, B, H, r, T, ragged):
     """Ranks 64 and 128, also with per-token ranks: heads that end inside a tile of 16, tokens inside one of 32,
-    fewer tiles than waves and more.  Every attended token's logits are there, nothing behind them is touched,
-    and the output is the call's without them, bit for bit."""
+    fewer tiles than waves and more.  Every attended token's logits are there, nothing behind them is touched (seven
+    rows of large values lie behind the tokens), and the output is the call's without them, bit for bit."""
     from paper_2603_23914_amd import binding as ap
     d = 64
     case = wl.decode_case(dtype, B, H, d, r, T, steps=0, seed=35, append=False)
     q = wl.step_query(case, 0)
     print(f"scores at small ranks {dtype} B={B} H={H} r={r} T={T} ragged={ragged}", flush=True)
     dq, dCk, dCv, dBk, dBv = (to_dev(x, dtype) for x in (q, case.Ck, case.Cv, case.Bk, case.Bv))
-    T_cap = case.Ck.shape[1]
+    assert dCk.shape[1] == T
+    T_cap = T + 7
+    dCk, dCv = (torch.cat([x, torch.full((B, 7, r), 1.0e3, dtype=x.dtype, device="cuda")], dim=1) for x in (dCk, dCv))
     out, out2 = (torch.empty((B, H, d), dtype=torch.float32, device="cuda") for _ in range(2))
     lse = torch.empty((B, H), dtype=torch.float32, device="cuda")
     scores = torch.full((B, T_cap, H), 123.0, dtype=torch.float32, device="cuda")
@@ -97,7 +99,7 @@ def test_scores_at_small_ranks(dtype, B, H, r, T, ragged):
     A = np.exp(to_host64(scores)[:, :T, :].transpose(0, 2, 1) - to_host64(lse)[:, :, None])
     ref = oracle_probs(dtype, q, case.Ck, case.Bk, T, None if rank is None else rank.cpu().numpy())
     assert np.abs(A - ref).max() <= PROB_TOL * ref.max()
-    assert (scores[:, T:] == 123.0).all()
+    assert scores[:, T:].numel() == B * 7 * H and (scores[:, T:] == 123.0).all()
     assert torch.equal(out, out2)
 
 
