@@ -349,11 +349,12 @@ def test_bases_of_a_batch_with_large_gram_tiles(B, n, HD, l):
 @pytest.mark.parametrize("B,l", [
     (35, 256),                 # 8 pairs of blocks a matrix: a pair less keeps to one workgroup per CU
     (30, 258),                 # 9, with two rows in the last block but one and none in the last
-    (36, 256),                 # not even so
+    (36, 256),                 # 252 workgroups with a pair less: the largest batch
+    (37, 256),                 # 259: every step takes all pairs
 ])
 def test_bases_of_a_batch_that_leaves_out_a_pair(B, l):
-    """The order of the pairs of blocks where each step leaves one out and makes up for it later: the bounds
-    of the test of single sequences, on every sequence."""
+    """The order of the pairs of blocks where each step leaves one out and makes up for it later, and the first batch
+    where none does: the bounds of the test of single sequences, on every sequence."""
     dtype, n, HD = "f16", 320, 320
     X = np.stack([cache_matrix(53, b, n, HD, 128, dtype) for b in range(B)])
     Omega = wl.store(wl.rng_for(53, 7).standard_normal((l, HD)), dtype)
