@@ -43,6 +43,13 @@ def run(ap, step, q, kn, vn, Ck, Cv, Bk, Bv, T, dt_out):
     ("f16", 65, 48, 48, 64, 640, 33, 6.0e3),         # coefficients to the end of fp16, and down where
     ("f16", 65, 48, 48, 64, 640, 33, 2.0e-6),        # most of them are subnormal
     ("bf16", 65, 48, 48, 64, 640, 33, 1.0e30),
+    ("bf16", 32, 40, 40, 128, 640, 257, 1.0),        # expansion, eight splits: two rounds of four
+    ("bf16", 51, 40, 40, 128, 640, 150, 1.0),        # five splits, the second round with one
+    ("bf16", 43, 64, 64, 64, 640, 170, 1.0),         # five, ragged column tile
+    ("bf16", 37, 64, 32, 128, 640, 193, 1.0),        # six, grouped queries
+    ("bf16", 64, 32, 32, 256, 256, 97, 1.0),         # expansion, wide heads
+    ("f16", 64, 64, 64, 128, 256, 128, 1.0),         # fp16 has one round at most: four splits
+    ("f16", 51, 40, 40, 128, 640, 150, 1.0),         # five: the expansion per sequence
 ])
 def test_shared_basis(dtype, B, H, Hkv, d, r, T, scale, step):
     from paper_2603_23914_amd import binding as ap
