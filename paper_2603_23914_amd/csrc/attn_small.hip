@@ -102,9 +102,9 @@ attn_small(const SmallParams p) {
     }
   // logits out (LOGITS), through a buffer that drops what lies past its end: no lane has a branch, so the waits
   // for the next tile's rows, which are asked for first, do not count the stores behind them in
-  __amdgpu_buffer_rsrc_t logits;
+  buffer_t logits;
   if constexpr (LOGITS)
-    logits = __builtin_amdgcn_make_buffer_rsrc(p.scores + (size_t)b * H * p.T_cap, 0, (int)((uint32_t)p.T_cap * (uint32_t)H * 4u), 0x00020000);
+    logits = make_buffer(p.scores + (size_t)b * H * p.T_cap, (uint32_t)p.T_cap * (uint32_t)H * 4u);
   const uint16_t* Cb = p.Ck + (size_t)b * p.T_cap * R + g * 8;
   const uint16_t* Vb = p.Cv + (size_t)b * p.T_cap * R;
   // tiles of this split (the same cuts as attn_partial's)

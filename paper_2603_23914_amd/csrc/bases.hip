@@ -47,9 +47,6 @@ __device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, in
   }
 }
 
-// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 constexpr int kFirstCheck = 4;         // sweeps before this one do not ask whether the matrix is done
 constexpr int kFullEvery = 4, kFullFrom = 8;   // steps and sweeps that turn the pairs within the blocks too
 constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done

@@ -22,21 +22,6 @@
 namespace ap {
 namespace {
 
-typedef __amdgpu_buffer_rsrc_t buffer_t;
-// A raw buffer over `bytes` bytes: loads past them return zeros and move nothing, without a branch.
-__device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ u32x4_t buffer_load16(buffer_t rsrc, uint32_t offset) {
-  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 0));
-}
-__device__ __forceinline__ float buffer_load4(buffer_t rsrc, uint32_t offset) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, offset, 0, 0));
-}
-
-// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 struct RowsParams {
   const uint16_t* Bm;     // [B][r][HD] (bstride elements between sequences, 0 = shared)
   int64_t bstride;

@@ -1,5 +1,6 @@
 // Small per-lane building blocks shared by the bandwidth-bound kernels: 16-bit dot products
-// with fp32 accumulation and sums across lanes on the DPP path of the vector ALU.
+// with fp32 accumulation, sums across lanes on the DPP path of the vector ALU, loads that end with their buffer and
+// a barrier that leaves loads in flight.
 #pragma once
 #include "ap_common.hpp"
 
@@ -17,6 +18,21 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c, BF16Tag) 
 }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr float kLn2 = 0.6931471805599453f;
+
+// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+typedef __amdgpu_buffer_rsrc_t buffer_t;
+// A raw buffer over `bytes` bytes: loads past them return zeros, stores are dropped, and nothing moves, without a branch.
+__device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4_t buffer_load16(buffer_t rsrc, uint32_t offset) {
+  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 0));
+}
+__device__ __forceinline__ float buffer_load4(buffer_t rsrc, uint32_t offset) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, offset, 0, 0));
+}
 
 template <class Tag>
 __device__ __forceinline__ float dot8(const u32x4_t& a, const u32x4_t& b, float c) {

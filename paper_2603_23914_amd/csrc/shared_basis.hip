@@ -17,18 +17,6 @@
 namespace ap {
 namespace {
 
-// Workgroup barrier for LDS traffic only: __syncthreads() may also wait for loads in flight.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-typedef __amdgpu_buffer_rsrc_t buffer_t;
-// A raw buffer over `bytes` bytes: loads past them return zeros and move nothing, without a branch.
-__device__ __forceinline__ buffer_t make_buffer(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ u32x4_t buffer_load16(buffer_t rsrc, uint32_t offset) {
-  return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset, 0, 0));
-}
-
 // Workgroups go round the XCDs: unit numbers in one run per XCD, so that neighbouring units (the same
 // basis rows, the same head's slice) meet in one L2.  Numbers >= units are spare.
 __device__ __forceinline__ int run_per_xcd(int id, int units) { return (id & 7) * ((units + 7) >> 3) + (id >> 3); }
@@ -40,7 +28,6 @@ struct ProjectParams {
   const uint16_t* q;        // [B][H][d]
   uint16_t* Qp;             // [B][2][Hp][r]
   int B, H, G, Hp, HD, r, row0, T_cap;
-  int dots;                 // jobs of the first kind (0: fold only, 2: both rows)
   int dot_units, fold_units, dot_blocks;
   float scale;
 };
@@ -538,7 +525,7 @@ ap_status launch_shared_project(ap_dtype dt, const void* Bk, const void* Bv, con
                                 int r, int row, int T_cap, float scale, hipStream_t stream) {
   ProjectParams p{{(const uint16_t*)Bk, (const uint16_t*)Bv}, {(const uint16_t*)k_new, (const uint16_t*)v_new},
                   {(uint16_t*)Ck, (uint16_t*)Cv}, (const uint16_t*)q, (uint16_t*)Qp, B, H, H / H_kv, Hp, H_kv * d, r,
-                  row, T_cap, k_new ? 2 : 0, 0, 0, 0, scale};
+                  row, T_cap, 0, 0, 0, scale};
   const int nb = B > 16 ? 2 : 1;
   p.dot_units = k_new ? r / 16 * 2 * ((B + 16 * nb - 1) / (16 * nb)) : 0;
   p.fold_units = H_kv * ((r + 127) / 128) * ((B * p.G + 63) / 64);
