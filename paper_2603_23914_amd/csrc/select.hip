@@ -315,8 +315,10 @@ __global__ void __launch_bounds__(kThreads) select_ranks_kernel(const SelectPara
 //   - A token's position in front of which nothing else has to be counted comes from ballots: tokens in front
 //     of a cut in each (64 tokens, cut), prefix sums of these by a wave per cut.  Equal keys are counted only where
 //     a cut falls among them.
-// Measured: 64 rows of 4225 tokens, two groups, 19-23 us -> 10 (T = 4225; 27 -> 11 with four groups); one row of 32768, four groups, 51 us split over 16
-// workgroups -> 34; 64 rows of 16384: 57 -> 33.
+// With 32 tokens per thread the kernel is at its 128 registers and keeps 138 to 240 scalar ones in vector lanes (three
+// vector ones in scratch with seven cuts).
+// Measured: 64 rows of 4225 tokens, two groups, 19-23 us -> 10 (27 -> 11 with four groups); one row of 32768, four
+// groups, 51 us split over 16 workgroups -> 34; 64 rows of 16384: 57 -> 33.
 // ------------------------------------------------------------------------------------------
 constexpr int kRowMax = 32768;
 template <int CTRL, int ROW_MASK = 0xf>
