@@ -205,7 +205,7 @@ __device__ __forceinline__ void split3(float x, float y, uint32_t (&v)[3]) {
 }
 
 // A workgroup (512 threads) merges and expands 16 (sequence, query head) columns of one key/value head.
-// The merge (32 lanes a column) leaves U* (times a half to one) in LDS; the waves then take every eighth group of 32
+// The merge (32 lanes a column) leaves U*, times L or what is left of it, in LDS; the waves then take every eighth group of 32
 // basis rows.  A lane loads VEC = d / 16 consecutive elements of eight rows: product i holds the hidden columns VEC a + i, so a
 // lane ends with VEC consecutive columns per accumulator row.
 //   bfloat16  U* as three 16-bit parts, eight rows of an element the operand of one product (byte permutes); the
@@ -214,8 +214,8 @@ __device__ __forceinline__ void split3(float x, float y, uint32_t (&v)[3]) {
 //             finite, or a workgroup with such sums, does the fp32 products
 //   fp16      fp32 products (v_mfma_f32_16x16x4_f32), four rows each: fp16 has too few exponents for parts of a
 //             sum that is small beside its column's largest
-// 64 x 640, 40 heads, four splits: bfloat16 13.0 us (26.3 with a workgroup per head and sequence), most of it loads on
-// their way; fp16 15.9 us (12.1 with three fp16 parts, which were 7e-4 off where 2^-30 of the largest was all).
+// 64 x 640, 40 heads, four splits: bfloat16 12.9 us (26.3 with a workgroup per head and sequence), most of it loads on
+// their way; fp16 16.1 us (12.1 with three fp16 parts, which were 7e-4 off where 2^-30 of the largest was all).
 template <class Tag, bool OUT_F32, int VEC>
 __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p) {
   constexpr int d = VEC * 16, DW = VEC / 2;                   // DW dwords of a row per lane
@@ -290,9 +290,9 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
   if (ci + 32 < S) wgt[c * sp + ci + 32] = w1;
   if (p.lse && ci == 0 && ct * 16 + c < N) p.lse[(size_t)b * H + h] = (m + log2f(L)) * kLn2;
   __builtin_amdgcn_wave_barrier();                            // a column's weights stay within its half wave
-  // ---- sum_s w_s U_s, divided by the power of two that brings L to [0.5, 1): with the division by what is left of L
-  // left to the results, which are fewer, nothing on the way is larger than with U* itself
-  const int le = __builtin_amdgcn_frexp_expf(L);
+  // ---- sum_s w_s U_s; the division by L is left to the results, which are fewer.  bfloat16, where the sums may be near
+  // the end of fp32: but for a power of two that brings L to [0.5, 1), so that nothing is larger than with U* itself
+  const int le = kParts ? __builtin_amdgcn_frexp_expf(L) : 0;
   f32x4_t ua[kChunks];
 #pragma unroll
   for (int k = 0; k < kChunks; ++k) ua[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -309,20 +309,20 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
       }
     }
   }
-  bool tiny = false;
+  uint32_t least = ~0u;                                       // twice the bits of the smallest |U*| but 0, less 1
 #pragma unroll
   for (int k = 0; k < kChunks; ++k) {
     if (128 * k + 4 * ci < r) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ua[k][e] = ldexpf(ua[k][e], -le);
       if constexpr (kParts) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ua[k][e] = ldexpf(ua[k][e], -le);
         uint32_t v[2][3];
 #pragma unroll
         for (int e = 0; e < 2; ++e) split3(ua[k][2 * e], ua[k][2 * e + 1], v[e]);
 #pragma unroll
         for (int q = 0; q < 3; ++q) *(u32x2_t*)(parts + (q * 16 + c) * pitch + 128 * k + 4 * ci) = u32x2_t{v[0][q], v[1][q]};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tiny |= ua[k][e] != 0.f && fabsf(ua[k][e]) < 0x1p-100f;
+        for (int e = 0; e < 4; ++e) least = min(least, (__builtin_bit_cast(uint32_t, ua[k][e]) << 1) - 1u);
       } else {
         *(f32x4_t*)(ustar + c * pitch32 + 128 * k + 4 * ci) = ua[k];
       }
@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
   }
   int whole = 0;                                              // bfloat16: U* is in LDS as fp32 after all
   if constexpr (kParts) {
-    const bool any = __any(tiny);
+    const bool any = __any(least < (__builtin_bit_cast(uint32_t, 0x1p-100f) << 1) - 1u);
     if (lane == 0) flags[w] = any;
     lds_barrier();
 #pragma unroll
@@ -368,19 +368,28 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
         for (int e = 0; e < 4; ++e) uf[t + e] = v[e];
       }
     }
-    f32x4_t part[VEC];                                        // a group's sum by itself: shorter chains of roundings
+    constexpr int kC = VEC < 16 ? 2 : 1;                      // sums of a few rows each, added up in pairs: fewer roundings
+    f32x4_t part[kC][VEC];                                    // on the way
 #pragma unroll
     for (int t = 0; t < 8; ++t)                               // rows 8 g' + t, g' = 0 .. 3
 #pragma unroll
       for (int i = 0; i < VEC; ++i) {
         const float x = i & 1 ? hi_to_f32(src[t][i >> 1], Tag{}) : lo_to_f32(src[t][i >> 1], Tag{});
         const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-        part[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, uf[t], t ? part[i] : zero, 0, 0, 0);
+        part[t % kC][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, uf[t], t < kC ? zero : part[t % kC][i], 0, 0, 0);
       }
+#pragma unroll
+    for (int k = kC / 2; k > 0; k >>= 1)
+#pragma unroll
+      for (int j = 0; j < k; ++j)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part[j][i][e] += part[j + k][i][e];
 #pragma unroll
     for (int i = 0; i < VEC; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][e] += part[i][e];
+      for (int e = 0; e < 4; ++e) acc[i][e] += part[0][i][e];
   };
   auto use_group = [&](const uint32_t (&src)[8][DW], int gi) {
     if constexpr (kParts) {
@@ -413,12 +422,12 @@ __global__ void __launch_bounds__(512) shared_expand(const SharedExpandParams p)
     }
   }
   if constexpr (kParts) {
-    int again = whole;
+    float nothing = 0.f;                                      // NaN once something is not finite
 #pragma unroll
     for (int i = 0; i < VEC; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) again |= !__builtin_isfinite(acc[i][e]);
-    if (__any(again)) {
+      for (int e = 0; e < 4; ++e) nothing = fmaf(acc[i][e], 0.f, nothing);
+    if (whole || __any(nothing != 0.f)) {
 #pragma unroll
       for (int i = 0; i < VEC; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
       for (int gi = w; gi < groups; gi += 8) {
@@ -487,7 +496,7 @@ void launch_expand(const SharedExpandParams& p, int d, hipStream_t stream) {
     case 32: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 2>), grid, dim3(512), lds, stream, p); break;
     case 64: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 4>), grid, dim3(512), lds, stream, p); break;
     case 128: hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 8>), grid, dim3(512), lds, stream, p); break;
-    default:
+    default:                                                  // (fp16 does not come here: shared_expand_applies)
       if constexpr (__is_same(Tag, BF16Tag))
         hipLaunchKernelGGL((shared_expand<Tag, OUT_F32, 16>), grid, dim3(512), lds, stream, p);
       break;
@@ -510,13 +519,13 @@ bool shared_project_applies(int B, int H, int H_kv, int d, int r, bool appends) 
 }
 // The expansion's merge is longer than that of a workgroup per head (all columns' sums pass through B H / 16
 // workgroups, four splits at a time): few splits and much to expand.  Us a call there / here: 64 x 256, 64 heads
-// 34.4 / 29.8, 64 x 640, 64 heads of 64 60.5 / 54.3, but 48 x 256, 40 heads 27.2 / 28.0, 40 x 320, 32 heads of 256
-// 29.5 / 30.8.  The fp32 products of fp16 are worth it with one round of splits and heads up to 128: 64 x 256, 64
-// heads 32.9 / 30.4, 64 x 448, 32 heads 33.0 / 31.9, but with six and eight splits 40 x 640, 32 heads 32.1 / 35.7 and
-// 32 x 640, 40 heads 35.6 / 38.9, with heads of 256 48 x 320, 32 heads 28.1 / 33.9.
+// 34.4 / 28.7, 64 x 640, 64 heads of 64 60.5 / 53.5, but 48 x 256, 40 heads 27.2 / 28.0.  The fp32 products of fp16
+// are worth it with one round of splits and heads up to 128: 64 x 256, 64 heads 32.9 / 30.1, 64 x 448, 32 heads
+// 33.0 / 31.8, but with six and eight splits 40 x 640, 32 heads 32.1 / 35.7 and 32 x 640, 40 heads 35.6 / 38.9, with
+// heads of 256 48 x 320, 32 heads 28.1 / 33.9.
 bool shared_expand_applies(ap_dtype dt, int B, int H, int d, int r, int S) {
   if (dt == AP_F16 && (S > 4 || d > 128)) return false;
-  return S <= 8 && (int64_t)B * r * H * d * 2 >= (d > 128 ? 224ll : 192ll) << 20;
+  return S <= 8 && (int64_t)B * r * H * d * 2 >= (192ll << 20);
 }
 
 // Fold of q (and, with k_new and v_new, both appended rows) on shared bases, r % 64 == 0.
