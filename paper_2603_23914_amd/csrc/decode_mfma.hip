@@ -448,6 +448,7 @@ struct AttnParams {
   float* part_ml;       // [B][S][H][2]   (softmax reference exponent in log2 units, sum)
   float* part_U;        // [B][S][H][r]
   int B, T, T_cap, r, H, nsplit;
+  int hgroups;          // head groups of 16 MT heads (the last may be smaller), a workgroup each
   int xcd_aware;        // workgroup numbering, see wg_coords
   int nh;               // C_v LDS ring depth in 16-row units (even, >= 2)
   // rank-ragged launches only: the group lists of ap_select_ranks and the per-token ranks
@@ -494,8 +495,16 @@ struct AttnParams {
 // on XCD b % 8 and its splits are neighbours in that XCD's dispatch order: the folded query of
 // a sequence is fetched from HBM once and found in L2 by the other splits.  Smaller batches
 // keep the plain numbering, which spreads a sequence's splits over all XCDs.
-__device__ __forceinline__ void wg_coords(int nsplit, int xcd_aware, int& b, int& s) {
-  const int id = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
+// The head groups of a split are neighbours on one XCD in either numbering: the first one's
+// coefficient rows are in that L2 when the others ask for them.
+__device__ __forceinline__ void wg_coords(int nsplit, int hgroups, int xcd_aware, int& b, int& s, int& hg) {
+  int id = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
+  hg = 0;
+  if (hgroups > 1) {
+    const int k = id >> 3;
+    hg = k % hgroups;
+    id = (k / hgroups) * 8 + (id & 7);
+  }
   if (xcd_aware) {
     const int k = id >> 3;
     b = (k / nsplit) * 8 + (id & 7);
@@ -529,6 +538,7 @@ struct WaveCtx {
 
   int w, lane, n, g, b, s;
   int r, T, H, nh, nsplit, dbg;
+  int h0;            // first head of this workgroup's group
   int pitch, nblk, unit_bytes;
   char* ring;
   f32x4_t* xchg;     // [4 score waves][16*MT heads][9]: 8 slots (4*tt+g) + 1 pad per head
@@ -562,13 +572,15 @@ struct WaveCtx {
     w = __builtin_amdgcn_readfirstlane(tid >> 6);
     lane = tid & 63; n = lane & 15; g = lane >> 4;
     r = uni(p.r); T = uni(p.T); H = uni(p.H); nh = uni(p.nh); nsplit = uni(p.nsplit); dbg = uni(p.dbg);
-    wg_coords(nsplit, uni(p.xcd_aware), b, s);
+    int hg;
+    wg_coords(nsplit, uni(p.hgroups), uni(p.xcd_aware), b, s, hg);
+    h0 = hg * 16 * MT;
     Tv = T - uni(p.defer_v);
     pnew = uni_ptr(p.pnew);
     pnew_split = uni_ptr(p.pnew_split);
     T_cap = uni(p.T_cap);
     scores = uni_ptr(p.scores);
-    if (scores) scores += (size_t)b * H * T_cap;
+    if (scores) scores += (size_t)b * H * T_cap + h0;
     // ring unit geometry: 16 rows of (cpr+1) 16-byte chunks (one pad chunk per row shifts
     // consecutive rows across the LDS banks)
     const int cpr = row_bytes_of(r) >> 4;
@@ -739,7 +751,7 @@ struct WaveCtx {
       for (int q = Q0; q < Q1; ++q)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if (owner[q] && o_hh[q] < H && slot + i < valid) {
+          if (owner[q] && h0 + o_hh[q] < H && slot + i < valid) {
             const int tok = RAGGED ? idxb[t * kTile + slot + i] : tok0(t) + slot + i;
             scores[(size_t)tok * H + o_hh[q]] = sc[q][i] * kLn2;
           }
@@ -775,9 +787,9 @@ struct WaveCtx {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           if (li == i) { pdef[q] = pr[q][i]; pr[q][i] = 0.f; }
-        if (owner[q] && li >= 0 && li < 4 && o_hh[q] < H) {
-          pnew[(size_t)b * H + o_hh[q]] = pdef[q];
-          if (o_hh[q] == 0) pnew_split[b] = s;
+        if (owner[q] && li >= 0 && li < 4 && h0 + o_hh[q] < H) {
+          pnew[(size_t)b * H + h0 + o_hh[q]] = pdef[q];
+          if (h0 + o_hh[q] == 0) pnew_split[b] = s;
         }
       }
     }
@@ -836,7 +848,7 @@ struct WaveCtx {
       valid[sub] = tile_valid(t0 + sub);
       newl[sub] = tile_new(t0 + sub);
     }
-    if (scores && o_hh < H) {                   // logits out, for importance tracking: [token][head]
+    if (scores && h0 + o_hh < H) {              // logits out, for importance tracking: [token][head]
 #pragma unroll
       for (int sub = 0; sub < 4; ++sub)
 #pragma unroll
@@ -871,9 +883,9 @@ struct WaveCtx {
         if (li == 1) { pdef = p1; p1 = 0.f; }
         if (li == 2) { pdef = p2; p2 = 0.f; }
         if (li == 3) { pdef = p3; p3 = 0.f; }
-        if (li >= 0 && li < 4 && o_hh < H) {
-          pnew[(size_t)b * H + o_hh] = pdef;
-          if (o_hh == 0) pnew_split[b] = s;
+        if (li >= 0 && li < 4 && h0 + o_hh < H) {
+          pnew[(size_t)b * H + h0 + o_hh] = pdef;
+          if (h0 + o_hh == 0) pnew_split[b] = s;
         }
       }
       u32x2_t hi, lo = {0, 0};
@@ -902,8 +914,8 @@ struct WaveCtx {
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       const float l_tot = sum8(l_part[q]);
-      if (owner[q] && (lane & 7) == 0 && o_hh[q] < H) {
-        const size_t pb = ((size_t)b * nsplit + s) * H + o_hh[q];
+      if (owner[q] && (lane & 7) == 0 && h0 + o_hh[q] < H) {
+        const size_t pb = ((size_t)b * nsplit + s) * H + h0 + o_hh[q];
         part_ml[pb * 2 + 0] = m_ref[q];
         part_ml[pb * 2 + 1] = l_tot;
       }
@@ -962,10 +974,10 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
   constexpr int NBW = (RMAX / 64 + 3) / 4;                // int8: scale blocks per score wave
   constexpr int NKW = TS ? RMAX / 32 : (I8 ? 2 * NBW : (RMAX / 32 + 3) / 4);   // score k-steps per score wave
   constexpr int NA = I8 ? NBW : NKW;                      // 16-byte row loads per 16-row half
-  constexpr int Hp = MT * 16;
   AP_T_ENTRY
   WaveCtx<Tag, MT, SPLIT, RAGGED, Q, TS> cx;
   cx.init(p);
+  const int Hp = (cx.H + 15) & ~15;                       // heads of all groups, as Qp is laid out
   float* part_ml = uni_ptr(p.part_ml);
   const int w = cx.w, n = cx.n, g = cx.g, r = cx.r, T = cx.T;
   const int nks = I8 ? r >> 6 : r >> 5;                   // all units
@@ -991,7 +1003,10 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       if (unit < my_nks) {
 #endif
         const int col = I8 ? (w + 4 * unit) * 64 + g * 16 + (i & 1) * 8 : (ufirst + ustep * i) * 32 + g * 8;
-        const uint16_t* qrow = Qp + (((size_t)cx.b * 2) * Hp + (mt * 16 + n)) * r + col;
+        // (a head tile of the last group past all heads repeats the last tile: nothing of it is stored)
+        int hq = cx.h0 + mt * 16;
+        hq = (hq < Hp ? hq : Hp - 16) + n;
+        const uint16_t* qrow = Qp + (((size_t)cx.b * 2) * Hp + hq) * r + col;
         qhi[i][mt] = *(const u32x4_t*)qrow;
         if (SPLIT) qlo[i][mt] = *(const u32x4_t*)(qrow + (size_t)Hp * r);
         if (I4) {                                          // the column order of code_row8_i4: 0,4,1,5,2,6,3,7
@@ -1488,7 +1503,7 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
     float* ubase = part_U + ((size_t)cx.b * cx.nsplit + cx.s) * cx.H * r;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const int head = mt * 16 + n;
+      const int head = cx.h0 + mt * 16 + n;
       if (head < cx.H) {
         float* urow = ubase + (size_t)head * r;
 #pragma unroll
@@ -1548,8 +1563,8 @@ template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_partial(const AttnParams p) {
   {
-    int b, s;
-    wg_coords(p.nsplit, p.xcd_aware, b, s);
+    int b, s, hg;
+    wg_coords(p.nsplit, p.hgroups, p.xcd_aware, b, s, hg);
     if (b >= p.B) return;
   }
   // The roles are inlined: called as functions they would spill their callee-saved registers
@@ -1597,6 +1612,34 @@ int choose_nsplit(int B, int T) {
   return s;
 }
 
+// Head groups: workgroups that share a split's tokens, each with a part of the heads.  A split of a short
+// context is a few tiles, and its partial sums (heads x rank floats, written here and read by the merge) are as
+// many bytes as its coefficients: g groups with a g-th of the splits write a g-th of them, and the coefficients
+// that all groups of a split fetch come out of one L2.  The price is more, if lighter, tiles one after the other.
+// Measured over 180 shapes (us a pass, one group / two): 8 sequences of 1153 tokens, 32 heads, rank 512
+// 35.4 / 32.9, of 4600 tokens (5 tiles a split) 42.9 / 43.2; 16 of 1153, 40 heads, rank 640 86.7 / 79.2; 21 of
+// 3001, 32 heads, rank 256 (8 tiles) 30.8 / 33.6; 8 gathered rows of 1153, 32 heads, rank 512 25.6 / 24.2 per step.
+// Four head tiles beyond rank 512 keep more accumulators than registers in one group: 16 x 4000 tokens, rank 640
+// int8 99.7 / 72.5, bf16 94.8 / 77.0, fp16 83.7 / 72.9, fp16 with 4225 x 64 229.9 / 247.5.
+int choose_nsplit(int B, int T, int hgroups) {   // (never more than one group takes: the workspace holds those)
+  const int s1 = choose_nsplit(B, T), s = choose_nsplit(B * hgroups, T);
+  return s < s1 ? s : s1;
+}
+int choose_head_groups(const DecodeArgs& a, bool quant, bool ragged) {
+  const int nw = (a.H + 15) / 16;
+  auto tiles = [&](int g) {                // of one workgroup at g groups
+    const int s = choose_nsplit(a.B, a.T, g);
+    return ragged ? ((a.T + kTile - 1) / kTile + a.F + s - 1) / s : ((a.T + s - 1) / s + kTile - 1) / kTile;
+  };
+  if (nw == 1) return 1;
+  if (tiles(nw) == 1) return nw;           // a workgroup per head tile, and still one tile each
+  const int t1 = tiles(1);
+  if (t1 <= 2 && (a.r >= 192 || tiles(2) == t1)) return 2;
+  if (ragged || a.r < 512) return 1;
+  if (t1 == 3) return 2;
+  return nw == 4 && a.r > 512 && (quant || a.dt == AP_BF16 || t1 <= 8) ? 2 : 1;
+}
+
 struct WsLayout {
   size_t qp, ml, u, po, pn, mml, mu, total;
 };
@@ -1625,6 +1668,10 @@ WsLayout ws_layout(int B, int H, int d, int T, int r) {
 template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
 ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
   constexpr bool I8 = Q != 0;
+  if constexpr (MT == 4 && RMAX > 512 && !RAGGED && (SPLIT || I8)) {
+    set_error("ap_decode_attn: H=%d r=%d always takes head groups", p.H, p.r);
+    return AP_ERR_UNSUPPORTED;
+  } else {
   const int cpr = (Q == 2 ? p.r / 2 : (I8 ? p.r : 2 * p.r)) / 16;
   const size_t unit = (size_t)((kHalf * (cpr + 1) + 63) / 64) * 1024;
   constexpr bool TS = !RAGGED && !I8 && RMAX == 128;
@@ -1665,17 +1712,20 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
   }
   p.B = B;
   p.xcd_aware = B % 8 == 0 ? 1 : 0;
+  // head groups: whole eights of (sequence, split), a workgroup past the end leaves at once
+  const int units = p.hgroups > 1 ? (B * p.nsplit + 7) / 8 * 8 * p.hgroups : B * p.nsplit;
   hipEvent_t ev0, ev1;
   if (prof_events(&ev0, &ev1))             // timing on: the events carry this launch's own start and end
-    hipExtLaunchKernelGGL(kern, dim3(B * p.nsplit), dim3(512), (uint32_t)lds, stream, ev0, ev1, 0u, p);
+    hipExtLaunchKernelGGL(kern, dim3(units), dim3(512), (uint32_t)lds, stream, ev0, ev1, 0u, p);
   else
-    hipLaunchKernelGGL(kern, dim3(B * p.nsplit), dim3(512), lds, stream, p);
+    hipLaunchKernelGGL(kern, dim3(units), dim3(512), lds, stream, p);
   return AP_OK;
+  }
 }
 
 template <class Tag, bool SPLIT>
 ap_status dispatch_attn(const AttnParams& p, int B, hipStream_t stream) {
-  const int nw = (p.H + 15) / 16;
+  const int nw = ((p.H + 15) / 16 + p.hgroups - 1) / p.hgroups;
   if constexpr (!SPLIT) {                 // fp16 arithmetic: int8 coefficients ride on it
     if (p.Sk && p.qbits == 4) {
       switch (nw) {
@@ -1749,8 +1799,9 @@ ap_status run_decode(const DecodeArgs& a) {
   const bool small = !quant && attn_small_applies(a.H, a.r, a.T, one_pass_v) &&
                      (!a.scores || (int64_t)a.T_cap * a.H * 4 < (1ll << 32));
   int* pnew_split = (int*)((char*)a.workspace + ws_layout(a.B, a.H, a.d, a.T, a.r).pn + (size_t)a.B * a.H * 4);
-  const int S = choose_nsplit(a.B, a.T);     // the same count for both kernels (twice the splits for
-                                             // the small-rank kernel measured slower)
+  // (the small-rank kernel takes the count of one head group: twice the splits measured slower)
+  const int hgroups = small ? 1 : choose_head_groups(a, quant, ragged);
+  const int S = choose_nsplit(a.B, a.T, hgroups);
   const WsLayout wl = ws_layout(a.B, a.H, a.d, a.T, a.r);
   char* ws = (char*)a.workspace;
   uint16_t* Qp = (uint16_t*)(ws + wl.qp);
@@ -1797,7 +1848,7 @@ ap_status run_decode(const DecodeArgs& a) {
   p.Cv = (const uint16_t*)a.Cv;
   p.part_ml = ml;
   p.part_U = U;
-  p.T = a.T; p.T_cap = a.T_cap; p.r = a.r; p.H = a.H; p.nsplit = S;
+  p.T = a.T; p.T_cap = a.T_cap; p.r = a.r; p.H = a.H; p.nsplit = S; p.hgroups = hgroups;
   p.scores = a.scores;
   p.defer_v = one_pass_v ? 1 : 0;
   p.pnew = (float*)(ws + wl.pn);
