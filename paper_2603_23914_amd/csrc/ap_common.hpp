@@ -197,6 +197,9 @@ ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, const void* Ck, con
                             const int32_t* rank_v, const int32_t* bucket_off, const int32_t* bucket_idx, int F,
                             int B, int H, int T, int T_cap, int r, int nsplit, bool defer_v,
                             hipStream_t stream);
+// short contexts, a head per workgroup from the folded query to the output (attn_heads.hip); Qp null: folded there too
+bool attn_heads_applies(int B, int H, int d, int T, int r, bool appends);
+ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, float scale);
 // key-only compression on the matrix cores (keyonly_mfma.hip)
 bool keyonly_mfma_applies(int H, int H_kv, int d, int r);
 int keyonly_mfma_splits(int B, int H_kv, int T);

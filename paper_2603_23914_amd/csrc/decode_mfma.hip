@@ -1814,6 +1814,11 @@ ap_status run_decode(const DecodeArgs& a) {
   const bool pair_v = a.v_new && !one_pass_v && a.k_new;
   // one basis for all sequences: matrix products where they are the shorter way
   const bool shared = a.basis_batch_stride == 0 && !one_pass_v;
+  // short contexts: what follows the appends in one launch, with the fold where nothing is appended.  (With the rule
+  // for the value row overridden a step and its two halves stay on the kernels that the override is about.)
+  const bool heads = !quant && !ragged && v_min < 0 && !one_pass_v &&
+                     attn_heads_applies(a.B, a.H, a.d, a.T, a.r, a.k_new != nullptr);
+  if (heads && !a.k_new) return launch_attn_heads(a, nullptr, a.sm_scale * kLog2e);
   if (shared && shared_project_applies(a.B, a.H, Hkv, a.d, a.r, a.k_new != nullptr)) {
     st = launch_shared_project(a.dt, a.Bk, a.Bv, a.k_new, a.v_new, a.q, (void*)a.Ck, (void*)a.Cv, Qp, a.B, a.H, Hkv, Hp, a.d,
                                a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream);
@@ -1842,6 +1847,7 @@ ap_status run_decode(const DecodeArgs& a) {
                            a.B, 0, 0, 8, HDkv, a.r, a.T - 1, a.T_cap, 1.0f, a.stream);
     if (st != AP_OK) return st;
   }
+  if (heads) return launch_attn_heads(a, Qp, 1.f);
   AttnParams p{};
   p.Qp = Qp;
   p.Ck = (const uint16_t*)a.Ck;
