@@ -72,6 +72,16 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi, Tag t) {
   return (uint32_t)f32_to_bits(lo, t) | ((uint32_t)f32_to_bits(hi, t) << 16);
 }
 
+// Where element (head h, column j) of a folded query lies in its part of Hp r elements (Hp a multiple of 16, r of 8):
+// in rows of r columns, [Hp][r], or tiled, [Hp / 16][r / 8][16][8], which basis_rows writes in long runs, a few columns
+// of all heads at a time.
+struct FoldedLayout {
+  bool tiled;
+  __host__ __device__ constexpr size_t at(int h, int j, int r) const {
+    return (size_t)(h >> 4) * 16 * r + (h & 15) * (tiled ? 8 : r) + (j >> 3) * (tiled ? 128 : 8) + (j & 7);
+  }
+};
+
 // ---- launchers (defined in the .hip files) -------------------------------------
 struct DecodeArgs {
   const void* q;
@@ -192,14 +202,14 @@ ap_status launch_valueonly_attn(const void* q, const void* K, const void* Cv, co
                                 float sm_scale, ap_dtype dt, void* workspace, hipStream_t stream);
 // small uniform ranks (attn_small.hip): partial results in attn_partial's layout
 bool attn_small_applies(int H, int r, int T, bool defer_v);
-ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, const void* Ck, const void* Cv, float* part_ml,
+ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, FoldedLayout folded, const void* Ck, const void* Cv, float* part_ml,
                             float* part_U, float* pnew, float* scores, const int32_t* rank_k,
                             const int32_t* rank_v, const int32_t* bucket_off, const int32_t* bucket_idx, int F,
                             int B, int H, int T, int T_cap, int r, int nsplit, bool defer_v,
                             hipStream_t stream);
 // short contexts, a head per workgroup from the folded query to the output (attn_heads.hip); Qp null: folded there too
 bool attn_heads_applies(int B, int H, int d, int T, int r, bool appends);
-ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, float scale);
+ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, FoldedLayout folded, float scale);
 // key-only compression on the matrix cores (keyonly_mfma.hip)
 bool keyonly_mfma_applies(int H, int H_kv, int d, int r);
 int keyonly_mfma_splits(int B, int H_kv, int T);

@@ -26,7 +26,8 @@ constexpr int kThreads = 1024, kWaves = kThreads / 64, kRows = kThreads / 8;   /
 struct HeadsParams {
   const uint16_t* q;      // FOLD: [B][H][d]
   const uint16_t* Bk;     // FOLD: [B or 1][r][HD]
-  const uint16_t* Qp;     // else: [B][2][Hp][r], high and low parts of the folded query
+  const uint16_t* Qp;     // else: folded queries, high and low parts
+  FoldedLayout folded;
   const uint16_t* Ck;     // [B][T_cap][r]
   const uint16_t* Cv;
   const uint16_t* Bv;     // [B or 1][r][HD]
@@ -76,7 +77,7 @@ __global__ void __launch_bounds__(kThreads) attn_heads(const HeadsParams p) {
   if constexpr (!FOLD) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      const uint16_t* src = p.Qp + (((size_t)b * 2) * p.Hp + h) * r + (l8 + 8 * c) * 8;
+      const uint16_t* src = p.Qp + ((size_t)b * 2) * p.Hp * r + p.folded.at(h, (l8 + 8 * c) * 8, r);
       qh[c] = *(const u32x4_t*)src;
       ql[c] = *(const u32x4_t*)(src + (size_t)p.Hp * r);
     }
@@ -248,9 +249,9 @@ bool attn_heads_applies(int B, int H, int d, int T, int r, bool appends) {
   return work <= most;
 }
 
-ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, float scale) {
+ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, FoldedLayout folded, float scale) {
   const int Hp = (a.H + 15) / 16 * 16;
-  const HeadsParams p{(const uint16_t*)a.q, (const uint16_t*)a.Bk, Qp, (const uint16_t*)a.Ck, (const uint16_t*)a.Cv,
+  const HeadsParams p{(const uint16_t*)a.q, (const uint16_t*)a.Bk, Qp, folded, (const uint16_t*)a.Ck, (const uint16_t*)a.Cv,
                       (const uint16_t*)a.Bv, a.basis_batch_stride, a.out, a.lse, a.scores, a.B, a.H, a.H / a.H_kv, Hp,
                       a.H_kv * a.d, a.T, a.T_cap, a.dt_out == AP_F32, scale};
   const size_t lds = (size_t)(a.T + kRows - 1) / kRows * kRows * 4;

@@ -35,7 +35,8 @@ constexpr int kTileBytesMax = kTok * (2 * 128 + 16);     // a wave's LDS region 
 #define AP_SMALL_WPE (MT * NKS <= 6 ? 2 : 1)
 
 struct SmallParams {
-  const uint16_t* Qp;   // [B][2][Hp][r] folded queries, hi + lo
+  const uint16_t* Qp;   // folded queries, hi + lo parts
+  FoldedLayout folded;
   const uint16_t* Ck;   // [B][T_cap][r]
   const uint16_t* Cv;
   float* part_ml;       // [B][S][H][2]
@@ -96,7 +97,7 @@ attn_small(const SmallParams p) {
   for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const uint16_t* qp = p.Qp + (((size_t)b * 2) * Hp + mt * 16 + n) * R + ks * 32 + g * 8;
+      const uint16_t* qp = p.Qp + ((size_t)b * 2) * Hp * R + p.folded.at(mt * 16 + n, ks * 32 + g * 8, R);
       qh[ks][mt] = *(const u32x4_t*)qp;
       if (SPLIT) ql[ks][mt] = *(const u32x4_t*)(qp + (size_t)Hp * R);
     }
@@ -437,12 +438,12 @@ bool attn_small_applies(int H, int r, int T, bool defer_v) {
   return (r == 64 || r == 128) && H <= 64 && mt * nks <= 12 && (!defer_v || T >= 2);
 }
 
-ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, const void* Ck, const void* Cv, float* part_ml,
+ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, FoldedLayout folded, const void* Ck, const void* Cv, float* part_ml,
                             float* part_U, float* pnew, float* scores, const int32_t* rank_k,
                             const int32_t* rank_v, const int32_t* bucket_off, const int32_t* bucket_idx, int F,
                             int B, int H, int T, int T_cap, int r, int nsplit, bool defer_v,
                             hipStream_t stream) {
-  SmallParams p{Qp, (const uint16_t*)Ck, (const uint16_t*)Cv, part_ml, part_U, pnew, scores,
+  SmallParams p{Qp, folded, (const uint16_t*)Ck, (const uint16_t*)Cv, part_ml, part_U, pnew, scores,
                 B, T, T_cap, r, H, nsplit, B % 8 == 0 ? 1 : 0, defer_v ? 1 : 0,
                 rank_k, rank_v, bucket_off, bucket_idx, F};
   const bool ragged = rank_k != nullptr || rank_v != nullptr;   // as everywhere in the library

@@ -439,7 +439,8 @@ __device__ __forceinline__ P* uni_ptr(P* ptr) {
 // attn_partial
 // ------------------------------------------------------------------------------------------
 struct AttnParams {
-  const uint16_t* Qp;   // [B][2][Hp][r]
+  const uint16_t* Qp;   // folded queries, hi + lo parts
+  FoldedLayout folded;
   const uint16_t* Ck;   // [B][T_cap][r]
   const uint16_t* Cv;
   const uint16_t* Sk;   // int8 / 4-bit coefficients only: fp16 scales [B][T_cap][r/64]
@@ -987,6 +988,7 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
   // q' operands (B operand of the score MFMA): lane (h=n, g) holds columns 32ks+8g..+7
   // (int8: columns 64m+16g..+7 for a block's first k-step, 64m+16g+8..+15 for its second)
   const uint16_t* Qp = uni_ptr(p.Qp);
+  const FoldedLayout folded{uni(p.folded.tiled) != 0};
   u32x4_t qhi[NKW][MT];
   u32x4_t qlo[SPLIT ? NKW : 1][MT];
 #pragma unroll
@@ -1006,7 +1008,7 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
         // (a head tile of the last group past all heads repeats the last tile: nothing of it is stored)
         int hq = cx.h0 + mt * 16;
         hq = (hq < Hp ? hq : Hp - 16) + n;
-        const uint16_t* qrow = Qp + (((size_t)cx.b * 2) * Hp + hq) * r + col;
+        const uint16_t* qrow = Qp + ((size_t)cx.b * 2) * Hp * r + folded.at(hq, col, r);
         qhi[i][mt] = *(const u32x4_t*)qrow;
         if (SPLIT) qlo[i][mt] = *(const u32x4_t*)(qrow + (size_t)Hp * r);
         if (I4) {                                          // the column order of code_row8_i4: 0,4,1,5,2,6,3,7
@@ -1814,19 +1816,22 @@ ap_status run_decode(const DecodeArgs& a) {
   const bool pair_v = a.v_new && !one_pass_v && a.k_new;
   // one basis for all sequences: matrix products where they are the shorter way
   const bool shared = a.basis_batch_stride == 0 && !one_pass_v;
+  FoldedLayout folded{false};              // as the launch writes it that folds
   // short contexts: what follows the appends in one launch, with the fold where nothing is appended.  (With the rule
   // for the value row overridden a step and its two halves stay on the kernels that the override is about.)
   const bool heads = !quant && !ragged && v_min < 0 && !one_pass_v &&
                      attn_heads_applies(a.B, a.H, a.d, a.T, a.r, a.k_new != nullptr);
-  if (heads && !a.k_new) return launch_attn_heads(a, nullptr, a.sm_scale * kLog2e);
+  if (heads && !a.k_new) return launch_attn_heads(a, nullptr, folded, a.sm_scale * kLog2e);
   if (shared && shared_project_applies(a.B, a.H, Hkv, a.d, a.r, a.k_new != nullptr)) {
     st = launch_shared_project(a.dt, a.Bk, a.Bv, a.k_new, a.v_new, a.q, (void*)a.Ck, (void*)a.Cv, Qp, a.B, a.H, Hkv, Hp, a.d,
                                a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream);
   } else if (Hkv == a.H) {
+    folded.tiled = true;
     st = launch_basis_rows(a.dt, a.Bk, a.basis_batch_stride, a.k_new, a.q, (void*)a.Ck, Qp, a.B, a.H, Hp,
                            a.d, a.H * a.d, a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream,
                            pair_v ? a.Bv : nullptr, pair_v ? a.v_new : nullptr, pair_v ? (void*)a.Cv : nullptr);
   } else if (pair_v && rows_grouped_applies(a.H / Hkv, a.d, HDkv)) {
+    folded.tiled = true;
     st = launch_rows_grouped(a.dt, a.Bk, a.Bv, a.basis_batch_stride, a.k_new, a.v_new, a.q, (void*)a.Ck, (void*)a.Cv, Qp,
                              a.B, a.H, Hkv, Hp, a.d, a.r, a.T - 1, a.T_cap, a.sm_scale * kLog2e, a.stream);
   } else {
@@ -1847,9 +1852,10 @@ ap_status run_decode(const DecodeArgs& a) {
                            a.B, 0, 0, 8, HDkv, a.r, a.T - 1, a.T_cap, 1.0f, a.stream);
     if (st != AP_OK) return st;
   }
-  if (heads) return launch_attn_heads(a, Qp, 1.f);
+  if (heads) return launch_attn_heads(a, Qp, folded, 1.f);
   AttnParams p{};
   p.Qp = Qp;
+  p.folded = folded;
   p.Ck = (const uint16_t*)a.Ck;
   p.Cv = (const uint16_t*)a.Cv;
   p.part_ml = ml;
@@ -1879,7 +1885,7 @@ ap_status run_decode(const DecodeArgs& a) {
   // small uniform ranks take the kernel whose waves work alone on whole tiles (attn_small.hip);
   // everything else the two-role kernel
   if (small)
-    st = launch_attn_small(a.dt, Qp, a.Ck, a.Cv, ml, U, (float*)(ws + wl.pn), a.scores, a.rank_k, a.rank_v,
+    st = launch_attn_small(a.dt, Qp, folded, a.Ck, a.Cv, ml, U, (float*)(ws + wl.pn), a.scores, a.rank_k, a.rank_v,
                            a.bucket_off, a.bucket_idx, a.F, a.B, a.H, a.T, a.T_cap, a.r, S, one_pass_v, a.stream);
   else
     st = dispatch_attn<Tag, SPLIT>(p, a.B, a.stream);
