@@ -480,7 +480,7 @@ struct AttnParams {
 //                     stream the C_v rows HBM -> LDS with direct-to-LDS loads through a ring
 //                     of 16-row units, several tiles ahead, so no VGPR is spent on staging
 //                     and every LDS byte is read exactly once.
-//   softmax:          the score waves, 4*MT heads each (eight lanes per head): they keep
+//   softmax:          the score waves (three roles: waves 4-7, and the sum waves are 8-11), 4*MT heads each (eight lanes per head): they keep
 //                     (reference exponent, sum) and publish the weights in MFMA operand layout
 //                     plus a per-head rescale factor.  (Token-split mode: all eight waves.)
 // The sum waves are a tile behind: they add up tile t-1 in two parts, next to the scores and next
@@ -488,6 +488,9 @@ struct AttnParams {
 // ready") keep the roles in step.  A tile then costs about what its longer role needs; with the
 // softmax of tile t on all eight waves, between the scores and the sum, it cost that plus the
 // softmax (us a pass: 21 sequences, 32 / 8 heads, rank 256 36.7 -> 34.7, 8 of rank 512 36.9 -> 36.2).
+// Three roles (R3, see three_roles): the softmax has four waves of its own and is a tile behind the scores, the
+// weighted sum one further, so a tile costs what its longest role needs and one barrier; partial scores and weights
+// are kept for two tiles.
 // The softmax reference exponent only moves when a score exceeds it by more than kLazy, so the
 // rescale factor is 1 on almost every tile.
 //
@@ -529,10 +532,12 @@ __device__ __forceinline__ void wg_coords(int nsplit, int hgroups, int xcd_aware
 // tile is then complete without the other waves' partial sums, and one pair of barriers covers
 // four tiles: at small ranks the tile loop is bound by that dependency chain, not by memory.
 // Q: coefficient storage, 0 = 16-bit, 1 = int8 codes, 2 = 4-bit codes (both with fp16 scales).
-template <class Tag, int MT, bool SPLIT, bool RAGGED, int Q, bool TS = false>
+template <class Tag, int MT, bool SPLIT, bool RAGGED, int Q, bool TS, bool R3>
 struct WaveCtx {
   static constexpr bool I8 = Q != 0, I4 = Q == 2;
-  static constexpr int NSUB = TS ? 4 : 1;   // tiles per barrier pair
+  static constexpr int NSUB = TS ? 4 : R3 ? 2 : 1;   // tiles per barrier pair; three roles: tiles whose weights are kept
+  static constexpr int SM0 = R3 ? 4 : 0;             // the first wave that takes softmaxes
+  static constexpr int NWAVE = R3 ? 12 : 8;
   static constexpr int HPW = TS ? 2 * MT : 4 * MT;   // heads finalised per wave (token-split: all eight)
   // bytes of a coefficient row
   static __device__ __forceinline__ int row_bytes_of(int r) { return I4 ? r >> 1 : (I8 ? r : 2 * r); }
@@ -542,7 +547,7 @@ struct WaveCtx {
   int h0;            // first head of this workgroup's group
   int pitch, nblk, unit_bytes;
   char* ring;
-  f32x4_t* xchg;     // [4 score waves][16*MT heads][9]: 8 slots (4*tt+g) + 1 pad per head
+  f32x4_t* xchg;     // [1, or 2 tiles (R3)][4 score waves][16*MT heads][9]: 8 slots (4*tt+g) + 1 pad per head
   u32x4_t* Pbuf;     // [MT][hi,lo][64 lanes]
   float* abuf;       // [16*MT] rescale factors
   uint16_t* vsb;     // I8: [2][r/64][32] value scales of the tile in flight (fp16 bits)
@@ -590,7 +595,7 @@ struct WaveCtx {
     unit_bytes = nblk * 1024;
     ring = smem;
     xchg = (f32x4_t*)(smem + nh * unit_bytes);
-    Pbuf = (u32x4_t*)(xchg + 4 * 16 * MT * 9);
+    Pbuf = (u32x4_t*)(xchg + (R3 ? 2 : 1) * 4 * 16 * MT * 9);
     abuf = (float*)(Pbuf + NSUB * MT * 2 * 64);
     row_bytes = (uint32_t)row_bytes_of(r);
     vsb = (uint16_t*)(abuf + NSUB * 16 * MT);
@@ -624,13 +629,13 @@ struct WaveCtx {
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       const int hl = 8 * q + (lane >> 3);
-      owner[q] = hl < HPW && (TS || w < 4);
-      o_hh[q] = owner[q] ? w * HPW + hl : 0;
+      owner[q] = hl < HPW && (TS || (w >= SM0 && w < SM0 + 4));
+      o_hh[q] = owner[q] ? (w - SM0) * HPW + hl : 0;
       m_ref[q] = -INFINITY; l_part[q] = 0.f;
     }
   }
 
-  // RAGGED: tiles of this split, their token indices and ranks into LDS (all 512 threads).
+  // RAGGED: tiles of this split, their token indices and ranks into LDS (all threads).
   __device__ __forceinline__ void build_tile_table(const AttnParams& p) {
     const int F = uni(p.F);
     const int32_t* boff = uni_ptr(p.bucket_off) + (size_t)b * (F + 1);
@@ -665,7 +670,7 @@ struct WaveCtx {
       while (y) { const int tmp = x % y; x = y; y = tmp; }
       if (x == 1 || ntl <= 1) break;
     }
-    for (int e = threadIdx.x; e < ntl * kTile; e += 512) {
+    for (int e = threadIdx.x; e < ntl * kTile; e += 64 * NWAVE) {
       const int i = e >> 5, l = e & 31;
       const int isrc = ntl > 1 ? (int)((uint32_t)(i * stride) % (uint32_t)ntl) : 0;
       const int j = s + isrc * nsplit;
@@ -741,7 +746,7 @@ struct WaveCtx {
     f32x4_t sc[NP];
 #pragma unroll
     for (int q = Q0; q < Q1; ++q) {
-      const int xi = o_hh[q] * 9 + (lane & 7);
+      const int xi = (R3 ? (t & 1) * 4 * 16 * MT * 9 : 0) + o_hh[q] * 9 + (lane & 7);
       sc[q] = xchg[xi];
 #pragma unroll
       for (int sw = 1; sw < 4; ++sw) sc[q] += xchg[sw * 16 * MT * 9 + xi];
@@ -796,7 +801,7 @@ struct WaveCtx {
     }
 #pragma unroll
     for (int q = Q0; q < Q1; ++q) {
-      const int mt = o_hh[q] >> 4, ln = (o_hh[q] & 15) + 16 * o_gg;
+      const int mt = (R3 ? (t & 1) * MT : 0) + (o_hh[q] >> 4), ln = (o_hh[q] & 15) + 16 * o_gg;
       if (I8) {
         // int8 coefficients: the weights stay fp32 (the sum waves fold the value scales in before
         // rounding); the two 16-byte slots of a lane hold tokens 4g .. 4g+3 and 16+4g .. +3
@@ -826,7 +831,7 @@ struct WaveCtx {
           if (SPLIT) *(ph + 2 * 64) = lo;               // [mt][1][ln]
         }
       }
-      if (owner[q] && (lane & 7) == 0) abuf[o_hh[q]] = alpha[q];
+      if (owner[q] && (lane & 7) == 0) abuf[(R3 ? (t & 1) * 16 * MT : 0) + o_hh[q]] = alpha[q];
     }
   }
 
@@ -964,7 +969,7 @@ struct WaveCtx {
 #define AP_T_REPORT
 #endif
 
-template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
+template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q, bool R3>
 __device__ __forceinline__ void score_role(const AttnParams& p) {
   constexpr bool I8 = Q != 0, I4 = Q == 2;
   constexpr uint32_t UB = I4 ? 32 : 64;                   // bytes of a row per unit (a scale block, or a k-step)
@@ -976,7 +981,7 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
   constexpr int NKW = TS ? RMAX / 32 : (I8 ? 2 * NBW : (RMAX / 32 + 3) / 4);   // score k-steps per score wave
   constexpr int NA = I8 ? NBW : NKW;                      // 16-byte row loads per 16-row half
   AP_T_ENTRY
-  WaveCtx<Tag, MT, SPLIT, RAGGED, Q, TS> cx;
+  WaveCtx<Tag, MT, SPLIT, RAGGED, Q, TS, R3> cx;
   cx.init(p);
   const int Hp = (cx.H + 15) & ~15;                       // heads of all groups, as Qp is laid out
   float* part_ml = uni_ptr(p.part_ml);
@@ -1173,9 +1178,10 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       // tile t's value scales for the sum waves (buffer t & 1: its previous reader, the weighted sum
       // of tile t - 2, ended before the last barrier of tile t - 1), tile t + 1's key scales for the
       // score waves (buffer (t + 1) & 1: last read for tile t - 1)
-      put_scales(cx.vsb + (t & 1) * nsb * kTile, vsr);
+      // (three roles: tile t's weighted sum is a barrier further on, and so are its value scales)
+      if (!R3 || t > 0) put_scales(cx.vsb + ((R3 ? t - 1 : t) & 1) * nsb * kTile, vsr);
       if (t + 1 < cx.ntl) put_scales(cx.ksb + ((t + 1) & 1) * nsb * kTile, ksr);
-      if (t + 1 < cx.ntl) load_scales(Sv_b, vsr, t + 1);
+      if (R3 ? t > 0 : t + 1 < cx.ntl) load_scales(Sv_b, vsr, R3 ? t : t + 1);
       if (t + 2 < cx.ntl) load_scales(Sk_b, ksr, t + 2);
     } else {
       int nlive = NKW;
@@ -1186,14 +1192,16 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
       if (!(cx.dbg & 2)) score_tile<Tag, MT, SPLIT, NKW>(A, qhi, qlo, sp, nlive);
     }
     AP_TICK(1)
+    f32x4_t* xt = cx.xchg + (R3 ? (t & 1) * 4 * 16 * MT * 9 : 0);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      cx.xchg[(w * 16 * MT + mt * 16 + n) * 9 + g] = sp[mt][0];
-      cx.xchg[(w * 16 * MT + mt * 16 + n) * 9 + 4 + g] = sp[mt][1];
+      xt[(w * 16 * MT + mt * 16 + n) * 9 + g] = sp[mt][0];
+      xt[(w * 16 * MT + mt * 16 + n) * 9 + 4 + g] = sp[mt][1];
     }
     if (t + 1 < cx.ntl) load_A(t + 1, A);                 // lands while the tile is finished
     wg_barrier();                                         // partial scores of tile t ready
     AP_TICK(2)
+    if constexpr (R3) return;                             // the softmax waves take it from here
     cx.finalize_softmax(cx.tile_valid(t), cx.tile_new(t), t);
     AP_TICK(3)
     wg_barrier();                                         // weights of tile t ready
@@ -1214,12 +1222,31 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
   }
   for (int t = 0; t < cx.ntl; ++t) tile_step(t);
   AP_T_STAMP(62)
-  cx.store_ml(part_ml);
+  if constexpr (R3) {
+    if (I8 && cx.ntl > 0) put_scales(cx.vsb + ((cx.ntl - 1) & 1) * nsb * kTile, vsr);
+    if (cx.ntl > 0) wg_barrier();                         // the last tile's weights and value scales ready
+  } else {
+    cx.store_ml(part_ml);
+  }
   AP_TICK(6)
   AP_T_REPORT
 }
 
-template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
+// Three roles: the softmax of tile t while the score waves are at tile t + 1 and the sum waves at tile t - 1.
+template <class Tag, int MT, bool SPLIT, bool RAGGED, int Q>
+__device__ __forceinline__ void softmax_role(const AttnParams& p) {
+  WaveCtx<Tag, MT, SPLIT, RAGGED, Q, false, true> cx;
+  cx.init(p);
+  if constexpr (Q != 0) wg_barrier();                     // the score waves' first key scales
+  for (int t = 0; t < cx.ntl; ++t) {
+    wg_barrier();                                         // partial scores of tile t ready
+    cx.finalize_softmax(cx.tile_valid(t), cx.tile_new(t), t);
+  }
+  if (cx.ntl > 0) wg_barrier();                           // the last tile's weights ready
+  cx.store_ml(uni_ptr(p.part_ml));
+}
+
+template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q, bool R3>
 __device__ __forceinline__ void sum_role(const AttnParams& p) {
   constexpr bool I8 = Q != 0, I4 = Q == 2;
   constexpr bool TS = !RAGGED && !I8 && RMAX == 128;              // token-split mode (see WaveCtx)
@@ -1231,12 +1258,12 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
   constexpr int MAXBLK = (kHalf * (RB / 16 + 1) + 63) / 64;       // 1 KiB blocks per ring unit
   constexpr int NSLOT = (MAXBLK + 3) / 4;
   AP_T_ENTRY
-  WaveCtx<Tag, MT, SPLIT, RAGGED, Q, TS> cx;
+  WaveCtx<Tag, MT, SPLIT, RAGGED, Q, TS, R3> cx;
   cx.init(p);
   float* part_U = uni_ptr(p.part_U);
   float* part_ml = uni_ptr(p.part_ml);
   const int n = cx.n, g = cx.g, r = cx.r, lane = cx.lane;
-  const int cp = cx.w - 4;                                // which 64 bytes of every group
+  const int cp = cx.w - (R3 ? 8 : 4);                     // which 64 bytes of every group
   const int RT = cx.nh >> 1;                              // ring capacity in tiles
 
   // ---- this wave's share of a C_v ring unit: 1 KiB blocks cp, cp+4, ...; per lane the
@@ -1403,16 +1430,18 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
     u32x4_t Phi[MT], Plo[MT];
     f32x4_t P32[I8 ? MT : 1][2];
     float alpha[MT];
-    auto read_weights = [&]() {
+    auto read_weights = [&](int t) {
+      const u32x4_t* Pt = cx.Pbuf + (R3 ? (t & 1) * MT * 2 * 64 : 0);
+      const float* at = cx.abuf + (R3 ? (t & 1) * 16 * MT : 0);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        alpha[mt] = cx.abuf[mt * 16 + n];
-        Phi[mt] = cx.Pbuf[(mt * 2 + 0) * 64 + lane];
-        if (SPLIT) Plo[mt] = cx.Pbuf[(mt * 2 + 1) * 64 + lane];
+        alpha[mt] = at[mt * 16 + n];
+        Phi[mt] = Pt[(mt * 2 + 0) * 64 + lane];
+        if (SPLIT) Plo[mt] = Pt[(mt * 2 + 1) * 64 + lane];
         else { u32x4_t z = {0, 0, 0, 0}; Plo[mt] = z; }
         if constexpr (I8) {
           P32[mt][0] = __builtin_bit_cast(f32x4_t, Phi[mt]);
-          P32[mt][1] = __builtin_bit_cast(f32x4_t, cx.Pbuf[(mt * 2 + 1) * 64 + lane]);
+          P32[mt][1] = __builtin_bit_cast(f32x4_t, Pt[(mt * 2 + 1) * 64 + lane]);
         }
       }
     };
@@ -1450,13 +1479,40 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
     // bf16 61.6 -> 59.1); a longer one is better off with the requests in two parts (rank 512 68.7 / 69.2).
     const bool early = kWhole && RT == 2;
     const int done = early ? 1 : 2;
-    for (int t = 0; t < cx.ntl; ++t) {
+    auto landed = [&](int t, int upto) {                 // waits for tile t; tiles t + 1 .. upto may stay in flight
+      upto = upto < cx.ntl ? upto : cx.ntl - 1;
+      if (RAGGED) {
+        int pending = 0;
+        for (int lt = t + 1; lt <= upto; ++lt) pending += 2 * tile_requests(lt);
+        wait_vmcnt(pending);
+      } else {
+        wait_vmcnt((upto - t) * 2 * n_issue);
+      }
+    };
+    // Three roles, one barrier a tile: in step i the scores of tile i, the softmax of tile i - 1 and the weighted sum
+    // of tile i - 2, whose slots are asked for again in the step after.
+    if constexpr (R3) {
+      for (int i = 0; i <= cx.ntl && cx.ntl > 0; ++i) {
+        if (i == 1) {
+#pragma nounroll
+          for (int lt = 1; lt < RT && lt < cx.ntl; ++lt) issue_tile(lt);
+        } else if (i >= 3 && i - 3 + RT < cx.ntl) {
+          issue_tile(i - 3 + RT);
+        }
+        if (i >= 2) {
+          read_weights(i - 2);
+          add_part(i - 2, First{}, Last{});
+        }
+        if (i >= 1) landed(i - 1, i >= 3 ? i - 3 + RT : RT - 1);
+        wg_barrier();
+      }
+    } else for (int t = 0; t < cx.ntl; ++t) {
       AP_T_STAMP(t)
       // tile t-2's slots are free (every sum wave passed the last barrier of tile t-1 after it)
       const int refill = t >= done && t - done + RT < cx.ntl ? t - done + RT : -1;
       if (refill >= 0 && !early) issue_half(refill, 0);
       if (t > 0) {
-        read_weights();                                  // the next softmax overwrites them: before the barrier
+        read_weights(t - 1);                             // the next softmax overwrites them: before the barrier
         add_part(t - 1, First{}, Mid{});
       }
       AP_TICK(1)
@@ -1473,21 +1529,13 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
       AP_TICK(3)
       {
         // tile t's rows must have landed; the tiles issued after it may stay in flight
-        int upto = t >= done ? t - done + RT : RT - 1;
-        upto = upto < cx.ntl ? upto : cx.ntl - 1;
-        if (RAGGED) {
-          int pending = 0;
-          for (int lt = t + 1; lt <= upto; ++lt) pending += 2 * tile_requests(lt);
-          wait_vmcnt(pending);
-        } else {
-          wait_vmcnt((upto - t) * 2 * n_issue);
-        }
+        landed(t, t >= done ? t - done + RT : RT - 1);
       }
       wg_barrier();                                      // weights of tile t ready; its rows visible to every wave
       AP_TICK(4)
     }
     if (cx.ntl > 0) {
-      read_weights();
+      read_weights(cx.ntl - 1);
       add_part(cx.ntl - 1, First{}, Mid{});
       add_part(cx.ntl - 1, Mid{}, Last{});
     }
@@ -1554,15 +1602,15 @@ __device__ __forceinline__ void sum_role(const AttnParams& p) {
 
 template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
 __device__ __noinline__ void score_role_call(const AttnParams& p) {
-  score_role<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
+  score_role<Tag, MT, RMAX, SPLIT, RAGGED, Q, false>(p);
 }
 template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
 __device__ __noinline__ void sum_role_call(const AttnParams& p) {
-  sum_role<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
+  sum_role<Tag, MT, RMAX, SPLIT, RAGGED, Q, false>(p);
 }
 
-template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q, bool R3>
+__global__ void __launch_bounds__(R3 ? 768 : 512) __attribute__((amdgpu_waves_per_eu(R3 ? 3 : 2, R3 ? 3 : 2)))
 attn_partial(const AttnParams p) {
   {
     int b, s, hg;
@@ -1574,12 +1622,15 @@ attn_partial(const AttnParams p) {
   // at the start of every wave.  Only the largest shape (64 heads at rank 640), whose two roles
   // do not fit one register allocation without spilling inside the tile loop, keeps the calls.
   constexpr bool kOutline = MT == 4 && RMAX > 512;
-  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < 4) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w < 4) {
     if constexpr (kOutline) score_role_call<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
-    else score_role<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
+    else score_role<Tag, MT, RMAX, SPLIT, RAGGED, Q, R3>(p);
+  } else if (R3 && w < 8) {
+    if constexpr (R3) softmax_role<Tag, MT, SPLIT, RAGGED, Q>(p);
   } else {
     if constexpr (kOutline) sum_role_call<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
-    else sum_role<Tag, MT, RMAX, SPLIT, RAGGED, Q>(p);
+    else sum_role<Tag, MT, RMAX, SPLIT, RAGGED, Q, R3>(p);
   }
 }
 
@@ -1667,45 +1718,72 @@ WsLayout ws_layout(int B, int H, int d, int T, int r) {
   return w;
 }
 
-template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q>
+// LDS of a launch: the value ring, in units of 16 rows, takes what the rest leaves.
+template <int MT, int RMAX, bool RAGGED, int Q, bool R3>
+struct AttnLds {
+  static constexpr size_t kBudget = 160 * 1024;
+  static constexpr bool TS = !RAGGED && Q == 0 && RMAX == 128;
+  size_t unit, fixed;
+  int ntl_cap;
+  explicit AttnLds(const AttnParams& p) {
+    constexpr int kept = TS ? 4 : R3 ? 2 : 1;              // tiles whose weights are kept (see WaveCtx)
+    unit = (size_t)((kHalf * ((Q == 2 ? p.r / 2 : (Q ? p.r : 2 * p.r)) / 16 + 1) + 63) / 64) * 1024;
+    fixed = (size_t)(R3 ? 2 : 1) * 4 * 16 * MT * 9 * 16 + (size_t)kept * MT * (2 * 64 * 16 + 16 * 4);
+    if (Q) fixed += (size_t)4 * (p.r / 64) * kTile * 2;    // value and key scales of two tiles
+    ntl_cap = 0;
+    if (RAGGED) {
+      // every group may end in a partial tile; tiles are dealt round-robin to the splits
+      const int ntiles_max = (p.T + kTile - 1) / kTile + p.F;
+      ntl_cap = (ntiles_max + p.nsplit - 1) / p.nsplit;
+      fixed += (size_t)ntl_cap * (kTile + 4) * 4;
+    }
+  }
+  int ring() const {
+    if (fixed >= kBudget) return 0;
+    const int nh = (int)((kBudget - fixed) / unit);
+    if (TS) return nh >= 24 ? 24 : nh >= 16 ? 16 : 0;      // four tiles are consumed per round: a ring of 8 or 12
+    return nh > 12 ? 12 : nh & ~1;
+  }
+};
+
+// Where twelve waves in three roles take the place of eight in two, as far as each finds its registers: quantised
+// rows, whose tiles are bound by the chain of conversion, scores, softmax and barriers, and gathered ones; other rows at
+// ranks 192 and 256 with more than one head tile, from four tiles a split on (launch_attn).  Us a pass, two roles / three:
+// int8, 40 heads, 64 x 3000 tokens, rank 256 1.18 times as fast, 16 x 4224, 32 heads, rank 512 61.4 / 59.3; 32768
+// gathered tokens, eight steps and their selection 289 / 277; 16 x 4224, 40 heads, rank 192 bf16 33.8 / 32.5.  16-bit rows
+// of rank 512, which are bound by memory, lost 1 to 2 % (197.6 / 200.1), splits of one to three tiles the same.
+// (Registers would be left for the key rows of a second tile: asked for two tiles ahead they cost 1 to 6 %.)
+constexpr bool three_roles(int MT, int RMAX, bool SPLIT, bool RAGGED, int Q) {
+  if (Q == 0 && !RAGGED) return RMAX == 256 && MT > 1;
+  return RMAX <= (MT <= 2 ? 640 : MT == 3 && !SPLIT ? 512 : 256);
+}
+
+template <class Tag, int MT, int RMAX, bool SPLIT, bool RAGGED, int Q, bool R3 = false>
 ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
-  constexpr bool I8 = Q != 0;
-  if constexpr (MT == 4 && RMAX > 512 && !RAGGED && (SPLIT || I8)) {
+  constexpr bool kThree = three_roles(MT, RMAX, SPLIT, RAGGED, Q);
+  if constexpr (!R3 && kThree && Q == 0) {
+    const bool room = AttnLds<MT, RMAX, RAGGED, Q, true>(p).ring() >= 6;    // a ring of three tiles
+    const int n_tok = (p.T + p.nsplit - 1) / p.nsplit;
+    if (room && (RAGGED || n_tok > 3 * kTile)) return launch_attn<Tag, MT, RMAX, SPLIT, RAGGED, Q, true>(p, B, stream);
+  }
+  if constexpr (!R3 && kThree && Q != 0) {
+    return launch_attn<Tag, MT, RMAX, SPLIT, RAGGED, Q, true>(p, B, stream);
+  } else if constexpr (MT == 4 && RMAX > 512 && !RAGGED && (SPLIT || Q != 0)) {
     set_error("ap_decode_attn: H=%d r=%d always takes head groups", p.H, p.r);
     return AP_ERR_UNSUPPORTED;
   } else {
-  const int cpr = (Q == 2 ? p.r / 2 : (I8 ? p.r : 2 * p.r)) / 16;
-  const size_t unit = (size_t)((kHalf * (cpr + 1) + 63) / 64) * 1024;
-  constexpr bool TS = !RAGGED && !I8 && RMAX == 128;
-  constexpr int NSUB = TS ? 4 : 1;
-  size_t fixed = (size_t)4 * 16 * MT * 9 * 16 + (size_t)NSUB * MT * 2 * 64 * 16 + (size_t)NSUB * MT * 16 * 4;
-  if (I8) fixed += (size_t)4 * (p.r / 64) * kTile * 2;     // value and key scales of two tiles
-  if (RAGGED) {
-    // every group may end in a partial tile; tiles are dealt round-robin to the splits
-    const int ntiles_max = (p.T + kTile - 1) / kTile + p.F;
-    p.ntl_cap = (ntiles_max + p.nsplit - 1) / p.nsplit;
-    fixed += (size_t)p.ntl_cap * (kTile + 4) * 4;
-  }
-  const size_t budget = 160 * 1024;
-  AP_REQUIRE(fixed + (TS ? 2 : 4) * unit <= budget, AP_ERR_UNSUPPORTED,   // two tiles; always so at H <= 64, r <= 640
+  const AttnLds<MT, RMAX, RAGGED, Q, R3> m(p);
+  const int nh = m.ring();
+  AP_REQUIRE(nh >= (m.TS ? 16 : 4), AP_ERR_UNSUPPORTED,    // two tiles (eight); always so at H <= 64, r <= 640
              "ap_decode_attn: H=%d r=%d needs more LDS than 160 KiB", p.H, p.r);
-  int nh = (int)((budget - fixed) / unit);
-  if (TS) {
-    // four tiles are consumed per round: a ring of 8 or 12 tiles (16-row units come in pairs)
-    nh = nh >= 24 ? 24 : 16;
-    AP_REQUIRE(fixed + (size_t)nh * unit <= budget, AP_ERR_UNSUPPORTED,
-               "ap_decode_attn: H=%d r=%d needs more LDS than 160 KiB", p.H, p.r);
-  } else {
-    if (nh > 12) nh = 12;
-    nh &= ~1;
-  }
+  p.ntl_cap = m.ntl_cap;
   p.nh = nh;
-  size_t lds = (size_t)nh * unit + fixed;
-  auto kern = attn_partial<Tag, MT, RMAX, SPLIT, RAGGED, Q>;
+  const size_t lds = (size_t)nh * m.unit + m.fixed;
+  auto kern = attn_partial<Tag, MT, RMAX, SPLIT, RAGGED, Q, R3>;
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)budget);
+                                       (int)m.kBudget);
     if (e != hipSuccess) {
       set_error("hipFuncSetAttribute: %s", hipGetErrorString(e));
       return AP_ERR_HIP;
@@ -1718,9 +1796,9 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
   const int units = p.hgroups > 1 ? (B * p.nsplit + 7) / 8 * 8 * p.hgroups : B * p.nsplit;
   hipEvent_t ev0, ev1;
   if (prof_events(&ev0, &ev1))             // timing on: the events carry this launch's own start and end
-    hipExtLaunchKernelGGL(kern, dim3(units), dim3(512), (uint32_t)lds, stream, ev0, ev1, 0u, p);
+    hipExtLaunchKernelGGL(kern, dim3(units), dim3(R3 ? 768 : 512), (uint32_t)lds, stream, ev0, ev1, 0u, p);
   else
-    hipLaunchKernelGGL(kern, dim3(units), dim3(512), lds, stream, p);
+    hipLaunchKernelGGL(kern, dim3(units), dim3(R3 ? 768 : 512), lds, stream, p);
   return AP_OK;
   }
 }

@@ -1,7 +1,8 @@
-"""GPU parity where a split's heads are shared out to workgroups (short contexts): one, two, three and four
-head tiles, the last one partly filled, one tile of 16 heads or two per workgroup, batches whose splits make
+"""GPU parity of attention over token splits, in its forms.  Short contexts, where a split's heads are shared out to
+workgroups: one, two, three and four head tiles, the last one partly filled, one tile of 16 heads or two per workgroup, batches whose splits make
 whole eights and not, every coefficient format, gathered rows with the logits written, and the fused step whose
-newest value row the expansion produces."""
+newest value row the expansion produces.  Longer splits, whose softmax has waves of its own: fewer tiles than that
+pipeline is deep, as many as the value ring holds and more, for every coefficient format it serves."""
 import math
 
 import numpy as np
@@ -30,11 +31,20 @@ CASES = [  # dtype, B, H, H_kv, d, r, T, mode
     ("f16", 8, 40, 40, 32, 192, 600, "i8"),
     ("f16", 3, 64, 64, 32, 640, 700, "i8"),
     ("f16", 8, 32, 32, 32, 256, 700, "i4"),
+    ("bf16", 64, 40, 40, 32, 192, 520, "attend"),     # five tiles a split
+    ("f16", 64, 24, 8, 64, 256, 1500, "late"),        # twelve, the last token's value row not there yet
+    ("bf16", 32, 64, 8, 64, 256, 1100, "attend"),     # four head tiles: a ring of three tiles
+    ("f16", 1, 16, 16, 64, 640, 20, "i8"),            # one tile
+    ("f16", 64, 20, 20, 32, 512, 250, "i8"),          # two tiles a split
+    ("f16", 64, 40, 8, 64, 448, 1100, "i8"),          # nine, three head tiles
+    ("f16", 64, 32, 8, 128, 640, 900, "i4"),          # eight
+    ("f16", 16, 16, 16, 64, 512, 1700, "ragged"),
+    ("bf16", 32, 32, 8, 64, 256, 1300, "ragged"),
 ]
 
 
 @pytest.mark.parametrize("dtype,B,H,H_kv,d,r,T,mode", CASES)
-def test_head_groups(dtype, B, H, H_kv, d, r, T, mode):
+def test_forms_of_the_split_kernel(dtype, B, H, H_kv, d, r, T, mode):
     from paper_2603_23914_amd import binding as ap
     steps = 1 if mode in ("step", "late") else 0
     case = wl.decode_case(dtype, B, H_kv, d, r, T - steps, steps=steps, seed=H * 7 + T, append=steps > 0)
