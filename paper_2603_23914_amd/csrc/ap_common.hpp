@@ -80,6 +80,8 @@ struct FoldedLayout {
   __host__ __device__ constexpr size_t at(int h, int j, int r) const {
     return (size_t)(h >> 4) * 16 * r + (h & 15) * (tiled ? 8 : r) + (j >> 3) * (tiled ? 128 : 8) + (j & 7);
   }
+  // eight columns on
+  __host__ __device__ constexpr uint32_t chunk() const { return tiled ? 128 : 8; }
 };
 
 // ---- launchers (defined in the .hip files) -------------------------------------

@@ -234,18 +234,18 @@ __global__ void __launch_bounds__(kThreads) attn_heads(const HeadsParams p) {
 }  // namespace
 
 // Where a head per workgroup is the shorter way: its rows come out of L2 at some 120 GB/s per CU, T r 4 bytes for
-// every 256 workgroups, against the launches that it saves, two without an append, else one.  Above rank 128 the other
-// way is attn_partial, which loses less to a short context than attn_small does.  Us a pass there / here, 32 heads of
-// 128 in bf16: one sequence of 321 tokens, rank 64 step 14.8 / 10.0, attention alone 14.2 / 5.5; 8 of 800, rank 128
-// 21.1 / 15.8, 19.6 / 10.4; 8 of 321, rank 256 19.5 / 18.6, 17.1 / 12.3; of 800 21.2 / 23.4 (left there), 18.5 / 16.5;
-// 16 of 800, rank 128 25.1 / 25.4 (left there), 22.5 / 19.1; 15 of 1930, 16 heads of 64, rank 64 12.1 / 16.3 (left there).
+// every 256 workgroups, against the launches that it saves, two without an append, else one.  Us a pass over token
+// splits / here, 32 heads of 128 in bf16: one sequence of 321 tokens, rank 64 step 14.8 / 10.0, attention alone 14.2 / 5.5; 8 of
+// 700, rank 128 16.5 / 15.5, 16.1 / 10.3; 8 of 321, rank 256 19.5 / 18.6, 17.1 / 12.3; of 800 21.2 / 23.4 (left there),
+// 18.5 / 16.5; 16 of 300, rank 128 17.9 / 21.0 (left there), 16.9 / 14.7.
 bool attn_heads_applies(int B, int H, int d, int T, int r, bool appends) {
   if (r % 64 != 0 || r > 256 || (d != 64 && d != 128)) return false;
   const int64_t rounds = ((int64_t)B * H + 255) / 256, work = (int64_t)T * r * rounds;
-  if (rounds > 2 || (rounds == 2 && r > 128 && appends)) return false;
-  int64_t most = r <= 128 ? (appends ? 128 << 10 : 256 << 10) : (appends ? 96 << 10 : 192 << 10);
-  if (rounds == 2 && r > 128) most = most * 3 / 4;
-  if (H <= 16) most = most * 3 / 8;                    // a head tile of their own costs the other kernels less
+  if (rounds > 2 || (rounds == 2 && r > 64 && appends)) return false;
+  int64_t most = appends ? (r <= 128 ? 88 << 10 : 96 << 10) : r == 64 ? 256 << 10 : r == 128 ? 208 << 10 : 192 << 10;
+  if (rounds == 2 && r > 64) most = most * 3 / 4;
+  // a head tile of their own costs the other kernels less: 15 of 1930, 16 heads of 64, rank 64 12.1 / 16.3 a step
+  if (H <= 16) most /= 2 * rounds;
   return work <= most;
 }
 

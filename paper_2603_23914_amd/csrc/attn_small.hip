@@ -93,11 +93,13 @@ attn_small(const SmallParams p) {
 
   // folded queries: B operand of the score product, lane (head n of tile mt, g): columns 32 ks + 8 g ..
   u32x4_t qh[NKS][MT], ql[SPLIT ? NKS : 1][MT];
+  const uint16_t* qb = p.Qp + (size_t)b * 2 * Hp * R + p.folded.at(n, g * 8, R);
+  const uint32_t qstep = 4 * p.folded.chunk();
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const uint16_t* qp = p.Qp + ((size_t)b * 2) * Hp * R + p.folded.at(mt * 16 + n, ks * 32 + g * 8, R);
+      const uint16_t* qp = qb + mt * 16 * R + ks * qstep;
       qh[ks][mt] = *(const u32x4_t*)qp;
       if (SPLIT) ql[ks][mt] = *(const u32x4_t*)(qp + (size_t)Hp * R);
     }

@@ -994,6 +994,8 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
   // (int8: columns 64m+16g..+7 for a block's first k-step, 64m+16g+8..+15 for its second)
   const uint16_t* Qp = uni_ptr(p.Qp);
   const FoldedLayout folded{uni(p.folded.tiled) != 0};
+  const uint32_t chunk = folded.chunk();
+  const uint16_t* qb = Qp + ((size_t)cx.b * 2) * Hp * r + folded.at(n, I8 ? g * 16 : g * 8, r);
   u32x4_t qhi[NKW][MT];
   u32x4_t qlo[SPLIT ? NKW : 1][MT];
 #pragma unroll
@@ -1009,11 +1011,11 @@ __device__ __forceinline__ void score_role(const AttnParams& p) {
 #else
       if (unit < my_nks) {
 #endif
-        const int col = I8 ? (w + 4 * unit) * 64 + g * 16 + (i & 1) * 8 : (ufirst + ustep * i) * 32 + g * 8;
+        const int col = I8 ? (w + 4 * unit) * 64 + (i & 1) * 8 : (ufirst + ustep * i) * 32;   // and the lane's own, in qb
         // (a head tile of the last group past all heads repeats the last tile: nothing of it is stored)
         int hq = cx.h0 + mt * 16;
-        hq = (hq < Hp ? hq : Hp - 16) + n;
-        const uint16_t* qrow = Qp + ((size_t)cx.b * 2) * Hp * r + folded.at(hq, col, r);
+        hq = hq < Hp ? hq : Hp - 16;
+        const uint16_t* qrow = qb + (uint32_t)(hq * r) + (uint32_t)(col >> 3) * chunk;
         qhi[i][mt] = *(const u32x4_t*)qrow;
         if (SPLIT) qlo[i][mt] = *(const u32x4_t*)(qrow + (size_t)Hp * r);
         if (I4) {                                          // the column order of code_row8_i4: 0,4,1,5,2,6,3,7
@@ -1665,6 +1667,19 @@ int choose_nsplit(int B, int T) {
   return s;
 }
 
+// Tiles of a split; F groups of gathered rows may each end in a partial one.
+int split_tiles(int T, int S, int F) {
+  return F ? ((T + kTile - 1) / kTile + F + S - 1) / S : ((T + S - 1) / S + kTile - 1) / kTile;
+}
+// Ranks 64 and 128: how many tiles a split has at most for the kernel in roles; attn_small, whose every wave starts
+// with the folded query of all heads, pays from more on (us a pass, there / in roles: one sequence of 8000 tokens, 40
+// heads, rank 128 24.2 / 17.8, 64 of 1000, 8 tiles, 49.6 / 44.9, of 4225, 33 tiles, 73.0 / 76.5; rank 64, 21 of 700 18.4 / 17.5,
+// 64 of 300, 3 tiles, 22.8 / 23.3; gathered with logits, rank 128, 4 of 8000 37.7 / 36.4, 8 of 8000 43.0 / 44.1).
+int small_rank_tiles(int H, int r, bool ragged) {
+  if (H <= 16) return r == 64 ? 0 : 3;
+  return r == 64 ? 2 : ragged ? 4 : 16;
+}
+
 // Head groups: workgroups that share a split's tokens, each with a part of the heads.  A split of a short
 // context is a few tiles, and its partial sums (heads x rank floats, written here and read by the merge) are as
 // many bytes as its coefficients: g groups with a g-th of the splits write a g-th of them, and the coefficients
@@ -1680,14 +1695,11 @@ int choose_nsplit(int B, int T, int hgroups) {   // (never more than one group t
 }
 int choose_head_groups(const DecodeArgs& a, bool quant, bool ragged) {
   const int nw = (a.H + 15) / 16;
-  auto tiles = [&](int g) {                // of one workgroup at g groups
-    const int s = choose_nsplit(a.B, a.T, g);
-    return ragged ? ((a.T + kTile - 1) / kTile + a.F + s - 1) / s : ((a.T + s - 1) / s + kTile - 1) / kTile;
-  };
+  auto tiles = [&](int g) { return split_tiles(a.T, choose_nsplit(a.B, a.T, g), ragged ? a.F : 0); };
   if (nw == 1) return 1;
   if (tiles(nw) == 1) return nw;           // a workgroup per head tile, and still one tile each
   const int t1 = tiles(1);
-  if (t1 <= 2 && (a.r >= 192 || tiles(2) == t1)) return 2;
+  if (t1 <= 2 && (a.r >= (ragged ? 512 : 192) || tiles(2) == t1)) return 2;
   if (ragged || a.r < 512) return 1;
   if (t1 == 3) return 2;
   return nw == 4 && a.r > 512 && (quant || a.dt == AP_BF16 || t1 <= 8) ? 2 : 1;
@@ -1763,8 +1775,7 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
   constexpr bool kThree = three_roles(MT, RMAX, SPLIT, RAGGED, Q);
   if constexpr (!R3 && kThree && Q == 0) {
     const bool room = AttnLds<MT, RMAX, RAGGED, Q, true>(p).ring() >= 6;    // a ring of three tiles
-    const int n_tok = (p.T + p.nsplit - 1) / p.nsplit;
-    if (room && (RAGGED || n_tok > 3 * kTile)) return launch_attn<Tag, MT, RMAX, SPLIT, RAGGED, Q, true>(p, B, stream);
+    if (room && split_tiles(p.T, p.nsplit, RAGGED ? p.F : 0) > (RAGGED ? 1 : 3)) return launch_attn<Tag, MT, RMAX, SPLIT, RAGGED, Q, true>(p, B, stream);
   }
   if constexpr (!R3 && kThree && Q != 0) {
     return launch_attn<Tag, MT, RMAX, SPLIT, RAGGED, Q, true>(p, B, stream);
@@ -1842,7 +1853,8 @@ ap_status dispatch_attn(const AttnParams& p, int B, hipStream_t stream) {
       return p.r <= 256   ? launch_attn<Tag, NWV, 256, SPLIT, true, false>(p, B, stream)     \
              : p.r <= 512 ? launch_attn<Tag, NWV, 512, SPLIT, true, false>(p, B, stream)     \
                           : launch_attn<Tag, NWV, 640, SPLIT, true, false>(p, B, stream);    \
-    if (p.r <= 128) return launch_attn<Tag, NWV, 128, SPLIT, false, false>(p, B, stream);    \
+    if (p.r <= 128 && split_tiles(p.T, p.nsplit, 0) > small_rank_tiles(p.H, p.r, false))     \
+      return launch_attn<Tag, NWV, 128, SPLIT, false, false>(p, B, stream);                  \
     return p.r <= 256   ? launch_attn<Tag, NWV, 256, SPLIT, false, false>(p, B, stream)      \
            : p.r <= 512 ? launch_attn<Tag, NWV, 512, SPLIT, false, false>(p, B, stream)      \
                         : launch_attn<Tag, NWV, 640, SPLIT, false, false>(p, B, stream);
@@ -1877,6 +1889,7 @@ ap_status run_decode(const DecodeArgs& a) {
                           !(ragged && attn_small_applies(a.H, a.r, a.T, false));
   // (attn_small reaches a sequence's logits by 32-bit offsets)
   const bool small = !quant && attn_small_applies(a.H, a.r, a.T, one_pass_v) &&
+                     split_tiles(a.T, choose_nsplit(a.B, a.T), ragged ? a.F : 0) > small_rank_tiles(a.H, a.r, ragged) &&
                      (!a.scores || (int64_t)a.T_cap * a.H * 4 < (1ll << 32));
   int* pnew_split = (int*)((char*)a.workspace + ws_layout(a.B, a.H, a.d, a.T, a.r).pn + (size_t)a.B * a.H * 4);
   // (the small-rank kernel takes the count of one head group: twice the splits measured slower)
