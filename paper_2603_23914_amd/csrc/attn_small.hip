@@ -20,6 +20,7 @@
 #include "lane_ops.hpp"
 #include "mfma_ops.hpp"
 #include <hip/hip_ext.h>
+#include <algorithm>
 #include <type_traits>
 
 namespace ap {
@@ -44,6 +45,8 @@ struct SmallParams {
   float* pnew;          // [B][H] weight of the deferred newest token (fused step)
   float* scores;        // [B][T_cap][H] scaled logits in natural-log units, or null
   int B, T, T_cap, r, H, nsplit, xcd_aware, defer_v;
+  FastDiv by_split;     // nsplit
+  int tiles, more;      // tiles of a split, and how many (the first) splits have one more
   // per-token ranks (RAGGED): the group lists of ap_select_ranks and the rank arrays
   const int32_t* rank_k;      // [B][T] or null (= r)
   const int32_t* rank_v;
@@ -78,11 +81,11 @@ attn_small(const SmallParams p) {
   const int id = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
   int b, su;
   if (p.xcd_aware) {                                 // a sequence's splits are neighbours on one XCD
-    const int k = id >> 3;
-    b = (k / p.nsplit) * 8 + (id & 7);
-    su = k - (k / p.nsplit) * p.nsplit;
+    const int k = id >> 3, q = p.by_split(k);
+    b = q * 8 + (id & 7);
+    su = k - q * p.nsplit;
   } else {
-    b = id / p.nsplit;
+    b = p.by_split(id);
     su = id - b * p.nsplit;
   }
   if (b >= p.B) return;
@@ -110,13 +113,12 @@ attn_small(const SmallParams p) {
     logits = make_buffer(p.scores + (size_t)b * H * p.T_cap, (uint32_t)p.T_cap * (uint32_t)H * 4u);
   const uint16_t* Cb = p.Ck + (size_t)b * p.T_cap * R + g * 8;
   const uint16_t* Vb = p.Cv + (size_t)b * p.T_cap * R;
-  // tiles of this split (the same cuts as attn_partial's)
+  // tiles of this split
   int t_lo = 0, ntl = 0;
   const int32_t* bidx = nullptr;
   if constexpr (!RAGGED) {
-    const int ntiles = (T + kTok - 1) / kTok;
-    t_lo = (int)(((int64_t)su * ntiles) / S);
-    ntl = (int)(((int64_t)(su + 1) * ntiles) / S) - t_lo;
+    t_lo = su * p.tiles + (su < p.more ? su : p.more);
+    ntl = p.tiles + (su < p.more ? 1 : 0);
   } else {
     const int F = p.F;
     const int32_t* boff = p.bucket_off + (size_t)b * (F + 1);
@@ -132,7 +134,7 @@ attn_small(const SmallParams p) {
       ts[f + 1] = ts[f] + ((c + kTok - 1) >> 5);
     }
     const int ntot = ts[8];
-    ntl = su < ntot ? (ntot - su + S - 1) / S : 0;
+    ntl = su < ntot ? p.by_split(ntot - su + S - 1) : 0;
     ntl = ntl < kMaxSmallTiles ? ntl : kMaxSmallTiles;   // the host sizes the splits so that this never cuts
     for (int i = threadIdx.x; i < ntl; i += 256) {
       const int j = su + i * S;
@@ -447,6 +449,8 @@ ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, FoldedLayout folded
                             hipStream_t stream) {
   SmallParams p{Qp, folded, (const uint16_t*)Ck, (const uint16_t*)Cv, part_ml, part_U, pnew, scores,
                 B, T, T_cap, r, H, nsplit, B % 8 == 0 ? 1 : 0, defer_v ? 1 : 0,
+                FastDiv(nsplit, std::max((int64_t)B * nsplit, (int64_t)(T + kTok - 1) / kTok + F + nsplit)),
+                (T + kTok - 1) / kTok / nsplit, (T + kTok - 1) / kTok % nsplit,
                 rank_k, rank_v, bucket_off, bucket_idx, F};
   const bool ragged = rank_k != nullptr || rank_v != nullptr;   // as everywhere in the library
   const int nb = B * nsplit;

@@ -18,6 +18,7 @@
 #include "ap_common.hpp"
 #include "lane_ops.hpp"
 #include "mfma_ops.hpp"
+#include <algorithm>
 
 namespace ap {
 namespace {
@@ -32,6 +33,7 @@ struct RowsParams {
   int H, Hp, d, HD, r, row0, T_cap;
   int rpw;                // consecutive rows per wave (a workgroup owns 4 * rpw rows)
   float scale;
+  FastDiv by_heads;       // FOLD: Hp
   // PAIR: a second DOT job of the same shape in the same launch (blockIdx.z = 1), e.g. the
   // value row of a step appended next to the key row
   const uint16_t* Bm2;
@@ -154,7 +156,7 @@ __global__ void __launch_bounds__(256) basis_rows(const RowsParams p) {
     uint16_t* Qb = p.Qp + (size_t)b * 2 * p.Hp * r;
     constexpr FoldedLayout tiles{true};
     for (int i = tid; i < p.Hp * rpw; i += 256) {
-      const int jq = i / p.Hp, h = i - jq * p.Hp, jl = 4 * jq;
+      const int jq = p.by_heads(i), h = i - jq * p.Hp, jl = 4 * jq;
       if (j0 + jl < r) {
         uint16_t hi[4], lo[4];
 #pragma unroll
@@ -265,7 +267,8 @@ struct MergeExpandParams {
   void* out;                // [B][H][d]
   float* lse;               // [B][H] or null
   float* pout;              // SLICED: [B][nslice][H d]
-  int B, H, G, r, S, nslice, js, plain;
+  int B, H, HD, r, S, nslice, js, plain;
+  FastDiv by_first, by_slice, by_group;   // B with a shared basis, else H; nslice; G
 };
 constexpr int kFewSplits = 8;
 
@@ -286,21 +289,22 @@ __global__ void __launch_bounds__(NT) merge_expand(const MergeExpandParams p) {
   if ((total & 7) == 0 && !p.plain) id = (id & 7) * (total >> 3) + (id >> 3);
   int b, h, sl;
   if (p.bstride == 0) {
-    b = (int)(id % (uint32_t)p.B);
-    const uint32_t t = id / (uint32_t)p.B;
-    sl = (int)(t % (uint32_t)p.nslice);
-    h = (int)(t / (uint32_t)p.nslice);
+    const uint32_t t = p.by_first(id);
+    b = (int)(id - t * (uint32_t)p.B);
+    h = (int)p.by_slice(t);
+    sl = (int)t - h * p.nslice;
   } else {
-    h = (int)(id % (uint32_t)H);
-    const uint32_t t = id / (uint32_t)H;
-    sl = (int)(t % (uint32_t)p.nslice);
-    b = (int)(t / (uint32_t)p.nslice);
+    const uint32_t t = p.by_first(id);
+    h = (int)(id - t * (uint32_t)H);
+    b = (int)p.by_slice(t);
+    sl = (int)t - b * p.nslice;
   }
+  const int kvh = (int)p.by_group((uint32_t)h);
   const int j0 = sl * js;
   // ---- requests: B_v rows, then (m, l), then the first sums
   const int rg = tid / LPR, cc = tid % LPR;
-  const size_t HD = (size_t)(H / p.G) * d;
-  const uint16_t* Bb = p.Bv + (size_t)b * p.bstride + (size_t)j0 * HD + (size_t)(h / p.G) * d;
+  const size_t HD = (size_t)p.HD;
+  const uint16_t* Bb = p.Bv + (size_t)b * p.bstride + (size_t)j0 * HD + (size_t)kvh * d;
   u32x4_t wv[kRows];
   const uint32_t row_bytes = (uint32_t)HD * 2;
   const auto brow = make_buffer(Bb, (uint32_t)(js - 1) * row_bytes + d * 2);
@@ -835,7 +839,7 @@ ap_status launch_rows_grouped(ap_dtype dt, const void* Bk, const void* Bv, int64
                               const void* v_new, const void* q, void* Ck, void* Cv, void* Qp, int B, int H, int H_kv,
                               int Hp, int d, int r, int row, int T_cap, float scale, hipStream_t stream) {
   const RowsParams p{(const uint16_t*)Bk, bstride, (const uint16_t*)k_new, (const uint16_t*)q, (uint16_t*)Ck,
-                     (uint16_t*)Qp, H, Hp, d, H_kv * d, r, row, T_cap, 4, scale, (const uint16_t*)Bv,
+                     (uint16_t*)Qp, H, Hp, d, H_kv * d, r, row, T_cap, 4, scale, FastDiv(Hp, (int64_t)Hp * r), (const uint16_t*)Bv,
                      (const uint16_t*)v_new, (uint16_t*)Cv};
   return dt == AP_F16 ? launch_rows_grouped<F16Tag>(p, H / H_kv, B, stream) : launch_rows_grouped<BF16Tag>(p, H / H_kv, B, stream);
 }
@@ -849,7 +853,7 @@ ap_status launch_basis_rows(ap_dtype dt, const void* Bm, int64_t bstride, const 
                             int r, int row0, int T_cap, float scale, hipStream_t stream,
                             const void* Bm2, const void* x2, void* C2) {
   RowsParams p{(const uint16_t*)Bm, bstride, (const uint16_t*)x, (const uint16_t*)q,
-               (uint16_t*)C, (uint16_t*)Qp, H, Hp, d, HD, r, row0, T_cap, 4, scale,
+               (uint16_t*)C, (uint16_t*)Qp, H, Hp, d, HD, r, row0, T_cap, 4, scale, FastDiv(Hp, (int64_t)Hp * r),
                (const uint16_t*)Bm2, (const uint16_t*)x2, (uint16_t*)C2};
   const bool dot = x != nullptr, fold = q != nullptr, pair = Bm2 != nullptr;
   if (pair && !(dot && x2 && C2)) {
@@ -1055,7 +1059,8 @@ ap_status launch_merge_expand(ap_dtype dt, bool out_f32, const float* part_ml, c
   // grouped queries, whose heads share a slice that every XCD would then fetch (40 x 32/8 heads, rank 448
   // 43.6 / 52.5).
   const int plain = bstride && H == H_kv && (d == 64 || d == 128) && (int64_t)B * r * H_kv * d * 2 >= (32ll << 20);
-  MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H / H_kv, r, nsplit, nslice, js, plain};
+  MergeExpandParams p{part_ml, part_U, (const uint16_t*)Bv, bstride, out, lse, pout, B, H, H_kv * d, r, nsplit, nslice, js, plain,
+                      FastDiv(bstride ? H : B, (int64_t)B * H * nslice), FastDiv(nslice, (int64_t)std::max(B, H) * nslice), FastDiv(H / H_kv, H)};
   if (dt == AP_F16) {
     if (out_f32) launch_me_form<F16Tag, true>(p, d, nt, stream);
     else launch_me_form<F16Tag, false>(p, d, nt, stream);

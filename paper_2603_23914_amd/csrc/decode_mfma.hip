@@ -28,6 +28,7 @@
 #include "mfma_ops.hpp"
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
@@ -451,13 +452,18 @@ struct AttnParams {
   int B, T, T_cap, r, H, nsplit;
   int hgroups;          // head groups of 16 MT heads (the last may be smaller), a workgroup each
   int xcd_aware;        // workgroup numbering, see wg_coords
+  FastDiv by_split, by_group;  // nsplit, hgroups
+  // tokens (token-split mode: tiles) of a split, and how many (the first) splits have one more; for splits without and
+  // with one more token: tiles, tokens of a tile, and how many (the first) tiles have one more
+  int part, more;
+  int tiles[2], tile_part[2], tile_more[2];
   int nh;               // C_v LDS ring depth in 16-row units (even, >= 2)
   // rank-ragged launches only: the group lists of ap_select_ranks and the per-token ranks
   const int32_t* rank_k;      // [B][T] or null (= r)
   const int32_t* rank_v;
   const int32_t* bucket_off;  // [B][F+1]
   const int32_t* bucket_idx;  // [B][T]
-  int F;
+  int F, inv_F;               // inv_F: ceil(65536 / F), divides numbers below 8192 by F
   int ntl_cap;          // most tiles a split can own (sizes the LDS index table)
   // fused decode step: the newest token (row T-1) is scored like every other, but its value
   // row does not exist yet; its softmax weight is exported and the expansion pass adds it
@@ -501,21 +507,21 @@ struct AttnParams {
 // keep the plain numbering, which spreads a sequence's splits over all XCDs.
 // The head groups of a split are neighbours on one XCD in either numbering: the first one's
 // coefficient rows are in that L2 when the others ask for them.
-__device__ __forceinline__ void wg_coords(int nsplit, int hgroups, int xcd_aware, int& b, int& s, int& hg) {
+__device__ __forceinline__ void wg_coords(const AttnParams& p, int& b, int& s, int& hg) {
   int id = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
   hg = 0;
-  if (hgroups > 1) {
-    const int k = id >> 3;
-    hg = k % hgroups;
-    id = (k / hgroups) * 8 + (id & 7);
+  if (p.hgroups > 1) {
+    const int k = id >> 3, q = p.by_group(k);
+    hg = k - q * p.hgroups;
+    id = q * 8 + (id & 7);
   }
-  if (xcd_aware) {
-    const int k = id >> 3;
-    b = (k / nsplit) * 8 + (id & 7);
-    s = k - (k / nsplit) * nsplit;
+  if (p.xcd_aware) {
+    const int k = id >> 3, q = p.by_split(k);
+    b = q * 8 + (id & 7);
+    s = k - q * p.nsplit;
   } else {
-    b = id / nsplit;
-    s = id - b * nsplit;
+    b = p.by_split(id);
+    s = id - b * p.nsplit;
   }
 }
 
@@ -579,8 +585,10 @@ struct WaveCtx {
     lane = tid & 63; n = lane & 15; g = lane >> 4;
     r = uni(p.r); T = uni(p.T); H = uni(p.H); nh = uni(p.nh); nsplit = uni(p.nsplit); dbg = uni(p.dbg);
     int hg;
-    wg_coords(nsplit, uni(p.hgroups), uni(p.xcd_aware), b, s, hg);
-    h0 = hg * 16 * MT;
+    wg_coords(p, b, s, hg);
+    b = uni(b);
+    s = uni(s);
+    h0 = uni(hg) * 16 * MT;
     Tv = T - uni(p.defer_v);
     pnew = uni_ptr(p.pnew);
     pnew_split = uni_ptr(p.pnew_split);
@@ -602,9 +610,9 @@ struct WaveCtx {
     ksb = vsb + 2 * (r >> 6) * kTile;
     tok_a = 0; tok_h = kTile; tok_rem = 0;
     if (!RAGGED && TS) {
-      const int ntiles = (T + kTile - 1) / kTile;
-      t_lo = (int)(((int64_t)s * ntiles) / nsplit);
-      ntl = (int)(((int64_t)(s + 1) * ntiles) / nsplit) - t_lo;
+      const int more = uni(p.more);
+      t_lo = s * uni(p.part) + (s < more ? s : more);
+      ntl = uni(p.part) + (s < more ? 1 : 0);
     } else if (!RAGGED) {
       // The splits share the TOKENS evenly, not the 32-token tiles: a split of n tokens walks
       // ceil(n / 32) tiles of floor(n / tiles) or one more tokens each.  A tile still fetches the
@@ -615,11 +623,11 @@ struct WaveCtx {
       // as long as before (a tile costs the same whether 31 or 32 of its rows count, and the
       // longest split still walks 34), but every split now does the same work at any T.
       t_lo = 0;
-      tok_a = (int)(((int64_t)s * T) / nsplit);
-      const int n_tok = (int)(((int64_t)(s + 1) * T) / nsplit) - tok_a;
-      ntl = (n_tok + kTile - 1) / kTile;
-      tok_h = ntl > 0 ? n_tok / ntl : 0;
-      tok_rem = n_tok - tok_h * ntl;
+      const int more = uni(p.more), with = s < more ? 1 : 0;
+      tok_a = s * uni(p.part) + (s < more ? s : more);
+      ntl = uni(p.tiles[with]);
+      tok_h = uni(p.tile_part[with]);
+      tok_rem = uni(p.tile_more[with]);
     } else {
       idxb = (int*)(vsb + (I8 ? 4 * (r >> 6) * kTile : 0));
       meta = idxb + uni(p.ntl_cap) * kTile;
@@ -657,22 +665,18 @@ struct WaveCtx {
     }
     const int ntot = ts[8];
     t_lo = 0;
-    ntl = s < ntot ? (ntot - s + nsplit - 1) / nsplit : 0;
+    ntl = s < ntot ? uni((int)p.by_split(ntot - s + nsplit - 1)) : 0;
     const int cap = uni(p.ntl_cap);
     ntl = ntl < cap ? ntl : cap;           // never beyond the table (host sizes it for the worst case)
-    // Visiting order: the split's tiles come in group order (high ranks first); walked with a
-    // stride of about ntl / F (coprime to ntl) high- and low-rank tiles alternate, so that the
-    // short tiles' products run while the long tiles' rows are still on their way.
-    int stride = ntl / (F > 0 ? F : 1);
-    stride = stride < 1 ? 1 : stride;
-    for (;; ++stride) {
-      int x = stride, y = ntl;
-      while (y) { const int tmp = x % y; x = y; y = tmp; }
-      if (x == 1 || ntl <= 1) break;
-    }
+    // Visiting order: the split's tiles come in group order (high ranks first); cut into F runs of equal length, of
+    // which each gives a tile in turn, high- and low-rank tiles alternate, so that the short tiles' products run while
+    // the long tiles' rows are still on their way.
+    const uint32_t inv = (uint32_t)uni(p.inv_F);
+    const int run = (int)((uint32_t)ntl * inv >> 16), longer = ntl - run * F;
     for (int e = threadIdx.x; e < ntl * kTile; e += 64 * NWAVE) {
       const int i = e >> 5, l = e & 31;
-      const int isrc = ntl > 1 ? (int)((uint32_t)(i * stride) % (uint32_t)ntl) : 0;
+      const int q = (int)((uint32_t)i * inv >> 16), k0 = i - q * F;      // tile q of run k0
+      const int isrc = k0 * run + (k0 < longer ? k0 : longer) + q;
       const int j = s + isrc * nsplit;
       int o0 = off[0], o1 = off[1], t0 = 0;
 #pragma unroll
@@ -1616,7 +1620,7 @@ __global__ void __launch_bounds__(R3 ? 768 : 512) __attribute__((amdgpu_waves_pe
 attn_partial(const AttnParams p) {
   {
     int b, s, hg;
-    wg_coords(p.nsplit, p.hgroups, p.xcd_aware, b, s, hg);
+    wg_coords(p, b, s, hg);
     if (b >= p.B) return;
   }
   // The roles are inlined: called as functions they would spill their callee-saved registers
@@ -1789,6 +1793,15 @@ ap_status launch_attn(AttnParams p, int B, hipStream_t stream) {
              "ap_decode_attn: H=%d r=%d needs more LDS than 160 KiB", p.H, p.r);
   p.ntl_cap = m.ntl_cap;
   p.nh = nh;
+  const int total = m.TS ? (p.T + kTile - 1) / kTile : p.T;
+  p.part = total / p.nsplit;
+  p.more = total % p.nsplit;
+  for (int with = 0; with < 2; ++with) {
+    const int n = p.part + with, tiles = (n + kTile - 1) / kTile;
+    p.tiles[with] = tiles;
+    p.tile_part[with] = tiles ? n / tiles : 0;
+    p.tile_more[with] = tiles ? n % tiles : 0;
+  }
   const size_t lds = (size_t)nh * m.unit + m.fixed;
   auto kern = attn_partial<Tag, MT, RMAX, SPLIT, RAGGED, Q, R3>;
   static bool attr_set = false;
@@ -1952,6 +1965,8 @@ ap_status run_decode(const DecodeArgs& a) {
   p.part_ml = ml;
   p.part_U = U;
   p.T = a.T; p.T_cap = a.T_cap; p.r = a.r; p.H = a.H; p.nsplit = S; p.hgroups = hgroups;
+  p.by_split = FastDiv(S, std::max((int64_t)a.B * S + 7, (int64_t)(a.T + kTile - 1) / kTile + a.F + S));
+  p.by_group = FastDiv(hgroups, ((int64_t)a.B * S + 7) * hgroups);
   p.scores = a.scores;
   p.defer_v = one_pass_v ? 1 : 0;
   p.pnew = (float*)(ws + wl.pn);
@@ -1967,6 +1982,7 @@ ap_status run_decode(const DecodeArgs& a) {
     p.bucket_off = a.bucket_off;
     p.bucket_idx = a.bucket_idx;
     p.F = a.F;
+    p.inv_F = (65536 + a.F - 1) / a.F;
   }
 #ifdef AP_KERNEL_TIMERS
   if (const char* e = getenv("AP_DEBUG_ATTN")) p.dbg = atoi(e);
