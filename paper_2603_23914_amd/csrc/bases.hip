@@ -12,8 +12,8 @@
 //                                   S = L L^T (chol_panel, panels of 32 columns),
 //                                   P = L^-1 M (tri_inverse, gemm_nn; fp64 accumulation)
 //     Rayleigh-Ritz:           Zt = P X^T [l, n] fp32,  S = Zt Zt^T [l, l]  (= P X^T X P^T)
-//                              S = J Lambda J^T by one-sided Jacobi on the rows of S (jacobi_pair)
-//                              D = (J^T P)[:r] in decreasing order of Lambda,  sigma = sqrt(Lambda)
+//                              S = L L^T,  L = J Sigma V^T by one-sided Jacobi on the columns of L (jacobi_pair)
+//                              D = (J^T P)[:r] in decreasing order of Sigma, the singular values
 //
 // The matrices that lose information when rounded (M, whose singular values span the square of the
 // cache's spectrum, and the small Gram matrices) stay in fp32 / fp64; what goes back into the matrix
@@ -47,10 +47,11 @@ __device__ __forceinline__ void matrix_of(int id, int per, int batch, int& b, in
   }
 }
 
-constexpr int kFirstCheck = 4;         // sweeps before this one do not ask whether the matrix is done
+constexpr int kFirstCheck = 4;         // sweeps before this one do not ask whether the matrix is done (jacobi_check)
 constexpr int kFullEvery = 4, kFullFrom = 8;   // steps and sweeps that turn the pairs within the blocks too
-constexpr int kJacobiSweeps = 12;      // at most; a matrix without a rotation in a sweep is done
-constexpr int kSweepSlots = 16;        // rotation counters per matrix, one per sweep
+constexpr int kJacobiSweeps = 10;      // at most
+constexpr int kSweepSlots = 16;        // per matrix: pairs of blocks that had work, one count per sweep, then whether a
+                                       // sweep has work, one flag per sweep from kFirstCheck on
 constexpr float kJacobiTol = 1e-5f;    // |a.b| <= tol |a||b|: far below what 16-bit storage of the result keeps
 
 // ---- out[c][r] = in[r][c] for 16-bit elements; columns rows .. ld_out-1 of out are zero-filled.
@@ -317,17 +318,26 @@ void launch_gram(const float* A, int64_t a_bstride, int lda, double* S, int64_t 
     hipLaunchKernelGGL(gram_split, dim3(t32 * (t32 + 1) / 2, batch), dim3(256), 0, st, A, a_bstride, lda, S, s_bstride, l, m);
 }
 
+// ---- the largest diagonal entry of S and the sum of all: out[b], out[batch + b].  grid (batch), 256 threads.
 __global__ void __launch_bounds__(256)
-diag_max(const double* __restrict__ S, int64_t s_bstride, int l, double* __restrict__ dmax) {
+diag_stats(const double* __restrict__ S, int64_t s_bstride, int l, double* __restrict__ out) {
   const double* Sb = S + (size_t)blockIdx.x * s_bstride;
-  __shared__ double red[4];
-  double m = 0.0;
-  for (int i = threadIdx.x; i < l; i += 256) m = fmax(m, Sb[(size_t)i * l + i]);
+  __shared__ double red[8];
+  double m = 0.0, sum = 0.0;
+  for (int i = threadIdx.x; i < l; i += 256) {
+    const double v = Sb[(size_t)i * l + i];
+    m = fmax(m, v);
+    sum += v;
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  sum = wave_sum_d(sum);
+  if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = m; red[4 + (threadIdx.x >> 6)] = sum; }
   __syncthreads();
-  if (threadIdx.x == 0) dmax[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+    out[gridDim.x + blockIdx.x] = (red[4] + red[5]) + (red[6] + red[7]);
+  }
 }
 
 // ---- Cholesky S = L L^T, fp64, in panels of 32 columns, one launch per panel; off the diagonal the
@@ -344,7 +354,9 @@ diag_max(const double* __restrict__ S, int64_t s_bstride, int l, double* __restr
 //      A pivot below 1e-13 of the largest diagonal entry (dmax) marks a direction that the rows
 //      do not span: its column of L and its diagonal entry are zero, its row of L^-1 is zero,
 //      so the corresponding row of P = L^-1 M is zero and drops out later.
+//      FACTOR: X takes the diagonal blocks themselves, lower triangles.
 //      grid (tiles from the diagonal down * batch), 256 threads.  l even.
+template <bool FACTOR>
 __global__ void __launch_bounds__(256)
 chol_panel(double* __restrict__ S, double* __restrict__ X, int l, int c0, const double* __restrict__ dmax, int batch) {
   constexpr int P = 33, PC = 34;
@@ -476,7 +488,7 @@ chol_panel(double* __restrict__ S, double* __restrict__ X, int l, int c0, const 
     double* Xd = X + (size_t)b * l * l + (size_t)c0 * l + c0;
     for (int e = tid; e < 1024; e += 256) {
       const int i = e >> 5, c = e & 31;
-      if (c0 + i < l && c0 + c < l) Xd[(size_t)i * l + c] = Di[i * P + c];
+      if (c0 + i < l && c0 + c < l) Xd[(size_t)i * l + c] = !FACTOR ? Di[i * P + c] : i >= c ? Lc[c * PC + i] : 0.0;
     }
     return;
   }
@@ -577,12 +589,14 @@ tri_inverse(const double* __restrict__ S, double* __restrict__ X, int l, int bat
   }
 }
 
-// S [l][l] -> X = L^-1 (lower triangle of blocks), S is overwritten.
-void launch_cholesky(double* S, double* X, int l, double* dmax, int batch, hipStream_t st) {
-  hipLaunchKernelGGL(diag_max, dim3(batch), dim3(256), 0, st, S, (int64_t)l * l, l, dmax);
+// S [l][l] -> L below the diagonal blocks of S; X: L^-1 (lower triangle of blocks) or, FACTOR, L's diagonal blocks.
+template <bool FACTOR>
+void launch_cholesky(double* S, double* X, int l, double* dstat, int batch, hipStream_t st) {
+  hipLaunchKernelGGL(diag_stats, dim3(batch), dim3(256), 0, st, S, (int64_t)l * l, l, dstat);
   for (int c0 = 0; c0 < l; c0 += 32)
-    hipLaunchKernelGGL(chol_panel, dim3((l - c0 + 31) / 32 * batch), dim3(256), 0, st, S, X, l, c0, dmax, batch);
-  if (l > 32) hipLaunchKernelGGL(tri_inverse, dim3(((l + 31) / 32 - 1) * batch), dim3(256), 0, st, S, X, l, batch);
+    hipLaunchKernelGGL(chol_panel<FACTOR>, dim3((l - c0 + 31) / 32 * batch), dim3(256), 0, st, S, X, l, c0, dstat, batch);
+  if (!FACTOR && l > 32)
+    hipLaunchKernelGGL(tri_inverse, dim3(((l + 31) / 32 - 1) * batch), dim3(256), 0, st, S, X, l, batch);
 }
 
 // ---- C = A B with A [M][K] fp64, B [K][N] fp32, fp64 accumulation; C as fp32 and / or in 16-bit
@@ -670,17 +684,25 @@ gemm_nn(const double* __restrict__ A, int64_t a_bstride, int lda, const float* _
     }
 }
 
-// ---- W [l][lp] fp32 <- S [l][l] fp64, columns l .. lp-1 zero; the sweeps' rotation counters to zero.
-//      grid (ceil(l * lp / 256), batch), 256 threads.
+// ---- W [l][lp] fp32 <- L^T, L [l][l] fp64 lower triangular: blocks of 32 below the diagonal in S, on it in X;
+//      columns l .. lp-1 zero; the sweeps' counters and flags to zero.
+//      grid (lp / 32, lp / 32, batch), 256 threads.
 __global__ void __launch_bounds__(256)
-jacobi_init(const double* __restrict__ S, int64_t s_bstride, float* __restrict__ W, int64_t w_bstride, int l, int lp,
-            int* __restrict__ rotations) {
-  const int e = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-  if (e < l * lp) {
-    const int i = e / lp, c = e - i * lp;
-    W[(size_t)b * w_bstride + e] = c < l ? (float)S[(size_t)b * s_bstride + (size_t)i * l + c] : 0.f;
+jacobi_init(const double* __restrict__ S, const double* __restrict__ X, float* __restrict__ W, int64_t w_bstride, int l,
+            int lp, int* __restrict__ state) {
+  __shared__ float tile[32 * 33];
+  const int b = blockIdx.z, c0 = blockIdx.x * 32, j0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+  const double* L = (c0 == j0 ? X : S) + (size_t)b * l * l;
+#pragma unroll
+  for (int k = 0; k < 32; k += 8) {
+    const int c = c0 + y + k, j = j0 + x;                // row c of L
+    tile[(y + k) * 33 + x] = c0 >= j0 && c < l && j < l ? (float)L[(size_t)c * l + j] : 0.f;
   }
-  if (e < kSweepSlots) rotations[b * kSweepSlots + e] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 32; k += 8)
+    if (j0 + y + k < l) W[(size_t)b * w_bstride + (size_t)(j0 + y + k) * lp + c0 + x] = tile[x * 33 + y + k];
+  if (c0 == 0 && j0 == 0 && threadIdx.x < 2 * kSweepSlots) state[b * 2 * kSweepSlots + threadIdx.x] = 0;
 }
 
 // The pairs of blocks that a launch takes from the round-robin over nblk blocks: those of one step, `skip` left
@@ -689,8 +711,10 @@ struct PairSet { int step, skip, gather, count; };
 
 // ---- One-sided Jacobi on the rows of W [l][lp] (fp32), block version.  The rows are cut into blocks
 //      of 16; one launch takes disjoint pairs of blocks (round-robin over the blocks), a workgroup per
-//      pair.  For a symmetric positive semi-definite W = S the rows converge to lambda_i j_i^T, the
-//      eigenvectors scaled by their eigenvalues.
+//      pair.  For W = L^T, S = L L^T, the rows converge to sigma_i j_i^T, S's eigenvectors scaled by the square
+//      roots of its eigenvalues.  (From W = S they converge to lambda_i j_i^T in more sweeps: 7 against 6 for
+//      singular values j^-0.7 after two power iterations, 12 against 7 for j^-1.5, more than 15 against 9 where nothing was
+//      iterated, simulated on the host.)
 //      A workgroup never holds its 32 rows: it forms their Gram matrix G on the fp32 matrix
 //      instructions, turns pairs of rows in two-sided rotations of G (steps of 16 disjoint pairs, the same
 //      rotations that the rows themselves would see) while the product Q of the rotations is
@@ -712,18 +736,19 @@ struct PairSet { int step, skip, gather, count; };
 //      A pair (x, y) is turned as x - sn (y + ta x), y + sn (x - ta y), ta the tangent of half the angle: the
 //      cosine of a small angle rounds to 1 in fp32, and thousands of such rotations made the rows longer
 //      (sigma of 544 equal directions 4.9e-5 too large with cosine and sine, see the test of it).
-//      Measured at 16 matrices of 544 rows: 20 us a launch of 16 turns, 25 of 31, 5.4 ms in all, of a launch's
+//      Measured at 16 matrices of 544 rows: 20 us a launch of 16 turns, 25 of 31, 4.9 ms in all (from W = S, a
+//      last sweep that only looks and twelve sweeps' launches 5.4), of a launch's
 //      15.5 us inside the kernel 4.4 the rows and G (out of memory: the L2s do not hold them over a launch),
 //      1.6 its sum and the check, 5.5 the steps, 4.1 the rows' product.  31 turns in every launch, all pairs of
 //      a step in one launch and the rows asked for after the check: 24 us and 7.0 ms; with the rows
 //      themselves in LDS (blocks of 32, three dot products and a rotation of 544 columns per pair) 190 us a
 //      launch and 21.9 ms.
-//      rotations[b][sweep] counts the pairs of blocks that had work; a matrix whose previous sweep
-//      had none is done.
+//      state[b][sweep] counts the pairs of blocks that had work; from kFirstCheck on a sweep goes over the
+//      matrices that jacobi_check has flagged for it.
 //      grid (ps.count * batch), 512 threads.
 __global__ void __launch_bounds__(512)
 jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, PairSet ps, int sweep, int turns,
-            float tol, int* __restrict__ rotations, int batch) {
+            float tol, int* __restrict__ state, int batch) {
   constexpr int PITCH = 48;                             // 16 mod 32: two neighbouring rows fill the banks
   __shared__ float part[8][3 * 256];
   __shared__ float gm[2][32 * PITCH], qm[2][32 * PITCH];
@@ -733,7 +758,7 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, P
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int b, k;                                             // W stays in one XCD's L2
   matrix_of((int)blockIdx.x, ps.count, batch, b, k);
-  if (sweep >= kFirstCheck && rotations[b * kSweepSlots + sweep - 1] == 0) return;
+  if (sweep >= kFirstCheck && state[(2 * b + 1) * kSweepSlots + sweep] == 0) return;
   // round-robin over nblk blocks (nblk even; a block index >= the real count is an empty block)
   const int nm1 = nblk - 1;
   int ba, bb, step = ps.step;
@@ -823,7 +848,7 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, P
 #pragma unroll
   for (int q = 1; q < 8; ++q) any |= busy[q];
   if (any == 0) return;                                 // every pair is orthogonal already
-  if (tid == 0) atomicAdd(&rotations[b * kSweepSlots + sweep], 1);
+  if (tid == 0) atomicAdd(&state[2 * b * kSweepSlots + sweep], 1);
   const int sh = 1 - __builtin_amdgcn_frexp_expf(dmx);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
@@ -918,7 +943,93 @@ jacobi_pair(float* __restrict__ W, int64_t w_bstride, int l, int lp, int nblk, P
   }
 }
 
-// ---- eigenvalues = row norms.  grid (ceil(l / 4), batch), 256 threads: a wave per row.
+// ---- whether a matrix has work for sweep `sweep`: any two rows of W further from orthogonal than tol.  A sweep that
+//      only looks costs 34 launches of 10 us at 16 matrices of 544, this one launch.  A matrix whose last sweep had
+//      work in most of its `pairs` is flagged without a look.
+//      64 x 64 tiles of W W^T as in gram_f64, in fp32 products; the rows' norms from what goes through LDS.
+//      grid (tiles of the lower triangle * batch), 256 threads.
+__global__ void __launch_bounds__(256)
+jacobi_check(const float* __restrict__ W, int64_t w_bstride, int l, int lp, int sweep, int pairs, float tol,
+             int* __restrict__ state, int batch) {
+  __shared__ __attribute__((aligned(16))) float stage[2][128 * kGramPitch];
+  __shared__ float norm[128];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t64 = (l + 63) >> 6;
+  int b, t;
+  matrix_of((int)blockIdx.x, t64 * (t64 + 1) / 2, batch, b, t);
+  int* flag = state + (2 * b + 1) * kSweepSlots + sweep;
+  if (sweep > kFirstCheck && flag[-1] == 0) return;
+  if (2 * state[2 * b * kSweepSlots + sweep - 1] > pairs) {
+    if (t == 0 && tid == 0) *flag = 1;
+    return;
+  }
+  int ti = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+  while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
+  while (ti * (ti + 1) / 2 > t) --ti;
+  const int tj = t - ti * (ti + 1) / 2;
+  W += (size_t)b * w_bstride;
+  const int row = tid >> 3, piece = (tid & 7) * 4;       // a stage: 64 rows of either side, 32 columns each
+  const float* src[4];
+  float sq[4];
+  f32x4_t nx[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int i = (u < 2 ? ti : tj) * 64 + (u & 1) * 32 + row;
+    src[u] = W + (size_t)(i < l ? i : l - 1) * lp + piece;   // rows past the end repeat the last one
+    nx[u] = *(const f32x4_t*)src[u];
+    sq[u] = 0.f;
+  }
+  f32x4_t acc[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) acc[u][v] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int stages = lp >> 5;
+  const int ra = ((w >> 1) * 32 + n) * kGramPitch + 4 * g, rb = (64 + (w & 1) * 32 + n) * kGramPitch + 4 * g;
+  for (int c = 0; c < stages; ++c) {
+    float* buf = stage[c & 1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      *(f32x4_t*)(buf + (u * 32 + row) * kGramPitch + piece) = nx[u];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sq[u] = fmaf(nx[u][e], nx[u][e], sq[u]);
+      nx[u] = *(const f32x4_t*)(src[u] + (c + 1 < stages ? c + 1 : c) * 32);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const f32x4_t a0 = *(const f32x4_t*)(buf + ra + 16 * h), a1 = *(const f32x4_t*)(buf + ra + 16 * kGramPitch + 16 * h);
+      const f32x4_t b0 = *(const f32x4_t*)(buf + rb + 16 * h), b1 = *(const f32x4_t*)(buf + rb + 16 * kGramPitch + 16 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[e], b0[e], acc[0][0], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[e], b1[e], acc[0][1], 0, 0, 0);
+        acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[e], b0[e], acc[1][0], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[e], b1[e], acc[1][1], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const float s = group_sum<8>(sq[u]);
+    if ((tid & 7) == 0) norm[u * 32 + row] = sqrtf(s);
+  }
+  lds_barrier();
+  int work = 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                      // element e of lane (n, g): row 4 g + e, column n
+        const int i = (w >> 1) * 32 + 16 * u + 4 * g + e, j = (w & 1) * 32 + 16 * v + n;
+        if (ti * 64 + i < l && tj * 64 + j < ti * 64 + i && fabsf(acc[u][v][e]) > tol * (norm[i] * norm[64 + j])) work = 1;
+      }
+  if (__ballot(work) != 0 && lane == 0) *flag = 1;
+}
+
+// ---- singular values = row norms.  grid (ceil(l / 4), batch), 256 threads: a wave per row.
 __global__ void __launch_bounds__(256)
 eig_norms(const float* __restrict__ W, int64_t w_bstride, int l, int lp, double* __restrict__ lam) {
   const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
@@ -931,29 +1042,35 @@ eig_norms(const float* __restrict__ W, int64_t w_bstride, int l, int lp, double*
 }
 
 // ---- rows in decreasing order of their norm (ties by row index); the r leading rows, normalised,
-//      become R [r][l] (fp64) and sigma[i] = sqrt(lambda_i).  grid (ceil(l / 4), batch), 256 threads:
-//      a wave per row, which counts the rows before its own (one workgroup per matrix, which also
-//      took the norms, needed 197 us at 16 x 544 rows).
+//      become R [r][l] (fp64) and sigma.  Thousands of rotations in fp32 change the rows' lengths by some 1e-6, all
+//      of them alike; what they may not change is the sum of squares, S's trace, which sigma is scaled to.
+//      grid (ceil(l / 4), batch), 256 threads: a wave per row, which counts the rows before its own (one workgroup per
+//      matrix, which also took the norms, needed 197 us at 16 x 544 rows).
 __global__ void __launch_bounds__(256)
-eig_select(const float* __restrict__ W, int64_t w_bstride, const double* __restrict__ lam, int l, int lp, int r,
-           double* __restrict__ R, int64_t r_bstride, float* __restrict__ sigma, int64_t sig_bstride) {
+eig_select(const float* __restrict__ W, int64_t w_bstride, const double* __restrict__ lam, const double* __restrict__ trace,
+           int l, int lp, int r, double* __restrict__ R, int64_t r_bstride, float* __restrict__ sigma, int64_t sig_bstride) {
   const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
   if (i >= l) return;
   const double* lb = lam + (size_t)b * l;
   const double li = lb[i];
   int p = 0;
-  for (int j = lane; j < l; j += 64) p += (lb[j] > li || (lb[j] == li && j < i)) ? 1 : 0;
+  double sum = 0.0;
+  for (int j = lane; j < l; j += 64) {
+    p += (lb[j] > li || (lb[j] == li && j < i)) ? 1 : 0;
+    sum = fma(lb[j], lb[j], sum);
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) p += __shfl_xor(p, o);
+  sum = wave_sum_d(sum);
   if (p >= r) return;
-  if (lane == 0 && sigma) sigma[(size_t)b * sig_bstride + p] = (float)sqrt(li);
+  if (lane == 0 && sigma) sigma[(size_t)b * sig_bstride + p] = (float)(sum > 0.0 ? li * sqrt(trace[b] / sum) : li);
   const double inv = li > 0.0 ? 1.0 / li : 0.0;
   const float* row = W + (size_t)b * w_bstride + (size_t)i * lp;
   for (int c = lane; c < l; c += 64) R[(size_t)b * r_bstride + (size_t)p * l + c] = (double)row[c] * inv;
 }
 
 struct BasesLayout {
-  size_t xt, yt, m32, p16, p32, zt, s64, linv, w32, rsel, state, dmax, lam, total;
+  size_t xt, yt, m32, p16, p32, zt, s64, linv, w32, rsel, state, dstat, lam, total;
   int n_pad, lp;
 };
 BasesLayout bases_layout(int B, int n, int HD, int l, int r) {
@@ -972,8 +1089,8 @@ BasesLayout bases_layout(int B, int n, int HD, int l, int r) {
   w.linv = take((size_t)B * l * l * 8);
   w.w32 = take((size_t)B * l * w.lp * 4);
   w.rsel = take((size_t)B * r * l * 8);
-  w.state = take((size_t)B * kSweepSlots * 4);
-  w.dmax = take((size_t)B * 8);
+  w.state = take((size_t)B * 2 * kSweepSlots * 4);
+  w.dstat = take((size_t)B * 2 * 8);
   w.lam = take((size_t)B * l * 8);
   w.total = off;
   return w;
@@ -1003,8 +1120,8 @@ ap_status run_bases(const BasesArgs& a) {
   double* Linv = (double*)(ws + w.linv);
   float* W = (float*)(ws + w.w32);
   double* Rsel = (double*)(ws + w.rsel);
-  int* rotations = (int*)(ws + w.state);
-  double* dmax = (double*)(ws + w.dmax);
+  int* state = (int*)(ws + w.state);
+  double* dstat = (double*)(ws + w.dstat);
   double* lam = (double*)(ws + w.lam);
   hipStream_t st = a.stream;
   const int np = w.n_pad;
@@ -1025,7 +1142,7 @@ ap_status run_bases(const BasesArgs& a) {
     if ((s = launch_gemm_nt(g2)) != AP_OK) return s;
     // rows of M made orthonormal
     launch_gram(M32, (int64_t)l * HD, HD, S, (int64_t)l * l, l, HD, B, st);
-    launch_cholesky(S, Linv, l, dmax, B, st);
+    launch_cholesky<false>(S, Linv, l, dstat, B, st);
     // (the fp32 copy is what D is made from in the end: the last iteration's only)
     launch_gemm_nn<Tag>(Linv, (int64_t)l * l, l, M32, (int64_t)l * HD, HD, it == a.power_iters ? P32 : nullptr,
                         (int64_t)l * HD, P16, (int64_t)l * HD, HD, l, HD, l, 1, B, st);
@@ -1038,7 +1155,8 @@ ap_status run_bases(const BasesArgs& a) {
   launch_gram(Zt, (int64_t)l * np, np, S, (int64_t)l * l, l, n, B, st);
   const int lp = w.lp;
   const int64_t w_bs = (int64_t)l * lp;
-  hipLaunchKernelGGL(jacobi_init, dim3((l * lp + 255) / 256, B), dim3(256), 0, st, S, (int64_t)l * l, W, w_bs, l, lp, rotations);
+  launch_cholesky<true>(S, Linv, l, dstat, B, st);       // (Linv: the diagonal blocks)
+  hipLaunchKernelGGL(jacobi_init, dim3(lp / 32, lp / 32, B), dim3(256), 0, st, S, Linv, W, w_bs, l, lp, state);
   int nblk = (l + 15) / 16;
   nblk += nblk & 1;                                      // an even number of blocks (the last may be empty)
   const int P = nblk / 2, nm1 = nblk - 1;
@@ -1052,16 +1170,21 @@ ap_status run_bases(const BasesArgs& a) {
   const bool spare = P >= 8 && P * B > 256 && (P - 1) * B <= 256;
   auto turn = [&](int sweep, PairSet ps, int turns) {
     hipLaunchKernelGGL(jacobi_pair, dim3(ps.count * B), dim3(512), 0, st, W, w_bs, l, lp, nblk, ps, sweep, turns, kJacobiTol,
-                       rotations, B);
+                       state, B);
   };
-  for (int sweep = 0; sweep < kJacobiSweeps; ++sweep)
+  const int t64 = (l + 63) / 64;
+  for (int sweep = 0; sweep < kJacobiSweeps; ++sweep) {
+    if (sweep >= kFirstCheck)
+      hipLaunchKernelGGL(jacobi_check, dim3(t64 * (t64 + 1) / 2 * B), dim3(256), 0, st, W, w_bs, l, lp, sweep, P * nm1, kJacobiTol,
+                         state, B);
     for (int step = 0; step < nm1; ++step) {
       const bool out = spare && step < 2 * run;
       turn(sweep, PairSet{step, out ? skip : P, 0, out ? P - 1 : P}, step % kFullEvery == 0 || sweep >= kFullFrom ? 31 : 16);
       if (out && (step + 1) % run == 0) turn(sweep, PairSet{step + 1 - run, skip, 1, run}, 16);
     }
+  }
   hipLaunchKernelGGL(eig_norms, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, l, lp, lam);
-  hipLaunchKernelGGL(eig_select, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, lam, l, lp, r, Rsel, (int64_t)r * l, a.sigma,
+  hipLaunchKernelGGL(eig_select, dim3((l + 3) / 4, B), dim3(256), 0, st, W, w_bs, lam, dstat + B, l, lp, r, Rsel, (int64_t)r * l, a.sigma,
                      (int64_t)r);
   // D = R P  [r, HD]
   launch_gemm_nn<Tag>(Rsel, (int64_t)r * l, l, P32, (int64_t)l * HD, HD, nullptr, 0, (uint16_t*)a.Bm, (int64_t)r * HD,

@@ -413,3 +413,29 @@ def test_bases_rotations_keep_lengths(l):
     drift = np.mean(sig[0] / exact - 1)
     print(f"  drift {drift:.1e}", flush=True)
     assert abs(drift) <= 8 * (l / 16) * 2.0 ** -24 / 2
+
+
+@pytest.mark.parametrize("power,l", [(1.5, 288), (3.0, 130)])
+def test_bases_of_steep_spectra(power, l):
+    """Singular values that fall as j^-1.5 and j^-3 without power iterations, where rows of the Gram matrix would take
+    more sweeps than there are: the images X d_i are orthogonal up to D's rounding, sigma their lengths, in order, and
+    the singular values of X for all directions that stand well above the roundings of the 16-bit block P (2^-11 of
+    sigma_1)."""
+    dtype, n, HD = "f16", 640, 576
+    rng = wl.rng_for(59, l)
+    U, W = (np.linalg.qr(rng.standard_normal((m, l)))[0] for m in (n, HD))
+    X = wl.store((U * np.arange(1.0, l + 1) ** -power * 300.0) @ W.T, dtype)
+    Omega = wl.store(wl.rng_for(59, 1).standard_normal((l, HD)), dtype)
+    print(f"bases of steep spectra power={power} l={l}", flush=True)
+    D, sig = gpu_bases(X[None], Omega, l, 0, dtype)
+    Xd, Dd = oracle.promote(X, dtype), oracle.promote(D[0], dtype)
+    exact = np.linalg.svd(Xd, compute_uv=False)
+    eps = 2.0 ** -11
+    Z = Xd @ Dd.T
+    s = np.linalg.norm(Z, axis=0)
+    G = Z.T @ Z
+    off = np.abs(G - np.diag(np.diag(G)))
+    assert (off <= eps * s[0] * (s[:, None] + s[None, :]) + 2e-5 * np.outer(s, s)).all()
+    assert np.abs(sig[0] - s).max() <= 2 * eps * s[0] and np.diff(sig[0]).max() <= 1e-6 * sig[0][0]
+    top = int((exact[:l] > 64 * eps * exact[0]).sum())
+    assert np.abs(sig[0][:top] - exact[:top]).max() <= 2 * eps * exact[0]
