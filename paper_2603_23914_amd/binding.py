@@ -129,7 +129,14 @@ def _p(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# The current stream's handle without a Stream object around it: 0.3 us a call against 2.9, a fifth of what a short
+# step takes on the host.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device()) or None
     if stream is None:
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
