@@ -12,7 +12,7 @@
 //   sums     U^T[column, head] += C_v^T[column, token] . P^T[token, head]: the wave's C_v tile
 //            (32 rows of 2r bytes) goes through a private, padded LDS region and is read back
 //            as dwords of eight token rows, transposed with byte permutes.
-// The four waves of a workgroup take every fourth tile of the split and keep their own
+// The four (eight) waves of a workgroup take every fourth (eighth) tile of the split and keep their own
 // (reference exponent, sum, U); at the end they are combined through LDS, one wave after the
 // other (a fixed order: the result is deterministic), and written in the partial-result layout
 // of attn_partial, so the merge and expansion kernels behind it are the same.
@@ -27,8 +27,6 @@ namespace ap {
 namespace {
 
 constexpr int kTok = 32;
-constexpr int kWaves = 4;
-constexpr int kTileBytesMax = kTok * (2 * 128 + 16);     // a wave's LDS region (r = 128)
 
 // Registers are capped for two waves per SIMD where a wave's q' and U (all heads) leave room
 // for it without spilling (rank 64 up to 48 heads, rank 128 up to 16 heads): measured 5-7 %
@@ -62,8 +60,8 @@ constexpr int kMaxSmallTiles = 136;     // tiles a split can own with per-token 
 // list position) of its tiles into LDS; a wave then gathers a tile's rows through the index
 // list.  Columns at or beyond a tile's rank are not fetched (their loads are redirected to the
 // row's first chunk) and enter the products as zeros.
-template <class Tag, int MT, int NKS, bool RAGGED, bool LOGITS>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AP_SMALL_WPE)))
+template <class Tag, int MT, int NKS, bool RAGGED, bool LOGITS, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(AP_SMALL_WPE)))
 attn_small(const SmallParams p) {
   constexpr int Hp = MT * 16;
   // bf16 carries 8 significant bits: folded queries and weights go to the matrix cores as hi + lo
@@ -73,9 +71,11 @@ attn_small(const SmallParams p) {
   constexpr int CPR = R / 8;                         // 16-byte chunks per coefficient row
   constexpr int NV = CPR / 2;                        // value chunks per lane and tile (32 rows / 64 lanes)
   constexpr int kPitch = 2 * R + 16;                 // LDS row pitch: consecutive row quads on different banks
-  __shared__ __attribute__((aligned(16))) char vt[kWaves][kTileBytesMax];
+  constexpr int kTileBytes = kTok * kPitch;          // a wave's LDS region
+  constexpr int kChains = kWaves / 4;                // fours of waves, combined next to each other
+  __shared__ __attribute__((aligned(16))) char vt[kWaves][kTileBytes];
   __shared__ float st_m[kWaves][Hp], st_l[kWaves][Hp], st_p[kWaves][Hp];
-  static_assert(kWaves * kTileBytesMax >= Hp * R * 4, "the combine buffer reuses the tile regions");
+  static_assert(4 * kTileBytes >= Hp * R * 4, "the combine buffer reuses the tile regions");
   __shared__ int meta[RAGGED ? kMaxSmallTiles : 1][4];
 
   const int id = __builtin_amdgcn_readfirstlane((int)blockIdx.x);
@@ -136,7 +136,7 @@ attn_small(const SmallParams p) {
     const int ntot = ts[8];
     ntl = su < ntot ? p.by_split(ntot - su + S - 1) : 0;
     ntl = ntl < kMaxSmallTiles ? ntl : kMaxSmallTiles;   // the host sizes the splits so that this never cuts
-    for (int i = threadIdx.x; i < ntl; i += 256) {
+    for (int i = threadIdx.x; i < ntl; i += 64 * kWaves) {
       const int j = su + i * S;
       int o0 = off[0], o1 = off[1], tf = 0;
 #pragma unroll
@@ -386,23 +386,25 @@ attn_small(const SmallParams p) {
     if (g == 0) { st_m[wave][mt * 16 + n] = m[mt]; st_l[wave][mt * 16 + n] = lt2; st_p[wave][mt * 16 + n] = pt; }
   }
   __syncthreads();                                     // also: every wave is done with its tile region
-  float* Ubuf = (float*)&vt[0][0];                     // [Hp][R]
+  float* Ubuf = (float*)&vt[0][0];                     // [kChains][Hp][R]
   float f[MT];                                         // this wave's weight 2^(m_w - m*) per head
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int h = mt * 16 + n;
-    const float ms = fmaxf(fmaxf(st_m[0][h], st_m[1][h]), fmaxf(st_m[2][h], st_m[3][h]));
+    float ms = st_m[0][h];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, st_m[w][h]);
     f[mt] = m[mt] > -INFINITY ? fast_exp2(m[mt] - ms) : 0.f;    // a wave without tiles adds nothing
   }
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    if (wave == w) {
+  for (int w = 0; w < 4; ++w) {
+    if ((wave & 3) == w) {
       // U[i][j][mt][e] is (head 16 mt + n, column 32 i + 8 g + 2 e + j)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int i = 0; i < NKS; ++i) {
-          float* dst = Ubuf + (size_t)(mt * 16 + n) * R + 32 * i + 8 * g;
+          float* dst = Ubuf + (size_t)((wave >> 2) * Hp + mt * 16 + n) * R + 32 * i + 8 * g;
           f32x4_t v0 = {U[i][0][mt][0], U[i][1][mt][0], U[i][0][mt][1], U[i][1][mt][1]};
           f32x4_t v1 = {U[i][0][mt][2], U[i][1][mt][2], U[i][0][mt][3], U[i][1][mt][3]};
           v0 *= f[mt];
@@ -416,11 +418,17 @@ attn_small(const SmallParams p) {
   }
   // ---- out: the split's sums and statistics, coalesced
   const size_t pb = ((size_t)b * S + su) * H;
-  for (int i = threadIdx.x * 4; i < H * R; i += 256 * 4)
-    *(f32x4_t*)(p.part_U + pb * R + i) = *(const f32x4_t*)(Ubuf + i);
+  for (int i = threadIdx.x * 4; i < H * R; i += 64 * kWaves * 4) {
+    f32x4_t v = *(const f32x4_t*)(Ubuf + i);
+#pragma unroll
+    for (int c = 1; c < kChains; ++c) v += *(const f32x4_t*)(Ubuf + (size_t)c * Hp * R + i);
+    *(f32x4_t*)(p.part_U + pb * R + i) = v;
+  }
   if ((int)threadIdx.x < H) {
     const int h = threadIdx.x;
-    const float ms = fmaxf(fmaxf(st_m[0][h], st_m[1][h]), fmaxf(st_m[2][h], st_m[3][h]));
+    float ms = st_m[0][h];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) ms = fmaxf(ms, st_m[w][h]);
     float L = 0.f, pn = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
@@ -454,14 +462,21 @@ ap_status launch_attn_small(ap_dtype dt, const uint16_t* Qp, FoldedLayout folded
                 rank_k, rank_v, bucket_off, bucket_idx, F};
   const bool ragged = rank_k != nullptr || rank_v != nullptr;   // as everywhere in the library
   const int nb = B * nsplit;
+  // Eight waves, two per SIMD, where a split's gathered tiles pay for as many copies of the folded query and the
+  // registers allow it: importance loop of 64 x 4225 tokens, rank 64, 32 heads 68.8 -> 67.0 us, 40 heads 82.4 -> 78.1, of
+  // 2200 (18 tiles a split) 52.5 -> 50.6, of 1000 (9) 42.1 -> 42.5.  Rows that are not gathered are the same or slower.
+  const bool eight = ((T + kTok - 1) / kTok + F + nsplit - 1) / nsplit >= 12;
   const int mt = (H + 15) / 16, nks = r / 32;
   hipEvent_t ev0, ev1;
   const bool timed = prof_events(&ev0, &ev1);          // the coefficient-streaming kernel of this call
 #define AP_AS3(TAG, M, N, RG)                                                                          \
   do {                                                                                                 \
-    auto kern = scores ? attn_small<TAG, M, N, RG, true> : attn_small<TAG, M, N, RG, false>;           \
-    if (timed) hipExtLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, stream, ev0, ev1, 0u, p);           \
-    else hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, stream, p);                                  \
+    constexpr int W8 = RG && M * N <= 6 ? 8 : 4;                                                       \
+    const int W = eight ? W8 : 4;                                                                      \
+    auto kern = W == 8 ? (scores ? attn_small<TAG, M, N, RG, true, W8> : attn_small<TAG, M, N, RG, false, W8>)       \
+                       : (scores ? attn_small<TAG, M, N, RG, true, 4> : attn_small<TAG, M, N, RG, false, 4>);        \
+    if (timed) hipExtLaunchKernelGGL(kern, dim3(nb), dim3(64 * W), 0, stream, ev0, ev1, 0u, p);        \
+    else hipLaunchKernelGGL(kern, dim3(nb), dim3(64 * W), 0, stream, p);                               \
   } while (0)
 #define AP_AS2(TAG, M, N)                                                                              \
   do { if (ragged) AP_AS3(TAG, M, N, true); else AP_AS3(TAG, M, N, false); } while (0)

@@ -115,3 +115,39 @@ def test_forms_of_the_split_kernel(dtype, B, H, H_kv, d, r, T, mode):
                 assert np.abs(got_s[b, :T, h] - s).max() <= 2e-3 * np.abs(s).max()
         assert_close(to_host64(out)[b], ref, dtype, f"{mode} sequence {b}")
         assert np.abs(to_host64(lse)[b] - ref_l).max() <= 2e-3 * np.abs(ref_l).max()
+
+
+@pytest.mark.parametrize("dtype,B,H,r,T,scores", [
+    ("bf16", 64, 40, 64, 1700, True),     # fourteen tiles a split, some waves with one more than others
+    ("f16", 64, 17, 64, 1400, False),     # twelve
+    ("bf16", 128, 9, 128, 800, True),     # fourteen, one head tile at rank 128
+    ("f16", 128, 48, 64, 700, True),      # twelve, three head tiles
+])
+def test_gathered_small_ranks_over_long_splits(dtype, B, H, r, T, scores):
+    """Ranks 64 and 128 by rank group where a split is a dozen tiles and more: eight waves share them."""
+    from paper_2603_23914_amd import binding as ap
+    d = 32
+    case = wl.decode_case(dtype, B, H, d, r, T, steps=0, seed=H + T, append=False)
+    P = lambda x: oracle.promote(x, dtype)
+    q = torch.from_numpy(wl.rng_for(B, H, T).standard_normal((B, H, d)).astype(np.float32)).to(TORCH_DT[dtype]).cuda()
+    dCk, dCv, dBk, dBv = (to_dev(x, dtype) for x in (case.Ck, case.Cv, case.Bk, case.Bv))
+    out = torch.full((B, H, d), float("nan"), dtype=torch.float32, device="cuda")
+    ws = workspace(ap.ap_decode_workspace_bytes(B, H, d, T, r, ap._DT[TORCH_DT[dtype]]))
+    mass = torch.from_numpy(wl.rng_for(T, r, H).random((B, T)).astype(np.float32)).cuda()
+    rank, idx = (torch.empty((B, T), dtype=torch.int32, device="cuda") for _ in range(2))
+    off = torch.empty((B, 3), dtype=torch.int32, device="cuda")
+    ap.ap_select_ranks(mass, (r, 16), (1, 4), 4, rank, off, idx, workspace(ap.ap_select_workspace_bytes(B, T, 2)))
+    s_out = torch.full((B, dCk.shape[1], H), float("nan"), dtype=torch.float32, device="cuda") if scores else None
+    ap.ap_decode_attn(q, dCk, dCv, dBk, dBv, out, ws, T=T, sm_scale=1.0 / math.sqrt(d), rank_v=rank, bucket_off=off,
+                      bucket_idx=idx, F=2, scores=s_out)
+    torch.cuda.synchronize()
+    for b in range(0, B, 7):
+        live = np.arange(r)[None, :] < rank[b].cpu().numpy()[:, None]
+        ck, cv, bk, bv = P(case.Ck)[b][:T], P(case.Cv)[b][:T] * live, P(case.Bk)[b], P(case.Bv)[b]
+        for h in range(H):
+            cols = slice(h * d, h * d + d)
+            s = ck @ (bk[:, cols] @ to_host64(q)[b, h]) / math.sqrt(d)
+            w = np.exp(s - s.max())
+            assert_close(to_host64(out)[b, h], (w / w.sum()) @ cv @ bv[:, cols], dtype, f"sequence {b} head {h}")
+            if scores:
+                assert np.abs(s_out[b, :T, h].double().cpu().numpy() - s).max() <= 2e-3 * np.abs(s).max()
