@@ -224,8 +224,8 @@ ap_status launch_attn_heads(const DecodeArgs& a, const uint16_t* Qp, FoldedLayou
 // key-only compression on the matrix cores (keyonly_mfma.hip)
 bool keyonly_mfma_applies(int H, int H_kv, int d, int r);
 int keyonly_mfma_splits(int B, int H_kv, int T);
-ap_status launch_keyonly_mfma(ap_dtype dt, const uint16_t* Qp, const void* Ck, const void* V, float* out_part,
-                              float* lse_part, int B, int H, int H_kv, int T, int T_cap, int r, int S,
+ap_status launch_keyonly_mfma(ap_dtype dt, const void* q, const void* Bk, int64_t bstride, float scale, const void* Ck,
+                              const void* V, float* out_part, float* lse_part, int B, int H, int H_kv, int T, int T_cap, int r, int S,
                               hipStream_t stream);
 size_t keyonly_attn_workspace(int B, int H, int H_kv, int d, int T, int r);
 ap_status launch_keyonly_attn(const void* q, const void* Ck, const void* Bk, int64_t bstride, const void* V,

@@ -5,6 +5,9 @@
 // The flash-decode kernels on the vector ALU spend H*d fused multiply-adds per token on the value
 // sum alone and are bound by that arithmetic once the keys are this small.  Here a wave takes a
 // tile of 32 tokens of ONE key/value head and all the query heads that share it:
+//   fold     q'[j, head] = scale B_k[j, slice] . q_head, a workgroup for itself: rank x 256 bytes of the basis out of
+//            L2 while the first tile is on its way, 16 basis rows x the heads per product, hi + lo parts through
+//            LDS; a launch of its own took 5 us (8 sequences of 8191 tokens, 32 / 8 heads, rank 64: 40.4 -> 35.9 us a pass);
 //   scores   S[token, head] = C_k[token, :r] . q'[head, :r]   MFMA 16x16x32, coefficient rows
 //            straight from global memory into the A operand (16 rows x 64 bytes per load),
 //            the folded queries (hi + lo halves for bf16) resident as B operands;
@@ -37,38 +40,50 @@ constexpr int kWaves = 4;
 // so the pair's coefficient rows, which every head reads, are fetched from HBM once.
 template <class Tag, int NKS>
 __global__ void __launch_bounds__(256)
-keyonly_mfma(const uint16_t* __restrict__ Qp, const uint16_t* __restrict__ Ck,
-             const uint16_t* __restrict__ V, float* __restrict__ out_part, float* __restrict__ lse_part,
-             int B, int H, int QG, int T, int T_cap, int r, int S, int per) {
+keyonly_mfma(const uint16_t* __restrict__ q, const uint16_t* __restrict__ Bk, int64_t bstride, float scale,
+             const uint16_t* __restrict__ Ck, const uint16_t* __restrict__ V, float* __restrict__ out_part,
+             float* __restrict__ lse_part, int B, int H, int QG, int T, int T_cap, int r, int S, int per,
+             FastDiv by_heads, FastDiv by_split) {
+  constexpr int kFoldPitch = 32 * NKS + 8;               // elements; 16-byte aligned, rows on different banks
+  constexpr int kRowTiles = (2 * NKS + kWaves - 1) / kWaves;   // 16 basis rows each, per wave
   __shared__ __attribute__((aligned(16))) char vt[kWaves][kTok * kPitch];
+  __shared__ __attribute__((aligned(16))) uint16_t fold[2][16 * kFoldPitch];
   // bf16 carries 8 significant bits: folded queries and weights go to the matrix cores as hi + lo
   // pairs; fp16 (11 bits) needs no second half
   constexpr bool SPLIT = std::is_same<Tag, BF16Tag>::value;
-  const int Hkv = H / QG;
-  const int id = blockIdx.x, k = id >> 3;
-  const int kvh = k % Hkv, p = (k / Hkv) * 8 + (id & 7);
+  const int Hkv = (int)by_heads.d;
+  const int id = blockIdx.x, k = id >> 3, pk = by_heads(k);
+  const int kvh = k - pk * Hkv, p = pk * 8 + (id & 7);
   if (p >= B * S) return;
-  const int b = p / S, su = p - b * S;
+  const int b = by_split(p), su = p - b * S;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
   const int h0 = kvh * QG;
   const size_t HD = (size_t)Hkv * 128;
 
-  // folded queries of head h0 + n (zero beyond the heads of the group and beyond the rank)
-  u32x4_t qh[NKS], ql[SPLIT ? NKS : 1];
+  // the fold's operands: basis row n of a tile, query head h0 + n (zero beyond the heads of the group)
+  u32x4_t fb[kRowTiles][4], fq[4];
+  {
+    const uint16_t* qrow = q + ((size_t)b * H + h0 + (n < QG ? n : 0)) * 128 + g * 8;
+    const u32x4_t z = {0, 0, 0, 0};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const u32x4_t v = *(const u32x4_t*)(qrow + c * 32);
+      fq[c] = n < QG ? v : z;
+    }
+    const uint16_t* bcol = Bk + (size_t)b * bstride + (size_t)kvh * 128 + g * 8;
+#pragma unroll
+    for (int i = 0; i < kRowTiles; ++i) {
+      const int j = (wave + kWaves * i) * 16 + n;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) fb[i][c] = *(const u32x4_t*)(bcol + (size_t)(j < r ? j : r - 1) * HD + c * 32);
+    }
+  }
   uint32_t koff[NKS];
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) {
     const int col = ks * 32 + g * 8;
-    const u32x4_t z = {0, 0, 0, 0};
-    qh[ks] = z;
-    if (SPLIT) ql[ks] = z;
     koff[ks] = col < r ? (uint32_t)col : 0u;          // columns beyond the rank re-read column 0
-    if (n < QG && col < r) {
-      const uint16_t* qp = Qp + (((size_t)b * 2) * H + h0 + n) * r + col;
-      qh[ks] = *(const u32x4_t*)qp;
-      if (SPLIT) ql[ks] = *(const u32x4_t*)(qp + (size_t)H * r);
-    }
   }
   const uint16_t* Cb = Ck + (size_t)b * T_cap * r;
   const uint16_t* Vb = V + (size_t)b * T_cap * HD + (size_t)kvh * 128 + n * 8;
@@ -106,6 +121,34 @@ keyonly_mfma(const uint16_t* __restrict__ Qp, const uint16_t* __restrict__ Ck,
 
   int t = wave;
   if (t < ntiles) load_tile(t);
+  // the folded queries: a lane of the product has four rank positions of head n (zero beyond the rank)
+#pragma unroll
+  for (int i = 0; i < kRowTiles; ++i) {
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = Mfma<Tag>::run(fb[i][c], fq[c], acc);
+    const int j = (wave + kWaves * i) * 16 + 4 * g;
+    if (j < 32 * NKS) {
+      u32x2_t hi = {0, 0}, lo = {0, 0};
+      if (j < r) {                                       // (r is a multiple of eight)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const float x = acc[2 * e] * scale, y = acc[2 * e + 1] * scale;
+          hi[e] = cvt_pack(x, y, Tag{});
+          lo[e] = cvt_pack(x - lo_to_f32(hi[e], Tag{}), y - hi_to_f32(hi[e], Tag{}), Tag{});
+        }
+      }
+      *(u32x2_t*)(fold[0] + n * kFoldPitch + j) = hi;
+      if (SPLIT) *(u32x2_t*)(fold[1] + n * kFoldPitch + j) = lo;
+    }
+  }
+  lds_barrier();
+  u32x4_t qh[NKS], ql[SPLIT ? NKS : 1];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) {
+    qh[ks] = *(const u32x4_t*)(fold[0] + n * kFoldPitch + ks * 32 + g * 8);
+    if (SPLIT) ql[ks] = *(const u32x4_t*)(fold[1] + n * kFoldPitch + ks * 32 + g * 8);
+  }
   for (; t < ntiles; t += kWaves) {
     const int cnt = t1 - (t0 + t * kTok);               // tokens of this tile that exist (>= 1)
     // the previous tile's reads of the LDS region are done: their results fed its MFMAs
@@ -214,16 +257,18 @@ int keyonly_mfma_splits(int B, int H_kv, int T) {
   return s < 1 ? 1 : s;
 }
 
-ap_status launch_keyonly_mfma(ap_dtype dt, const uint16_t* Qp, const void* Ck, const void* V, float* out_part,
-                              float* lse_part, int B, int H, int H_kv, int T, int T_cap, int r, int S,
+ap_status launch_keyonly_mfma(ap_dtype dt, const void* q, const void* Bk, int64_t bstride, float scale, const void* Ck,
+                              const void* V, float* out_part, float* lse_part, int B, int H, int H_kv, int T, int T_cap, int r, int S,
                               hipStream_t stream) {
   const int QG = H / H_kv;
   const int per = ((T + S - 1) / S + kTok - 1) / kTok * kTok;
   const dim3 grid(8 * H_kv * ((B * S + 7) / 8));
   const int nks = (r + 31) / 32;
+  const FastDiv by_heads(H_kv, (int64_t)B * S * H_kv), by_split(S, (int64_t)B * S + 8);
 #define AP_KM(TAG, N)                                                                                       \
-  hipLaunchKernelGGL((keyonly_mfma<TAG, N>), grid, dim3(256), 0, stream, Qp, (const uint16_t*)Ck,           \
-                     (const uint16_t*)V, out_part, lse_part, B, H, QG, T, T_cap, r, S, per)
+  hipLaunchKernelGGL((keyonly_mfma<TAG, N>), grid, dim3(256), 0, stream, (const uint16_t*)q, (const uint16_t*)Bk, bstride, \
+                     scale, (const uint16_t*)Ck, (const uint16_t*)V, out_part, lse_part, B, H, QG, T, T_cap, r, S, per,  \
+                     by_heads, by_split)
   if (dt == AP_F16) {
     switch (nks) { case 1: AP_KM(F16Tag, 1); break; case 2: AP_KM(F16Tag, 2); break; case 3: AP_KM(F16Tag, 3); break;
                    default: AP_KM(F16Tag, 4); break; }

@@ -708,14 +708,15 @@ ap_status launch_keyonly_attn(const void* q, const void* Ck, const void* Bk, int
   uint16_t* Qp = (uint16_t*)ws;
   float* parts = (float*)(ws + keyonly_qp_bytes(B, H, r));
   float* lparts = (float*)(ws + keyonly_qp_bytes(B, H, r) + round_up((size_t)P * B * H * d * 4, 256));
-  // q' = scale * log2(e) * B_k[:, slice] q_h for every head, written as hi + lo pairs
-  ap_status st = launch_fold_heads(dt, Bk, bstride, q, Qp, B, H, H_kv, H, d, r, sm_scale * kLog2e, stream);
-  if (st != AP_OK) return st;
   float* op = P > 1 ? parts : out;
   float* lp = (P > 1 || !lse) ? lparts : lse;
+  ap_status st;
   if (mfma) {
-    st = launch_keyonly_mfma(dt, Qp, Ck, V, op, lp, B, H, H_kv, T, T_cap, r, P / 4, stream);
+    st = launch_keyonly_mfma(dt, q, Bk, bstride, sm_scale * kLog2e, Ck, V, op, lp, B, H, H_kv, T, T_cap, r, P / 4, stream);
   } else {
+    // q' = scale * log2(e) * B_k[:, slice] q_h for every head, written as hi + lo pairs
+    st = launch_fold_heads(dt, Bk, bstride, q, Qp, B, H, H_kv, H, d, r, sm_scale * kLog2e, stream);
+    if (st != AP_OK) return st;
 #define AP_KL(TAG)                                                                                          \
   switch (d) {                                                                                              \
     case 32: st = launch_keyonly_partial<TAG, 4>(Qp, Ck, V, op, lp, B, H, QG, T, T_cap, r, P, stream); break;  \

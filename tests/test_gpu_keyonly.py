@@ -148,3 +148,35 @@ def test_keyonly_rejects_bad_arguments():
     assert ap.ap_keyonly_workspace_bytes(1, 8, 2, 64, 16, 644) == 0      # rank not a multiple of 8
     assert ap.ap_keyonly_workspace_bytes(1, 8, 2, 48, 16, 64) == 0    # head width not supported
     assert ap.ap_keyonly_workspace_bytes(1, 8, 3, 64, 16, 64) == 0    # key/value heads must divide the heads
+
+
+@pytest.mark.parametrize("dtype,B,H,Hkv,r,T,shared", [
+    ("bf16", 2, 16, 1, 24, 40, False),       # a rank inside one step of 32, sixteen heads
+    ("f16", 1, 3, 1, 104, 700, False),       # seven tiles of basis rows, the last one half
+    ("bf16", 9, 40, 8, 112, 130, True),      # one basis for all sequences
+    ("f16", 3, 40, 40, 128, 31, False),      # a head of its own per slice, a single partial tile
+])
+def test_fold_within_the_matrix_core_kernel(dtype, B, H, Hkv, r, T, shared):
+    """The query is folded by every workgroup for itself: ranks that end inside a product of 16 basis rows or a step of
+    32 columns (the rows behind the basis hold large values, which may not show), few heads and sixteen."""
+    from paper_2603_23914_amd import binding as ap
+    d, tdt = 128, TORCH_DT[dtype]
+    rng = wl.rng_for(61, B, H, r)
+    dev = lambda *s: torch.from_numpy(rng.standard_normal(s).astype(np.float32)).to(tdt).cuda()
+    q, Ck, V = dev(B, H, d), dev(B, T + 3, r), dev(B, T + 3, Hkv * d)
+    nb = 1 if shared else B
+    room = torch.full((nb * r * Hkv * d + 64 * Hkv * d,), 1.0e4, dtype=tdt, device="cuda")
+    Bk = room[:nb * r * Hkv * d].view(nb, r, Hkv * d)
+    Bk.copy_(dev(nb, r, Hkv * d) / math.sqrt(Hkv * d))
+    out = torch.full((B, H, d), float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.full((B, H), float("nan"), dtype=torch.float32, device="cuda")
+    ws = workspace(ap.ap_keyonly_workspace_bytes(B, H, Hkv, d, T, r))
+    ap.ap_keyonly_attn(q, Ck, Bk[0] if shared else Bk, V, out, ws, T=T, sm_scale=1.0 / math.sqrt(d), lse=lse)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(H):
+            cols = slice(h // (H // Hkv) * d, h // (H // Hkv) * d + d)
+            s = to_host64(Ck)[b, :T] @ (to_host64(Bk)[b % nb][:, cols] @ to_host64(q)[b, h]) / math.sqrt(d)
+            w = np.exp(s - s.max())
+            assert_close(to_host64(out)[b, h], (w / w.sum()) @ to_host64(V)[b, :T, cols], dtype, f"sequence {b} head {h}")
+            assert abs(to_host64(lse)[b, h] - (s.max() + math.log(w.sum()))) <= 2e-3 * max(1.0, abs(s.max()))
